@@ -114,6 +114,8 @@ struct spp_ctx {
     uint64_t    btab_stamp[kBatchSlots] = {};    // last use
     uint64_t    sample_calls = 0;
     int         sample_flags_clean = 0; // the flags of the next call have been cleared on the stream
+    spp::DevBuf hopsums;                // fanout sampling: sums per 256 targets and per granule of edges, all zero between calls
+    int         hopsums_clean = 0;      // they are
     // gather workspaces
     // two sets, used alternately: the classification of a call may run while the miss copy of the
     // call before still reads its own set
@@ -134,7 +136,7 @@ struct spp_ctx {
     spp::DevBuf bins;                   // general propagation: per row block the (row, weight) entries of a hop, and the fill counts
     int         bin_lds_set = 0, sum_lds_set = 0;   // dynamic LDS bytes its two kernels have been allowed
     int         tile_lds_set = 0;       // dynamic LDS bytes the dense-hop kernel has been allowed on this device
-    int         dedup_lds_set = 0;      // the LDS dedup kernel of the sampler has been allowed its 128 KB
+    int         dedup_lds_set = 0;      // the LDS dedup kernel of the sampler has been allowed its 76 KB
     int         x_lds_set = 0;          // the two kernels of the chunked layout have been allowed theirs
     int         vip_pushed[SPP_MAX_L] = {};          // last vip_propagate: hop done in push form?
     int64_t     vip_frontier_edges[SPP_MAX_L] = {};  // last vip_propagate: out-edges of each hop's frontier

@@ -158,21 +158,18 @@ inline void grid_scan(hipStream_t st, int grid, const int64_t* n_ptr, In in, Out
 // and Tail get the sequence's total and derive what they need from it.  (Where Fin sets a flag
 // that those workgroups also read, they combine it with the launch-invariant condition under
 // which Fin sets it, so that either value of the flag gives the same outcome.)
-// Two hooks let independent work ride in the same launches (a launch costs more than most of
-// these steps): Head: void operator()(int j, unsigned x, unsigned gx) const runs before the
-// reduction, Tail: void operator()(int j, unsigned x, unsigned gx, int total) const after the write
+// A hook lets independent work ride in the second launch (a launch costs more than most of these
+// steps): Tail: void operator()(int j, unsigned x, unsigned gx, int total) const after the write
 // pass; x is the workgroup's index among the gx of sequence j.
 struct NoHook {
-    __device__ void operator()(int, unsigned, unsigned) const {}
     __device__ void operator()(int, unsigned, unsigned, int) const {}
 };
 
-template <class In, class Head>
-__global__ void __launch_bounds__(kBlock) bscan_reduce_kernel(In in, int* partial, Head head) {
+template <class In>
+__global__ void __launch_bounds__(kBlock) bscan_reduce_kernel(In in, int* partial) {
     __shared__ int lds[4];
     const BatchBlock bb = batch_block();
     const int j = bb.j;
-    head(j, bb.x, gridDim.x);
     int64_t b, e;
     scan_range(in.n(j), bb.x, b, e);
     int acc = 0;
@@ -209,19 +206,18 @@ __global__ void __launch_bounds__(kBlock) bscan_write_kernel(In in, Out out, Fin
     tail(j, bb.x, gridDim.x, seq_total);
 }
 
-template <class In, class Out, class Fin, class Head = NoHook, class Tail = NoHook>
-inline void grid_scan_batched(hipStream_t st, int grid, int nbatch, In in, Out out, Fin fin, int* partial,
-                              Head head = Head(), Tail tail = Tail()) {
-    bscan_reduce_kernel<In, Head><<<dim3(grid, nbatch), kBlock, 0, st>>>(in, partial, head);
+template <class In, class Out, class Fin, class Tail = NoHook>
+inline void grid_scan_batched(hipStream_t st, int grid, int nbatch, In in, Out out, Fin fin, int* partial, Tail tail = Tail()) {
+    bscan_reduce_kernel<In><<<dim3(grid, nbatch), kBlock, 0, st>>>(in, partial);
     bscan_write_kernel<In, Out, Fin, Tail><<<dim3(grid, nbatch), kBlock, 0, st>>>(in, out, fin, partial, tail);
 }
 
 // The same with a value function of its own for the second launch (one that reads what the first
 // launch's function left behind instead of computing the value again).
-template <class In, class In2, class Out, class Fin, class Head = NoHook, class Tail = NoHook>
+template <class In, class In2, class Out, class Fin, class Tail = NoHook>
 inline void grid_scan_batched_two(hipStream_t st, int grid, int nbatch, In in, In2 in2, Out out, Fin fin, int* partial,
-                                  Head head = Head(), Tail tail = Tail()) {
-    bscan_reduce_kernel<In, Head><<<dim3(grid, nbatch), kBlock, 0, st>>>(in, partial, head);
+                                  Tail tail = Tail()) {
+    bscan_reduce_kernel<In><<<dim3(grid, nbatch), kBlock, 0, st>>>(in, partial);
     bscan_write_kernel<In2, Out, Fin, Tail><<<dim3(grid, nbatch), kBlock, 0, st>>>(in2, out, fin, partial, tail);
 }
 

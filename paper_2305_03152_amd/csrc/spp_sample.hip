@@ -1,48 +1,38 @@
 // Node-wise fanout sampling into per-layer message-flow graphs (Sec. 2.3; the process of Sec. 3.1).
 //
 // Up to 64 minibatches are sampled by one set of launches: every kernel has a second grid dimension
-// that names the minibatch, and each minibatch has its own id table, flat-id buffer and counts, so
-// the minibatches never interact.  Per hop h, all on the context's stream with every count kept on
-// the device:
-//   1. grid scan of c_i = min(f_h, d(S_{h-1}[i]))            -> indptr of MFG h, e_h
-//   2. sample: a group of G lanes (G = 8/16/32/64 >= f_h) per target draws its slots in parallel
-//      (one Philox block per lane), resolves Floyd's "already taken" rule with ballots, reads the
-//      neighbour ids and stores them in flat (edge) order
-//   3. dedup: for every sampled id the position of its first appearance among S_{h-1} followed by
-//      the hop's flat list (an index below n_{h-1} means the vertex is an earlier one)
-//   4. grid scan of "this flat entry is the first appearance of a new id"
-//                                                            -> S_h appended in order, n_h, src of those entries
-//   5. relabel: src[e] of a repeated id = its index in S_{h-1}, or the src of its first appearance
-// Step 3 is where the ids meet.  A hop of up to 16 x 8192 ids (with S_{h-1}) is deduplicated in LDS:
-// the ids are dealt by hash to up to 16 partitions, one workgroup per partition keeps an id table of
-// 16384 slots in LDS (128 KB), reads the minibatch's whole list (a few hundred KB, from L2), inserts
-// the ids of its partition with LDS atomics (smallest position wins) and, after a barrier, writes
-// out what each of them resolved to.  Global memory sees only sequential reads and writes.  (The
-// earlier form, a table in global memory fed by the sample kernel, was bound by the rate of global
-// atomics, about 16 G/s: 0.31 ms for the 5 M inserts of the last hop of 64 minibatches.)  Larger hops
-// keep that form: the id table (open addressing, global memory) is right-sized per hop on the device:
-// once e_h is known, the hop uses the first 2^k >= 2 (n_{h-1} + e_h) slots of the minibatch's region,
-// clears exactly those, and the sample kernel offers S_{h-1} (value = index, which is below any
-// position offered at this hop, so earlier vertices keep their ids) next to the new ids with atomic
-// minima; the scan's first pass then reads what each entry resolved to.  The worst-case bound on
-// |S_L| only sizes the allocation: a Mid minibatch reaches 66k of 1.08M possible vertices, and a
-// table laid out for the bound (32 MB per minibatch, touched at random) pushed the feature rows out
-// of the caches (the hit copy ran 20 % slower) besides missing L2 itself.  Which form a hop takes is
-// decided per minibatch on the device, from the hop's size.
+// that names the minibatch, and each minibatch has its own workspace and counts, so the minibatches
+// never interact.  Every count is kept on the device; all work is on the context's stream.  Per hop h,
+// whatever the form:
+//   1. prefix sums of c_i = min(f_h, d(S_{h-1}[i]))          -> indptr of MFG h, e_h
+//   2. every target draws its subset (Philox words numbered by slot, Floyd's rule) and reads the ids
+//   3. for every sampled id the position of its first appearance among S_{h-1} followed by the hop's
+//      edges (an index below n_{h-1} means the vertex is an earlier one)
+//   4. the first appearances of new ids are numbered in order -> S_h, n_h, src of those edges
+//   5. src of a repeated id = its index in S_{h-1}, or the src of its first appearance
+// Step 3 is where the ids meet.  With fanouts they meet in LDS (the hop_* kernels below: three
+// launches per hop, one after the last hop).  The other form keeps a table in global memory (open
+// addressing, 64-bit entries, six launches per hop: two per prefix sum); it is bound by the rate of
+// global atomics, about 16 G/s, and serves the sampler with given probabilities, whose sizes no
+// fanout bounds, calls that ask for it (SPP_SAMPLE_GLOBAL_TABLE) and calls whose edge bounds would make
+// the LDS form's workspace the larger one by far.  Its table is right-sized per hop on the device: once
+// e_h is known, the hop uses the first 2^k >= 2 (n_{h-1} + e_h) slots of the minibatch's region, clears
+// exactly those, and the sample kernel offers S_{h-1} (value = index, which is below any position
+// offered at this hop, so earlier vertices keep their ids) next to the new ids with atomic minima; the
+// scan's first pass then reads what each entry resolved to.
 //
-// Launches per call with fanouts: six per hop (two for each scan, the sample kernel, the
-// deduplication) and the last hop's relabel; the seeds are put in place at the head of hop 1's first
-// scan launch and the relabel of hop h-1 rides at the head of hop h's.  The per-minibatch pointers
-// (a table too large for an argument block) stay on the device between calls and are stored again
-// only when a call brings other buffers.
+// The per-minibatch pointers (a table too large for an argument block) stay on the device between
+// calls and are stored again only when a call brings other buffers.
 //
-// The same machinery serves the sampler with given transition probabilities (Sec. 3.1, paragraph
-// after Prop. 1): a target takes every entry of its row independently with the entry's probability,
-// so step 1 is a counting pass with the random draws (one wavefront per target, ballots) and step 2
-// repeats the draws to place the taken entries; no fanout bounds the sizes, so the counting pass
-// also checks the caller's capacities and abandons a minibatch that would exceed them.
+// The sampler with given transition probabilities (Sec. 3.1, paragraph after Prop. 1): a target takes
+// every entry of its row independently with the entry's probability, so step 1 is a counting pass
+// with the random draws (one wavefront per target, ballots) and step 2 repeats the draws to place the
+// taken entries; no fanout bounds the sizes, so the counting pass also checks the caller's capacities
+// and abandons a minibatch that would exceed them.
 #include "spp_common.h"
 #include "spp_device.h"
+
+#include <algorithm>
 
 namespace spp {
 
@@ -55,8 +45,7 @@ struct BatchDesc {
     int32_t*       indptr[SPP_MAX_L];
     int32_t*       src[SPP_MAX_L];
     int64_t*       counts;              // n[0..MAX_L], e[0..MAX_L]
-    uint32_t*      tinfo;               // [0] mask, [1] shift of the table for the current hop, [2] abandoned (workspace),
-                                        // [3] log2 of the LDS partitions of the current hop, or kGlobalTable
+    uint32_t*      tinfo;               // [0] mask, [1] shift of the table for the current hop, [2] abandoned (workspace)
     unsigned long long* taken;          // 64-bit count of taken entries of the current hop (given probabilities only)
     int64_t        ncap;                // capacities of the caller's buffers (checked on the device
     int64_t        ecap[SPP_MAX_L];     //   only when sizes are not bounded by fanouts)
@@ -105,7 +94,6 @@ struct SampleArgs {
     int32_t*       cnt;                 // one region of `cnt_stride` per-target counts per minibatch (given probabilities)
     int64_t        cnt_stride;
     int*           ovf;                 // set when a minibatch was abandoned for lack of capacity
-    int            force_global;        // SPP_SAMPLE_GLOBAL_TABLE: every hop deduplicates in the global-memory table
 };
 
 __device__ __forceinline__ unsigned long long* tab_of(const SampleArgs& a, int j) { return a.tab + (int64_t)j * a.cap; }
@@ -145,22 +133,6 @@ __global__ void __launch_bounds__(kBlock) seeds_kernel(SampleArgs a, BatchTable*
     const BatchBlock bb = batch_block();
     seeds_rows(a, t, dyn.d[bb.j], bb.j, bb.x, gridDim.x);
 }
-// The same riding at the head of the first launch of hop 1's scan (fanout sampling), whose values
-// then come from the seeds themselves: the table's copy is written by that very launch.
-struct SeedsHead {
-    SampleArgs a; BatchTable* t; BatchDynAll dyn;
-    __device__ void operator()(int j, unsigned x, unsigned gx) const { seeds_rows(a, t, dyn.d[j], j, x, gx); }
-};
-struct CountInSeeds {
-    SampleArgs a; BatchDynAll dyn;
-    __device__ int64_t n(int j) const { return dyn.d[j].nseeds; }
-    __device__ int operator()(int j, int64_t i) const {
-        int32_t v = dyn.d[j].seeds[i];
-        if (v < 0 || v >= a.N) v = 0;
-        const int64_t d = a.rowptr[v + 1] - a.rowptr[v];
-        return d < a.f ? (int)d : a.f;
-    }
-};
 
 // ---- step 1 ----
 // With given probabilities sizes are not bounded by fanouts: the 64-bit count of the counting pass
@@ -198,20 +170,6 @@ __device__ __forceinline__ void hop_table(const SampleArgs& a, int64_t n_prev, i
     shift = 22;
     while (capj < want && (int64_t)capj < a.cap) { capj <<= 1; --shift; }
 }
-// Where a hop's ids are deduplicated: in LDS, dealt to 2^k partitions of at most kLdsPartKeys ids on
-// average (k returned), or in the table in global memory (kGlobalTable).  A function of the hop's size
-// alone, so every workgroup of a launch that has the scan's total takes the same decision.
-constexpr int kLdsSlots = 16384;                 // slots of a partition's table (64-bit entries: 128 KB of LDS)
-constexpr int kLdsPartKeys = kLdsSlots / 2;
-constexpr int kLdsMaxPartsLog2 = 4;
-constexpr uint32_t kGlobalTable = 0xFFFFFFFFu;
-__device__ __forceinline__ uint32_t hop_mode(const SampleArgs& a, int64_t n_prev, int e_h) {
-    const int64_t keys = n_prev + (int64_t)(uint32_t)e_h;
-    if (a.t != nullptr || a.force_global || keys > ((int64_t)kLdsPartKeys << kLdsMaxPartsLog2)) return kGlobalTable;
-    uint32_t k = 0;
-    while (((int64_t)kLdsPartKeys << k) < keys) ++k;
-    return k;
-}
 struct CountFin {
     SampleArgs a; const BatchTable* t;
     __device__ void operator()(int j, int total) const {
@@ -230,7 +188,6 @@ struct CountFin {
         hop_table(a, c[a.h - 1], total, capj, shift);
         t->b[j].tinfo[0] = capj - 1;
         t->b[j].tinfo[1] = (uint32_t)shift;
-        t->b[j].tinfo[3] = hop_mode(a, c[a.h - 1], total);
     }
 };
 
@@ -242,7 +199,6 @@ struct TableClear {
     SampleArgs a; const BatchTable* t;
     __device__ void operator()(int j, unsigned x, unsigned gx, int total) const {
         if (t->b[j].tinfo[2] || hop_overflows(a, t->b[j])) return;
-        if (hop_mode(a, t->b[j].counts[a.h - 1], total) != kGlobalTable) return;     // deduplicated in LDS: no table to empty
         unsigned long long* tab = tab_of(a, j);
         uint32_t capj;
         int shift;
@@ -275,7 +231,6 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a, const Batc
     unsigned long long* tab = tab_of(a, jb);
     const uint32_t mask = t->b[jb].tinfo[0];
     const int shift = (int)t->b[jb].tinfo[1];
-    const bool global_table = t->b[jb].tinfo[3] == kGlobalTable;
 
     for (int64_t first = wave * kGroupsPerWave; first < n_prev; first += nwaves * kGroupsPerWave) {
         const int64_t i = first + (lane / G);
@@ -316,7 +271,6 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a, const Batc
             e = (int64_t)off + j;
             gids[e] = gid;
         }
-        if (!global_table) continue;               // the ids meet in LDS, in the launch that follows
         // the table was emptied for this hop, so the target is offered again with its index; the
         // group's last lane does it when it has no neighbour of its own (c < G), else lane 0 after
         // its neighbour
@@ -336,144 +290,659 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a, const Batc
     }
 }
 
-// ---- step 3 in LDS ----
-// One workgroup per (partition, minibatch).  An id belongs to the partition named by the top bits of
-// its hash; its slot comes from the bits below.  Entries are (id << 32 | position), empty = all ones;
-// an insertion keeps the smallest position offered for an id.  A partition holds 8192 ids on average
-// and 16384 at most; more than that in one partition (ids that share their hash's top bits by the
-// thousand) cannot be held: the call then reports an error and the minibatch's output is not valid.
+// ---- fanout sampling, three launches per hop ----
+// The ids of a hop are deduplicated in LDS, partition by partition: an id belongs to the partition
+// named by the top k bits of a multiplicative hash, and one workgroup of hop_dedup_kernel keeps a
+// table for one partition.  What used to bound the hop was everything around that: each partition's
+// workgroup read the whole hop's ids twice (half of a call of one minibatch), two launches per prefix
+// sum, and hops above 131072 ids went through a table in global memory at the rate of global atomics.
+// Here
+//   hop_sample_kernel  draws a tile's subsets and leaves the tile's ids already dealt to the
+//                      partitions: a run of (id, position) entries per tile, ordered by partition;
+//   hop_dedup_kernel   walks only the runs of its own partition, whatever the hop's size, and marks the
+//                      entries that repeat an id in place (nothing is scattered by edge);
+//   hop_number_kernel  puts a tile's entries back in edge order in LDS and numbers the first appearances.
+// No launch is spent on prefix sums and nothing ever waits for another workgroup: the sums that a
+// workgroup needs (edges of the targets before its tile, new vertices before its tile) are kept per 256
+// targets / per tile by the launches before it (one atomic add per tile), and the workgroup adds up
+// the few hundred sums before its own itself.
+// Per call, 3 hops: one minibatch of 1024 seeds on 2.4M vertices 0.21 -> 0.105 ms (waited for), 64 of
+// them on 12M vertices 0.385 -> 0.256 ms, 8 of 4096 seeds with fanouts 20/15/10 on a 4M-vertex RMAT
+// graph (hops of a million ids) 0.86 -> 0.45 ms.
+constexpr int kHopTargets = 256;                 // most targets of a tile, and targets per kept edge sum
+constexpr int kHopEdges = 4096;                  // most edges of a tile
+constexpr int kHopSlots = 8192;                  // slots of a partition's table (64 KB of LDS: two workgroups per CU)
+constexpr int kHopSlotBits = 13;
+constexpr int kHopPartKeys = 7168;               // ids a partition may hold on average, by the hop's bound
+constexpr int kHopMaxPartsLog2 = 8;
+constexpr int kHopGranules = 1024;               // most granules (runs of tiles, one tile as a rule) per hop
+constexpr uint32_t kRepeat = 0x80000000u;        // marks a repeat in an entry's upper half, above the position it repeats
 constexpr int kDedupBlock = 1024;
-__device__ __forceinline__ bool lds_insert_min(unsigned long long* tab, uint32_t slot, uint32_t key, uint32_t value) {
-    const unsigned long long want = ((unsigned long long)key << 32) | value;
-    for (int probes = 0; probes < kLdsSlots; ++probes) {
-        unsigned long long cur = tab[slot];
-        if (cur == kEmpty) {
-            const unsigned long long old = atomicCAS(&tab[slot], (unsigned long long)kEmpty, want);
-            if (old == kEmpty) return true;
-            cur = old;
-        }
-        if ((uint32_t)(cur >> 32) == key) {
-            if (want < cur) atomicMin(&tab[slot], want);
-            return true;
-        }
-        slot = (slot + 1) & (kLdsSlots - 1);
-    }
-    return false;
-}
-__device__ __forceinline__ uint32_t lds_find(const unsigned long long* tab, uint32_t slot, uint32_t key) {
-    for (int probes = 0; probes < kLdsSlots; ++probes) {
-        const unsigned long long cur = tab[slot];
-        if ((uint32_t)(cur >> 32) == key) return (uint32_t)cur;
-        if (cur == kEmpty) break;
-        slot = (slot + 1) & (kLdsSlots - 1);
-    }
-    return 0xFFFFFFFFu;                            // not reached for an id that was inserted
-}
-// Only one id in 2^k belongs to the workgroup's partition, so the ids that do are first gathered, per
-// wavefront, in a small queue in LDS (ballot, rank among the lanes that have one) and handed out 64
-// at a time: the atomics of an insertion then run with every lane busy.  (With each lane inserting
-// the ids it had read itself, an atomic instruction served 8 lanes of 64 and the LDS pipeline, which
-// takes one instruction at a time, set the pace: 0.37 ms for the last hop of 64 minibatches.)
-constexpr int kQueue = 2 * kWave;                 // entries a wavefront's queue holds
-struct WaveQueue {
-    unsigned long long* q;                        // this wavefront's kQueue entries: (id << 32 | payload)
-    int n;                                        // entries queued (the same in every lane)
-    // Queues `item` of the lanes where `has` is set.  Returns true when 64 entries are ready: `out` is
-    // this lane's (the queue keeps the rest).
-    __device__ __forceinline__ bool push(bool has, unsigned long long item, unsigned long long& out) {
-        const uint64_t m = __ballot(has);
-        if (has) q[n + __popcll(m & ((1ull << lane_id()) - 1ull))] = item;
-        n += __popcll(m);
-        if (n < kWave) return false;
-        out = q[lane_id()];
-        const unsigned long long rest = q[kWave + lane_id()];     // n < 2 * 64: at most 64 entries stay
-        n -= kWave;
-        if (lane_id() < n) q[lane_id()] = rest;
-        return true;
-    }
-    // What is left at the end: true in the lanes that get an entry.
-    __device__ __forceinline__ bool drain(unsigned long long& out) {
-        const bool mine = lane_id() < n;
-        if (mine) out = q[lane_id()];
-        n = 0;
-        return mine;
-    }
-};
+constexpr int kDirectSeeds = 4096;               // up to this many seeds, hop 1 sums the seeds before a tile itself
 
-__global__ void __launch_bounds__(kDedupBlock) dedup_lds_kernel(SampleArgs a, const BatchTable* __restrict__ t) {
-    extern __shared__ unsigned long long ltab[];
-    const int jb = blockIdx.x;                     // partitions are the slow index: the workgroups of partitions
-    const uint32_t part = blockIdx.y;              // that a minibatch does not use come last and leave at once
-    const uint32_t k = t->b[jb].tinfo[3];
-    if (t->b[jb].tinfo[2] || k == kGlobalTable || part >= (1u << k)) return;
-    const int64_t n_prev = t->b[jb].counts[a.h - 1];
-    const int64_t e_h = t->b[jb].counts[kE + a.h];
-    const int32_t* __restrict__ S = t->b[jb].S;
-    const int32_t* __restrict__ gids = gids_of(a, jb);
-    int32_t* __restrict__ flat = flat_of(a, jb);
-    WaveQueue wq;
-    wq.q = ltab + kLdsSlots + (threadIdx.x >> 6) * kQueue;
-    wq.n = 0;
-    for (int i = threadIdx.x; i < kLdsSlots; i += kDedupBlock) ltab[i] = kEmpty;
-    __syncthreads();
-    // hash bits: the top k name the partition, the 14 below them the slot
-    auto mine = [&](uint32_t key) { return k == 0 || ((key * 0x9E3779B1u) >> (32 - k)) == part; };
-    auto slot_of = [&](uint32_t key) { return ((key * 0x9E3779B1u) << k) >> (32 - 14); };
-    // The lists are short (tens of thousands of ids) and every workgroup of the minibatch reads all of
-    // them, so a pass is a chain of L2 round trips: eight loads per thread are in flight at a time.
-    // Whole wavefronts walk the rounds together (the queue's ballots need every lane).
-    constexpr int kU = 8;
-    bool ok = true;
-    auto insert = [&](unsigned long long item) {
-        const uint32_t key = (uint32_t)(item >> 32);
-        ok = lds_insert_min(ltab, slot_of(key), key, (uint32_t)item) && ok;
-    };
-    auto insert_all = [&](const int32_t* __restrict__ ids, int64_t count, int64_t first_value) {
-        const int64_t rounds = (count + (int64_t)kDedupBlock * kU - 1) / ((int64_t)kDedupBlock * kU);
-        for (int64_t r = 0; r < rounds; ++r) {
-            const int64_t i0 = r * kDedupBlock * kU + threadIdx.x;
-            uint32_t key[kU];
+// What the hop's kernels share.
+struct HopArgs {
+    const int64_t* rowptr;
+    const int32_t* col;
+    int64_t        N;
+    uint64_t*      ent;                 // per minibatch `ent_stride` entries (id << 32 | position), tile after tile, by partition
+    int64_t        ent_stride;          //   inside a tile; position: an index into S_{h-1}, or n_{h-1} + edge.  The upper half
+                                        //   of an edge whose id appeared before becomes kRepeat | the first position of the id
+    uint32_t*      seg;                 // per minibatch: [partition][tile] the run's start in the tile << 16 | its length
+    int64_t        seg_stride;
+    int64_t*       row0;                // per minibatch, per member of S_{L-1}: where its row starts in col[], its length
+    int32_t*       deg;
+    int64_t        node_stride;
+    uint32_t*      csum;                // per minibatch two arrays of `csum_stride`, used by odd and even hops: edges of the
+    int64_t        csum_stride;         //   hop per 256 targets; all zero between calls
+    uint32_t*      fsum;                // per minibatch kHopGranules: first appearances per granule of tiles; all zero between calls
+    unsigned long long* totals;
+    int*           bad;
+    int*           bad_next;
+    int64_t*       mirror;              // pinned host memory for the counts and flags of a call that is waited for, or null
+    int            n_items;
+    int            L, h, f, f_next;     // f_next: fanout of hop h + 1 (0 at the last hop)
+    uint64_t       seed;
+};
+__device__ __forceinline__ uint32_t* csum_of(const HopArgs& a, int j, int h) {
+    return a.csum + ((int64_t)j * 2 + (h & 1)) * a.csum_stride;
+}
+// Targets per tile: 256 where the call fills the chip with such tiles (about two per CU), fewer below
+// that, so that a single minibatch spreads over the CUs; the edges of a tile fit its LDS array.
+__host__ __device__ __forceinline__ int hop_tile_cap(int f) { return f <= 16 ? 256 : f <= 32 ? 128 : 64; }
+__host__ __device__ __forceinline__ int hop_tile_targets(int64_t n_prev, int n_items, int f) {
+    const int cap = hop_tile_cap(f);
+    int T = 16;
+    while (T < cap && (int64_t)T * 1024 <= n_prev * n_items) T <<= 1;
+    return T;
+}
+// log2 of the partitions: few enough ids per partition for its table, and (small calls) enough
+// partitions for half the CUs while each keeps 2048 ids by the bound.
+__host__ __device__ __forceinline__ int hop_parts_log2(int64_t n_prev, int n_items, int f) {
+    const int64_t keys = n_prev * (1 + f);
+    int k = 0;
+    while (k < kHopMaxPartsLog2 && (keys >> k) > kHopPartKeys) ++k;
+    while (k < kHopMaxPartsLog2 && ((int64_t)n_items << k) < 128 && (keys >> k) > 2048) ++k;
+    return k;
+}
+// log2 of the tiles per granule.
+__host__ __device__ __forceinline__ int hop_granule_log2(uint32_t ntiles) {
+    int g = 0;
+    while ((ntiles >> g) >= (uint32_t)kHopGranules) ++g;
+    return g;
+}
+
+// The seeds of a call: hop 1 takes them from its argument block.
+struct SeedsArg {
+    BatchDynAll dyn;
+    __device__ __forceinline__ int64_t n(const BatchDesc&, int j, int) const { return dyn.d[j].nseeds; }
+    __device__ __forceinline__ uint32_t batch_lo(const BatchDesc&, int j) const { return dyn.d[j].batch_lo; }
+};
+struct NoSeedsArg {
+    __device__ __forceinline__ int64_t n(const BatchDesc& b, int, int h) const { return b.counts[h - 1]; }
+    __device__ __forceinline__ uint32_t batch_lo(const BatchDesc& b, int) const { return b.batch_lo; }
+};
+__device__ __forceinline__ int32_t checked_seed(const HopArgs& a, int32_t v) {
+    if (v >= 0 && v < a.N) return v;
+    atomicOr(a.bad, 1);                          // reported; vertex 0 keeps later row reads in range
+    return 0;
+}
+__device__ __forceinline__ void start_counts(BatchDesc& b, const BatchDyn& dyn) {
+    int64_t* c = b.counts;
+    for (int k = 1; k <= SPP_MAX_L; ++k) c[k] = 0;
+    for (int k = 0; k <= SPP_MAX_L; ++k)
+        if (k != 1) c[kE + k] = 0;               // e_1 is written by the tile that ends hop 1
+    c[0] = dyn.nseeds;
+    b.batch_lo = dyn.batch_lo;
+}
+
+// More seeds than hop 1 sums by itself: S_0, its rows and the edge sums of hop 1 in a launch before it.
+__global__ void __launch_bounds__(kBlock) hop_seeds_kernel(HopArgs a, BatchTable* t, BatchDynAll dyn) {
+    __shared__ int lds[4];
+    const BatchBlock bb = batch_block();
+    const int j = bb.j;
+    const BatchDyn& d = dyn.d[j];
+    if (bb.x == 0 && threadIdx.x == 0) start_counts(t->b[j], d);
+    for (int64_t base = (int64_t)bb.x * kHopTargets; base < d.nseeds; base += (int64_t)gridDim.x * kHopTargets) {
+        const int64_t i = base + threadIdx.x;
+        int c = 0;
+        if (i < d.nseeds) {
+            const int32_t v = checked_seed(a, d.seeds[i]);
+            const int64_t r0 = a.rowptr[v], len = a.rowptr[v + 1] - r0;
+            t->b[j].S[i] = v;
+            a.row0[(int64_t)j * a.node_stride + i] = r0;
+            a.deg[(int64_t)j * a.node_stride + i] = (int32_t)len;
+            c = len < a.f ? (int)len : a.f;
+        }
+        const int sum = block_reduce_sum(c, lds);
+        if (threadIdx.x == 0) csum_of(a, j, 1)[base / kHopTargets] = (uint32_t)sum;
+    }
+}
+
+// A repeated id takes the local id of its first appearance (an earlier edge of the same hop, final
+// since the launch that numbered it), which the numbering left as a negative edge index.
+__device__ __forceinline__ void relabel_repeats(const BatchDesc& b, int h, unsigned x, unsigned gx) {
+    const int64_t e_h = b.counts[kE + h];
+    int32_t* src = b.src[h - 1];
+    for (int64_t e = (int64_t)x * kBlock + threadIdx.x; e < e_h; e += (int64_t)gx * kBlock) {
+        const int32_t v = src[e];
+        if (v < 0) src[e] = src[~v];
+    }
+}
+
+// Floyd's subset algorithm for one target, one draw per slot: m = d - f + j, t uniform on [0, m]; slot j
+// takes t unless an earlier slot already holds it, else m (which none holds).  A lane draws a whole
+// subset: the four words of a Philox block serve four slots (a lane per slot computed the block for
+// each of them and spent seven times the instructions).
+template <int F>
+__device__ __forceinline__ void floyd_positions(uint64_t seed, uint32_t batch_lo, uint32_t hop, uint32_t v, int32_t d, int f,
+                                                uint32_t (&pos)[F]) {
 #pragma unroll
-            for (int u = 0; u < kU; ++u)
-                if (i0 + u * kDedupBlock < count) key[u] = (uint32_t)ids[i0 + u * kDedupBlock];
+    for (int q = 0; q < F / 4; ++q) {
+        if (4 * q >= f) continue;
+        const Philox4 r = philox4x32_10(v, (uint32_t)q, hop, batch_lo, (uint32_t)seed, (uint32_t)(seed >> 32));
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const bool has = i0 + u * kDedupBlock < count && mine(key[u]);
-                unsigned long long item;
-                if (wq.push(has, ((unsigned long long)key[u] << 32) | (uint32_t)(first_value + i0 + u * kDedupBlock), item)) insert(item);
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t m = (uint32_t)(d - f + 4 * q + i);
+            uint32_t t = __umulhi(r.w[i], m + 1u);
+            bool held = false;
+#pragma unroll
+            for (int p = 0; p < 4 * q + i; ++p) held |= pos[p] == t;
+            pos[4 * q + i] = held ? m : t;
+        }
+    }
+}
+
+// One tile of T consecutive targets at a time.  With F <= 16 slots (F >= f) a lane draws a target's
+// subset, else a group of F lanes does (the comparisons of 64 slots do not belong in one lane).  The
+// ids meet in an LDS array in edge order, from which the tile's entries are dealt to the partitions: a
+// wavefront ranks 64 entries at a time among those of the same partition with ballots over the
+// partition's bits, so the deal needs no LDS atomics (a handful of partitions made them collide) and
+// keeps the order.  Bound by the latency of the random reads of col[].
+template <int F, class Seeds>
+__global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchTable* __restrict__ t, Seeds seeds) {
+    constexpr bool kFirst = !__is_same(Seeds, NoSeedsArg);
+    constexpr int kEdges = F <= 16 ? kHopTargets * F : kHopEdges;       // T * f, at most
+    static_assert(kEdges <= kHopEdges, "a tile's edges");
+    __shared__ int32_t gid_lds[kEdges];
+    __shared__ uint16_t rank_lds[kEdges + kHopTargets];
+    __shared__ int32_t tv[kHopTargets], toff[kHopTargets], tdeg[kHopTargets];
+    __shared__ int64_t trow[kHopTargets];
+    __shared__ uint32_t cnt[kBlock / kWave][1 << kHopMaxPartsLog2];      // entries, then first place, per wavefront and partition
+    __shared__ int scan_lds[4];
+    static_assert((1 << kHopMaxPartsLog2) <= kBlock && kHopTargets <= kBlock, "one partition and one target per thread");
+    const BatchBlock bb = batch_block();
+    const int jb = bb.j;
+    BatchDesc& b = t->b[jb];
+    const int64_t n_prev = seeds.n(b, jb, a.h);
+    const uint32_t batch_lo = seeds.batch_lo(b, jb);
+    const int f = a.f;
+    const int T = hop_tile_targets(n_prev, a.n_items, f);
+    const int k = hop_parts_log2(n_prev, a.n_items, f);
+    const int64_t ntiles = n_prev > 0 ? (n_prev + T - 1) / T : 1;
+    int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
+    int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
+    int32_t* __restrict__ S = b.S;
+    int32_t* __restrict__ indptr = b.indptr[a.h - 1];
+    uint64_t* __restrict__ ent = a.ent + (int64_t)jb * a.ent_stride;
+    uint32_t* __restrict__ seg = a.seg + (int64_t)jb * a.seg_stride;
+    const uint32_t* __restrict__ csum = csum_of(a, jb, a.h);
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+
+    if constexpr (kFirst) {
+        if (bb.x == 0 && threadIdx.x == 0) start_counts(b, seeds.dyn.d[jb]);
+    }
+    for (int64_t tile = bb.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t i0 = tile * T;
+        const int nt = n_prev - i0 < T ? (int)(n_prev - i0) : T;
+        // edges of the targets before the tile
+        int before = 0;
+        if constexpr (kFirst) {
+            for (int64_t i = threadIdx.x; i < i0; i += kBlock) {
+                const int32_t v = checked_seed(a, seeds.dyn.d[jb].seeds[i]);
+                const int64_t d = a.rowptr[v + 1] - a.rowptr[v];
+                before += d < f ? (int)d : f;
+            }
+        } else {
+            const int64_t g0 = i0 / kHopTargets;
+            for (int64_t g = threadIdx.x; g < g0; g += kBlock) before = uadd(before, (int)csum[g]);
+            const int64_t i = g0 * kHopTargets + threadIdx.x;
+            if (i < i0) { const int d = deg[i]; before += d < f ? d : f; }
+        }
+        int c = 0, c_next = 0;
+        if ((int)threadIdx.x < nt) {
+            const int64_t i = i0 + threadIdx.x;
+            int32_t v, d;
+            int64_t r0;
+            if constexpr (kFirst) {
+                v = checked_seed(a, seeds.dyn.d[jb].seeds[i]);
+                r0 = a.rowptr[v];
+                d = (int32_t)(a.rowptr[v + 1] - r0);
+                S[i] = v; row0[i] = r0; deg[i] = d;
+            } else {
+                v = S[i]; r0 = row0[i]; d = deg[i];
+            }
+            tv[threadIdx.x] = v; trow[threadIdx.x] = r0; tdeg[threadIdx.x] = d;
+            c = d < f ? d : f;
+            c_next = d < a.f_next ? d : a.f_next;
+        }
+        if (threadIdx.x < (1u << k))
+            for (int w = 0; w < kBlock / kWave; ++w) cnt[w][threadIdx.x] = 0;
+        int n_e;
+        const int off = block_exclusive_scan(c, scan_lds, n_e);
+        if ((int)threadIdx.x < nt) toff[threadIdx.x] = off;
+        const int64_t ebase = (int64_t)(uint32_t)block_reduce_sum(before, scan_lds);      // its barriers publish the targets
+        if (a.f_next) {                          // the targets are targets of the next hop too
+            const int s = block_reduce_sum(c_next, scan_lds);
+            if (threadIdx.x == 0 && s) atomicAdd(&csum_of(a, jb, a.h + 1)[i0 / kHopTargets], (uint32_t)s);
+        }
+        if ((int)threadIdx.x < nt) indptr[i0 + threadIdx.x] = (int32_t)(ebase + off);
+        if (tile == ntiles - 1 && threadIdx.x == 0) {
+            indptr[n_prev] = (int32_t)(ebase + n_e);
+            b.counts[kE + a.h] = ebase + n_e;
+            atomicAdd(&a.totals[2], (unsigned long long)(ebase + n_e));
+        }
+        // the draws
+        if constexpr (F <= 16) {
+            if ((int)threadIdx.x < nt) {
+                const int32_t d = tdeg[threadIdx.x];
+                const int n = d < f ? d : f;
+                uint32_t pos[F];
+#pragma unroll
+                for (int u = 0; u < F; ++u) pos[u] = (uint32_t)u;        // d <= f: the whole row, in row order
+                if (d > f) floyd_positions<F>(a.seed, batch_lo, (uint32_t)a.h, (uint32_t)tv[threadIdx.x], d, f, pos);
+                const int64_t r0 = trow[threadIdx.x];
+                int32_t gid[F];
+#pragma unroll
+                for (int u = 0; u < F; ++u) if (u < n) gid[u] = a.col[r0 + pos[u]];
+#pragma unroll
+                for (int u = 0; u < F; ++u) if (u < n) gid_lds[off + u] = gid[u];
+            }
+        } else {
+            constexpr int kGroups = kBlock / F;
+            const int jl = lane & (F - 1);           // slot handled by this lane
+            const int gbase = lane - jl;             // first lane of the group inside the wavefront
+            const uint64_t gmask = (F == 64) ? ~0ull : (((1ull << (F & 63)) - 1ull) << gbase);
+            for (int q0 = 0; q0 < nt; q0 += kGroups) {
+                const int q = q0 + (int)threadIdx.x / F;
+                const bool valid = q < nt;
+                const int d = valid ? tdeg[q] : 0;
+                const bool floyd = d > f;
+                uint32_t pos = (uint32_t)jl;
+                if (__any(floyd)) {
+                    const uint32_t m = (uint32_t)(d - f + jl);
+                    uint32_t tt = 0;
+                    if (floyd && jl < f) {
+                        const uint32_t r = rand32(a.seed, batch_lo, (uint32_t)a.h, (uint32_t)tv[q], (uint32_t)jl);
+                        tt = __umulhi(r, m + 1u);
+                        pos = tt;
+                    }
+                    for (int jj = 1; jj < f; ++jj) {
+                        const uint32_t tj = (uint32_t)__shfl((int)tt, gbase + jj, kWave);
+                        const uint64_t hit = __ballot(floyd && jl < jj && pos == tj) & gmask;
+                        if (jl == jj && hit != 0ull) pos = m;
+                    }
+                }
+                if (valid && jl < (floyd ? f : d)) gid_lds[toff[q] + jl] = a.col[trow[q] + (int64_t)pos];
             }
         }
-    };
-    insert_all(S, n_prev, 0);
-    insert_all(gids, e_h, n_prev);
-    {
-        unsigned long long item;
-        if (wq.drain(item)) insert(item);
+        __syncthreads();
+        // the tile's entries (its edges, then its targets), dealt to the partitions; a wavefront takes 64
+        // consecutive entries of every 256
+        const int n_ent = n_e + nt;
+        auto key_of = [&](int x) { return (uint32_t)(x < n_e ? gid_lds[x] : tv[x - n_e]); };
+        auto part_of = [&](uint32_t key) { return k == 0 ? 0u : (key * 0x9E3779B1u) >> (32 - k); };
+        for (int x0 = 0; x0 < n_ent; x0 += kBlock) {
+            const int x = x0 + (int)threadIdx.x;
+            const bool has = x < n_ent;
+            const uint32_t p = has ? part_of(key_of(x)) : 0u;
+            uint64_t same = __ballot(has);
+            for (int bit = 0; bit < k; ++bit) {
+                const bool one = (p >> bit) & 1u;
+                const uint64_t bm = __ballot(one);
+                same &= one ? bm : ~bm;
+            }
+            const uint32_t below = (uint32_t)__popcll(same & lt_mask);
+            const uint32_t prior = cnt[wave][p];
+            if (has && below == 0) cnt[wave][p] = prior + (uint32_t)__popcll(same);
+            if (has) rank_lds[x] = (uint16_t)(prior + below);
+        }
+        __syncthreads();
+        {
+            uint32_t c4[kBlock / kWave], mine = 0;
+            if (threadIdx.x < (1u << k))
+#pragma unroll
+                for (int w = 0; w < kBlock / kWave; ++w) { c4[w] = cnt[w][threadIdx.x]; mine += c4[w]; }
+            int all;
+            uint32_t st = (uint32_t)block_exclusive_scan((int)mine, scan_lds, all);
+            if (threadIdx.x < (1u << k)) {
+                seg[(int64_t)threadIdx.x * ntiles + tile] = (st << 16) | mine;
+#pragma unroll
+                for (int w = 0; w < kBlock / kWave; ++w) { cnt[w][threadIdx.x] = st; st += c4[w]; }
+            }
+        }
+        __syncthreads();
+        const int64_t ent0 = ebase + i0;
+        for (int x = threadIdx.x; x < n_ent; x += kBlock) {      // the same entries as above: a wavefront's own places
+            const uint32_t key = key_of(x);
+            const uint32_t value = x < n_e ? (uint32_t)(n_prev + ebase + x) : (uint32_t)(i0 + x - n_e);
+            ent[ent0 + cnt[wave][part_of(key)] + rank_lds[x]] = ((uint64_t)key << 32) | value;
+        }
+        __syncthreads();                         // the next tile overwrites the LDS arrays
     }
-    if (!ok) atomicOr(a.bad, 4);
-    __syncthreads();
-    auto resolve = [&](unsigned long long item) {
-        const uint32_t key = (uint32_t)(item >> 32);
-        flat[(uint32_t)item] = (int32_t)lds_find(ltab, slot_of(key), key);
+    if constexpr (!kFirst) {
+        // what the hop before left: its granules' sums, and the repeats of its ids
+        if (bb.x == 0)
+            for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)jb * kHopGranules + g] = 0u;
+        if (a.h > 1) relabel_repeats(b, a.h - 1, bb.x, gridDim.x);
+    }
+}
+
+// A partition's table: ids and smallest positions in two arrays (all ones: empty), buckets of four slots.
+// An insertion reads a bucket's ids at once, claims an empty slot with a 32-bit compare-and-swap if the
+// id is not there, and offers its position with an atomic minimum that returns nothing.  (64-bit
+// entries probed slot by slot took a 64-bit compare-and-swap, the dearest LDS instruction, at each of the
+// five or six probes of a wavefront's unluckiest lane.)  Returns the slot, or -1: no room.
+constexpr uint32_t kNoId = 0xFFFFFFFFu;
+__device__ __forceinline__ int hop_insert(uint32_t* ids, uint32_t* first, uint32_t home, uint32_t key, uint32_t pos) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    uint32_t bucket = home >> 2;
+    for (int probes = 0; probes < 128;) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(ids + 4 * bucket);
+        int hit = w.x == key ? 0 : w.y == key ? 1 : w.z == key ? 2 : w.w == key ? 3 : -1;
+        if (hit < 0) {
+            const int empty = w.x == kNoId ? 0 : w.y == kNoId ? 1 : w.z == kNoId ? 2 : w.w == kNoId ? 3 : -1;
+            if (empty < 0) { bucket = (bucket + 1) & (kHopSlots / 4 - 1); ++probes; continue; }
+            const uint32_t old = atomicCAS(&ids[4 * bucket + empty], kNoId, key);
+            if (old != kNoId && old != key) continue;          // another id took the slot: the bucket again
+            hit = empty;
+        }
+        const int slot = (int)(4 * bucket) + hit;
+        atomicMin(&first[slot], pos);
+        return slot;
+    }
+    return -1;
+}
+__device__ __forceinline__ int hop_find(const uint32_t* ids, uint32_t home, uint32_t key) {
+    uint32_t bucket = home >> 2;
+    for (int probes = 0; probes < 128; ++probes) {
+        for (int i = 0; i < 4; ++i) if (ids[4 * bucket + i] == key) return (int)(4 * bucket) + i;
+        bucket = (bucket + 1) & (kHopSlots / 4 - 1);
+    }
+    return 0;                                    // not reached for an id that was inserted
+}
+
+// One workgroup per partition (or several partitions in turn).  The runs of up to 1024 tiles are laid
+// end to end (a scan of their lengths in LDS), so that every lane has an entry whatever the length of
+// a run; a lane finds its run by bisection.  Entries go into the table, and after a barrier every edge
+// takes the smallest position of its id.  Up to 8192 entries a lane keeps its own in registers between
+// the two; beyond that they are walked twice.  A partition whose ids do not fit the table (a hop beyond
+// 256 partitions of 7168 ids, or ids that share their hash's top bits) is taken in 2^r parts by the next
+// r bits of the hash; at 19 bits in all at most four ids of a part share a bucket, because the hash is
+// a bijection of 32-bit ids: any input fits.
+__global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const BatchTable* __restrict__ t) {
+    extern __shared__ __align__(16) uint32_t dedup_lds[];
+    uint32_t* ids = dedup_lds;                                          // [kHopSlots]
+    uint32_t* firsts = ids + kHopSlots;                                 // [kHopSlots]
+    uint32_t* hist = firsts + kHopSlots;                                // [kHopGranules]
+    uint32_t* pre = hist + kHopGranules;                                // [kDedupBlock] entries before run i
+    uint32_t* adr = pre + kDedupBlock;                                  // [kDedupBlock] where run i lies, less pre[i]
+    uint32_t* wsum = adr + kDedupBlock;                                 // [kDedupBlock / kWave]
+    const int jb = blockIdx.x;                   // partitions are the slow index: workgroups without one come last
+    const BatchDesc& b = t->b[jb];
+    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1], e_h = (uint32_t)b.counts[kE + a.h];     // below 2^30 each
+    const int T = hop_tile_targets(n_prev, a.n_items, a.f);
+    const int k = hop_parts_log2(n_prev, a.n_items, a.f);
+    const uint32_t ntiles = n_prev > 0 ? (n_prev + T - 1) / T : 1;
+    if (blockIdx.y == 0) {                       // this hop's edge sums have been read: empty them
+        uint32_t* cs = csum_of(a, jb, a.h);
+        for (uint32_t g = threadIdx.x; g * kHopTargets < n_prev; g += kDedupBlock) cs[g] = 0u;
+    }
+    const int gshift = hop_granule_log2(ntiles);
+    const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
+    uint64_t* ent = a.ent + (int64_t)jb * a.ent_stride;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    auto resolve = [&](uint32_t at, uint32_t tile, uint32_t pos, int slot) {
+        if (pos < n_prev) return;
+        const uint32_t first = firsts[slot];
+        if (first == pos) atomicAdd(&hist[tile >> gshift], 1u);
+        else reinterpret_cast<uint32_t*>(ent + at)[1] = kRepeat | first;
     };
-    const int64_t rounds = (e_h + (int64_t)kDedupBlock * kU - 1) / ((int64_t)kDedupBlock * kU);
-    for (int64_t r = 0; r < rounds; ++r) {
-        const int64_t e0 = r * kDedupBlock * kU + threadIdx.x;
-        uint32_t key[kU];
+    const bool one_layout = ntiles <= (uint32_t)kDedupBlock;
+    const uint32_t top = 1u << (31 - __clz((int)(one_layout ? ntiles : (uint32_t)kDedupBlock)));
+
+    for (int part = blockIdx.y; part < (1 << k); part += gridDim.y) {
+        const uint32_t* __restrict__ seg = a.seg + (int64_t)jb * a.seg_stride + (int64_t)part * ntiles;
+        uint32_t total = 0;                      // entries of the runs laid out at present
+        auto lay_out = [&](uint32_t c0) {
+            __syncthreads();                     // the runs before are no longer read
+            uint32_t len = 0, at = 0;
+            const uint32_t tile = c0 + threadIdx.x;
+            if (tile < ntiles) {
+                const uint32_t s = seg[tile];
+                len = s & 0xFFFFu;
+                at = (uint32_t)indptr[tile * T] + tile * T + (s >> 16);
+            }
+            const uint32_t inc = (uint32_t)wave_inclusive_scan((int)len);
+            if (lane == kWave - 1) wsum[wave] = inc;
+            __syncthreads();
+            uint32_t base = 0, all = 0;
+            for (int w = 0; w < kDedupBlock / kWave; ++w) { const uint32_t v = wsum[w]; all += v; if (w < wave) base += v; }
+            const uint32_t ex = base + inc - len;
+            pre[threadIdx.x] = ex;
+            adr[threadIdx.x] = at - ex;
+            total = all;
+            __syncthreads();
+        };
+        auto run_of = [&](uint32_t x, uint32_t n) {  // the run of entry x of the n runs laid out: last one with pre[r] <= x
+            uint32_t r = 0;
+            for (uint32_t s = top; s > 0; s >>= 1)
+                if (r + s < n && pre[r + s] <= x) r += s;
+            return r;
+        };
+        // all entries of the partition, for the partitions that do not fit a lane's registers
+        auto walk = [&](auto&& fn) {
+            for (uint32_t c0 = 0; c0 < ntiles; c0 += kDedupBlock) {
+                if (!one_layout) lay_out(c0);
+                const uint32_t n = ntiles - c0 < (uint32_t)kDedupBlock ? ntiles - c0 : kDedupBlock;
+                for (uint32_t x = threadIdx.x; x < total; x += kDedupBlock) {
+                    const uint32_t r = run_of(x, n), at = adr[r] + x;
+                    fn(ent[at], at, c0 + r);
+                }
+            }
+        };
+        auto empty_table = [&]() {
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const u32x4 ones = {kNoId, kNoId, kNoId, kNoId};
+            for (int i = threadIdx.x; i < 2 * kHopSlots / 4; i += kDedupBlock) reinterpret_cast<u32x4*>(ids)[i] = ones;
+        };
+        auto hash_of = [](uint32_t key) { return key * 0x9E3779B1u; };
+        bool done = false;
+        int rbits = 0;
+        if (threadIdx.x < kHopGranules) hist[threadIdx.x] = 0u;
+        empty_table();
+        if (one_layout) lay_out(0); else __syncthreads();
+        constexpr int R = 8;
+        if (one_layout && total <= R * kDedupBlock) {
+            uint32_t pos[R], slot_run[R];        // slot << 16 | run (a run is one of 1024 at most)
+            bool ok = true;
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (e0 + u * kDedupBlock < e_h) key[u] = (uint32_t)gids[e0 + u * kDedupBlock];
+            for (int u0 = 0; u0 < R; u0 += 4) {
+                unsigned long long e[4];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const bool has = e0 + u * kDedupBlock < e_h && mine(key[u]);
-            unsigned long long item;
-            if (wq.push(has, ((unsigned long long)key[u] << 32) | (uint32_t)(e0 + u * kDedupBlock), item)) resolve(item);
+                for (int u = 0; u < 4; ++u)
+                    if (threadIdx.x + (u0 + u) * kDedupBlock < total) {
+                        slot_run[u0 + u] = run_of(threadIdx.x + (u0 + u) * kDedupBlock, ntiles);
+                        e[u] = ent[adr[slot_run[u0 + u]] + threadIdx.x + (u0 + u) * kDedupBlock];
+                    }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (threadIdx.x + (u0 + u) * kDedupBlock < total) {
+                        const uint32_t key = (uint32_t)(e[u] >> 32);
+                        pos[u0 + u] = (uint32_t)e[u];
+                        const int slot = hop_insert(ids, firsts, (hash_of(key) << k) >> (32 - kHopSlotBits), key, pos[u0 + u]);
+                        slot_run[u0 + u] |= (uint32_t)slot << 16;
+                        ok = ok && slot >= 0;
+                    }
+            }
+            if (!__syncthreads_or(!ok)) {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (threadIdx.x + u * kDedupBlock < total) {
+                        const uint32_t r = slot_run[u] & 0xFFFFu;
+                        resolve(adr[r] + threadIdx.x + u * kDedupBlock, r, pos[u], (int)(slot_run[u] >> 16));
+                    }
+                done = true;
+            } else {
+                rbits = 1;
+            }
+        } else {
+            while (k + rbits < 32 - kHopSlotBits && ((n_prev + e_h) >> (k + rbits)) > (uint32_t)kHopSlots) ++rbits;
+        }
+        while (!done) {
+            done = true;
+            __syncthreads();
+            if (threadIdx.x < kHopGranules) hist[threadIdx.x] = 0u;
+            for (uint32_t r = 0; r < (1u << rbits) && done; ++r) {
+                empty_table();
+                __syncthreads();
+                auto in_part = [&](uint32_t key) { return rbits == 0 || ((hash_of(key) << k) >> (32 - rbits)) == r; };
+                auto home_of = [&](uint32_t key) { return (hash_of(key) << (k + rbits)) >> (32 - kHopSlotBits); };
+                bool ok = true;
+                walk([&](uint64_t e, uint32_t, uint32_t) {
+                    const uint32_t key = (uint32_t)(e >> 32);
+                    // an entry that an earlier attempt has marked repeats an id whose first entry is still there
+                    if (!(key & kRepeat) && in_part(key)) ok = hop_insert(ids, firsts, home_of(key), key, (uint32_t)e) >= 0 && ok;
+                });
+                if (__syncthreads_or(!ok)) { ++rbits; done = false; break; }
+                walk([&](uint64_t e, uint32_t at, uint32_t tile) {
+                    const uint32_t key = (uint32_t)(e >> 32);
+                    if ((uint32_t)e >= n_prev && !(key & kRepeat) && in_part(key))
+                        resolve(at, tile, (uint32_t)e, hop_find(ids, home_of(key), key));
+                });
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < kHopGranules && hist[threadIdx.x])
+            atomicAdd(&a.fsum[(int64_t)jb * kHopGranules + threadIdx.x], hist[threadIdx.x]);
+        __syncthreads();
+    }
+}
+static_assert(kHopGranules <= kDedupBlock, "one granule per thread");
+
+// Numbers the first appearances, a granule of tiles at a time: a tile's entries go back to edge order
+// through LDS, the new vertices are appended to S_h in order, and the row of a vertex that will be a
+// target of the next hop is looked up here, once.
+__global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const BatchTable* __restrict__ t) {
+    __shared__ uint32_t what[kHopEdges];         // per edge of the tile: the upper half of its entry
+    __shared__ int scan_lds[4];
+    __shared__ uint32_t next_sum[1024 / kHopTargets + 2];
+    const BatchBlock bb = batch_block();
+    const int jb = bb.j;
+    const BatchDesc& b = t->b[jb];
+    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1];
+    const int T = hop_tile_targets(n_prev, a.n_items, a.f);
+    const uint32_t ntiles = n_prev > 0 ? (n_prev + T - 1) / T : 1;
+    const int gshift = hop_granule_log2(ntiles);
+    const uint32_t ngran = (ntiles + (1u << gshift) - 1) >> gshift;
+    const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
+    const uint64_t* __restrict__ ent = a.ent + (int64_t)jb * a.ent_stride;
+    const uint32_t* __restrict__ fsum = a.fsum + (int64_t)jb * kHopGranules;
+    int32_t* __restrict__ src = b.src[a.h - 1];
+    int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
+    int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
+    for (uint32_t g = bb.x; g < ngran; g += gridDim.x) {
+        int before = 0;
+        for (uint32_t i = threadIdx.x; i < g; i += kBlock) before = uadd(before, (int)fsum[i]);
+        uint32_t id0 = n_prev + (uint32_t)block_reduce_sum(before, scan_lds);      // the next new vertex
+        const uint32_t tend = ((g + 1) << gshift) < ntiles ? (g + 1) << gshift : ntiles;
+        for (uint32_t tile = g << gshift; tile < tend; ++tile) {
+            const uint32_t i0 = tile * T, i1 = i0 + T < n_prev ? i0 + T : n_prev;
+            const uint32_t ebase = (uint32_t)indptr[i0], n_e = (uint32_t)indptr[i1] - ebase;
+            const uint32_t n_ent = n_e + (i1 - i0);
+            for (uint32_t x = threadIdx.x; x < n_ent; x += kBlock) {
+                const uint64_t e = ent[ebase + i0 + x];
+                if ((uint32_t)e >= n_prev) what[(uint32_t)e - n_prev - ebase] = (uint32_t)(e >> 32);
+            }
+            __syncthreads();
+            for (uint32_t e0 = 0; e0 < n_e; e0 += kBlock * 4) {
+                const uint32_t e = e0 + threadIdx.x * 4;       // four consecutive edges
+                uint32_t w[4];
+                int mine = 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    w[u] = e + u < n_e ? what[e + u] : kRepeat;
+                    mine += w[u] < kRepeat ? 1 : 0;
+                }
+                if (threadIdx.x < sizeof(next_sum) / sizeof(next_sum[0])) next_sum[threadIdx.x] = 0u;
+                int total;
+                uint32_t id = id0 + (uint32_t)block_exclusive_scan(mine, scan_lds, total);
+                int64_t r0[4];
+                int32_t rlen[4];
+                if (a.f_next) {                  // all four rows' bounds are in flight together
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (w[u] < kRepeat) {
+                            r0[u] = a.rowptr[w[u]];
+                            rlen[u] = (int32_t)(a.rowptr[w[u] + 1] - r0[u]);
+                        }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (e + u >= n_e) continue;
+                    int32_t out;
+                    if (w[u] < kRepeat) {
+                        b.S[id] = (int32_t)w[u];
+                        if (a.f_next) {
+                            row0[id] = r0[u];
+                            deg[id] = rlen[u];
+                            atomicAdd(&next_sum[id / kHopTargets - id0 / kHopTargets], (uint32_t)(rlen[u] < a.f_next ? rlen[u] : a.f_next));
+                        }
+                        out = (int32_t)id++;
+                    } else {
+                        // an earlier vertex, or (left for the relabel) a first appearance earlier in this hop
+                        const uint32_t first = w[u] & ~kRepeat;
+                        out = first < n_prev ? (int32_t)first : ~(int32_t)(first - n_prev);
+                    }
+                    src[ebase + e + u] = out;
+                }
+                if (a.f_next) {
+                    __syncthreads();
+                    if (threadIdx.x < sizeof(next_sum) / sizeof(next_sum[0]) && next_sum[threadIdx.x])
+                        atomicAdd(&csum_of(a, jb, a.h + 1)[id0 / kHopTargets + threadIdx.x], next_sum[threadIdx.x]);
+                    __syncthreads();
+                }
+                id0 += (uint32_t)total;
+            }
+            __syncthreads();                     // the next tile overwrites what[]
+        }
+        if (g == ngran - 1 && threadIdx.x == 0) {
+            b.counts[a.h] = id0;
+            if (a.h == a.L) {
+                atomicAdd(&a.totals[1], (unsigned long long)id0);
+                atomicAdd(&a.totals[0], 1ull);
+                if (a.mirror) {
+                    int64_t* m = a.mirror + (int64_t)jb * 2 * kE;
+                    for (int q = 0; q < 2 * kE; ++q) m[q] = q == a.h ? (int64_t)id0 : b.counts[q];
+                    if (jb == 0) {
+                        int* fl = reinterpret_cast<int*>(a.mirror + (int64_t)kMaxBatches * 2 * kE);
+                        fl[0] = *a.bad; fl[1] = 0;
+                    }
+                }
+            }
         }
     }
-    {
-        unsigned long long item;
-        if (wq.drain(item)) resolve(item);
-    }
+}
+
+// After the last hop: its repeats, and what the next call expects empty.
+__global__ void __launch_bounds__(kBlock) hop_last_kernel(HopArgs a, const BatchTable* __restrict__ t) {
+    const BatchBlock bb = batch_block();
+    if (bb.x == 0)
+        for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)bb.j * kHopGranules + g] = 0u;
+    relabel_repeats(t->b[bb.j], a.h, bb.x, gridDim.x);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.bad_next[threadIdx.x] = 0;
 }
 
 // ---- steps 1 and 2 with given transition probabilities ----
@@ -642,16 +1111,13 @@ __global__ void __launch_bounds__(kBlock) general_sample_kernel(SampleArgs a, co
 struct NewIn {
     SampleArgs a; const BatchTable* t;
     __device__ int64_t n(int j) const { return t->b[j].tinfo[2] ? 0 : t->b[j].counts[kE + a.h]; }
-    // With the table in global memory, what the entry resolved to is read from its slot here (a
-    // random 8-byte read that moves a whole line) and kept in the slot's place; the outcome is left
-    // in the entry's place in the hop's src array (-2 first appearance, -1 repeat) for the second pass.
+    // What the entry resolved to is read from its slot here (a random 8-byte read that moves a whole
+    // line) and kept in the slot's place; the outcome is left in the entry's place in the hop's src
+    // array (-2 first appearance, -1 repeat) for the second pass.
     __device__ int operator()(int j, int64_t e) const {
         int32_t* __restrict__ flat = flat_of(a, j);
-        uint32_t val = (uint32_t)flat[e];
-        if (t->b[j].tinfo[3] == kGlobalTable) {
-            val = (uint32_t)tab_of(a, j)[val];
-            flat[e] = (int32_t)val;
-        }
+        const uint32_t val = (uint32_t)tab_of(a, j)[(uint32_t)flat[e]];
+        flat[e] = (int32_t)val;
         const int first = (int64_t)val == t->b[j].counts[a.h - 1] + e ? 1 : 0;
         t->b[j].src[a.h - 1][e] = first ? -2 : -1;
         return first;
@@ -728,13 +1194,6 @@ __global__ void __launch_bounds__(kBlock) relabel_kernel(SampleArgs a, const Bat
     // the call's last launch: nothing of this call touches the other set of flags
     if (a.h == a.L && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.bad_next[threadIdx.x] = 0;
 }
-// The relabel of hop h-1 riding at the head of hop h's first scan launch (it reads the table, the
-// flat ids and the counts of hop h-1, which that launch only reads too).
-struct RelabelPrev {
-    SampleArgs a; const BatchTable* t;         // a.h = the hop to relabel
-    __device__ void operator()(int j, unsigned x, unsigned gx) const { relabel_rows(a, t, j, x, gx); }
-};
-
 // Stores a table of per-minibatch pointers in device memory, sixteen entries per launch (a launch's
 // argument block holds 4 KB).  Only needed when a call brings buffers that no slot holds.
 constexpr int kStoreChunk = 16;
@@ -743,6 +1202,9 @@ __global__ void __launch_bounds__(kBlock) batch_table_store_kernel(BatchTableChu
     const uint64_t* s = reinterpret_cast<const uint64_t*>(&src);
     uint64_t* d = reinterpret_cast<uint64_t*>(&dst->b[first]);
     for (unsigned i = threadIdx.x; i < sizeof(BatchTableChunk) / sizeof(uint64_t); i += kBlock) d[i] = s[i];
+}
+__global__ void __launch_bounds__(kBlock) hop_sums_clear_kernel(uint32_t* p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = 0u;
 }
 // [0] error flag, [1] capacity flag of a call
 __global__ void sample_flags_clear_kernel(int* bad) {
@@ -769,6 +1231,43 @@ extern "C" int spp_mfg_bound(int32_t nseeds, const int32_t* fanouts, int32_t L, 
         n_bound[h] = n < N ? n : N;
     }
     return SPP_OK;
+}
+
+// The launches of a fanout-sampling call: three per hop and one after the last (the call on hops of a few
+// thousand edges takes 0.09 ms instead of 0.14 with six per hop).
+static void launch_hops(spp_ctx* ctx, spp::HopArgs a, spp::BatchTable* dt, const spp::BatchDynAll& dyn, const int32_t* fanouts,
+                        const int64_t* nb, const int64_t* eb, int max_seeds, size_t dedup_lds, hipStream_t st) {
+    using namespace spp;
+    // workgroups per minibatch: what the bound needs, eight per CU in the whole call at most (they take
+    // several tiles then); multiples of 8: see batch_block()
+    const int64_t share = std::max<int64_t>(8, (int64_t)ctx->num_cu * 8 / a.n_items);
+    auto grid = [&](int64_t need) {
+        const int64_t g = need < 1 ? 1 : (need < share ? need : share);
+        return dim3((unsigned)((g + 7) & ~(int64_t)7), (unsigned)a.n_items);
+    };
+    const bool direct = max_seeds <= kDirectSeeds;
+    for (int h = 1; h <= a.L; ++h) {
+        a.h = h; a.f = fanouts[h - 1]; a.f_next = h < a.L ? fanouts[h] : 0;
+        if (h == 1 && !direct) hop_seeds_kernel<<<grid((max_seeds + kHopTargets - 1) / kHopTargets), kBlock, 0, st>>>(a, dt, dyn);
+        const int64_t tiles = std::max<int64_t>(std::min<int64_t>(1024 / a.n_items, nb[h - 1] / 16), nb[h - 1] / hop_tile_cap(a.f)) + 1;
+        const int G = a.f <= 8 ? 8 : a.f <= 16 ? 16 : a.f <= 32 ? 32 : 64;
+        auto sample = [&](auto seeds) {
+            using Seeds = decltype(seeds);
+            switch (G) {
+                case 8:  hop_sample_kernel<8, Seeds><<<grid(tiles), kBlock, 0, st>>>(a, dt, seeds); break;
+                case 16: hop_sample_kernel<16, Seeds><<<grid(tiles), kBlock, 0, st>>>(a, dt, seeds); break;
+                case 32: hop_sample_kernel<32, Seeds><<<grid(tiles), kBlock, 0, st>>>(a, dt, seeds); break;
+                default: hop_sample_kernel<64, Seeds><<<grid(tiles), kBlock, 0, st>>>(a, dt, seeds); break;
+            }
+        };
+        if (h == 1 && direct) sample(SeedsArg{dyn}); else sample(NoSeedsArg{});
+        // as many partitions as the bound has, two workgroups per CU twice over at most
+        const int64_t parts = (int64_t)1 << hop_parts_log2(nb[h - 1], a.n_items, a.f);
+        const int64_t most = std::max<int64_t>(1, (int64_t)ctx->num_cu * 4 / a.n_items);
+        hop_dedup_kernel<<<dim3((unsigned)a.n_items, (unsigned)std::min(parts, most)), kDedupBlock, dedup_lds, st>>>(a, dt);
+        hop_number_kernel<<<grid(std::min<int64_t>(tiles, kHopGranules)), kBlock, 0, st>>>(a, dt);
+    }
+    hop_last_kernel<<<grid((eb[a.L] + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, dt);
 }
 
 // Both samplers: sizes bounded by `fanouts`, or (d_t given) every entry of a row taken with its
@@ -834,14 +1333,33 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
     SPP_HIP(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
 
+    // Fanout sampling deduplicates in LDS (hop_* kernels).  Its workspace grows with the edge bounds, the id
+    // table of the other form with the vertex bounds: where wide fanouts on a small graph make the first by
+    // far the larger one, the call keeps the table, so that what fitted a GPU's memory still does.
+    int64_t ent_stride = 0, seg_stride = 0;
+    for (int h = 1; h <= L && !general; ++h) {
+        const int64_t ents = eb[h] + nb[h - 1];
+        const int64_t tiles = std::max<int64_t>(1024 / n_items, nb[h - 1] / hop_tile_cap(fanouts[h - 1])) + 2;
+        const int64_t segs = std::min(tiles, nb[h - 1] / 16 + 2) << hop_parts_log2(nb[h - 1], n_items, fanouts[h - 1]);
+        if (ents > ent_stride) ent_stride = ents;
+        if (segs > seg_stride) seg_stride = segs;
+    }
     // table region per minibatch: twice the most keys a hop can hold (all ids so far plus the hop's entries)
     const int64_t max_keys = general ? nb[L] + emax : nb[L];
     const uint32_t cap = next_pow2((uint64_t)(2 * max_keys > 1024 ? 2 * max_keys : 1024));
+    const size_t hop_bytes = (size_t)n_items * (size_t)(ent_stride * 8 + seg_stride * 4);
+    const size_t tab_bytes = (size_t)n_items * ((size_t)cap * 8 + (size_t)emax * 8);
+    const bool in_lds = !general && !(flags & SPP_SAMPLE_GLOBAL_TABLE) && hop_bytes <= tab_bytes + ((size_t)1 << 30);
     // workgroups per minibatch in the scans and the table clear: the whole call gets about 4 per CU
     const int per_batch = (ctx->num_cu * 4 + n_items - 1) / n_items;
     const int scan_grid = ((per_batch < 32 ? 32 : per_batch) + 7) & ~7;     // multiples of 8: see batch_block()
-    SPP_TRY(ctx->table.reserve((size_t)cap * sizeof(uint64_t) * n_items));
-    SPP_TRY(ctx->flat.reserve((size_t)emax * sizeof(int32_t) * n_items * 2));        // what the ids resolve to, and the ids
+    if (in_lds) {
+        SPP_TRY(ctx->table.reserve((size_t)ent_stride * sizeof(uint64_t) * n_items));
+        SPP_TRY(ctx->flat.reserve((size_t)seg_stride * sizeof(uint32_t) * n_items));
+    } else {
+        SPP_TRY(ctx->table.reserve((size_t)cap * sizeof(uint64_t) * n_items));
+        SPP_TRY(ctx->flat.reserve((size_t)emax * sizeof(int32_t) * n_items * 2));        // what the ids resolve to, and the ids
+    }
     SPP_TRY(ctx->slots.reserve((size_t)(4 * sizeof(uint32_t) + sizeof(unsigned long long)) * kMaxBatches + 64 +
                                (general ? (size_t)nb[L] * sizeof(int32_t) * n_items : 0)));
     unsigned long long* taken = ctx->slots.as<unsigned long long>();
@@ -895,16 +1413,31 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
     SPP_TRY(ctx->nodeinfo.reserve((size_t)a.node_stride * n_items * (sizeof(int64_t) + sizeof(int32_t)) + 64));
     a.row0 = ctx->nodeinfo.as<int64_t>();
     a.deg = reinterpret_cast<int32_t*>(a.row0 + (size_t)a.node_stride * n_items);
-    const size_t dedup_lds = ((size_t)kLdsSlots + (size_t)(kDedupBlock / kWave) * kQueue) * sizeof(unsigned long long);
-    if (!general && !ctx->dedup_lds_set) {
-        SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&dedup_lds_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)dedup_lds));
-        ctx->dedup_lds_set = 1;
+    constexpr size_t dedup_lds = sizeof(uint32_t) * (2 * kHopSlots + kHopGranules + 2 * kDedupBlock + kDedupBlock / kWave);
+    HopArgs ha;
+    if (in_lds) {
+        if (!ctx->dedup_lds_set) {
+            SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&hop_dedup_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)dedup_lds));
+            ctx->dedup_lds_set = 1;
+        }
+        ha.rowptr = g->rowptr; ha.col = g->col; ha.N = g->N;
+        ha.ent = ctx->table.as<uint64_t>(); ha.ent_stride = ent_stride;
+        ha.seg = ctx->flat.as<uint32_t>(); ha.seg_stride = seg_stride;
+        ha.row0 = a.row0; ha.deg = a.deg; ha.node_stride = a.node_stride;
+        ha.csum_stride = nb[L - 1] / kHopTargets + 2;
+        const size_t sum_words = (size_t)n_items * (2 * (size_t)ha.csum_stride + kHopGranules);
+        if (ctx->hopsums.bytes < sum_words * sizeof(uint32_t)) ctx->hopsums_clean = 0;
+        SPP_TRY(ctx->hopsums.reserve(sum_words * sizeof(uint32_t)));
+        ha.csum = ctx->hopsums.as<uint32_t>();
+        ha.fsum = ha.csum + 2 * (size_t)ha.csum_stride * n_items;
+        ha.totals = reinterpret_cast<unsigned long long*>(ctx->totals); ha.bad = d_bad; ha.bad_next = d_bad_next;
+        ha.mirror = (flags & SPP_SYNC) ? ctx->h_pinned + 64 : nullptr;       // kMaxBatches x 18 counts, then the flags
+        ha.n_items = n_items; ha.L = L; ha.seed = seed;
     }
     a.totals = reinterpret_cast<unsigned long long*>(ctx->totals); a.bad = d_bad; a.ovf = d_bad + 1; a.bad_next = d_bad_next;
     a.L = L; a.h = 0; a.f = 0; a.seed = seed;
     a.t = nullptr;
-    a.force_global = (flags & SPP_SAMPLE_GLOBAL_TABLE) ? 1 : 0;
     a.cnt = reinterpret_cast<int32_t*>(tinfo + 4 * kMaxBatches + 16); a.cnt_stride = nb[L];
 
     auto capped = [&](int64_t need, int64_t lim) {
@@ -924,26 +1457,21 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
             memcpy(&mirror[slot], &ht, sizeof(BatchTable));
             ctx->btab_n[slot] = n_items;
         }
-        // with given probabilities the counting kernel needs the seeds in place before the first scan
-        if (general) seeds_kernel<<<dim3(capped((max_seeds + kBlock - 1) / kBlock, 1 << 20), n_items), kBlock, 0, st>>>(a, dt, dyn);
-        for (int h = 1; h <= L; ++h) {
+        if (in_lds) {
+            if (!ctx->hopsums_clean)
+                hop_sums_clear_kernel<<<ctx->num_cu, kBlock, 0, st>>>(ctx->hopsums.as<uint32_t>(), (int64_t)(ctx->hopsums.bytes / sizeof(uint32_t)));
+            ctx->hopsums_clean = 0;         // set again once this call's last kernel is enqueued
+            launch_hops(ctx, ha, dt, dyn, fanouts, nb, eb, max_seeds, dedup_lds, st);
+            ctx->hopsums_clean = 1;
+        } else {
+            seeds_kernel<<<dim3(capped((max_seeds + kBlock - 1) / kBlock, 1 << 20), n_items), kBlock, 0, st>>>(a, dt, dyn);
+        }
+        for (int h = 1; h <= L && !in_lds; ++h) {
             a.h = h; a.f = general ? 0 : fanouts[h - 1]; a.t = general ? d_t[h - 1] : nullptr;
             const dim3 wgrid(capped((nb[h - 1] * kWave + kBlock - 1) / kBlock, share), n_items);   // a wavefront per target
             if (general) general_count_kernel<<<wgrid, kBlock, 0, st>>>(a, dt);
-            // the relabel of the hop before and the emptying of this hop's table ride in the scan's launches
-            if (h > 1 && !general) {
-                SampleArgs ap = a;
-                ap.h = h - 1;
-                grid_scan_batched(st, scan_grid, n_items, CountIn{a, dt}, CountOut{a, dt}, CountFin{a, dt}, partial,
-                                  RelabelPrev{ap, dt}, TableClear{a, dt});
-            } else if (!general) {
-                // hop 1: the seeds are put in place by the scan's first launch, which counts from the seeds themselves
-                grid_scan_batched_two(st, scan_grid, n_items, CountInSeeds{a, dyn}, CountIn{a, dt}, CountOut{a, dt},
-                                      CountFin{a, dt}, partial, SeedsHead{a, dt, dyn}, TableClear{a, dt});
-            } else {
-                grid_scan_batched(st, scan_grid, n_items, CountIn{a, dt}, CountOut{a, dt}, CountFin{a, dt}, partial,
-                                  NoHook(), TableClear{a, dt});
-            }
+            // the emptying of this hop's table rides in the scan's second launch
+            grid_scan_batched(st, scan_grid, n_items, CountIn{a, dt}, CountOut{a, dt}, CountFin{a, dt}, partial, TableClear{a, dt});
             if (general) {
                 general_sample_kernel<<<wgrid, kBlock, 0, st>>>(a, dt);
             } else {
@@ -955,24 +1483,20 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
                     case 32: sample_kernel<32><<<sgrid, kBlock, 0, st>>>(a, dt); break;
                     default: sample_kernel<64><<<sgrid, kBlock, 0, st>>>(a, dt); break;
                 }
-                // hops small enough meet in LDS (the workgroups of the others leave at once); a hop whose bound
-                // already exceeds what the partitions hold has no workgroup to launch
-                int64_t parts = 1;
-                while (parts < (1 << kLdsMaxPartsLog2) && parts * kLdsPartKeys < nb[h - 1] + eb[h]) parts <<= 1;
-                dedup_lds_kernel<<<dim3(n_items, (unsigned)parts), kDedupBlock, dedup_lds, st>>>(a, dt);
             }
             grid_scan_batched_two(st, scan_grid, n_items, NewIn{a, dt}, NewInKept{a, dt}, NewOut{a, dt}, NewFin{a, dt}, partial);
-            if (h == L || general)
-                relabel_kernel<<<dim3(capped((eb[h] + kBlock - 1) / kBlock, share), n_items), kBlock, 0, st>>>(a, dt);
+            relabel_kernel<<<dim3(capped((eb[h] + kBlock - 1) / kBlock, share), n_items), kBlock, 0, st>>>(a, dt);
         }
         ctx->sample_flags_clean = 1;
     }
     SPP_HIP(hipGetLastError());
     if (flags & SPP_SYNC) {
         int64_t* hp = ctx->h_pinned + 64;            // kMaxBatches x 18 counts, then the flags
-        for (int j = 0; j < n_items; ++j)
-            SPP_HIP(hipMemcpyAsync(hp + j * 2 * kE, items[j].io->d_counts, 2 * kE * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        SPP_HIP(hipMemcpyAsync(hp + kMaxBatches * 2 * kE, d_bad, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+        if (!in_lds) {                               // else the last hop's numbering has stored them there
+            for (int j = 0; j < n_items; ++j)
+                SPP_HIP(hipMemcpyAsync(hp + j * 2 * kE, items[j].io->d_counts, 2 * kE * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+            SPP_HIP(hipMemcpyAsync(hp + kMaxBatches * 2 * kE, d_bad, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+        }
         SPP_HIP(hipStreamSynchronize(st));
         for (int j = 0; j < n_items; ++j)
             for (int k = 0; k <= SPP_MAX_L; ++k) {
@@ -982,7 +1506,6 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
         const int* fl = reinterpret_cast<const int*>(hp + kMaxBatches * 2 * kE);
         SPP_CHECK((fl[0] & 1) == 0, SPP_E_ARG, "spp_sample_mfg: a seed lies outside [0, N)");
         SPP_CHECK((fl[0] & 2) == 0, SPP_E_ARG, "spp_sample_mfg_general: a transition probability lies outside [0, 1]; it was taken as 0");
-        SPP_CHECK((fl[0] & 4) == 0, SPP_E_HIP, "spp_sample_mfg: more than %d ids of one hop share a hash partition; the minibatch's output is not valid", kLdsSlots);
         SPP_CHECK(fl[1] == 0, SPP_E_CAPACITY, "spp_sample_mfg_general: a minibatch exceeded the capacity of its buffers and was abandoned");
     }
     return SPP_OK;
