@@ -8,8 +8,10 @@
 //   (chunk, row block) piece padded to a multiple of four entries, 2 + 2 bytes per entry (source
 //   inside the chunk, row inside the block), with tables for both walks: where every chunk starts,
 //   and per row block where each chunk's piece lies and how many vectors precede it.
-// Either is built once per graph by a radix sort of packed edge keys, then read back and compared
-// with the edges it was built from before anything walks it.
+// The row blocks are one stable partition of the CSR's edges by the block of their destination: the CSR
+// is sorted by source already.  The chunked layout is built by a radix sort of packed edge keys.  Either
+// is built once per graph, then read back and compared with the edges it was built from before
+// anything walks it.
 #include "spp_common.h"
 #include "spp_device.h"
 
@@ -38,70 +40,254 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// key[e] = (row block of u, v, u inside its block) for the e-th edge v -> u of the CSR.
-__global__ void __launch_bounds__(kBlock) tile_keys_kernel(int64_t N, const int64_t* __restrict__ rowptr,
-                                                           const int32_t* __restrict__ col, int rbits, int vbits,
-                                                           uint64_t* __restrict__ keys) {
-    const int lane = lane_id();
-    const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * kBlock) >> 6;
-    const uint64_t rmask = (1ull << rbits) - 1;
-    for (int64_t v = wave; v < N; v += nwaves) {
-        const int64_t b = rowptr[v], e = rowptr[v + 1];
-        for (int64_t i = b + lane; i < e; i += kWave) {
-            const uint64_t u = (uint64_t)(uint32_t)col[i];          // validated at graph creation
-            keys[i] = ((u >> rbits) << (vbits + rbits)) | ((uint64_t)v << rbits) | (u & rmask);
-        }
+// ---- the row-block layout ----------------------------------------------------------------------
+// A workgroup takes tiles of 4096 consecutive edges; a wavefront walks its sixteenth of a tile 64 edges at
+// a time and ranks them among those of the same block with ballots over the block's bits, which keeps
+// the edges of a block in CSR order, that is sorted by source.  One counting pass, one scan of the
+// (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
+// runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
+// 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
+// edges: the kernels of a build 9.2 -> 1.0 ms: 0.70 in the placing pass, which issues 137 vector
+// instructions per 64 edges (0.42 ms of it), 0.11 in the counting pass, 0.17 in the read-back.  Tiles of
+// 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
+constexpr int kPartTile = 4096;
+constexpr int kPartBlock = 1024;
+constexpr int kPartWaves = kPartBlock / kWave;
+constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
+constexpr int kPartMaxBlocks = 512;                      // 2^23 vertices in blocks of 2^14 rows
+
+// Adds a 64-bit mix of an edge to a sum; the edges of two structures are compared by their sums.  One
+// 32-bit and one 32x32 -> 64 product: the kernels here are bound by their instructions (a wavefront's
+// instruction occupies its SIMD for four clocks, a product for sixteen), and a stronger mix was half
+// of the read-back's time.
+__device__ __forceinline__ void edge_mix(unsigned long long& sum, uint32_t v, uint32_t u) {
+    const uint32_t x = v * 0x9E3779B1u + u;
+    sum += (unsigned long long)(x ^ (x >> 15)) * (u ^ 0x85EBCA77u ^ (v << 7));
+}
+__device__ __forceinline__ void add_mix(unsigned long long mine, unsigned long long* sum) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
+    if (lane_id() == 0 && mine) atomicAdd(sum, mine);
+}
+// The wavefront's lanes whose value agrees with this lane's in the low BITS bits.
+template <int BITS>
+__device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
+    const uint64_t all = __ballot(has);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int bit = 0; bit < BITS; ++bit) {
+        const uint32_t m = (uint32_t)((int32_t)(value << (31 - bit)) >> 31);      // all ones where the bit is set
+        const uint64_t bm = __ballot(m != 0u);
+        lo &= ~((uint32_t)bm ^ m);
+        hi &= ~((uint32_t)(bm >> 32) ^ m);
     }
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// From the sorted keys: the edge words, and first[g] = first e whose (row block, source chunk)
-// index g = block * nch + chunk is >= g (indices after the last one keep the value M they were
-// filled with).
-__global__ void __launch_bounds__(kBlock) tile_lists_kernel(const uint64_t* __restrict__ keys, int64_t M, int rbits,
-                                                            int vbits, int nch, uint32_t* __restrict__ t_edge,
-                                                            int64_t* __restrict__ first) {
+// tile_row[t] = the vertex whose row holds the first edge of tile t.
+__global__ void __launch_bounds__(kBlock) part_rows_kernel(int64_t N, const int64_t* __restrict__ rowptr,
+                                                           int32_t* __restrict__ tile_row) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    const uint64_t rmask = (1ull << rbits) - 1, vmask = (1ull << vbits) - 1;
-    auto index_of = [&](uint64_t k) {
-        return (int64_t)(k >> (vbits + rbits)) * nch + (int64_t)(((k >> rbits) & vmask) >> kTileSrcLoBits);
-    };
-    for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < M; e += stride) {
-        const uint64_t k = keys[e];
-        const uint32_t v = (uint32_t)((k >> rbits) & vmask);
-        t_edge[e] = ((v & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (uint32_t)(k & rmask);
-        const int64_t g = index_of(k);
-        const int64_t prev = e > 0 ? index_of(keys[e - 1]) : -1;
-        for (int64_t r = prev + 1; r <= g; ++r) first[r] = e;
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
+        const int64_t b = rowptr[v], e = rowptr[v + 1];
+        for (int64_t t = (b + kPartTile - 1) / kPartTile; t * kPartTile < e; ++t) tile_row[t] = (int32_t)v;
     }
 }
 
-// Reads the structure back the way the propagation kernel does and compares every edge with the
-// sorted key it was made from, so that a kernel that gathers through it never sees a source or a
-// row out of range.  One workgroup per row block; the block's chunk bounds sit in LDS.
-__global__ void __launch_bounds__(kBlock) tile_verify_kernel(const uint64_t* __restrict__ keys, int rbits, int vbits,
-                                                             int nch, const uint32_t* __restrict__ t_edge,
-                                                             const int64_t* __restrict__ first, int64_t N, int64_t M,
-                                                             int* __restrict__ bad) {
-    extern __shared__ uint32_t bound[];
-    const uint64_t rmask = (1ull << rbits) - 1, vmask = (1ull << vbits) - 1;
-    for (int64_t rb = blockIdx.x; rb * ((int64_t)1 << rbits) < N; rb += gridDim.x) {
-        const int64_t b0 = first[rb * nch], len = first[(rb + 1) * nch] - b0;
-        if (b0 < 0 || len < 0 || b0 + len > M || len > 0xFFFFFFFFll) { if (threadIdx.x == 0) *bad = 1; continue; }
+// hist[block * ntiles + tile] = edges of the tile that end in the block.
+__global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t M, const int32_t* __restrict__ col, int rbits,
+                                                                int nrb, int64_t ntiles,
+                                                                uint32_t* __restrict__ hist) {
+    constexpr int kCopies = 8;                   // a lane adds to one of eight copies: most edges of a tile end in few blocks
+    __shared__ uint32_t cnt[kPartMaxBlocks][kCopies];
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        for (int i = threadIdx.x; i < kPartMaxBlocks * kCopies; i += kPartBlock) (&cnt[0][0])[i] = 0u;
+        const int64_t e0 = tile * kPartTile + threadIdx.x;
+        uint32_t u[kPartPer];
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) u[k] = e0 + k * kPartBlock < M ? (uint32_t)col[e0 + k * kPartBlock] : 0xFFFFFFFFu;
         __syncthreads();
-        for (int c = threadIdx.x; c <= nch; c += kBlock) bound[c] = (uint32_t)(first[rb * nch + c] - b0);
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k)
+            if (e0 + k * kPartBlock < M) atomicAdd(&cnt[u[k] >> rbits][threadIdx.x & (kCopies - 1)], 1u);
         __syncthreads();
-        for (int64_t p = threadIdx.x; p < len; p += kBlock) {
-            const uint64_t k = keys[b0 + p];
-            const uint32_t w = t_edge[b0 + p];
-            const int c = tile_chunk_of(bound, nch, (uint32_t)p);
-            const bool ok = (int64_t)(k >> (vbits + rbits)) == rb && tile_source(w, c) == (uint32_t)((k >> rbits) & vmask) &&
-                            (w & kTileRowMask) == (uint32_t)(k & rmask) && (int64_t)tile_source(w, c) < N &&
-                            (rb << rbits) + (int64_t)(w & kTileRowMask) < N;
-            if (!ok) *bad = 1;
+        if ((int)threadIdx.x < nrb) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int w = 0; w < kCopies; ++w) c += cnt[threadIdx.x][w];
+            hist[(int64_t)threadIdx.x * ntiles + tile] = c;
         }
+        __syncthreads();
     }
 }
+
+template <int BITS>
+__global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
+                                                                const int32_t* __restrict__ col, int rbits,
+                                                                int nrb, int64_t ntiles, const int32_t* __restrict__ tile_row,
+                                                                const uint32_t* __restrict__ offs,
+                                                                uint32_t* __restrict__ t_edge,
+                                                                unsigned long long* __restrict__ mix) {
+    __shared__ uint32_t words[kPartTile];        // first: where rows start in the tile; then the edge words by block
+    __shared__ uint16_t blk_of[kPartTile];
+    __shared__ uint16_t cnt[kPartWaves][kPartMaxBlocks];      // edges, then first place, per wavefront and block
+    __shared__ uint32_t gshift[kPartMaxBlocks];  // where the block's run goes in t_edge, less where it starts in words[]
+    __shared__ uint32_t wave_top[kPartWaves];
+    __shared__ uint32_t wsum[kPartWaves];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    const uint32_t rmask = (1u << rbits) - 1u;
+    unsigned long long sum = 0;
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t base = tile * kPartTile;
+        const int count = M - base < kPartTile ? (int)(M - base) : kPartTile;
+        const uint32_t we0 = wave * (kPartTile / kPartWaves) + lane;
+        const int32_t* __restrict__ tcol = col + base;
+        // all that the tile reads is asked for before the first barrier
+        const int64_t v0 = tile_row[tile], v1 = tile + 1 < ntiles ? tile_row[tile + 1] : N - 1;
+        uint32_t u[kPartPer];
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) u[k] = we0 + k * kWave < (uint32_t)count ? (uint32_t)tcol[we0 + k * kWave] : 0u;
+        const uint32_t goff = (int)threadIdx.x < nrb ? offs[(int64_t)threadIdx.x * ntiles + tile] : 0u;
+        int64_t v = v0 + 1 + threadIdx.x;
+        int64_t p = v <= v1 ? rowptr[v] - base : count;
+        for (int i = threadIdx.x; i < kPartWaves * kPartMaxBlocks / 2; i += kPartBlock) reinterpret_cast<uint32_t*>(&cnt[0][0])[i] = 0u;
+        for (int i = threadIdx.x; i < kPartTile; i += kPartBlock) words[i] = 0u;
+        __syncthreads();
+        // a row that starts inside the tile leaves its number (less the first row's) at its first edge; of
+        // empty rows that start at the same edge the last one counts
+        while (v <= v1) {
+            if (p < count) atomicMax(&words[p], (uint32_t)(v - v0));
+            v += kPartBlock;
+            if (v <= v1) p = rowptr[v] - base;
+        }
+        __syncthreads();
+        // an edge's source: the last number at or before it, in this wavefront's part of the tile ...
+        uint32_t top = 0;
+        for (int k = kPartPer - 1; k >= 0 && top == 0; --k) {
+            const uint32_t m = words[we0 + k * kWave];
+            const uint64_t marks = __ballot(m != 0u);
+            if (marks) top = (uint32_t)__shfl((int)m, 63 - __clzll((long long)marks), kWave);
+        }
+        if (lane == 0) wave_top[wave] = top;
+        __syncthreads();
+        top = 0;                                 // ... or before it
+        for (int w = 0; w < wave; ++w) top = wave_top[w] ? wave_top[w] : top;
+        uint32_t place[kPartPer];                // block << 16 | rank among the wavefront's edges of the block
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) {
+            const bool has = we0 + k * kWave < (uint32_t)count;
+            const uint32_t m = words[we0 + k * kWave];
+            const uint64_t marks = __ballot(m != 0u);
+            uint32_t s = top;
+            if (marks) {
+                const uint64_t upto = marks & (lt_mask | (1ull << lane));
+                const uint32_t t = (uint32_t)__shfl((int)m, upto ? 63 - __clzll((long long)upto) : 0, kWave);
+                if (upto) s = t;
+                top = (uint32_t)__shfl((int)m, 63 - __clzll((long long)marks), kWave);
+            }
+            s += (uint32_t)v0;
+            const uint32_t blk = u[k] >> rbits;
+            const uint64_t same = lanes_alike<BITS>(has, blk);
+            const uint32_t below = (uint32_t)__popcll(same & lt_mask);
+            const uint32_t prior = has ? cnt[wave][blk] : 0u;
+            if (has && below == 0) cnt[wave][blk] = (uint16_t)(prior + (uint32_t)__popcll(same));
+            place[k] = (blk << 16) | (prior + below);
+            if (has) edge_mix(sum, s, u[k]);
+            u[k] = ((s & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (u[k] & rmask);
+        }
+        __syncthreads();
+        {   // per block: where its run starts in the tile, and each wavefront's part of it
+            const int blk = threadIdx.x;
+            uint32_t all = 0;
+            if (blk < kPartMaxBlocks)
+                for (int w = 0; w < kPartWaves; ++w) all += cnt[w][blk];
+            const uint32_t inc = (uint32_t)wave_inclusive_scan((int)all);
+            if (lane == kWave - 1) wsum[wave] = inc;
+            __syncthreads();
+            uint32_t st = inc - all;
+            for (int w = 0; w < wave; ++w) st += wsum[w];
+            if (blk < kPartMaxBlocks) {
+                gshift[blk] = goff - st;
+#pragma unroll 1
+                for (int w = 0; w < kPartWaves; ++w) { const uint32_t c = cnt[w][blk]; cnt[w][blk] = (uint16_t)st; st += c; }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k)
+            if (we0 + k * kWave < (uint32_t)count) {
+                const uint32_t at = cnt[wave][place[k] >> 16] + (place[k] & 0xFFFFu);
+                words[at] = u[k];
+                blk_of[at] = (uint16_t)(place[k] >> 16);
+            }
+        __syncthreads();
+#pragma unroll 4
+        for (int i = threadIdx.x; i < count; i += kPartBlock) t_edge[gshift[blk_of[i]] + (uint32_t)i] = words[i];
+        __syncthreads();                         // the next tile overwrites the LDS arrays
+    }
+    add_mix(sum, mix);
+}
+static_assert(kPartMaxBlocks <= kPartBlock, "one block per thread");
+
+// first[block * nch + c] = first edge of the block whose source is in chunk c (of 2^kTileSrcLoBits sources)
+// or a later one: where the tile that holds the chunk's first edge starts in the block, and the edges of
+// that tile before it.  One workgroup per chunk.
+__global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const int64_t* __restrict__ rowptr,
+                                                                const int32_t* __restrict__ col, int rbits, int nrb, int nch,
+                                                                int64_t ntiles, const uint32_t* __restrict__ offs,
+                                                                int64_t* __restrict__ first) {
+    __shared__ uint32_t cnt[kPartMaxBlocks];
+    const int c = blockIdx.x;
+    const int64_t at = rowptr[(int64_t)c << kTileSrcLoBits];             // at most M
+    const int64_t tile = at / kPartTile < ntiles ? at / kPartTile : ntiles - 1;
+    if (threadIdx.x < kPartMaxBlocks) cnt[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int64_t e = tile * kPartTile + threadIdx.x; e < at; e += kPartBlock) atomicAdd(&cnt[(uint32_t)col[e] >> rbits], 1u);
+    __syncthreads();
+    if ((int)threadIdx.x < nrb) first[(int64_t)threadIdx.x * nch + c] = (int64_t)offs[(int64_t)threadIdx.x * ntiles + tile] + cnt[threadIdx.x];
+    if (c == 0 && threadIdx.x == 0) first[(int64_t)nrb * nch] = M;
+}
+
+// Reads the structure back the way the propagation kernel does: every edge must lie in range (so that a
+// kernel that gathers through it never sees a source or a row out of range), and the edges' mixes must
+// add up to those of the CSR's.  `parts` workgroups per row block; the block's chunk bounds sit in LDS.
+__global__ void __launch_bounds__(kBlock) tile_verify_kernel(int rbits, int nch, const uint32_t* __restrict__ t_edge,
+                                                             const int64_t* __restrict__ first, int parts, int64_t N, int64_t M,
+                                                             unsigned long long* __restrict__ mix, int* __restrict__ bad) {
+    extern __shared__ uint32_t bound[];
+    const int64_t rb = blockIdx.x / parts;
+    const int j = blockIdx.x % parts;
+    const int64_t b0 = first[rb * nch], len = first[(rb + 1) * nch] - b0;
+    if (b0 < 0 || len < 0 || b0 + len > M || len > 0xFFFFFFFFll) { if (threadIdx.x == 0) *bad = 1; return; }
+    for (int c = threadIdx.x; c <= nch; c += kBlock) {
+        const int64_t f = first[rb * nch + c] - b0;
+        if (f < 0 || f > len || (c > 0 && first[rb * nch + c] < first[rb * nch + c - 1])) *bad = 1;
+        bound[c] = (uint32_t)f;
+    }
+    __syncthreads();
+    unsigned long long sum = 0;
+    const uint32_t beg = (uint32_t)(len * j / parts), end = (uint32_t)(len * (j + 1) / parts);
+    const uint32_t rows = N - (rb << rbits) < (1ll << rbits) ? (uint32_t)(N - (rb << rbits)) : 1u << rbits;
+    const uint32_t u0 = (uint32_t)(rb << rbits);
+    const uint32_t* __restrict__ words = t_edge + b0;
+    bool wrong = false;
+    for (int c = 0; c < nch; ++c) {              // the share's part of every chunk of sources
+        const uint32_t lo = bound[c] > beg ? bound[c] : beg, hi = bound[c + 1] < end ? bound[c + 1] : end;
+#pragma unroll 8
+        for (uint32_t p = lo + threadIdx.x; p < hi; p += kBlock) {
+            const uint32_t w = words[p], v = tile_source(w, c), r = w & kTileRowMask;
+            wrong |= v >= (uint32_t)N || r >= rows;
+            edge_mix(sum, v, u0 + r);
+        }
+    }
+    if (wrong) *bad = 1;
+    add_mix(sum, mix);
+}
+
+struct PartIn  { const uint32_t* h; __device__ int operator()(int64_t i) const { return (int)h[i]; } };
+struct PartOut { uint32_t* h; __device__ void operator()(int64_t i, int ex, int) const { h[i] = (uint32_t)ex; } };
+struct PartFin { __device__ void operator()(int) const {} };
 
 __global__ void block_first_from_tiles_kernel(const int64_t* __restrict__ tile_first, int nch, int64_t nrb,
                                               int64_t* __restrict__ block_first) {
@@ -122,44 +308,59 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
     const int rbits = (size_t)lds >= (sizeof(double) << kTileRowBits) + bound_bytes + 1024 ? kTileRowBits : kTileRowBits - 1;
     SPP_CHECK((size_t)lds >= (sizeof(double) << rbits) + bound_bytes + 1024, SPP_E_HIP,
               "row blocks: %d bytes of LDS per workgroup do not hold a block's sums and chunk bounds", lds);
-    int vbits = 1;
-    while (((int64_t)1 << vbits) < N) ++vbits;
     const int64_t nrb = (N + ((int64_t)1 << rbits) - 1) >> rbits;
-    int bbits = 1;
-    while (((int64_t)1 << bbits) < nrb) ++bbits;
+    SPP_CHECK(nrb <= kPartMaxBlocks, SPP_E_HIP, "row blocks: %lld blocks of 2^%d rows", (long long)nrb, rbits);
+    static_assert(kPartMaxBlocks <= 512, "nine bits name a block");
     g->tile_rbits = rbits; g->nrb = nrb; g->nch = nch;
     const int64_t nfirst = nrb * nch + 1;
     SPP_HIP(hipMalloc(&g->tile_first, (size_t)nfirst * sizeof(int64_t)));
     SPP_HIP(hipMalloc(&g->t_edge, (size_t)(M > 0 ? M : 1) * sizeof(uint32_t)));
     fill_i64_kernel<<<grid, kBlock, 0, st>>>(g->tile_first, nfirst, M);
     if (M > 0) {
-        uint64_t *ka = nullptr, *kb = nullptr, *sorted = nullptr;
-        int* d_bad = nullptr;
-        SPP_HIP(hipMalloc(&ka, (size_t)M * sizeof(uint64_t)));
-        hipError_t e = hipMalloc(&kb, (size_t)M * sizeof(uint64_t));
-        if (e == hipSuccess) e = hipMalloc(&d_bad, sizeof(int));
-        if (e != hipSuccess) {
-            (void)hipFree(ka); if (kb) (void)hipFree(kb);
-            set_error("row blocks: out of device memory for sort keys");
+        const int64_t ntiles = (M + kPartTile - 1) / kPartTile;
+        const int64_t nhist = nrb * ntiles;
+        const int scan_grid = 1024;
+        // one allocation: the counts, the scan's partial sums and length, the sums of the edges' mixes, a flag,
+        // and the tiles' first rows
+        struct { unsigned long long mix[2]; int64_t n; int bad; int unused; } head = {{0, 0}, nhist, 0, 0}, back;
+        const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)ntiles * sizeof(int32_t);
+        char* tmp = nullptr;
+        if (hipMalloc(&tmp, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            set_error("row blocks: out of device memory for %zu bytes of counts", bytes);
             return SPP_E_OOM;
         }
-        tile_keys_kernel<<<grid, kBlock, 0, st>>>(N, g->rowptr, g->col, rbits, vbits, ka);
-        int rc = radix_sort_u64(ctx, ka, kb, M, rbits, rbits + vbits + bbits, &sorted);
-        if (rc == SPP_OK) {
-            int bad = 0;
-            tile_lists_kernel<<<grid, kBlock, 0, st>>>(sorted, M, rbits, vbits, nch, g->t_edge, g->tile_first);
-            hipError_t e2 = hipMemsetAsync(d_bad, 0, sizeof(int), st);
-            if (e2 == hipSuccess) {
-                const int vgrid = (int)(nrb < (int64_t)ctx->num_cu * 8 ? nrb : (int64_t)ctx->num_cu * 8);
-                tile_verify_kernel<<<vgrid, kBlock, bound_bytes, st>>>(sorted, rbits, vbits, nch, g->t_edge, g->tile_first,
-                                                                       N, M, d_bad);
-                e2 = hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, st);
-            }
-            if (e2 == hipSuccess) e2 = hipStreamSynchronize(st);
-            if (e2 != hipSuccess) { set_error("row blocks: %s", hipGetErrorString(e2)); rc = SPP_E_HIP; }
-            else if (bad) { set_error("row blocks: the structure does not read back as the edges it was built from"); rc = SPP_E_HIP; }
+        unsigned long long* mix = reinterpret_cast<unsigned long long*>(tmp);
+        const int64_t* n_ptr = reinterpret_cast<const int64_t*>(tmp + 2 * sizeof(unsigned long long));
+        int* d_bad = reinterpret_cast<int*>(tmp + 3 * sizeof(int64_t));
+        uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(head));
+        int* partial = reinterpret_cast<int*>(hist + nhist);
+        int32_t* tile_row = partial + scan_grid;
+        int rc = SPP_OK;
+        hipError_t e = hipMemcpyAsync(tmp, &head, sizeof(head), hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) {
+            const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
+            part_rows_kernel<<<grid, kBlock, 0, st>>>(N, g->rowptr, tile_row);
+            part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(M, g->col, rbits, (int)nrb, ntiles, hist);
+            grid_scan(st, scan_grid, n_ptr, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
+            auto place = [&](auto kernel) {
+                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge, mix);
+            };
+            if (nrb <= 256) place(part_place_kernel<8>); else place(part_place_kernel<9>);
+            part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first);
+            const int64_t want = ((int64_t)ctx->num_cu * 8 + nrb - 1) / nrb;
+            const int parts = (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
+            tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
+                                                                                     mix + 1, d_bad);
+            e = hipMemcpyAsync(&back, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
         }
-        (void)hipFree(ka); (void)hipFree(kb); (void)hipFree(d_bad);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e != hipSuccess) { set_error("row blocks: %s", hipGetErrorString(e)); rc = SPP_E_HIP; }
+        else if (back.bad || back.mix[0] != back.mix[1]) {
+            set_error("row blocks: the structure does not read back as the edges it was built from"); rc = SPP_E_HIP;
+        }
+        (void)hipFree(tmp);
         SPP_TRY(rc);
     }
     SPP_HIP(hipMalloc(&g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
