@@ -353,6 +353,7 @@ __device__ __forceinline__ int64_t table_find(const unsigned long long* tab, uin
 constexpr int kTileSrcLoBits = 18;
 constexpr int kTileRowBits = 14;
 constexpr uint32_t kTileRowMask = (1u << kTileRowBits) - 1u;
+constexpr uint32_t kTileWinBytes = 16 * 448 * 4;    // windows of y in the dense-hop kernel's LDS: 448 values for each of 16 wavefronts
 
 __device__ __forceinline__ int tile_chunk_of(const uint32_t* bound, int nch, uint32_t p) {
     int lo = 0, hi = nch - 1;

@@ -303,10 +303,11 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
     int lds = 0;
     SPP_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
     const int nch = (int)((N + ((int64_t)1 << kTileSrcLoBits) - 1) >> kTileSrcLoBits);
-    // the fp64 sums of a block and the block's chunk bounds share the LDS of a workgroup
+    // the fp64 sums of a block, the wavefronts' windows of y and the block's chunk bounds share the LDS of a workgroup
     const size_t bound_bytes = (size_t)(nch + 1) * sizeof(uint32_t);
-    const int rbits = (size_t)lds >= (sizeof(double) << kTileRowBits) + bound_bytes + 1024 ? kTileRowBits : kTileRowBits - 1;
-    SPP_CHECK((size_t)lds >= (sizeof(double) << rbits) + bound_bytes + 1024, SPP_E_HIP,
+    const size_t beside = bound_bytes + kTileWinBytes + 1024;
+    const int rbits = (size_t)lds >= (sizeof(double) << kTileRowBits) + beside ? kTileRowBits : kTileRowBits - 1;
+    SPP_CHECK((size_t)lds >= (sizeof(double) << rbits) + beside, SPP_E_HIP,
               "row blocks: %d bytes of LDS per workgroup do not hold a block's sums and chunk bounds", lds);
     const int64_t nrb = (N + ((int64_t)1 << rbits) - 1) >> rbits;
     SPP_CHECK(nrb <= kPartMaxBlocks, SPP_E_HIP, "row blocks: %lld blocks of 2^%d rows", (long long)nrb, rbits);

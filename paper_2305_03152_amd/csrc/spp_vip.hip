@@ -9,11 +9,11 @@
 // Dense hops: the edges are stored grouped by blocks of 2^14 destination rows and sorted by source
 // inside a block.  A workgroup keeps the block's fp64 sums in LDS (128 KB), streams a share of the
 // block's edges (4 bytes each, read as 128-bit vectors) and adds y[source] to the row's sum with an
-// LDS atomic; because the sources ascend, neighbouring lanes gather from neighbouring lines of y and
-// a line fetched from L2 serves every edge of the block that needs it.  (A pull that walks one
-// row's in-list at a time fetches a line per edge: it ran at a third of this rate on every graph
-// measured, from 2.4M to 134M vertices.)  A second kernel adds the shares and finishes the vertex
-// (p^[h], running total, next hop's y).
+// LDS atomic; because the sources ascend, 64 consecutive edges need a short stretch of y, which the
+// wavefront holds in LDS where the edges are dense, and a line fetched from L2 serves every edge of
+// the block that needs it.  (A pull that walks one row's in-list at a time fetches a line per edge: it
+// ran at a third of this rate on every graph measured, from 2.4M to 134M vertices.)  A second kernel
+// adds the shares and finishes the vertex (p^[h], running total, next hop's y).
 //
 // Early hops touch few edges (hop 1 only the rows of T), so the kernel that writes a hop's y also
 // counts the hop's frontier (vertices with y != 0) and its out-edges; when that is a small share of
@@ -219,27 +219,44 @@ __global__ void __launch_bounds__(kBlock) vip_push_finish_kernel(VipHop a, const
     if (!a.last) write_frontier_stat(a.stat, verts, edges);
 }
 
-// Dense hops, blocked: one workgroup takes the j-th of `parts` equal shares of the edges that end
-// in one block of 2^rbits destination rows.  The block's fp64 sums live in LDS; the edges are
-// sorted by source, so the gathers of y sweep the vector once, neighbouring lanes read
-// neighbouring lines, and a line fetched from L2 serves every edge of the block that needs it
-// (in a row-ordered pull every edge fetches a line of its own).  The share's sums are written
-// to part[j][row]; the finish kernel adds the shares.
+// Dense hops, blocked: one workgroup takes the j-th of `parts` shares of the edges that end in one
+// block of 2^rbits destination rows.  The block's fp64 sums live in LDS; the edges are sorted by
+// source.  The share's sums are written to part[j][row]; the finish kernel adds the shares.  A share is
+// the j-th part of each of the block's sixteenths, one per wavefront: stretches where the LDS adds
+// set the pace and stretches where the gathers do then run side by side on a CU, and shares are alike
+// (contiguous shares: 190 us instead of 171).
 // An edge is one 32-bit word (low 18 bits of the source, row inside the block); the source's high
-// bits follow from the edge's position: the block's chunk bounds sit in LDS next to the sums, a
-// lane finds the chunk of the first of its four consecutive edges by bisection and steps forward
-// for the other three.
+// bits follow from the edge's position: the block's chunk bounds sit in LDS next to the sums.
+//
+// Gathered from memory, a y per edge costs the CU's address path a clock per lane: 196 us for 121M edges,
+// which is what the kernel took.  So a wavefront, which takes 512 consecutive edges per round, reads
+// the stretch of y that they need into a window of its own in LDS where that is at most kTileSpan values
+// (1.2 edges and more per source and row block: edges inside a partition), and the edges read the
+// window.  The stretch is known as soon as the round's first and last words have arrived, so the words
+// are asked for two rounds ahead and the window one round ahead.  Elsewhere the edges gather as before,
+// eight gathers per lane in flight.  (Deciding per 64 edges instead of per 512 took 315 us: a
+// wavefront's instruction occupies its SIMD for four clocks, and there were five times as many.)
+// 2.4M vertices, 121M edges: 171 us per hop instead of 211.  What bounds it now: the word stream alone
+// takes 98 us at the one workgroup per CU that the sums allow, the LDS adds (26 clocks per 64 edges)
+// 78, clearing and writing the sums 23, and the three overlap in part; more rounds of words in flight
+// (two, three or six more) change nothing.
 constexpr int kTileBlock = 1024;
+constexpr int kTileWaves = kTileBlock / kWave;
 constexpr int kTileUnroll = 2;          // 128-bit vectors (four edges) per lane and round
+constexpr int kTileRound = kTileUnroll * kWave;      // vectors of a wavefront's round
+constexpr uint32_t kTileWin = 448;      // what 160 KB of LDS leave per wavefront beside the block's sums (16384 in fp64)
+constexpr uint32_t kTileSpan = kTileWin - 4;
+static_assert(kTileWaves * kTileWin * sizeof(float) == kTileWinBytes, "the layout was built for this much LDS beside the sums");
 __global__ void __launch_bounds__(kTileBlock) vip_tile_kernel(const uint32_t* __restrict__ t_edge,
                                                               const int64_t* __restrict__ first, int nch, int parts,
-                                                              int rbits, const float* __restrict__ y,
+                                                              int rbits, uint32_t N, const float* __restrict__ y,
                                                               double* __restrict__ part, int64_t part_stride) {
     extern __shared__ double acc[];
     const int R = 1 << rbits;
-    uint32_t* bound = reinterpret_cast<uint32_t*>(acc + R);
+    float* win = reinterpret_cast<float*>(acc + R) + (threadIdx.x >> 6) * kTileWin;      // this wavefront's
+    uint32_t* bound = reinterpret_cast<uint32_t*>(acc + R) + kTileWaves * kTileWin;
     // share-major order: the workgroups that run at the same time take the same share of different
-    // blocks, i.e. the same part of y (block-major order: 228 us instead of 214)
+    // blocks, i.e. the same parts of y
     const int64_t nrb = gridDim.x / parts;
     const int64_t rb = blockIdx.x % nrb;
     const int j = (int)(blockIdx.x / nrb);
@@ -247,10 +264,12 @@ __global__ void __launch_bounds__(kTileBlock) vip_tile_kernel(const uint32_t* __
     for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
     for (int c = threadIdx.x; c <= nch; c += kTileBlock) bound[c] = (uint32_t)(first[rb * nch + c] - b0);
     __syncthreads();
-    const int64_t beg = b0 + len * j / parts, end = b0 + len * (j + 1) / parts;
+    const uint32_t lane = lane_id();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t piece = (int64_t)wave * parts + j;         // this wavefront's of the block's 16 * parts equal pieces
+    const int64_t beg = b0 + len * piece / (kTileWaves * parts), end = b0 + len * (piece + 1) / (kTileWaves * parts);
     // The edge stream is read four edges per lane (one 128-bit load): a CU keeps a limited number
-    // of misses in flight, so the bytes per request decide the streaming rate.  Software pipeline:
-    // the words of the next round are in flight while this round's gathers and LDS adds run.
+    // of misses in flight, so the bytes per request decide the streaming rate.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     int64_t a4 = (beg + 3) & ~(int64_t)3, e4 = end & ~(int64_t)3;
     if (a4 > end) a4 = end;
@@ -260,68 +279,117 @@ __global__ void __launch_bounds__(kTileBlock) vip_tile_kernel(const uint32_t* __
         const float v = y[tile_source(w, tile_chunk_of(bound, nch, (uint32_t)(e - b0)))];
         if (v != 0.0f) unsafeAtomicAdd(&acc[w & kTileRowMask], (double)v);
     };
-    for (int64_t e = beg + threadIdx.x; e < a4; e += kTileBlock) one(e);      // unaligned head
-    for (int64_t e = e4 + threadIdx.x; e < end; e += kTileBlock) one(e);      // tail
+    if (beg + lane < a4) one(beg + lane);        // unaligned head and tail, three edges at most
+    if (e4 + lane < end) one(e4 + lane);
     const u32x4* __restrict__ vs = reinterpret_cast<const u32x4*>(t_edge + a4);
-    const int64_t nvec = (e4 - a4) >> 2;
+    const uint32_t nvec = (uint32_t)((e4 - a4) >> 2);
     const uint32_t p0 = (uint32_t)(a4 - b0);                                   // position of the first vector's first edge
-    constexpr int64_t kRound = (int64_t)kTileUnroll * kTileBlock;
-    u32x4 s[kTileUnroll];
-    int ch[kTileUnroll];                 // chunk of the lane's current vector and where that chunk ends;
-    uint32_t ch_end[kTileUnroll];        // a lane's positions only grow, so both only move forward
-    int64_t q = threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < kTileUnroll; ++u) {
-        ch[u] = 0; ch_end[u] = 0;
-        if (q + u * kTileBlock < nvec) {
-            s[u] = __builtin_nontemporal_load(vs + q + u * kTileBlock);
-            ch[u] = tile_chunk_of(bound, nch, p0 + 4u * (uint32_t)(q + u * kTileBlock));
-            ch_end[u] = bound[ch[u] + 1];
-        }
-    }
-    for (; q < nvec; q += kRound) {
-        u32x4 sn[kTileUnroll];
+    const f32x4* __restrict__ y4 = reinterpret_cast<const f32x4*>(y);          // 16-byte aligned, a vector longer than N
+    constexpr uint32_t kStep = kTileRound;
+    struct Words { u32x4 v[kTileUnroll]; };
+    auto load = [&](uint32_t q0) {               // the words of the round that starts at vector q0
+        Words w;
 #pragma unroll
         for (int u = 0; u < kTileUnroll; ++u)
-            if (q + kRound + u * kTileBlock < nvec) sn[u] = __builtin_nontemporal_load(vs + q + kRound + u * kTileBlock);
-        float v[kTileUnroll][4];
+            if (q0 + u * kWave + lane < nvec) w.v[u] = __builtin_nontemporal_load(vs + (q0 + u * kWave + lane));
+        return w;
+    };
+    // how a round's edges find their values: in the window (from source w0 on), by gathers from one chunk of
+    // sources, or edge by edge (the last round, and rounds that cross into another chunk)
+    enum { kWindow, kGather, kEach };
+    int c = __builtin_amdgcn_readfirstlane(tile_chunk_of(bound, nch, p0));   // chunk of the latest round looked at; positions only grow
+    uint32_t cend = (uint32_t)__builtin_amdgcn_readfirstlane((int)bound[c + 1]);
+    f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;    // the window on its way
+    auto look = [&](uint32_t q0, const Words& w, uint32_t& base, uint32_t& w0) {
+        if (q0 + kTileRound > nvec) return (int)kEach;
+        const uint32_t at = p0 + 4 * q0;         // at + 511 < len = bound[nch]: c stays below nch
+        while (at >= cend) { ++c; cend = (uint32_t)__builtin_amdgcn_readfirstlane((int)bound[c + 1]); }
+        if (at + 4 * kTileRound > cend) return (int)kEach;
+        base = (uint32_t)c << kTileSrcLoBits;
+        const uint32_t lo = base + ((uint32_t)__builtin_amdgcn_readlane((int)w.v[0].x, 0) >> kTileRowBits);
+        const uint32_t hi = base + ((uint32_t)__builtin_amdgcn_readlane((int)w.v[kTileUnroll - 1].w, kWave - 1) >> kTileRowBits);
+        if (hi - lo >= kTileSpan) return (int)kGather;
+        w0 = lo & ~3u;
+        const uint32_t v = (w0 >> 2) + lane;
+        if (4 * v < N) y0 = y4[v];
+        if (lane < (kTileWin - 256) / 4 && 4 * (v + kWave) < N) y1 = y4[v + kWave];
+        return (int)kWindow;
+    };
+    uint32_t q0 = 0;
+    if (nvec > 0) {
+        Words cur = load(q0), nxt = load(q0 + kStep);
+        uint32_t base = 0, w0 = 0, base_n = 0, w0_n = 0;
+        int how = look(q0, cur, base, w0);
+        for (; q0 < nvec; q0 += kStep) {
+            const Words far = load(q0 + 2 * kStep);
+            if (how == kWindow) {
+                *reinterpret_cast<f32x4*>(win + 4 * lane) = y0;
+                if (lane < (kTileWin - 256) / 4) *reinterpret_cast<f32x4*>(win + 256 + 4 * lane) = y1;
+                __builtin_amdgcn_wave_barrier();
+            }
+            int how_n = kEach;
+            if (q0 + kStep < nvec) how_n = look(q0 + kStep, nxt, base_n, w0_n);
+            float v[kTileUnroll][4];
+            if (how == kWindow) {
+                const uint32_t off = base - w0;
 #pragma unroll
-        for (int u = 0; u < kTileUnroll; ++u)
-            if (q + u * kTileBlock < nvec) {
-                const uint32_t p = p0 + 4u * (uint32_t)(q + u * kTileBlock);
-                int c = ch[u];
-                uint32_t ce = ch_end[u];
-                while (p >= ce) { ++c; ce = bound[c + 1]; }      // p + 3 < len = bound[nch]: c stays below nch
-                if (p + 3 < ce) {                                  // the four edges share a chunk
-                    v[u][0] = y[tile_source(s[u].x, c)];
-                    v[u][1] = y[tile_source(s[u].y, c)];
-                    v[u][2] = y[tile_source(s[u].z, c)];
-                    v[u][3] = y[tile_source(s[u].w, c)];
-                } else {
-                    v[u][0] = y[tile_source(s[u].x, c)];
-                    while (p + 1 >= ce) { ++c; ce = bound[c + 1]; }
-                    v[u][1] = y[tile_source(s[u].y, c)];
-                    while (p + 2 >= ce) { ++c; ce = bound[c + 1]; }
-                    v[u][2] = y[tile_source(s[u].z, c)];
-                    while (p + 3 >= ce) { ++c; ce = bound[c + 1]; }
-                    v[u][3] = y[tile_source(s[u].w, c)];
+                for (int u = 0; u < kTileUnroll; ++u) {
+                    v[u][0] = win[off + (cur.v[u].x >> kTileRowBits)];
+                    v[u][1] = win[off + (cur.v[u].y >> kTileRowBits)];
+                    v[u][2] = win[off + (cur.v[u].z >> kTileRowBits)];
+                    v[u][3] = win[off + (cur.v[u].w >> kTileRowBits)];
                 }
-                ch[u] = c; ch_end[u] = ce;
+                __builtin_amdgcn_wave_barrier();
+            } else if (how == kGather) {
+                const float* __restrict__ yc = y + base;
+#pragma unroll
+                for (int u = 0; u < kTileUnroll; ++u) {
+                    v[u][0] = yc[cur.v[u].x >> kTileRowBits];
+                    v[u][1] = yc[cur.v[u].y >> kTileRowBits];
+                    v[u][2] = yc[cur.v[u].z >> kTileRowBits];
+                    v[u][3] = yc[cur.v[u].w >> kTileRowBits];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < kTileUnroll; ++u) {
+                    const uint32_t q = q0 + u * kWave + lane, p = p0 + 4 * q;
+                    v[u][0] = v[u][1] = v[u][2] = v[u][3] = 0.0f;
+                    if (q < nvec) {
+                        v[u][0] = y[tile_source(cur.v[u].x, tile_chunk_of(bound, nch, p))];
+                        v[u][1] = y[tile_source(cur.v[u].y, tile_chunk_of(bound, nch, p + 1))];
+                        v[u][2] = y[tile_source(cur.v[u].z, tile_chunk_of(bound, nch, p + 2))];
+                        v[u][3] = y[tile_source(cur.v[u].w, tile_chunk_of(bound, nch, p + 3))];
+                    }
+                }
             }
 #pragma unroll
-        for (int u = 0; u < kTileUnroll; ++u)
-            if (q + u * kTileBlock < nvec) {
-                if (v[u][0] != 0.0f) unsafeAtomicAdd(&acc[s[u].x & kTileRowMask], (double)v[u][0]);
-                if (v[u][1] != 0.0f) unsafeAtomicAdd(&acc[s[u].y & kTileRowMask], (double)v[u][1]);
-                if (v[u][2] != 0.0f) unsafeAtomicAdd(&acc[s[u].z & kTileRowMask], (double)v[u][2]);
-                if (v[u][3] != 0.0f) unsafeAtomicAdd(&acc[s[u].w & kTileRowMask], (double)v[u][3]);
+            for (int u = 0; u < kTileUnroll; ++u) {
+                if (v[u][0] != 0.0f) unsafeAtomicAdd(&acc[cur.v[u].x & kTileRowMask], (double)v[u][0]);
+                if (v[u][1] != 0.0f) unsafeAtomicAdd(&acc[cur.v[u].y & kTileRowMask], (double)v[u][1]);
+                if (v[u][2] != 0.0f) unsafeAtomicAdd(&acc[cur.v[u].z & kTileRowMask], (double)v[u][2]);
+                if (v[u][3] != 0.0f) unsafeAtomicAdd(&acc[cur.v[u].w & kTileRowMask], (double)v[u][3]);
             }
-#pragma unroll
-        for (int u = 0; u < kTileUnroll; ++u) s[u] = sn[u];
+            cur = nxt; nxt = far;
+            how = how_n; base = base_n; w0 = w0_n;
+        }
     }
     __syncthreads();
     double* __restrict__ out = part + (int64_t)j * part_stride + (rb << rbits);
     for (int i = threadIdx.x; i < R; i += kTileBlock) out[i] = acc[i];
+}
+// Shares per row block: what makes the fewest rounds of one workgroup per CU, counting 8192 edges' time for
+// what a share costs besides its edges (clearing and writing 128 KB of sums).  147 blocks on 256 CUs: 5
+// shares, 2.9 rounds of them (6 shares, the former rule's four workgroups per CU: 3.4, most of a
+// round idle).
+inline int tile_parts(int num_cu, int64_t nrb, int64_t M) {
+    int best = 1;
+    double best_cost = 0.0;
+    for (int p = 1; p <= 16 && nrb > 0; ++p) {
+        const double rounds = (double)((nrb * p + num_cu - 1) / num_cu);
+        const double cost = rounds * ((double)M / (double)(nrb * p) + 8192.0);
+        if (p == 1 || cost < best_cost) { best = p; best_cost = cost; }
+    }
+    return best;
 }
 
 __global__ void __launch_bounds__(kBlock) vip_tile_finish_kernel(VipHop a, const double* __restrict__ part, int parts,
@@ -889,10 +957,17 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
     __syncthreads();
     const int64_t b0 = first[rb * nch], len = (int64_t)cursor[rb];
     const int64_t beg = b0 + len * j / parts, end = b0 + len * (j + 1) / parts;
-    for (int64_t e = beg + threadIdx.x; e < end; e += kTileBlock) {
-        const unsigned long long x = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(bins) + e);
-        const uint32_t w = (uint32_t)x;                    // .x of the entry
-        if (w != 0u) unsafeAtomicAdd(&acc[(uint32_t)(x >> 32)], (double)__uint_as_float(w));
+    constexpr int U = 8;                       // entries in flight per thread (one: 325 us for 121M entries, eight: 208)
+    for (int64_t e0 = beg + threadIdx.x; e0 < end; e0 += U * kTileBlock) {
+        unsigned long long x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            x[u] = e0 + u * kTileBlock < end ? __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(bins) + e0 + u * kTileBlock) : 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t w = (uint32_t)x[u];             // .x of the entry
+            if (w != 0u) unsafeAtomicAdd(&acc[(uint32_t)(x[u] >> 32)], (double)__uint_as_float(w));
+        }
     }
     __syncthreads();
     double* __restrict__ out = part + (int64_t)j * part_stride + (rb << rbits);
@@ -952,8 +1027,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     const size_t fill_lds = binned ? 2 * (size_t)g->nrb * sizeof(uint32_t) : 0;
     const size_t sum_lds = binned ? sizeof(double) << g->tile_rbits : 0;
     if (binned) {
-        const int64_t want = ((int64_t)ctx->num_cu * 4 + g->nrb - 1) / g->nrb;
-        parts = (int)(want < 1 ? 1 : (want > 16 ? 16 : want));
+        parts = tile_parts(ctx->num_cu, g->nrb, g->M);
         SPP_TRY(ctx->acc.reserve((size_t)parts * (size_t)part_stride * sizeof(double)));
         acc = ctx->acc.as<double>();
         SPP_TRY(ctx->bins.reserve(((size_t)g->M + (size_t)g->nrb + 1) * sizeof(uint2)));
@@ -1023,17 +1097,10 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     SPP_HIP(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     const int64_t N = g->N;
-    SPP_TRY(ctx->y0.reserve((size_t)N * sizeof(float)));
-    SPP_TRY(ctx->y1.reserve((size_t)N * sizeof(float)));
+    SPP_TRY(ctx->y0.reserve((size_t)(N + 4) * sizeof(float)));       // dense hops read y as whole vectors of four
+    SPP_TRY(ctx->y1.reserve((size_t)(N + 4) * sizeof(float)));
     SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double) + sizeof(int)));
-    // dense hops over row blocks: shares per block for at most four workgroups per CU (on 147 blocks
-    // and 256 CUs, in block-major order: 6 shares 224 + 31 us for the kernel and the finish, 7 shares 234 + 34,
-    // 8 shares 279 + 38; in share-major order 6 shares 214 + 31, 8 shares 209 + 37)
-    int parts = 1;
-    if (g->nrb > 0) {
-        const int64_t want = (int64_t)ctx->num_cu * 4 / g->nrb;
-        parts = (int)(want < 1 ? 1 : (want > 16 ? 16 : want));
-    }
+    int parts = tile_parts(ctx->num_cu, g->nrb, g->M);
     // the chunked layout: with a row block per CU or more, one workgroup takes a whole block and
     // finishes its vertices itself (no partial sums leave the chip)
     if (g->has_x && g->nrb >= ctx->num_cu) parts = 1;
@@ -1043,7 +1110,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         const size_t push_bytes = (size_t)N * sizeof(double);
         SPP_TRY(ctx->acc.reserve(tile_bytes > push_bytes ? tile_bytes : push_bytes));
     }
-    const size_t lds_bytes = (sizeof(double) << g->tile_rbits) + (size_t)(g->nch + 1) * sizeof(uint32_t);
+    const size_t lds_bytes = (sizeof(double) << g->tile_rbits) + (size_t)(kTileWaves * kTileWin + g->nch + 1) * sizeof(uint32_t);
     const size_t x_lds_expand = (sizeof(float) << kXSrcBits) + sizeof(float);
     static_assert(kXPad == (1u << kXSrcBits), "a padding entry indexes the slot after the chunk's values");
     const size_t x_lds_reduce = (sizeof(double) << kTileRowBits) + (2 * kXGroup + 1) * sizeof(uint32_t);
@@ -1134,7 +1201,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 if (parts > 1) vip_tile_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, ctx->acc.as<double>(), parts, part_stride, N);
             } else {
                 vip_tile_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, lds_bytes, st>>>(
-                    g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, ycur, ctx->acc.as<double>(), part_stride);
+                    g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, (uint32_t)N, ycur, ctx->acc.as<double>(), part_stride);
                 vip_tile_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, ctx->acc.as<double>(), parts, part_stride, N);
             }
             ctx->vip_pushed[h - 1] = push ? 1 : 0;
