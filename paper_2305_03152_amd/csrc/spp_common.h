@@ -62,6 +62,7 @@ struct DevBuf {
 };
 
 constexpr int kNumTimers = SPP_T_COUNT;
+constexpr size_t kKeptSortBytes = (size_t)32 << 20;      // set-up workspaces up to this size stay with the context, larger ones do not
 
 // Several id lists gathered by one set of launches.  List j owns the virtual rows
 // [off[j], off[j] + cnt[j]); off[] is padded to multiples of kListAlign so that one workgroup's
@@ -132,6 +133,7 @@ struct spp_ctx {
     int64_t*    totals = nullptr;       // device int64[16], running sums since the last reset (see spp_ctx_totals)
     // vip workspaces
     spp::DevBuf y0, y1, tot, acc, frontier;
+    spp::DevBuf sortws, rankws;         // set-up: counts of a radix sort, keys and histograms of a ranking (bounded, see kKeptSortBytes)
     spp::DevBuf xvals;                  // dense hops over the chunked layout: y[source] of every entry
     spp::DevBuf bins;                   // general propagation: per row block the (row, weight) entries of a hop, and the fill counts
     int         bin_lds_set = 0, sum_lds_set = 0;   // dynamic LDS bytes its two kernels have been allowed

@@ -52,8 +52,8 @@ __device__ __forceinline__ int block_reduce_sum(int v, int* lds) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Grid scan in three launches over i in [0, n), n read from device memory (so no host round trip
-// is needed between dependent steps).  Work is cut into `gridDim.x` contiguous ranges.
+// Grid scan in three launches over i in [0, n), n given by the host or read from device memory (so no
+// host round trip is needed between dependent steps).  Work is cut into `gridDim.x` contiguous ranges.
 //   In:  int operator()(int64_t i) const            value of element i
 //   Out: void operator()(int64_t i, int ex, int v)  receives the exclusive prefix
 //   Fin: void operator()(int total) const           called once by one thread
@@ -95,11 +95,18 @@ __device__ __forceinline__ BatchBlock batch_block() {
     return bb;
 }
 
+struct ScanLength {
+    const int64_t* on_device;       // or null
+    int64_t        value;
+    ScanLength(const int64_t* p) : on_device(p), value(0) {}
+    ScanLength(int64_t v) : on_device(nullptr), value(v) {}
+    __device__ __forceinline__ int64_t get() const { return on_device ? *on_device : value; }
+};
 template <class In>
-__global__ void __launch_bounds__(kBlock) scan_reduce_kernel(const int64_t* n_ptr, In in, int* partial) {
+__global__ void __launch_bounds__(kBlock) scan_reduce_kernel(ScanLength n, In in, int* partial) {
     __shared__ int lds[4];
     int64_t b, e;
-    scan_range(*n_ptr, b, e);
+    scan_range(n.get(), b, e);
     int acc = 0;
     for (int64_t i = b + threadIdx.x; i < e; i += kBlock) acc = uadd(acc, in(i));
     int t = block_reduce_sum(acc, lds);
@@ -122,11 +129,10 @@ __global__ void __launch_bounds__(kBlock) scan_partials_kernel(int* partial, int
 }
 
 template <class In, class Out>
-__global__ void __launch_bounds__(kBlock) scan_write_kernel(const int64_t* n_ptr, In in, Out out,
-                                                            const int* partial) {
+__global__ void __launch_bounds__(kBlock) scan_write_kernel(ScanLength n, In in, Out out, const int* partial) {
     __shared__ int lds[4];
     int64_t b, e;
-    scan_range(*n_ptr, b, e);
+    scan_range(n.get(), b, e);
     int carry = partial[blockIdx.x];
     for (int64_t base = b; base < e; base += kBlock) {
         int64_t i = base + threadIdx.x;
@@ -139,10 +145,10 @@ __global__ void __launch_bounds__(kBlock) scan_write_kernel(const int64_t* n_ptr
 }
 
 template <class In, class Out, class Fin>
-inline void grid_scan(hipStream_t st, int grid, const int64_t* n_ptr, In in, Out out, Fin fin, int* partial) {
-    scan_reduce_kernel<In><<<grid, kBlock, 0, st>>>(n_ptr, in, partial);
+inline void grid_scan(hipStream_t st, int grid, ScanLength n, In in, Out out, Fin fin, int* partial) {
+    scan_reduce_kernel<In><<<grid, kBlock, 0, st>>>(n, in, partial);
     scan_partials_kernel<Fin><<<1, kBlock, 0, st>>>(partial, grid, fin);
-    scan_write_kernel<In, Out><<<grid, kBlock, 0, st>>>(n_ptr, in, out, partial);
+    scan_write_kernel<In, Out><<<grid, kBlock, 0, st>>>(n, in, out, partial);
 }
 
 // The same scan for several independent sequences at once, in two launches; batch_block() names the

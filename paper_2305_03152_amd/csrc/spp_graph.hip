@@ -321,9 +321,9 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         const int64_t ntiles = (M + kPartTile - 1) / kPartTile;
         const int64_t nhist = nrb * ntiles;
         const int scan_grid = 1024;
-        // one allocation: the counts, the scan's partial sums and length, the sums of the edges' mixes, a flag,
+        // one allocation: the counts, the scan's partial sums, the sums of the edges' mixes, a flag,
         // and the tiles' first rows
-        struct { unsigned long long mix[2]; int64_t n; int bad; int unused; } head = {{0, 0}, nhist, 0, 0}, back;
+        struct { unsigned long long mix[2]; int64_t unused; int bad, unused2; } head = {{0, 0}, 0, 0, 0}, back;
         const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)ntiles * sizeof(int32_t);
         char* tmp = nullptr;
         if (hipMalloc(&tmp, bytes) != hipSuccess) {
@@ -332,7 +332,6 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             return SPP_E_OOM;
         }
         unsigned long long* mix = reinterpret_cast<unsigned long long*>(tmp);
-        const int64_t* n_ptr = reinterpret_cast<const int64_t*>(tmp + 2 * sizeof(unsigned long long));
         int* d_bad = reinterpret_cast<int*>(tmp + 3 * sizeof(int64_t));
         uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(head));
         int* partial = reinterpret_cast<int*>(hist + nhist);
@@ -343,7 +342,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
             part_rows_kernel<<<grid, kBlock, 0, st>>>(N, g->rowptr, tile_row);
             part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(M, g->col, rbits, (int)nrb, ntiles, hist);
-            grid_scan(st, scan_grid, n_ptr, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
+            grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
             auto place = [&](auto kernel) {
                 kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge, mix);
             };

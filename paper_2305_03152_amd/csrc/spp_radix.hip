@@ -1,10 +1,9 @@
 // Stable least-significant-digit radix sort of 64-bit keys, 8 bits per pass, used at set-up time:
-// to build the transposed edge structure (edge keys packed as (row block of u, source v, row of u
-// inside its block), sorted on the block and source bits, which groups the edges by destination
-// row block and orders them by source inside a block) and to rank cache candidates and local
-// vertices (Sec. 3.2).
+// to build the chunked transposed edge structure and to rank cache candidates and local vertices
+// (Sec. 3.2).
 //
-// A tile is 4096 keys handled by one 256-thread workgroup; wavefront w owns the w-th quarter of
+// A tile is 4096 keys (1024 where the keys do not make four tiles of 4096 per CU: a pass over
+// 320k keys takes 23 us of kernels instead of 55) handled by one 256-thread workgroup; wavefront w owns the w-th quarter of
 // the tile and walks it in order, 64 keys at a time, so a key's stable rank among equal digits is
 // (count of that digit in earlier wavefronts' quarters) + (count earlier in its own quarter) +
 // (count in lower lanes of its own 64), the last from ballots.  Keys are then placed in digit
@@ -14,10 +13,7 @@
 
 namespace spp {
 
-constexpr int kTile = 4096;
-constexpr int kPerWave = kTile / 4;          // 1024 keys per wavefront
-constexpr int kBatches = kPerWave / kWave;   // 16 batches of 64
-
+template <int kTile>
 __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const uint64_t* __restrict__ keys, int64_t n,
                                                             int shift, int64_t ntiles,
                                                             uint32_t* __restrict__ hist) {
@@ -40,10 +36,12 @@ struct HistIn  { const uint32_t* h; __device__ int operator()(int64_t i) const {
 struct HistOut { uint32_t* h; __device__ void operator()(int64_t i, int ex, int) const { h[i] = (uint32_t)ex; } };
 struct NoFin   { __device__ void operator()(int) const {} };
 
+template <int kTile>
 __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(const uint64_t* __restrict__ keys,
                                                                uint64_t* __restrict__ out, int64_t n,
                                                                int shift, int64_t ntiles,
                                                                const uint32_t* __restrict__ offs) {
+    constexpr int kPerWave = kTile / 4, kBatches = kPerWave / kWave;         // batches of 64 per wavefront
     __shared__ uint32_t cnt[4][256];
     __shared__ uint32_t dstart[256];
     __shared__ uint32_t gbase[256];
@@ -116,48 +114,45 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(const uint64_t* _
     }
 }
 
+template <int kTile>
+static int sort_tiles(spp_ctx* ctx, uint64_t* src, uint64_t* dst, int64_t n, int bit_lo, int bit_hi, uint64_t** result) {
+    hipStream_t st = ctx->stream;
+    const int64_t ntiles = (n + kTile - 1) / kTile;
+    const int64_t nhist = 256 * ntiles;
+    const int scan_grid = (int)(nhist / 2048 < 1 ? 1 : (nhist / 2048 < 1024 ? nhist / 2048 : 1024));
+    const size_t bytes = (size_t)nhist * sizeof(uint32_t) + (size_t)scan_grid * sizeof(int);
+    // the counts of a large sort are not kept
+    DevBuf own;
+    DevBuf& ws = bytes <= kKeptSortBytes ? ctx->sortws : own;
+    SPP_TRY(ws.reserve(bytes));
+    uint32_t* hist = ws.as<uint32_t>();
+    int* partial = reinterpret_cast<int*>(hist + nhist);
+    const int grid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
+    for (int shift = bit_lo; shift < bit_hi; shift += 8) {
+        radix_hist_kernel<kTile><<<grid, kBlock, 0, st>>>(src, n, shift, ntiles, hist);
+        grid_scan(st, scan_grid, nhist, HistIn{hist}, HistOut{hist}, NoFin{}, partial);
+        radix_scatter_kernel<kTile><<<grid, kBlock, 0, st>>>(src, dst, n, shift, ntiles, hist);
+        uint64_t* t = src; src = dst; dst = t;
+    }
+    *result = src;
+    hipError_t e = hipGetLastError();
+    if (own.ptr) {
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        own.release();
+    }
+    if (e != hipSuccess) { set_error("radix_sort_u64: %s", hipGetErrorString(e)); return SPP_E_HIP; }
+    return SPP_OK;
+}
+
+// The sorted keys are complete on the context's stream; the host has not waited for them.
 int radix_sort_u64(spp_ctx* ctx, uint64_t* keys_a, uint64_t* keys_b, int64_t n, int bit_lo, int bit_hi,
                    uint64_t** result) {
     *result = keys_a;
     if (n <= 1 || bit_hi <= bit_lo) return SPP_OK;
     SPP_CHECK(n < (int64_t)0xFFFFFFFFll, SPP_E_ARG, "radix_sort_u64: %lld keys exceed the 32-bit offset range",
               (long long)n);
-    hipStream_t st = ctx->stream;
-    const int64_t ntiles = (n + kTile - 1) / kTile;
-    const int64_t nhist = 256 * ntiles;
-    uint32_t* hist = nullptr;
-    int64_t* d_n = nullptr;
-    int* partial = nullptr;
-    const int scan_grid = 1024;
-    SPP_HIP(hipMalloc(&hist, (size_t)nhist * sizeof(uint32_t)));
-    hipError_t e1 = hipMalloc(&d_n, sizeof(int64_t));
-    hipError_t e2 = hipMalloc(&partial, scan_grid * sizeof(int));
-    if (e1 != hipSuccess || e2 != hipSuccess) {
-        (void)hipFree(hist); if (d_n) (void)hipFree(d_n); if (partial) (void)hipFree(partial);
-        set_error("radix_sort_u64: workspace allocation failed");
-        return SPP_E_OOM;
-    }
-    int rc = SPP_OK;
-    hipError_t e = hipMemcpyAsync(d_n, &nhist, sizeof(int64_t), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);      // nhist lives on this stack frame
-    const int grid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
-    uint64_t* src = keys_a;
-    uint64_t* dst = keys_b;
-    for (int shift = bit_lo; shift < bit_hi && e == hipSuccess; shift += 8) {
-        radix_hist_kernel<<<grid, kBlock, 0, st>>>(src, n, shift, ntiles, hist);
-        grid_scan(st, scan_grid, d_n, HistIn{hist}, HistOut{hist}, NoFin{}, partial);
-        radix_scatter_kernel<<<grid, kBlock, 0, st>>>(src, dst, n, shift, ntiles, hist);
-        e = hipGetLastError();
-        uint64_t* t = src; src = dst; dst = t;
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        set_error("radix_sort_u64: %s", hipGetErrorString(e));
-        rc = SPP_E_HIP;
-    }
-    (void)hipFree(hist); (void)hipFree(d_n); (void)hipFree(partial);
-    *result = src;
-    return rc;
+    return n < (int64_t)ctx->num_cu * 4 * 4096 ? sort_tiles<1024>(ctx, keys_a, keys_b, n, bit_lo, bit_hi, result)
+                                               : sort_tiles<4096>(ctx, keys_a, keys_b, n, bit_lo, bit_hi, result);
 }
 
 }  // namespace spp
