@@ -248,11 +248,12 @@ int  spp_gather_join(spp_ctx* ctx);
  * memory lines they straddle.  It pays when a call misses a sizeable share of the store (an
  * eighth or more: then the fetch is 3 to 15 % faster) and costs a pass over that array
  * otherwise.
- * SPP_HIT_BESIDE_MISS changes the order of the call's two copies, never the result: by default the
+ * A call that joins its miss copy itself queues it before the hit copy, which runs beside it.
+ * SPP_HIT_BESIDE_MISS does the same with SPP_NO_JOIN, never changing the result: there, by default, the
  * stream waits for the miss copy of the call before, copies the hits with the whole chip and then
  * starts this call's miss copy; with the flag the miss copy is queued first (it starts when the
- * earlier one ends) and the hit copy runs beside it.  It pays in a loop of SPP_NO_JOIN calls whose
- * hit copy takes a sizeable part of the time between two miss copies.
+ * earlier one ends).  It pays in a loop of SPP_NO_JOIN calls whose hit copy takes a sizeable part of
+ * the time between two miss copies.
  * flags: SPP_SYNC, SPP_NO_JOIN, SPP_STORE_ORDER, SPP_HIT_BESIDE_MISS. */
 typedef struct {
     const int32_t* d_node_ids;

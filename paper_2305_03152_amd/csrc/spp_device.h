@@ -329,6 +329,23 @@ __device__ __forceinline__ bool table_claim(unsigned long long* tab, uint32_t ma
     }
 }
 
+// The value of `key`, whose first bucket the caller has loaded into s; false if it is not in the table.
+__device__ __forceinline__ bool table_find_in(const unsigned long long* tab, uint32_t bmask, int shift, uint32_t key,
+                                              unsigned long long (&s)[kBucketSlots], uint32_t& value) {
+    const uint32_t h0 = table_hash(key, shift);
+    uint32_t b = h0 >> 3;
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < kBucketSlots; ++k) {
+            const unsigned long long cur = table_pick(s, (h0 + k) & 7u);
+            if (cur == kEmpty) return false;
+            if ((uint32_t)(cur >> 32) == key) { value = (uint32_t)cur; return true; }
+        }
+        b = (b + 1) & bmask;
+        table_load_bucket(tab, b, s);
+    }
+}
+
 // Returns the slot index of `key`, or -1; `value` receives the stored value.
 __device__ __forceinline__ int64_t table_find(const unsigned long long* tab, uint32_t mask, int shift,
                                               uint32_t key, uint32_t& value) {

@@ -31,22 +31,25 @@ namespace spp {
 
 constexpr int kMissBlocks = 64;        // workgroups of the miss kernel (see gather_lists)
 constexpr int kMissThreads = 256;      // threads of each
-constexpr int kClsPer = 8;             // ids per thread: a workgroup classifies 2048 consecutive ids per round
-static_assert(kBlock * kClsPer == kListAlign, "a classification chunk must not straddle two lists");
+constexpr int kClsBlock = 1024;        // threads of the classification
+constexpr int kClsPer = 2;             // ids per thread: a workgroup classifies 2048 consecutive ids per round
+static_assert(kClsBlock * kClsPer == kListAlign, "a classification chunk must not straddle two lists");
 
 struct ClassifyArgs {
     ListTable      t;
-    int64_t        N, lo, hi;
+    uint32_t       N, lo, hi;          // at most 2^31: ids are 32-bit
     const unsigned long long* tab;     // null: no cache
     uint32_t       mask;
     int            shift;
     int64_t        limit;              // slots in use
     const int32_t* local_rank;         // null: the whole local shard is in device memory, row = g - lo
     int64_t        local_limit;        // ranks below this are in device memory (row = rank)
-    int64_t*       desc;               // per virtual row
+    int64_t*       desc;               // per virtual row that misses
     int32_t*       misslist;           // virtual rows that miss
     int64_t*       hitlist;            // rows served from the shard or the cache: source, list and row in the list (make_hit),
     int32_t*       hcount;             //   chunk by chunk: hitlist[chunk * kListAlign + i], i < hcount[chunk]
+    uint64_t*      stat;               // per chunk: ids local, cached, missed remote, read from the host-resident local rows,
+                                       //   16 bits each, added up by hit_items_kernel; null: added to counters and totals here
     unsigned long long* counters;      // [0] local, [1] cache hit, [2] rows in misslist, [3] bad id, [4] unused,
                                        // [5] local rows read from the host (part of [0] and of [2]), [6] rows in duplist,
                                        // [7] rows in the store-ordered list
@@ -61,23 +64,28 @@ struct PrologueArgs {
     int64_t        n_remote;           // rows of the remote store
 };
 
-// Zeroes the per-call counters and lays the lists out in the virtual row space.
-__global__ void gather_prologue_kernel(PrologueArgs p, unsigned long long* counters, int64_t* off, int64_t* cnt,
-                                       int64_t* minfo) {
-    if (threadIdx.x < 8) counters[threadIdx.x] = 0ull;
-    if (threadIdx.x == 0) {
-        minfo[2] = p.n_remote;
-        int64_t o = 0;
-        for (int j = 0; j < p.n_lists; ++j) {
-            int64_t c = p.n_ptr[j] ? *p.n_ptr[j] : p.n[j];
-            if (c < 0) c = 0;
-            if (c > p.n[j]) c = p.n[j];             // never beyond what the caller's buffers hold
-            off[j] = o;
-            cnt[j] = c;
-            o = (o + c + kListAlign - 1) / kListAlign * kListAlign;
-        }
-        off[p.n_lists] = o;
+// Zeroes the per-call counters and lays the lists out in the virtual row space, one list per lane (the
+// device counts of 64 lists read one after the other took 25 us).
+static_assert(kMaxLists <= kWave, "a list per lane");
+__global__ void __launch_bounds__(kWave) gather_prologue_kernel(PrologueArgs p, unsigned long long* counters, int64_t* off,
+                                                                int64_t* cnt, int64_t* minfo) {
+    const int j = threadIdx.x;
+    if (j < 8) counters[j] = 0ull;
+    if (j == 0) minfo[2] = p.n_remote;
+    int64_t c = 0;
+    if (j < p.n_lists) {
+        c = p.n_ptr[j] ? *p.n_ptr[j] : p.n[j];
+        if (c < 0) c = 0;
+        if (c > p.n[j]) c = p.n[j];                 // never beyond what the caller's buffers hold
     }
+    const long long padded = (c + kListAlign - 1) / kListAlign * kListAlign;
+    long long inc = padded;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const long long t = __shfl_up(inc, d, kWave);
+        if (j >= d) inc += t;
+    }
+    if (j < p.n_lists) { off[j] = inc - padded; cnt[j] = c; }
+    if (j == kWave - 1) off[p.n_lists] = inc;       // lists beyond the last one are empty
 }
 
 // Table of the call's missed vertices: the smallest power of two >= twice the miss list (>= 1024
@@ -193,85 +201,117 @@ struct ClaimedFin {
     __device__ void operator()(int total) const { *count = (unsigned long long)(uint32_t)total; }
 };
 
-// One workgroup classifies a chunk of 2048 consecutive ids of one list (eight consecutive ids per
-// thread, so that ranks from a scan over the threads follow the row order), then reserves room for
-// all of the chunk's misses in the miss list with a single atomic, so the list counter sees one
-// atomic per 2048 ids instead of one per wavefront; the chunk's hits go, in row order, to the
-// chunk's own part of the hit list.
-__global__ void __launch_bounds__(kBlock) classify_kernel(ClassifyArgs a) {
-    __shared__ int scan_lds[4];
-    __shared__ unsigned long long base_lds[2];
+// Adds the categories of a chunk (or of several) to the call's counters and the running sums.
+__device__ __forceinline__ void add_categories(unsigned long long* counters, unsigned long long* totals, unsigned long long n_local,
+                                               unsigned long long n_hit, unsigned long long n_rmiss, unsigned long long n_lhost) {
+    if (n_rmiss) atomicAdd(&totals[6], n_rmiss);
+    if (n_lhost) { atomicAdd(&counters[5], n_lhost); atomicAdd(&totals[7], n_lhost); }
+    if (n_local) { atomicAdd(&counters[0], n_local); atomicAdd(&totals[4], n_local); }
+    if (n_hit) { atomicAdd(&counters[1], n_hit); atomicAdd(&totals[5], n_hit); }
+}
+
+// One workgroup classifies a chunk of 2048 consecutive ids of one list (two consecutive ids per thread,
+// so that ranks from a scan over the threads follow the row order), then reserves room for all of the
+// chunk's misses in the miss list with a single atomic; the chunk's hits go, in row order, to the
+// chunk's own part of the hit list.  Bound by two dependent round trips, the ids and the buckets of the
+// cache's table: both of a thread's buckets are in flight together.  (Eight ids per thread probed the
+// table eight times in a row, and five sums per workgroup met on one line with 15 ns each: 2.9M ids in
+// 64 lists 81 us instead of 164, one list of 66k ids 12 instead of 23.)
+__global__ void __launch_bounds__(kClsBlock) classify_kernel(ClassifyArgs a) {
+    __shared__ uint32_t wave_sum[kClsBlock / kWave];
+    __shared__ uint32_t cat[4];
+    __shared__ unsigned long long base_lds;
     __shared__ ListLds ls;
     load_lists(a.t, ls);
     const int64_t total = ls.off[a.t.n_lists];
-    int n_local = 0, n_hit = 0, n_rmiss = 0, n_lhost = 0;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t bmask = a.mask >> 3;
     for (int64_t base = (int64_t)blockIdx.x * kListAlign; base < total; base += (int64_t)gridDim.x * kListAlign) {
         const int j = list_of(ls, a.t.n_lists, base);
         const int64_t lbeg = ls.off[j], n = ls.cnt[j];
         const int32_t* __restrict__ ids = a.t.ids[j];
-        uint32_t missbits = 0, hitbits = 0;
-        int64_t dk[kClsPer];
+        const int64_t i0 = base - lbeg + (int64_t)threadIdx.x * kClsPer;
+        if (threadIdx.x < 4) cat[threadIdx.x] = 0u;
+        uint32_t g[kClsPer], row[kClsPer];
+        bool have[kClsPer], local[kClsPer], remote[kClsPer], host[kClsPer];
+        unsigned long long bucket[kClsPer][kBucketSlots];
 #pragma unroll
         for (int k = 0; k < kClsPer; ++k) {
-            dk[k] = 0;
-            const int64_t i = base - lbeg + (int64_t)threadIdx.x * kClsPer + k;      // a thread takes consecutive rows:
-            if (i >= n) continue;                                                     // the lists come out in row order
-            const int64_t g = ids[i];
-            int64_t d = make_desc(kTagSkip, 0);
-            if (g < 0 || g >= a.N) {
-                atomicOr(&a.counters[3], 1ull);
-            } else if (g >= a.lo && g < a.hi) {
-                ++n_local;
-                const int64_t r = a.local_rank ? (int64_t)a.local_rank[g - a.lo] : g - a.lo;
-                if (!a.local_rank || r < a.local_limit) {
-                    d = make_desc(kTagLocal, r);
+            have[k] = i0 + k < n;
+            g[k] = have[k] ? (uint32_t)ids[i0 + k] : 0xFFFFFFFFu;          // a negative id lies outside [0, N) too
+        }
+#pragma unroll
+        for (int k = 0; k < kClsPer; ++k) {
+            local[k] = g[k] < a.N && g[k] >= a.lo && g[k] < a.hi;
+            remote[k] = g[k] < a.N && !local[k];
+            row[k] = 0u;
+            if (local[k]) row[k] = a.local_rank ? (uint32_t)a.local_rank[g[k] - a.lo] : g[k] - a.lo;
+            if (remote[k] && a.tab) table_load_bucket(a.tab, table_hash(g[k], a.shift) >> 3, bucket[k]);
+        }
+        uint32_t missbits = 0, hitbits = 0;
+        int tag[kClsPer];
+#pragma unroll
+        for (int k = 0; k < kClsPer; ++k) {
+            tag[k] = kTagSkip;
+            host[k] = false;
+            if (local[k]) {
+                if (!a.local_rank || (int64_t)row[k] < a.local_limit) {
+                    tag[k] = kTagLocal;
                     hitbits |= 1u << k;
                 } else {
-                    d = make_desc(kTagLocalHost, g - a.lo);
-                    ++n_lhost;
+                    tag[k] = kTagLocalHost;
+                    row[k] = g[k] - a.lo;
+                    host[k] = true;
                     missbits |= 1u << k;
                 }
-            } else {
+            } else if (remote[k]) {
                 uint32_t slot = 0;
-                const bool found = a.tab && table_find(a.tab, a.mask, a.shift, (uint32_t)g, slot) >= 0 &&
-                                   (int64_t)slot < a.limit;
-                if (found) { d = make_desc(kTagCache, slot); ++n_hit; hitbits |= 1u << k; }
-                else       { d = make_desc(kTagMiss, g < a.lo ? g : g - (a.hi - a.lo)); ++n_rmiss; missbits |= 1u << k; }
+                const bool found = a.tab && table_find_in(a.tab, bmask, a.shift, g[k], bucket[k], slot) && (int64_t)slot < a.limit;
+                if (found) { tag[k] = kTagCache; row[k] = slot; hitbits |= 1u << k; }
+                else       { tag[k] = kTagMiss; row[k] = g[k] < a.lo ? g[k] : g[k] - (a.hi - a.lo); missbits |= 1u << k; }
+            } else if (have[k]) {
+                atomicOr(&a.counters[3], 1ull);                   // an id outside [0, N)
             }
-            a.desc[lbeg + i] = d;
-            dk[k] = d;
         }
         // both lists are compacted with one scan: misses in the low half-word, hits in the high one
         // (a workgroup's totals are at most 2048 each)
-        int total_packed;
-        const int ex = block_exclusive_scan(__popc(missbits) | (__popc(hitbits) << 16), scan_lds, total_packed);
-        const int total_miss = total_packed & 0xFFFF, total_hit = total_packed >> 16;
-        if (threadIdx.x == 0) {
-            if (total_miss) base_lds[0] = atomicAdd(&a.counters[2], (unsigned long long)total_miss);
-            a.hcount[base / kListAlign] = total_hit;          // the chunk's hits go to the chunk's own part of the list
-        }
+        const uint32_t mine = (uint32_t)__popc(missbits) | ((uint32_t)__popc(hitbits) << 16);
+        const uint32_t inc = (uint32_t)wave_inclusive_scan((int)mine);
+        if (lane == kWave - 1) wave_sum[wave] = inc;
         __syncthreads();
-        unsigned long long mpos = base_lds[0] + (unsigned long long)(ex & 0xFFFF);
-        unsigned long long hpos = (unsigned long long)base + (unsigned long long)(ex >> 16);
+        uint32_t ex = inc - mine, all = 0;
+#pragma unroll
+        for (int w = 0; w < kClsBlock / kWave; ++w) { const uint32_t v = wave_sum[w]; all += v; if (w < wave) ex += v; }
+        const uint32_t total_miss = all & 0xFFFFu, total_hit = all >> 16;
+        uint32_t n_local = 0, n_hit = 0, n_rmiss = 0, n_lhost = 0;
 #pragma unroll
         for (int k = 0; k < kClsPer; ++k) {
-            const int32_t r = (int32_t)(base + (int64_t)threadIdx.x * kClsPer + k);
-            if (missbits & (1u << k)) a.misslist[mpos++] = r;
-            if (hitbits & (1u << k)) a.hitlist[hpos++] = make_hit(desc_tag(dk[k]) == kTagCache, desc_row(dk[k]), j, (int64_t)r - lbeg);
+            n_local += (uint32_t)__popcll(__ballot(local[k]));
+            n_lhost += (uint32_t)__popcll(__ballot(host[k]));
+            n_hit += (uint32_t)__popcll(__ballot(remote[k] && (hitbits >> k & 1u)));
+            n_rmiss += (uint32_t)__popcll(__ballot(remote[k] && (missbits >> k & 1u)));
         }
-        __syncthreads();                          // base_lds is reused by the next round
+        if (lane == 0) { atomicAdd(&cat[0], n_local); atomicAdd(&cat[1], n_hit); atomicAdd(&cat[2], n_rmiss); atomicAdd(&cat[3], n_lhost); }
+        if (threadIdx.x == 0) {
+            base_lds = total_miss ? atomicAdd(&a.counters[2], (unsigned long long)total_miss) : 0ull;
+            a.hcount[base / kListAlign] = (int32_t)total_hit;     // the chunk's hits go to the chunk's own part of the list
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (a.stat) a.stat[base / kListAlign] = (uint64_t)cat[0] | ((uint64_t)cat[1] << 16) | ((uint64_t)cat[2] << 32) | ((uint64_t)cat[3] << 48);
+            else add_categories(a.counters, a.totals, cat[0], cat[1], cat[2], cat[3]);
+        }
+        unsigned long long mpos = base_lds + (unsigned long long)(ex & 0xFFFFu);
+        int64_t hpos = base + (int64_t)(ex >> 16);
+#pragma unroll
+        for (int k = 0; k < kClsPer; ++k) {
+            const int64_t r = base + (int64_t)threadIdx.x * kClsPer + k;
+            if (missbits & (1u << k)) { a.misslist[mpos++] = (int32_t)r; a.desc[r] = make_desc(tag[k], row[k]); }
+            if (hitbits & (1u << k)) a.hitlist[hpos++] = make_hit(tag[k] == kTagCache, row[k], j, r - lbeg);
+        }
+        __syncthreads();                          // the LDS words are reused by the next round
     }
-    const int tl = block_reduce_sum(n_local, scan_lds);
-    const int th = block_reduce_sum(n_hit, scan_lds);
-    const int tm = block_reduce_sum(n_rmiss, scan_lds);
-    const int tlh = block_reduce_sum(n_lhost, scan_lds);
-    if (threadIdx.x == 0) {
-        if (tm) atomicAdd(&a.totals[6], (unsigned long long)tm);
-        if (tlh) { atomicAdd(&a.counters[5], (unsigned long long)tlh); atomicAdd(&a.totals[7], (unsigned long long)tlh); }
-        if (tl) { atomicAdd(&a.counters[0], (unsigned long long)tl); atomicAdd(&a.totals[4], (unsigned long long)tl); }
-        if (th) { atomicAdd(&a.counters[1], (unsigned long long)th); atomicAdd(&a.totals[5], (unsigned long long)th); }
-        if (blockIdx.x == 0) atomicAdd(&a.totals[3], 1ull);
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.totals[3], 1ull);
 }
 
 // Device-visible address of a row store that is either device memory or pinned host memory.
@@ -342,54 +382,56 @@ int launch_dup(spp_ctx* ctx, const PendingGather& pg) {
 // Device workspace of one gather call over `rows` virtual rows (padded): the counters and the
 // layout of the lists, one source descriptor per row, and the four row lists.
 namespace spp {
-// Lists the tiles that hold hits for the hit copy (see gather_hit_kernel): one workgroup per id list adds up
-// the tiles of the lists before it (a few thousand chunk counts at most) and then numbers its own.
-constexpr int kItemBlock = 1024;
-__global__ void __launch_bounds__(kItemBlock) hit_items_kernel(const int32_t* __restrict__ hcount, ListTable t, uint32_t vpr,
-                                                               uint32_t tile_vecs, uint64_t* __restrict__ item_list,
-                                                               uint32_t* __restrict__ n_items) {
-    __shared__ uint32_t wsum[kItemBlock / kWave];
-    __shared__ uint32_t carry;
+// Lists the tiles that hold hits for the hit copy (see gather_hit_kernel) and adds up the chunks'
+// categories.  A workgroup takes `per` consecutive chunks: it adds up the tiles of all chunks before its
+// own (a few thousand counts at most), then a wavefront writes a chunk's entries side by side.  (With
+// one workgroup per id list and a thread per chunk, 97k tiles of 1536-byte rows took 13 us, now 8.)
+constexpr int kItemBlock = 256;
+__global__ void __launch_bounds__(kItemBlock) hit_items_kernel(const int32_t* __restrict__ hcount, const uint64_t* __restrict__ stat,
+                                                               ListTable t, uint32_t vpr, uint32_t tile_vecs, int per,
+                                                               uint64_t* __restrict__ item_list, uint32_t* __restrict__ n_items,
+                                                               unsigned long long* counters, unsigned long long* totals) {
+    __shared__ int scan_lds[4];
+    __shared__ uint32_t at_lds[kItemBlock], nv_lds[kItemBlock];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const int64_t c0 = t.off[blockIdx.x] / kListAlign, c1 = t.off[blockIdx.x + 1] / kListAlign;
-    auto tiles_of = [&](int64_t c) { return ((uint32_t)hcount[c] * vpr + tile_vecs - 1) / tile_vecs; };
-    // all threads: the tiles of the chunks before this list's; leaves the sum in `carry`
+    const int64_t chunks = t.off[t.n_lists] / kListAlign;
+    const int64_t c0 = (int64_t)blockIdx.x * per, c1 = c0 + per < chunks ? c0 + per : chunks;
+    if (c0 >= chunks && blockIdx.x > 0) return;
+    auto tiles_of = [&](uint32_t vecs) { return (vecs + tile_vecs - 1) / tile_vecs; };
     uint32_t mine = 0;
-    for (int64_t c = threadIdx.x; c < c0; c += kItemBlock) mine += tiles_of(c);
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
-    if (lane == 0) wsum[wave] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t s = 0;
-        for (int w = 0; w < kItemBlock / kWave; ++w) s += wsum[w];
-        carry = s;
-    }
-    __syncthreads();
+    for (int64_t c = threadIdx.x; c < c0; c += kItemBlock) mine += tiles_of((uint32_t)hcount[c] * vpr);
+    uint32_t at = (uint32_t)block_reduce_sum((int)mine, scan_lds);
+    uint32_t cat[4] = {0, 0, 0, 0};
     for (int64_t cb = c0; cb < c1; cb += kItemBlock) {
         const int64_t c = cb + threadIdx.x;
-        const uint32_t n = c < c1 ? tiles_of(c) : 0u;
-        const uint32_t inc = (uint32_t)wave_inclusive_scan((int)n);
-        const uint32_t before = carry;           // read before this round's update (a barrier follows)
-        if (lane == kWave - 1) wsum[wave] = inc;
+        uint32_t nv = 0;
+        if (c < c1) {
+            nv = (uint32_t)hcount[c] * vpr;
+            const uint64_t s = stat[c];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cat[q] += (uint32_t)(s >> (16 * q)) & 0xFFFFu;
+        }
+        int total;
+        at_lds[threadIdx.x] = at + (uint32_t)block_exclusive_scan((int)tiles_of(nv), scan_lds, total);
+        nv_lds[threadIdx.x] = nv;
         __syncthreads();
-        uint32_t base = before, total = 0;
-        for (int w = 0; w < kItemBlock / kWave; ++w) { const uint32_t v = wsum[w]; total += v; if (w < wave) base += v; }
-        const uint32_t at = base + inc - n;
-        if (n) {
-            const uint32_t nv = (uint32_t)hcount[c] * vpr;
-            for (uint32_t k = 0; k < n; ++k) {
-                const uint32_t in_tile = nv - k * tile_vecs < tile_vecs ? nv - k * tile_vecs : tile_vecs;
-                item_list[at + k] = ((uint64_t)c << 32) | ((uint64_t)k << kHitTileBits) | in_tile;
+        const int nb = c1 - cb < kItemBlock ? (int)(c1 - cb) : kItemBlock;
+        for (int w = wave; w < nb; w += kItemBlock / kWave) {
+            const uint32_t v = nv_lds[w], n = tiles_of(v);
+            for (uint32_t k = lane; k < n; k += kWave) {
+                const uint32_t in_tile = v - k * tile_vecs < tile_vecs ? v - k * tile_vecs : tile_vecs;
+                item_list[at_lds[w] + k] = ((uint64_t)(cb + w) << 32) | ((uint64_t)k << kHitTileBits) | in_tile;
             }
         }
-        __syncthreads();
-        if (threadIdx.x == 0) carry = before + total;
+        at += (uint32_t)total;
         __syncthreads();
     }
-    if (blockIdx.x == (unsigned)t.n_lists - 1 && threadIdx.x == 0) *n_items = carry;
+    if (c1 == chunks && threadIdx.x == 0) *n_items = at;
+    uint32_t sum[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q] = (uint32_t)block_reduce_sum((int)cat[q], scan_lds);
+    if (threadIdx.x == 0) add_categories(counters, totals, sum[0], sum[1], sum[2], sum[3]);
 }
-
 
 struct GatherWs {
     unsigned long long* counters;   // [8]
@@ -401,6 +443,7 @@ struct GatherWs {
     int32_t* misslist;              // [rows]
     int32_t* duplist;               // [rows]
     int32_t* ordered;               // [rows]
+    uint64_t* stat;                 // [rows / kListAlign]
     int32_t* hcount;                // [rows / kListAlign]
 };
 constexpr size_t kWsHeadBytes = 2048;       // counters, off, cnt, minfo: (8 + 2 * (kMaxLists + 1) + 4) * 8 = 1136 bytes
@@ -416,7 +459,8 @@ static GatherWs carve_ws(void* head, void* desc, void* lists, int64_t rows) {
     w.misslist = static_cast<int32_t*>(lists) + 2 * rows;
     w.duplist = w.misslist + rows;
     w.ordered = w.duplist + rows;
-    w.hcount = w.ordered + rows;
+    w.stat = reinterpret_cast<uint64_t*>(w.ordered + rows);      // rows is a multiple of kListAlign
+    w.hcount = reinterpret_cast<int32_t*>(w.stat + rows / kListAlign);
     return w;
 }
 
@@ -427,7 +471,7 @@ static GatherWs carve_ws(void* head, void* desc, void* lists, int64_t rows) {
 constexpr int64_t kStaticRows = SPP_STATIC_GATHER_MAX_ROWS;
 static_assert(kStaticRows % kListAlign == 0, "the static workspace holds whole chunks");
 constexpr size_t kStaticBytes = kWsHeadBytes + (size_t)kStaticRows * (sizeof(int64_t) + 5 * sizeof(int32_t)) +
-                                (size_t)(kStaticRows / kListAlign) * sizeof(int32_t);
+                                (size_t)(kStaticRows / kListAlign) * (sizeof(uint64_t) + sizeof(int32_t));
 static __device__ __align__(256) unsigned char scratch[(kStaticBytes + 255) / 256 * 256];
 
 constexpr int kMaxDevices = 64;
@@ -542,8 +586,9 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
     }
     if (vbound > 0 && !fixed) {
         SPP_TRY(ctx->srcdesc[slot].reserve((size_t)vbound * sizeof(int64_t)));
-        // hit list (64-bit entries), miss list, copy list, misses in store order, hits per chunk
-        SPP_TRY(ctx->misslist[slot].reserve((size_t)vbound * sizeof(int32_t) * 5 + (size_t)(vbound / kListAlign) * sizeof(int32_t)));
+        // hit list (64-bit entries), miss list, copy list, misses in store order, categories and hits per chunk
+        SPP_TRY(ctx->misslist[slot].reserve((size_t)vbound * sizeof(int32_t) * 5 +
+                                            (size_t)(vbound / kListAlign) * (sizeof(uint64_t) + sizeof(int32_t))));
     }
     const GatherWs ws = fixed ? *fixed
                               : carve_ws(ctx->gcount[slot].ptr, ctx->srcdesc[slot].ptr, ctx->misslist[slot].ptr, vbound);
@@ -553,9 +598,10 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
     int64_t* minfo = ws.minfo;
     a.t.off = off; a.t.cnt = cnt;
     pro.n_remote = n_remote;
-    gather_prologue_kernel<<<1, 64, 0, st>>>(pro, counters, off, cnt, minfo);
+    gather_prologue_kernel<<<1, kWave, 0, st>>>(pro, counters, off, cnt, minfo);
     if (vbound > 0) {
-        a.N = N; a.lo = lo; a.hi = hi;
+        const auto id_bound = [](int64_t v) { return (uint32_t)(v < ((int64_t)1 << 31) ? v : (int64_t)1 << 31); };
+        a.N = id_bound(N); a.lo = id_bound(lo); a.hi = id_bound(hi);
         a.tab = cache && cache->limit > 0 ? reinterpret_cast<const unsigned long long*>(cache->table) : nullptr;
         a.mask = cache ? cache->table_mask : 0; a.shift = cache ? cache->table_shift : 0;
         a.limit = cache ? cache->limit : 0;
@@ -567,12 +613,25 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
         int32_t* duplist = ws.duplist;
         int32_t* ordered = ws.ordered;
         a.hcount = ws.hcount;
+        const int V = pick_vec(row_bytes, addr_bits);
+        const uint32_t vpr = (uint32_t)(row_bytes / V);
+        const int64_t vecs = vbound * vpr;
+        // hit copy: many small work items (one tile of 1024 vectors each; at most 256 workgroups per CU in
+        // the grid, which then take several tiles each) let the dispatcher balance the copy
+        const uint32_t tiles_per_chunk = (uint32_t)((kListAlign * vpr + kBlock * kHitUnroll - 1) / (kBlock * kHitUnroll));
+        const int64_t hneed = vbound / kListAlign * tiles_per_chunk;
+        const int grid = (int)(hneed < (int64_t)ctx->num_cu * 256 ? hneed : (int64_t)ctx->num_cu * 256);
+        // the tiles that hold hits, listed once the classification has counted them (not for the caller that
+        // must not allocate, nor where a chunk or a tile number does not fit the list's entries)
+        static_assert(kBlock * kHitUnroll < (1 << kHitTileBits), "an entry holds the vectors of a tile");
+        const bool list_items = !fixed && n_lists > 0 && tiles_per_chunk <= (1u << kHitTileBits);
+        a.stat = list_items ? ws.stat : nullptr;
         a.totals = reinterpret_cast<unsigned long long*>(ctx->totals);
         const int64_t cneed = vbound / kListAlign;
         const int cgrid = (int)(cneed < (int64_t)ctx->num_cu * 8 ? cneed : (int64_t)ctx->num_cu * 8);
         {
             ScopedTimer tc(ctx, SPP_T_GATHER_CLASSIFY, st);
-            classify_kernel<<<cgrid, kBlock, 0, st>>>(a);
+            classify_kernel<<<cgrid, kClsBlock, 0, st>>>(a);
             const int sgrid = ctx->num_cu * 4;
             if (store_order) {
                 uint32_t* first = ctx->gfirst.as<uint32_t>();
@@ -586,25 +645,19 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
                 gather_share_kernel<<<sgrid, kBlock, 0, st>>>(mtab, minfo, a.desc, a.misslist, duplist, counters, a.totals);
             }
         }
-        const int V = pick_vec(row_bytes, addr_bits);
-        const uint32_t vpr = (uint32_t)(row_bytes / V);
-        const int64_t vecs = vbound * vpr;
-        // hit copy: many small work items (one tile of 1024 vectors each; at most 256 workgroups per CU in
-        // the grid, which then take several tiles each) let the dispatcher balance the copy
-        const uint32_t tiles_per_chunk = (uint32_t)((kListAlign * vpr + kBlock * kHitUnroll - 1) / (kBlock * kHitUnroll));
-        const int64_t hneed = vbound / kListAlign * tiles_per_chunk;
-        const int grid = (int)(hneed < (int64_t)ctx->num_cu * 256 ? hneed : (int64_t)ctx->num_cu * 256);
-        // the tiles that hold hits, listed once the classification has counted them (not for the caller that
-        // must not allocate, nor where a chunk or a tile number does not fit the list's entries)
         uint64_t* item_list = nullptr;
         uint32_t* n_items = nullptr;
-        static_assert(kBlock * kHitUnroll < (1 << kHitTileBits), "an entry holds the vectors of a tile");
-        if (!fixed && n_lists > 0 && tiles_per_chunk <= (1u << kHitTileBits)) {
+        if (list_items) {
             SPP_TRY(ctx->hititems[slot].reserve((size_t)(hneed + 2) * sizeof(uint64_t)));
             n_items = ctx->hititems[slot].as<uint32_t>();
             item_list = ctx->hititems[slot].as<uint64_t>() + 2;
-            hit_items_kernel<<<n_lists, kItemBlock, 0, st>>>(a.hcount, a.t, vpr, (uint32_t)(kBlock * kHitUnroll), item_list, n_items);
         }
+        auto launch_items = [&]() {
+            if (!item_list) return;
+            const int per = cneed > 32 * 256 ? (int)((cneed + 255) / 256) : 32;
+            hit_items_kernel<<<(unsigned)((cneed + per - 1) / per), kItemBlock, 0, st>>>(a.hcount, ws.stat, a.t, vpr, (uint32_t)(kBlock * kHitUnroll), per,
+                                                                                        item_list, n_items, counters, a.totals);
+        };
         // The miss kernel is kept to 64 workgroups of 256 threads: they saturate the PCIe link (32
         // workgroups of 512 threads or 16 of 1024 reach 95 % of their rate, 64 of 512 less).  A CU
         // that hosts host-memory loads serves every other wavefront on it slowly, so each of these
@@ -654,32 +707,39 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
             SPP_HIP(hipEventRecord(ctx->ev_join[slot], ctx->side));
             return SPP_OK;
         };
+        // the counters are final once the classification has run, whether or not the misses have landed: the hit
+        // copy leaves them in pinned memory
+        int64_t* mirror = ctx->h_pinned + 40;
         auto launch_hit = [&]() {
             ScopedTimer th(ctx, SPP_T_GATHER_HIT, st);
             const char* loc = static_cast<const char*>(d_local);
             const char* cr = static_cast<const char*>(crow);
             switch (V) {
-                case 16: gather_hit_kernel<16><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed); break;
-                case 8:  gather_hit_kernel<8><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed); break;
-                case 4:  gather_hit_kernel<4><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed); break;
-                default: gather_hit_kernel<2><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed); break;
+                case 16: gather_hit_kernel<16><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed, counters, mirror); break;
+                case 8:  gather_hit_kernel<8><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed, counters, mirror); break;
+                case 4:  gather_hit_kernel<4><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed, counters, mirror); break;
+                default: gather_hit_kernel<2><<<grid, kBlock, 0, st>>>(a.hitlist, a.hcount, a.t, loc, cr, vpr, tiles_per_chunk, item_list, n_items, hneed, counters, mirror); break;
             }
         };
-        // Order of the copies.  The stream waits for the miss copy of the call before (its fetched
-        // rows have landed), runs the hit copy with the whole chip, queues this call's miss copy on
-        // the side stream and then copies the rows that shared a vertex of the earlier miss copy
-        // (device to device, beside the new miss copy; the call before is complete from there on).
-        // SPP_HIT_BESIDE_MISS queues the new miss copy first instead, so that it starts the moment
-        // the earlier one ends and the PCIe link never idles; the hit copy then runs beside it on
-        // the CUs it leaves free.  Measured on groups of 64 minibatches: 256-byte rows, a quarter
-        // of the group's time spent in the hit copy: pipeline 19 % faster, hit copy at 0.61 of
-        // the HBM peak instead of 0.69; 400-byte rows, link busy 95 % of the time anyway: 4.5 %
-        // faster, 0.66 instead of 0.73.  The default keeps the HBM-bound copy at its full rate.
-        if (flags & SPP_HIT_BESIDE_MISS) {
+        // Order of the copies.  A call that joins its own miss copy queues it first and copies the hits beside
+        // it on the CUs it leaves free: the two ran one after the other before (64 lists of 256-byte rows with
+        // a fifth missed: 0.2 of 3.7 ms; one list of 400-byte rows: also the 40 us between the two launches).
+        // With SPP_NO_JOIN the stream waits for the miss copy of the call before (its fetched rows have
+        // landed), runs the hit copy with the whole chip, queues this call's miss copy on the side stream and
+        // then copies the rows that shared a vertex of the earlier miss copy (device to device, beside the new
+        // miss copy; the call before is complete from there on).  SPP_HIT_BESIDE_MISS takes the first order
+        // there too, so that the new miss copy starts the moment the earlier one ends and the PCIe link never
+        // idles.  Measured on groups of 64 minibatches in a loop of unjoined calls: 256-byte rows, a quarter of
+        // the group's time spent in the hit copy: pipeline 19 % faster, hit copy at 0.61 of the HBM peak instead
+        // of 0.69; 400-byte rows, link busy 95 % of the time anyway: 4.5 % faster, 0.66 instead of 0.73.  There
+        // the default keeps the HBM-bound copy at its full rate.
+        if ((flags & SPP_HIT_BESIDE_MISS) || !(flags & SPP_NO_JOIN)) {
             if (miss_path) SPP_TRY(launch_miss());
             SPP_TRY(spp_gather_join(ctx));
+            launch_items();
             launch_hit();
         } else {
+            launch_items();
             const PendingGather before = ctx->pending;
             if (before.active) {
                 SPP_HIP(hipStreamWaitEvent(st, ctx->ev_join[before.slot], 0));
@@ -698,9 +758,7 @@ static int gather_lists(spp_ctx* ctx, const spp_cache* cache, const void* d_loca
         }
     }
     SPP_HIP(hipGetLastError());
-    int64_t* hp = ctx->h_pinned + 40;
-    // the counters are final once the classification has run, whether or not the misses have landed
-    SPP_HIP(hipMemcpyAsync(hp, counters, 7 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    if (vbound == 0) SPP_HIP(hipMemcpyAsync(ctx->h_pinned + 40, counters, 7 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     ctx->h_pinned[48] = row_bytes;
     ctx->h_pinned[49] = dremote ? 1 : 0;
     if (flags & SPP_SYNC) {

@@ -95,8 +95,7 @@ __device__ __forceinline__ int64_t make_hit(bool from_cache, int64_t src_row, in
 // have and leave at once where the chunk's hits end; a list that misses a tenth of its ids then
 // strews a tenth of empty workgroups among the busy ones, each of which waits out a load behind
 // the copy's own traffic before it can leave (5 % of the copy's time on 256-byte rows).  With the
-// list the surplus workgroups are the last of the grid.  One workgroup per id list: it adds up the
-// tiles of the lists before it (a few thousand chunk counts at most) and then numbers its own.
+// list the surplus workgroups are the last of the grid.
 constexpr int kHitTileBits = 16;         // tiles of a chunk that an entry of the list can name
 template <int V, int U = kHitUnroll>
 __global__ void __launch_bounds__(kBlock) gather_hit_kernel(const int64_t* __restrict__ hitlist,
@@ -104,8 +103,11 @@ __global__ void __launch_bounds__(kBlock) gather_hit_kernel(const int64_t* __res
                                                             const char* __restrict__ local,
                                                             const char* __restrict__ cache, uint32_t vpr,
                                                             uint32_t tiles_per_chunk, const uint64_t* __restrict__ item_list,
-                                                            const uint32_t* __restrict__ n_items, int64_t item_cap) {
+                                                            const uint32_t* __restrict__ n_items, int64_t item_cap,
+                                                            const unsigned long long* __restrict__ counters,
+                                                            int64_t* __restrict__ mirror) {
     typedef typename VecOf<V>::type vec_t;
+    if (blockIdx.x == 0 && threadIdx.x < 7) mirror[threadIdx.x] = (int64_t)counters[threadIdx.x];    // for the host
     // one tile: vectors [base, nv) of the chunk's hits, kBlock * U of them at most
     auto copy_tile = [&](int64_t chunk, uint32_t base, uint32_t nv) {
         const int64_t* __restrict__ hl = hitlist + chunk * kListAlign;
