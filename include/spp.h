@@ -99,10 +99,9 @@ void spp_graph_destroy(spp_graph* g);
  *       p^[0](u) = min(1, B/nT) for u in T, else 0
  *       p^[h](u) = 1 - prod over {v : u in adj(v)} of (1 - min(1, f_h/d(v)) * p^[h-1](v))    eq. (2)
  *       p(u)     = 1 - prod_{h=1..L} (1 - p^[h](u))                                         eq. (1)
- *     Products are carried as sums of log1p in fp64; results are stored as fp32.  The call waits
- *     for the device at most once per hop (it reads the size of the hop's frontier to choose
- *     between the push and the pull form), and not at all after the first pulled hop: the hops
- *     that follow are pulled without asking.
+ *     Products are carried as sums of log1p in fp64; results are stored as fp32.  The push and the
+ *     pull form of a hop are chosen between on the device, by the size of the hop's frontier (a hop
+ *     after a pulled one is pulled without looking): the call waits only with SPP_SYNC.
  *     d_p_total: fp32[N], required.  d_p_hop: fp32[L*N] (hop h at offset (h-1)*N) or NULL.
  *     flags: SPP_VIP_INCLUDE_HOP0, SPP_SYNC.  The graph must have been created with
  *     SPP_GRAPH_IN_LISTS (else SPP_E_ARG).  Vertices with d(v) = 0 contribute nothing. */
@@ -114,7 +113,7 @@ int  spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t* d_T, int
  * in push form over a sparse frontier (its out-edges were at most M/16), 0 if it was pulled over
  * the transposed structure; frontier_edges[h-1] = out-edges of the vertices with a non-zero weight at hop h
  * (the edges a hop has to touch at all), or -1 where the library did not ask: the hop after a pulled
- * hop is pulled too.  Either array may be NULL. */
+ * hop is pulled too.  Either array may be NULL.  Waits for the context's stream. */
 int  spp_vip_last_hops(spp_ctx* ctx, int32_t* pushed, int64_t* frontier_edges, int32_t L);
 
 /* (2) Replica cache (Sec. 3.2): among the vertices outside [lo,hi) with d_score > 0, the first

@@ -200,9 +200,14 @@ extern "C" int spp_stream_rates(spp_ctx* c, const void* d_a, void* d_b, int64_t 
 
 extern "C" int spp_vip_last_hops(spp_ctx* c, int32_t* pushed, int64_t* frontier_edges, int32_t L) {
     SPP_CHECK(c != nullptr && L >= 0 && L <= SPP_MAX_L, SPP_E_ARG, "spp_vip_last_hops: bad argument");
+    SPP_HIP(hipSetDevice(c->device));
+    SPP_HIP(hipStreamSynchronize(c->stream));        // the hops decide on the device how they are walked
+    const int hops = c->vip_hops < 0 ? -c->vip_hops : c->vip_hops;
+    const int64_t* m = c->h_pinned + spp::kHopMirror;
     for (int h = 0; h < L; ++h) {
-        if (pushed) pushed[h] = c->vip_pushed[h];
-        if (frontier_edges) frontier_edges[h] = c->vip_frontier_edges[h];
+        const bool given = c->vip_hops < 0 && h < hops;
+        if (pushed) pushed[h] = given ? 1 : h < hops ? (int32_t)m[2 * h] : 0;
+        if (frontier_edges) frontier_edges[h] = given ? -1 : h < hops ? m[2 * h + 1] : 0;
     }
     return SPP_OK;
 }

@@ -62,6 +62,8 @@ struct DevBuf {
 };
 
 constexpr int kNumTimers = SPP_T_COUNT;
+constexpr int kHopMirror = 2048;         // where a VIP propagation leaves, in the context's pinned mirror (int64 index), per hop
+                                         //   pushed?, frontier edges (or -1); then the flag for bad training ids
 constexpr size_t kKeptSortBytes = (size_t)32 << 20;      // set-up workspaces up to this size stay with the context, larger ones do not
 
 // Several id lists gathered by one set of launches.  List j owns the virtual rows
@@ -129,7 +131,7 @@ struct spp_ctx {
     spp::DevBuf gtable;                 // vertices missed by the current gather call (id -> first row)
     spp::DevBuf gfirst;                 // the same per row of the remote store (SPP_STORE_ORDER): first row that misses it
     int64_t*    h_pinned = nullptr;     // pinned host mirror (8192 int64): gather counters from 40, sampler counts from 64,
-                                        // per-workgroup frontier sizes of the VIP propagation from 2048
+                                        // how the last VIP propagation walked its hops from kHopMirror
     int64_t*    totals = nullptr;       // device int64[16], running sums since the last reset (see spp_ctx_totals)
     // vip workspaces
     spp::DevBuf y0, y1, tot, acc, frontier;
@@ -140,8 +142,7 @@ struct spp_ctx {
     int         tile_lds_set = 0;       // dynamic LDS bytes the dense-hop kernel has been allowed on this device
     int         dedup_lds_set = 0;      // the LDS dedup kernel of the sampler has been allowed its 76 KB
     int         x_lds_set = 0;          // the two kernels of the chunked layout have been allowed theirs
-    int         vip_pushed[SPP_MAX_L] = {};          // last vip_propagate: hop done in push form?
-    int64_t     vip_frontier_edges[SPP_MAX_L] = {};  // last vip_propagate: out-edges of each hop's frontier
+    int         vip_hops = 0;           // hops of the last propagation; negative: with given probabilities (always pushed)
     // timing: while enabled every timed piece of device work gets its own pair of events
     int         timing = 0;
     struct Span { int idx; hipEvent_t t0, t1; };

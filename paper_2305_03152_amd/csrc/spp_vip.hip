@@ -19,7 +19,9 @@
 // counts the hop's frontier (vertices with y != 0) and its out-edges; when that is a small share of
 // the graph the frontier is compacted into a list and the hop is done in push form instead: each
 // frontier vertex adds its y to the fp64 accumulator of every member of its row (atomic adds), and
-// one pass finishes all vertices.
+// one pass finishes all vertices.  Which form a hop takes is decided on the device: the launches of both
+// are queued and those of the other form leave at once (a few us each, where reading the frontier's
+// size back cost the host 35 to 60 us per hop, with nothing queued behind it).
 #include "spp_common.h"
 #include "spp_device.h"
 
@@ -29,7 +31,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int64_t kPushShare = 16;       // push when the frontier's out-edges are at most M/16
 constexpr int kStatBlocks = 2048;        // most workgroups that report a part of the next frontier's size
-constexpr int kStatMirror = 2048;        // where those reports land in the context's pinned mirror (int64 index)
+constexpr uint32_t kPushed = 1, kPulled = 2;
 
 struct VipHop {
     const int64_t* rowptr;     // forward CSR, for d(u)
@@ -133,6 +135,16 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
     for (int64_t i = tid; i < n; i += stride) p[i] = v;
 }
 
+// What a propagation starts from: no weights, no totals (if hop 0 counts), no bad id seen.
+__global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y, double* __restrict__ tot, int64_t N, int* bad) {
+    const int64_t stride = (int64_t)gridDim.x * kBlock, tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = tid; i < (N + 3) / 4; i += stride) reinterpret_cast<f32x4*>(y)[i] = z;      // y holds a vector more than N
+    if (tot)
+        for (int64_t i = tid; i < N; i += stride) tot[i] = 0.0;
+    if (tid == 0) *bad = 0;
+}
+
 // The frontier itself (any order): list[0 .. *cursor) = vertices whose y is not zero and whose row
 // is not empty; a row of more than kPieceEdges entries is listed once per piece of that many
 // entries (adjacent in the list), so that the kernels that walk the frontier's rows can hand the
@@ -145,13 +157,17 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
 constexpr int64_t kPieceEdges = 4096;
 __host__ __device__ inline int64_t frontier_list_capacity(int64_t N, int64_t M) { return N + M / kPieceEdges; }
 
+// With `how`: only if the hop is pushed.  With `acc`: also empties the accumulators of the vertices it looks at.
 template <int kListPer>
 __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* __restrict__ y,
                                                                    const int64_t* __restrict__ rowptr, int64_t N,
                                                                    int32_t* __restrict__ list,
-                                                                   unsigned long long* __restrict__ cursor) {
+                                                                   unsigned long long* __restrict__ cursor,
+                                                                   const uint32_t* __restrict__ how,
+                                                                   double* __restrict__ acc) {
     __shared__ int scan_lds[4];
     __shared__ unsigned long long start;
+    if (how && *how != kPushed) return;
     const int64_t round = (int64_t)kBlock * kListPer;
     auto pieces = [&](int64_t v) { return (int)((rowptr[v + 1] - rowptr[v] + kPieceEdges - 1) / kPieceEdges); };
     for (int64_t r0 = (int64_t)blockIdx.x * round; r0 < N; r0 += (int64_t)gridDim.x * round) {
@@ -161,6 +177,12 @@ __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* 
         const int64_t w0 = r0 + (int64_t)(threadIdx.x >> 6) * (kWave * kListPer);
         auto vertex = [&](int bit) { return w0 + 4 * ((int64_t)(bit >> 2) * kWave + lane_id()) + (bit & 3); };
         uint64_t nz = 0;
+        if (acc)                                 // 16-byte aligned; r0 is even
+            for (int64_t i = r0 + 2 * threadIdx.x; i < r0 + round && i < N; i += 2 * kBlock) {
+                typedef double f64x2 __attribute__((ext_vector_type(2)));
+                if (i + 1 < N) *reinterpret_cast<f64x2*>(acc + i) = f64x2{0.0, 0.0};
+                else acc[i] = 0.0;
+            }
 #pragma unroll
         for (int k = 0; k < kListPer / 4; ++k) {
             const int64_t v = vertex(4 * k);
@@ -189,9 +211,9 @@ __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* 
 }
 
 inline void launch_frontier_list(int grid, hipStream_t st, const float* y, const int64_t* rowptr, int64_t N, int32_t* list,
-                                 unsigned long long* cursor) {
-    if (N >= (int64_t)1 << 25) vip_frontier_list_kernel<64><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor);
-    else vip_frontier_list_kernel<8><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor);
+                                 unsigned long long* cursor, const uint32_t* how = nullptr, double* acc = nullptr) {
+    if (N >= (int64_t)1 << 22) vip_frontier_list_kernel<64><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how, acc);
+    else vip_frontier_list_kernel<8><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how, acc);
 }
 
 // Entry i of that list: where its piece of the row starts in col[] and how many entries it has.
@@ -213,10 +235,48 @@ __device__ __forceinline__ int32_t frontier_entry(const int32_t* __restrict__ li
     return v;
 }
 
-__global__ void __launch_bounds__(kBlock) vip_push_finish_kernel(VipHop a, const double* __restrict__ acc, int64_t N) {
+// How a hop is walked: pushed if its frontier's out-edges are at most M / kPushShare, as counted by the
+// kernel that wrote its y; pulled without looking after a pulled hop (frontiers that have grown large
+// rarely shrink, and either form is correct for any frontier).  One workgroup; also empties the
+// list's cursor.
+__global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long long* __restrict__ stat, int nstat, int64_t M,
+                                                            int h, uint32_t* __restrict__ how,
+                                                            unsigned long long* __restrict__ cursor,
+                                                            int64_t* __restrict__ mirror) {
+    __shared__ unsigned long long red[kBlock / kWave];
+    unsigned long long edges = 0;
+    for (int i = threadIdx.x; i < nstat; i += kBlock) edges += stat[2 * i + 1];
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) edges += __shfl_down((long long)edges, off, kWave);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = edges;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        edges = red[0] + red[1] + red[2] + red[3];
+        const bool asked = h == 1 || how[h - 1] == kPushed;
+        const bool push = asked && (int64_t)edges * kPushShare <= M;
+        how[h] = push ? kPushed : kPulled;
+        *cursor = 0ull;
+        mirror[2 * (h - 1)] = push ? 1 : 0;
+        mirror[2 * (h - 1) + 1] = asked ? (int64_t)edges : -1;
+    }
+}
+
+// Finishes all vertices: after a push from the accumulators, after a pull from the shares' sums (unless the
+// pull has finished its vertices itself).
+__global__ void __launch_bounds__(kBlock) vip_finish_kernel(VipHop a, const uint32_t* __restrict__ how, int fused_pull,
+                                                            const double* __restrict__ acc, int parts, int64_t part_stride,
+                                                            int64_t N, const int* __restrict__ bad, int64_t* __restrict__ bad_mirror) {
+    const bool push = *how == kPushed;
+    if (a.last && blockIdx.x == 0 && threadIdx.x == 0) *bad_mirror = *bad;
+    if (!push && fused_pull) return;
+    const int n = push ? 1 : parts;
     unsigned long long verts = 0, edges = 0;
-    vip_finish_all(a, N, [&](int64_t u) { return acc[u]; }, verts, edges);
-    if (!a.last) write_frontier_stat(a.stat, verts, edges);
+    vip_finish_all(a, N, [&](int64_t u) {
+        double S = acc[u];
+        for (int j = 1; j < n; ++j) S += acc[(int64_t)j * part_stride + u];
+        return S;
+    }, verts, edges);
+    if (!a.last && push) write_frontier_stat(a.stat, verts, edges);
 }
 
 // Dense hops, blocked: one workgroup takes the j-th of `parts` shares of the edges that end in one
@@ -250,8 +310,10 @@ static_assert(kTileWaves * kTileWin * sizeof(float) == kTileWinBytes, "the layou
 __global__ void __launch_bounds__(kTileBlock) vip_tile_kernel(const uint32_t* __restrict__ t_edge,
                                                               const int64_t* __restrict__ first, int nch, int parts,
                                                               int rbits, uint32_t N, const float* __restrict__ y,
-                                                              double* __restrict__ part, int64_t part_stride) {
+                                                              double* __restrict__ part, int64_t part_stride,
+                                                              const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
+    if (*how != kPulled) return;
     const int R = 1 << rbits;
     float* win = reinterpret_cast<float*>(acc + R) + (threadIdx.x >> 6) * kTileWin;      // this wavefront's
     uint32_t* bound = reinterpret_cast<uint32_t*>(acc + R) + kTileWaves * kTileWin;
@@ -392,17 +454,6 @@ inline int tile_parts(int num_cu, int64_t nrb, int64_t M) {
     return best;
 }
 
-__global__ void __launch_bounds__(kBlock) vip_tile_finish_kernel(VipHop a, const double* __restrict__ part, int parts,
-                                                                 int64_t part_stride, int64_t N) {
-    unsigned long long verts = 0, edges = 0;
-    vip_finish_all(a, N, [&](int64_t u) {
-        double S = part[u];
-        for (int j = 1; j < parts; ++j) S += part[(int64_t)j * part_stride + u];
-        return S;
-    }, verts, edges);
-    if (!a.last) write_frontier_stat(a.stat, verts, edges);
-}
-
 // ---- dense hops over the chunked layout -------------------------------------------------------
 // When y does not stay in the caches (10^8 vertices: 444 MB), the gathers of the kernel above fetch
 // a 128-byte line per edge and the hop runs at a tenth of the edge stream's rate.  The chunked
@@ -419,8 +470,10 @@ constexpr int kXUnroll = 4;              // vectors (four entries) per lane and 
 
 __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __restrict__ x_src,
                                                              const int64_t* __restrict__ chunk_first, int nch, int64_t N,
-                                                             const float* __restrict__ y, float* __restrict__ vals) {
+                                                             const float* __restrict__ y, float* __restrict__ vals,
+                                                             const uint32_t* __restrict__ how) {
     extern __shared__ float ych[];
+    if (*how != kPulled) return;
     constexpr int C = 1 << kXSrcBits;
     for (int c = blockIdx.x; c < nch; c += gridDim.x) {
         const int64_t v0 = (int64_t)c << kXSrcBits;
@@ -497,14 +550,15 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
 // group of kXGroup pieces at a time: prefix[k] = first vector of piece k in that sequence, start[k]
 // = where the piece lies in the arrays.  With one share per block the workgroup finishes the
 // block's vertices itself (p^[h], running total, next hop's y); otherwise it leaves its sums in
-// part[j] for vip_tile_finish_kernel.
+// part[j] for vip_finish_kernel.
 __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __restrict__ vals,
                                                              const uint16_t* __restrict__ x_row,
                                                              const uint32_t* __restrict__ x_start,
                                                              const uint32_t* __restrict__ x_prefix, int nch, int parts,
                                                              int64_t N, double* __restrict__ part, int64_t part_stride,
-                                                             VipHop a) {
+                                                             VipHop a, const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
+    if (*how != kPulled) return;
     constexpr int R = 1 << kTileRowBits;
     uint32_t* prefix = reinterpret_cast<uint32_t*>(acc + R);     // [kXGroup + 1]
     uint32_t* start = prefix + kXGroup + 1;                      // [kXGroup]
@@ -789,8 +843,10 @@ __global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t*
                                                                   const float* __restrict__ y,
                                                                   const int64_t* __restrict__ rowptr,
                                                                   const int32_t* __restrict__ col,
-                                                                  double* __restrict__ acc) {
+                                                                  double* __restrict__ acc,
+                                                                  const uint32_t* __restrict__ how) {
     __shared__ BinPortion po;
+    if (*how != kPushed) return;
     const int64_t nf = (int64_t)*nf_ptr;
     const PortionMap pm(nf);
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
@@ -1069,12 +1125,11 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
             vipg_finish_kernel<<<fill_grid, kBlock, 0, st>>>(acc, tot, (h == 1 && !include0) ? 1 : 0, h == L ? 1 : 0,
                                                              d_p_hop ? d_p_hop + (int64_t)(h - 1) * N : nullptr,
                                                              d_p_total, pnext, N, parts, part_stride);
-            ctx->vip_pushed[h - 1] = 1;
-            ctx->vip_frontier_edges[h - 1] = -1;
             float* tmp = pcur; pcur = pnext; pnext = tmp;
         }
     }
     SPP_HIP(hipGetLastError());
+    ctx->vip_hops = -L;
     if (flags & SPP_SYNC) {
         int bad = 0;
         SPP_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -1099,6 +1154,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     const int64_t N = g->N;
     SPP_TRY(ctx->y0.reserve((size_t)(N + 4) * sizeof(float)));       // dense hops read y as whole vectors of four
     SPP_TRY(ctx->y1.reserve((size_t)(N + 4) * sizeof(float)));
+    static_assert(2 * SPP_MAX_L + 1 <= 64, "fits the mirror");
     SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double) + sizeof(int)));
     int parts = tile_parts(ctx->num_cu, g->nrb, g->M);
     // the chunked layout: with a row block per CU or more, one workgroup takes a whole block and
@@ -1130,13 +1186,15 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         SPP_TRY(ctx->xvals.reserve((size_t)(g->x_entries > 0 ? g->x_entries : 4) * sizeof(float)));
     }
     // the kernels that write a hop's y run this many workgroups; each leaves the size of the part of
-    // the next frontier it saw (at most kStatBlocks pairs fit the pinned mirror)
+    // the next frontier it saw (at most kStatBlocks pairs)
     const int fill_grid = ctx->num_cu * 8 < kStatBlocks ? ctx->num_cu * 8 : kStatBlocks;
     const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + 2 * (size_t)kStatBlocks) * sizeof(unsigned long long)));
+    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + 2 * (size_t)kStatBlocks + SPP_MAX_L + 1) * sizeof(unsigned long long)));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));    // [2]: cursor of the list
     unsigned long long* fstat = fcount + 4;
+    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + 2 * kStatBlocks);      // [1 .. L]: how each hop is walked
+    int64_t* mirror = ctx->h_pinned + kHopMirror;
     float* ycur = ctx->y0.as<float>();
     float* ynext = ctx->y1.as<float>();
     double* tot = ctx->tot.as<double>();
@@ -1147,12 +1205,9 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
 
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
-        fill_f32_kernel<<<fill_grid, kBlock, 0, st>>>(ycur, N, 0.f);
-        if (include0) fill_f64_kernel<<<fill_grid, kBlock, 0, st>>>(tot, N, 0.0);
-        fill_f32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<float*>(d_bad), 1, 0.f);
+        vip_clear_kernel<<<fill_grid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, N, d_bad);
         vip_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_T, nT, N, p0, (double)fanouts[0], g->rowptr, ycur, tot, include0,
                                                       d_bad, fstat);
-        bool prev_pulled = false;
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
             VipHop a;
@@ -1164,59 +1219,33 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             a.first = (h == 1 && !include0) ? 1 : 0;
             a.last = (h == L) ? 1 : 0;
             a.stat = fstat;
-            // frontier of this hop and its out-edges, as counted by the kernel that wrote this hop's y;
-            // a small frontier is pushed, a large one pulled
-            // (after a pulled hop the next one is pulled without asking: frontiers that have grown large
-            // rarely shrink, either form is correct for any frontier, and the question costs a host
-            // round trip of about 25 us)
-            unsigned long long fc[2] = {0, 0};
-            if (!prev_pulled) {
-                const unsigned long long* hs = reinterpret_cast<const unsigned long long*>(ctx->h_pinned + kStatMirror);
-                SPP_HIP(hipMemcpyAsync(ctx->h_pinned + kStatMirror, fstat, 2 * (size_t)fill_grid * sizeof(unsigned long long),
-                                       hipMemcpyDeviceToHost, st));
-                SPP_HIP(hipStreamSynchronize(st));
-                for (int b = 0; b < fill_grid; ++b) { fc[0] += hs[2 * b]; fc[1] += hs[2 * b + 1]; }
-            }
-            const bool push = !prev_pulled && (int64_t)fc[1] * kPushShare <= g->M;
-            if (push) {
-                double* acc = ctx->acc.as<double>();
-                fill_f64_kernel<<<fill_grid, kBlock, 0, st>>>(acc, N, 0.0);
-                if (fc[0] > 0) {
-                    fill_f64_kernel<<<1, 64, 0, st>>>(reinterpret_cast<double*>(fcount + 2), 1, 0.0);
-                    launch_frontier_list(fill_grid, st, ycur, g->rowptr, N, flist, fcount + 2);
-                    // at most this many list entries (vertices and pieces of long rows); the kernel reads the count itself
-                    const int64_t entries = (int64_t)fc[0] + (int64_t)fc[1] / kPieceEdges;
-                    const int64_t pgrid = (int64_t)ctx->num_cu * 8, need = (entries + kWave - 1) / kWave;
-                    vip_push_flat_kernel<<<(unsigned)(need < pgrid ? need : pgrid), kBinBlock, 0, st>>>(
-                        flist, fcount + 2, ycur, g->rowptr, g->col, acc);
-                }
-                vip_push_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, acc, N);
-            } else if (g->has_x) {
+            double* acc = ctx->acc.as<double>();
+            const uint32_t* how_h = how + h;
+            vip_decide_kernel<<<1, kBlock, 0, st>>>(fstat, fill_grid, g->M, h, how, fcount + 2, mirror);
+            launch_frontier_list(fill_grid, st, ycur, g->rowptr, N, flist, fcount + 2, how_h, acc);
+            vip_push_flat_kernel<<<ctx->num_cu * 8, kBinBlock, 0, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, acc, how_h);
+            int fused = 0;
+            if (g->has_x) {
                 const int egrid = g->x_nch < ctx->num_cu * 4 ? g->x_nch : ctx->num_cu * 4;
                 vip_expand_kernel<<<egrid, kXBlock, x_lds_expand, st>>>(g->x_src, g->x_chunk_first, g->x_nch, N, ycur,
-                                                                        ctx->xvals.as<float>());
+                                                                        ctx->xvals.as<float>(), how_h);
                 vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(
-                    ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, ctx->acc.as<double>(),
-                    part_stride, a);
-                if (parts > 1) vip_tile_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, ctx->acc.as<double>(), parts, part_stride, N);
+                    ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, a, how_h);
+                fused = parts == 1;
             } else {
                 vip_tile_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, lds_bytes, st>>>(
-                    g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, (uint32_t)N, ycur, ctx->acc.as<double>(), part_stride);
-                vip_tile_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, ctx->acc.as<double>(), parts, part_stride, N);
+                    g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, (uint32_t)N, ycur, acc, part_stride, how_h);
             }
-            ctx->vip_pushed[h - 1] = push ? 1 : 0;
-            ctx->vip_frontier_edges[h - 1] = prev_pulled ? -1 : (int64_t)fc[1];     // -1: not asked
-            prev_pulled = !push;
+            vip_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N, d_bad, mirror + 2 * SPP_MAX_L);
             float* t = ycur; ycur = ynext; ynext = t;
         }
     }
     SPP_HIP(hipGetLastError());
+    ctx->vip_hops = L;
     // training ids are checked on the device; the flag is read when the caller asks to wait
     if (flags & SPP_SYNC) {
-        int bad = 0;
-        SPP_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
         SPP_HIP(hipStreamSynchronize(st));
-        SPP_CHECK(bad == 0, SPP_E_ARG, "spp_vip_propagate: a training vertex id lies outside [0, N)");
+        SPP_CHECK(mirror[2 * SPP_MAX_L] == 0, SPP_E_ARG, "spp_vip_propagate: a training vertex id lies outside [0, N)");
     }
     return SPP_OK;
 }
