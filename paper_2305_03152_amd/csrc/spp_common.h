@@ -142,6 +142,7 @@ struct spp_ctx {
     int         tile_lds_set = 0;       // dynamic LDS bytes the dense-hop kernel has been allowed on this device
     int         dedup_lds_set = 0;      // the LDS dedup kernel of the sampler has been allowed its 76 KB
     int         x_lds_set = 0;          // the two kernels of the chunked layout have been allowed theirs
+    int         push_lds_set = 0;       // dynamic LDS of the binned push kernels
     int         vip_hops = 0;           // hops of the last propagation; negative: with given probabilities (always pushed)
     // timing: while enabled every timed piece of device work gets its own pair of events
     int         timing = 0;

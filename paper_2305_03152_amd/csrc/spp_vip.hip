@@ -73,10 +73,6 @@ __device__ __forceinline__ void vip_finish_vertex(const VipHop& a, int64_t u, do
     }
 }
 
-__device__ __forceinline__ void vip_finish_vertex(const VipHop& a, int64_t u, double S, unsigned long long& verts,
-                                                  unsigned long long& edges) {
-    vip_finish_vertex(a, u, S, a.first ? 0.0 : a.tot[u], verts, edges);
-}
 // All vertices, grid-stride, four per thread and round: the four sums and running totals are in
 // flight together (one vertex per round leaves a pass over 10^8 vertices waiting on its own loads:
 // 0.87 ms where the bytes take 0.55).  sum_of(u) = S_h(u).
@@ -95,15 +91,31 @@ __device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf
 #pragma unroll
         for (int k = 0; k < U; ++k) vip_finish_vertex(a, u + k * stride, S[k], T0[k], verts, edges);
     }
-    for (; u < N; u += stride) vip_finish_vertex(a, u, sum_of(u), verts, edges);
+    for (; u < N; u += stride) vip_finish_vertex(a, u, sum_of(u), a.first ? 0.0 : a.tot[u], verts, edges);
+}
+
+// The R vertices from u0 on whose sums a workgroup of 1024 threads holds in LDS.
+template <int R>
+__device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, int64_t N, const double* acc,
+                                                 unsigned long long& verts, unsigned long long& edges) {
+    constexpr int U = 4, kThreads = 1024;
+    for (int i0 = threadIdx.x; i0 < R; i0 += U * kThreads) {
+        double T0[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) T0[k] = a.first || u0 + i0 + k * kThreads >= N ? 0.0 : a.tot[u0 + i0 + k * kThreads];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (u0 + i0 + k * kThreads < N) vip_finish_vertex(a, u0 + i0 + k * kThreads, acc[i0 + k * kThreads], T0[k], verts, edges);
+    }
 }
 
 // The next hop is pushed or pulled depending on the size of its frontier (vertices with y != 0 and
 // their out-edges); the kernel that writes the next hop's y counts both on the way, one pair per
-// workgroup (no atomics: same-address atomics cost about 15 ns each), and the host adds the pairs.
+// workgroup (no atomics: same-address atomics cost about 15 ns each), and vip_decide_kernel adds the pairs.
+template <int kThreads = kBlock>
 __device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long verts,
                                                     unsigned long long edges) {
-    __shared__ unsigned long long red[2][kBlock / kWave];
+    __shared__ unsigned long long red[2][kThreads / kWave];
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) {
         verts += __shfl_down((long long)verts, off, kWave);
@@ -111,9 +123,10 @@ __device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, un
     }
     if (lane_id() == 0) { red[0][threadIdx.x >> 6] = verts; red[1][threadIdx.x >> 6] = edges; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        stat[2 * blockIdx.x] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        stat[2 * blockIdx.x + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    if (threadIdx.x < 2) {
+        unsigned long long all = 0;
+        for (int w = 0; w < kThreads / kWave; ++w) all += red[threadIdx.x][w];
+        stat[2 * blockIdx.x + threadIdx.x] = all;
     }
 }
 
@@ -242,7 +255,7 @@ __device__ __forceinline__ int32_t frontier_entry(const int32_t* __restrict__ li
 __global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long long* __restrict__ stat, int nstat, int64_t M,
                                                             int h, uint32_t* __restrict__ how,
                                                             unsigned long long* __restrict__ cursor,
-                                                            int64_t* __restrict__ mirror) {
+                                                            int64_t* __restrict__ mirror, const int* __restrict__ bad) {
     __shared__ unsigned long long red[kBlock / kWave];
     unsigned long long edges = 0;
     for (int i = threadIdx.x; i < nstat; i += kBlock) edges += stat[2 * i + 1];
@@ -258,6 +271,7 @@ __global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long 
         *cursor = 0ull;
         mirror[2 * (h - 1)] = push ? 1 : 0;
         mirror[2 * (h - 1) + 1] = asked ? (int64_t)edges : -1;
+        if (h == 1) mirror[2 * SPP_MAX_L] = *bad;
     }
 }
 
@@ -265,9 +279,8 @@ __global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long 
 // pull has finished its vertices itself).
 __global__ void __launch_bounds__(kBlock) vip_finish_kernel(VipHop a, const uint32_t* __restrict__ how, int fused_pull,
                                                             const double* __restrict__ acc, int parts, int64_t part_stride,
-                                                            int64_t N, const int* __restrict__ bad, int64_t* __restrict__ bad_mirror) {
+                                                            int64_t N) {
     const bool push = *how == kPushed;
-    if (a.last && blockIdx.x == 0 && threadIdx.x == 0) *bad_mirror = *bad;
     if (!push && fused_pull) return;
     const int n = push ? 1 : parts;
     unsigned long long verts = 0, edges = 0;
@@ -639,8 +652,7 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
     const int64_t u0 = rb << kTileRowBits;
     if (parts == 1) {
         unsigned long long verts = 0, edges = 0;
-        for (int i = threadIdx.x; i < R; i += kXBlock)
-            if (u0 + i < N) vip_finish_vertex(a, u0 + i, acc[i], verts, edges);
+        vip_finish_block<R>(a, u0, N, acc, verts, edges);
     } else {
         double* __restrict__ out = part + (int64_t)j * part_stride + u0;
         for (int i = threadIdx.x; i < R; i += kXBlock) out[i] = acc[i];
@@ -736,11 +748,13 @@ constexpr int kBinPer = 8;               // edges per thread and round
 constexpr int kBinChunk = kBinBlock * kBinPer;
 constexpr int64_t kBinMaxBlocks = 16384; // row blocks whose two counters each fit the LDS of a workgroup
 
-// Frontier entries per portion: small frontiers are cut into small portions so that they still
-// spread over the chip.
+// Frontier entries per portion: every workgroup gets as many portions as every other, and small
+// frontiers are cut into small portions so that they still spread over the chip.
 __device__ __forceinline__ int64_t bin_portion_size(int64_t nf) {
-    const int64_t per = (nf + gridDim.x - 1) / gridDim.x;
-    return per < kWave ? kWave : (per > kBinBlock ? kBinBlock : per);
+    const int64_t rounds = (nf + (int64_t)gridDim.x * kBinBlock - 1) / ((int64_t)gridDim.x * kBinBlock);
+    const int64_t portions = rounds * gridDim.x;
+    const int64_t per = portions > 0 ? (nf + portions - 1) / portions : kWave;
+    return per < kWave ? kWave : per;
 }
 
 // Which list entries make up a portion.  A small frontier (at most two portions per workgroup) is
@@ -802,6 +816,27 @@ __device__ __forceinline__ int bin_vertex_of(const BinPortion& po, int nv, uint3
     return lo;
 }
 
+// Lays the rows of the portion's vertices end to end; returns the number of edges.  Ends with a barrier; the
+// caller puts one between the last use of a portion and the next call.
+__device__ __forceinline__ uint32_t bin_load_portion(BinPortion& po, const PortionMap& pm, int64_t portion,
+                                                     const int32_t* __restrict__ list, const float* __restrict__ p,
+                                                     const int64_t* __restrict__ rowptr) {
+    const int nv = pm.count(portion);
+    uint32_t deg = 0;
+    if ((int)threadIdx.x < nv) {
+        int64_t b;
+        const int32_t v = frontier_entry(list, pm.entry(portion, threadIdx.x), rowptr, b, deg);
+        po.row[threadIdx.x] = b;
+        po.p[threadIdx.x] = p[v];
+    }
+    uint32_t total;
+    const uint32_t ex = bin_block_scan(deg, po.wave_sum, total);
+    if ((int)threadIdx.x < nv) po.prefix[threadIdx.x] = ex;
+    if (threadIdx.x == 0) po.prefix[nv] = total;
+    __syncthreads();
+    return total;
+}
+
 // A thread's walk over ascending edges of the portion's sequence: where edge x sits in col[] and
 // t[], and the probability of its source.  Rows are entered by comparison with the row's end, so an
 // edge inside the row of the edge before costs an add.
@@ -834,36 +869,15 @@ __device__ __forceinline__ uint32_t bin_edge(uint32_t c0, int q) {
     return c0 + (threadIdx.x >> 6) * (kWave * kBinPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
 }
 
-// Push form of eq. (2) for the uniform weights: every frontier vertex adds y(v) into the
-// accumulator of every member of adj(v) (fp64 global atomics).  Portions of `per` frontier vertices
-// walked as one edge sequence, as above: with one wavefront per vertex the longest row set the
-// kernel's duration (138 us for the 1.2M out-edges of 24k training vertices, degrees up to 20k).
-__global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t* __restrict__ list,
-                                                                  const unsigned long long* __restrict__ nf_ptr,
-                                                                  const float* __restrict__ y,
-                                                                  const int64_t* __restrict__ rowptr,
-                                                                  const int32_t* __restrict__ col,
-                                                                  double* __restrict__ acc,
-                                                                  const uint32_t* __restrict__ how) {
-    __shared__ BinPortion po;
-    if (*how != kPushed) return;
-    const int64_t nf = (int64_t)*nf_ptr;
+// Calls f(u, weight) for every edge of this workgroup's portions.
+template <class F>
+__device__ __forceinline__ void push_walk(BinPortion& po, int64_t nf, const int32_t* __restrict__ list,
+                                          const float* __restrict__ y, const int64_t* __restrict__ rowptr,
+                                          const int32_t* __restrict__ col, F f) {
     const PortionMap pm(nf);
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
-        const int64_t mine = pm.entry(portion, threadIdx.x);
-        uint32_t deg = 0;
-        if ((int)threadIdx.x < nv) {
-            int64_t b;
-            const int32_t v = frontier_entry(list, mine, rowptr, b, deg);
-            po.row[threadIdx.x] = b;
-            po.p[threadIdx.x] = y[v];
-        }
-        uint32_t total;
-        const uint32_t ex = bin_block_scan(deg, po.wave_sum, total);
-        if ((int)threadIdx.x < nv) po.prefix[threadIdx.x] = ex;
-        if (threadIdx.x == 0) po.prefix[nv] = total;
-        __syncthreads();
+        const uint32_t total = bin_load_portion(po, pm, portion, list, y, rowptr);
         for (uint32_t c0 = 0; c0 < total; c0 += kBinChunk) {
             if (bin_edge(c0, 0) >= total) continue;
             BinCursor cu;
@@ -880,10 +894,159 @@ __global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t*
             }
 #pragma unroll
             for (int q = 0; q < kBinPer; ++q)
-                if (u[q] >= 0) unsafeAtomicAdd(&acc[u[q]], (double)w[q]);       // hardware fp64 add
+                if (u[q] >= 0) f((uint32_t)u[q], w[q]);
         }
         __syncthreads();
     }
+}
+
+// Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.
+__device__ __forceinline__ void bin_add_entries(double* acc, const uint2* __restrict__ bins, int64_t beg, int64_t end) {
+    constexpr int U = 8;                       // entries in flight per thread (one: 325 us for 121M entries, eight: 208)
+    for (int64_t e0 = beg + threadIdx.x; e0 < end; e0 += U * kTileBlock) {
+        unsigned long long x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            x[u] = e0 + u * kTileBlock < end ? __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(bins) + e0 + u * kTileBlock) : 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t w = (uint32_t)x[u];             // .x of the entry
+            if (w != 0u) unsafeAtomicAdd(&acc[(uint32_t)(x[u] >> 32)], (double)__uint_as_float(w));
+        }
+    }
+}
+
+// Push form of eq. (2) for the uniform weights: every frontier vertex adds y(v) into the
+// accumulator of every member of adj(v) (fp64 global atomics).  Portions of `per` frontier vertices
+// walked as one edge sequence, as above: with one wavefront per vertex the longest row set the
+// kernel's duration (138 us for the 1.2M out-edges of 24k training vertices, degrees up to 20k).
+__global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t* __restrict__ list,
+                                                                  const unsigned long long* __restrict__ nf_ptr,
+                                                                  const float* __restrict__ y,
+                                                                  const int64_t* __restrict__ rowptr,
+                                                                  const int32_t* __restrict__ col,
+                                                                  double* __restrict__ acc,
+                                                                  const uint32_t* __restrict__ how) {
+    __shared__ BinPortion po;
+    if (*how != kPushed) return;
+    push_walk(po, (int64_t)*nf_ptr, list, y, rowptr, col, [&](uint32_t u, float w) { unsafeAtomicAdd(&acc[u], (double)w); });    // hardware fp64 add
+}
+
+// The same push through bins, for graphs in the chunked layout.  The atomics above run at 21 G/s whatever
+// the walk (13.4M out-edges on 14M vertices: 616 us, counted and filled in 217 here, and the accumulators are cleared before and read
+// after them); here they are adds in LDS.  Every edge of the frontier becomes an entry (weight, row inside
+// its block of 2^kTileRowBits rows), the entries of a block lie side by side, and a workgroup per block
+// sums them and finishes the block's vertices.  A frontier that is pushed has at most M / kPushShare
+// out-edges, so the entries are packed (counted first, by a walk that reads 4 bytes per edge) and fit the
+// memory where a pulled hop keeps its values; reserving every block's in-edges would take 8 M bytes
+// beside it.  A fixed number of workgroups takes the portions in a fixed order in both walks, so
+// one row of counts per workgroup says where its entries of each block go, without atomics.
+constexpr int kPushGroups = 1024;        // workgroups of the two walks (four per CU)
+constexpr int kOffBins = 16;             // row blocks per workgroup of vip_bin_offsets_kernel
+constexpr int kOffRows = kPushGroups / (1024 / kOffBins);      // counts per thread there
+
+// off[g][r] = edges of workgroup g that end in row block r.
+__global__ void __launch_bounds__(kBinBlock) vip_bin_count_kernel(const int32_t* __restrict__ list,
+                                                                  const unsigned long long* __restrict__ nf_ptr,
+                                                                  const float* __restrict__ y,
+                                                                  const int64_t* __restrict__ rowptr,
+                                                                  const int32_t* __restrict__ col, int nrb,
+                                                                  uint32_t* __restrict__ off,
+                                                                  const uint32_t* __restrict__ how) {
+    __shared__ BinPortion po;
+    extern __shared__ uint32_t bin_lds[];
+    if (*how != kPushed) return;
+    for (int r = threadIdx.x; r < nrb; r += kBinBlock) bin_lds[r] = 0u;
+    __syncthreads();
+    push_walk(po, (int64_t)*nf_ptr, list, y, rowptr, col, [&](uint32_t u, float) { atomicAdd(&bin_lds[u >> kTileRowBits], 1u); });
+    for (int r = threadIdx.x; r < nrb; r += kBinBlock) off[(int64_t)blockIdx.x * nrb + r] = bin_lds[r];
+}
+
+// Turns the counts of each row block into the entries that the workgroups before put there, and leaves the
+// block's number of entries in total[].  A thread holds kOffRows counts of one block; a wavefront then
+// scans the 64 partial sums of one block.
+__global__ void __launch_bounds__(1024) vip_bin_offsets_kernel(uint32_t* __restrict__ off, int nrb,
+                                                               uint32_t* __restrict__ total, const uint32_t* __restrict__ how) {
+    __shared__ uint32_t sums[kOffBins][kWave + 1];
+    static_assert(1024 / kOffBins == kWave && 1024 / kWave == kOffBins, "a wavefront per block, a lane per partial sum");
+    if (*how != kPushed) return;
+    const int b = threadIdx.x % kOffBins, g = threadIdx.x / kOffBins;
+    const int r = blockIdx.x * kOffBins + b;
+    uint32_t c[kOffRows], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kOffRows; ++k) c[k] = r < nrb ? off[(int64_t)(g * kOffRows + k) * nrb + r] : 0u;
+#pragma unroll
+    for (int k = 0; k < kOffRows; ++k) mine += c[k];
+    sums[b][g] = mine;
+    __syncthreads();
+    {
+        const int w = threadIdx.x >> 6, lane = lane_id();
+        const uint32_t v = sums[w][lane], inc = (uint32_t)wave_inclusive_scan((int)v);
+        sums[w][lane] = inc - v;
+        if (lane == kWave - 1 && (int)(blockIdx.x * kOffBins + w) < nrb) total[blockIdx.x * kOffBins + w] = inc;
+    }
+    __syncthreads();
+    if (r >= nrb) return;
+    uint32_t run = sums[b][g];
+#pragma unroll
+    for (int k = 0; k < kOffRows; ++k) {
+        off[(int64_t)(g * kOffRows + k) * nrb + r] = run;
+        run += c[k];
+    }
+}
+
+// The entries; base[r] = first entry of row block r (base[nrb]: their number).
+__global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* __restrict__ list,
+                                                                 const unsigned long long* __restrict__ nf_ptr,
+                                                                 const float* __restrict__ y,
+                                                                 const int64_t* __restrict__ rowptr,
+                                                                 const int32_t* __restrict__ col, int nrb,
+                                                                 const uint32_t* __restrict__ off,
+                                                                 const uint32_t* __restrict__ total,
+                                                                 uint32_t* __restrict__ base, uint2* __restrict__ bins,
+                                                                 const uint32_t* __restrict__ how) {
+    __shared__ BinPortion po;
+    extern __shared__ uint32_t bin_lds[];        // where this workgroup's next entry of each row block goes
+    if (*how != kPushed) return;
+    const int per = (nrb + kBinBlock - 1) / kBinBlock;
+    const int r0 = (int)threadIdx.x * per, r1 = r0 + per < nrb ? r0 + per : nrb;
+    for (int r = threadIdx.x; r < nrb; r += kBinBlock) bin_lds[r] = total[r];
+    __syncthreads();
+    uint32_t sum = 0, all;
+    for (int r = r0; r < r1; ++r) sum += bin_lds[r];
+    uint32_t run = bin_block_scan(sum, po.wave_sum, all);
+    for (int r = r0; r < r1; ++r) {
+        const uint32_t c = bin_lds[r];
+        bin_lds[r] = run;
+        run += c;
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r < nrb; r += kBinBlock) {
+        const uint32_t b = bin_lds[r];
+        if (blockIdx.x == 0) base[r] = b;
+        bin_lds[r] = b + off[(int64_t)blockIdx.x * nrb + r];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) base[nrb] = all;
+    __syncthreads();
+    push_walk(po, (int64_t)*nf_ptr, list, y, rowptr, col, [&](uint32_t u, float w) {
+        bins[atomicAdd(&bin_lds[u >> kTileRowBits], 1u)] = make_uint2(__float_as_uint(w), u & kTileRowMask);
+    });
+}
+
+// Sums a row block's entries in LDS and finishes its vertices.
+__global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, const uint2* __restrict__ bins,
+                                                                    const uint32_t* __restrict__ base, int64_t N,
+                                                                    const uint32_t* __restrict__ how) {
+    extern __shared__ double acc[];
+    if (*how != kPushed) return;
+    constexpr int R = 1 << kTileRowBits;
+    for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
+    __syncthreads();
+    bin_add_entries(acc, bins, base[blockIdx.x], base[blockIdx.x + 1]);
+    __syncthreads();
+    unsigned long long verts = 0, edges = 0;
+    vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, verts, edges);
+    if (!a.last) write_frontier_stat<kTileBlock>(a.stat, verts, edges);
 }
 
 // log1p(-x) for 0 < x <= 1 to a few fp32 ulp.  All terms of a vertex's sum have one sign, so the
@@ -934,20 +1097,8 @@ __global__ void __launch_bounds__(kBinBlock) vipg_bin_fill_kernel(const int32_t*
         __syncthreads();
         if ((int64_t)portion >= pm.nportions) break;
         const int nv = pm.count(portion);
-        const int64_t mine = pm.entry(portion, threadIdx.x);
-        uint32_t deg = 0;
-        if ((int)threadIdx.x < nv) {
-            int64_t b;
-            const int32_t v = frontier_entry(list, mine, rowptr, b, deg);
-            po.row[threadIdx.x] = b;
-            po.p[threadIdx.x] = pcur[v];
-        }
-        uint32_t total;
-        const uint32_t ex = bin_block_scan(deg, po.wave_sum, total);
-        if ((int)threadIdx.x < nv) po.prefix[threadIdx.x] = ex;
-        if (threadIdx.x == 0) po.prefix[nv] = total;
         for (int r = threadIdx.x; r < nrb; r += kBinBlock) base[r] = 0u;
-        __syncthreads();                                   // publishes prefix[], row[], p[]
+        const uint32_t total = bin_load_portion(po, pm, portion, list, pcur, rowptr);
         // first walk: the portion's entries per bin
         for (uint32_t c0 = 0; c0 < total; c0 += kBinChunk) {
             if (bin_edge(c0, 0) >= total) continue;
@@ -1012,19 +1163,7 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
     for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
     __syncthreads();
     const int64_t b0 = first[rb * nch], len = (int64_t)cursor[rb];
-    const int64_t beg = b0 + len * j / parts, end = b0 + len * (j + 1) / parts;
-    constexpr int U = 8;                       // entries in flight per thread (one: 325 us for 121M entries, eight: 208)
-    for (int64_t e0 = beg + threadIdx.x; e0 < end; e0 += U * kTileBlock) {
-        unsigned long long x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            x[u] = e0 + u * kTileBlock < end ? __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(bins) + e0 + u * kTileBlock) : 0ull;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t w = (uint32_t)x[u];             // .x of the entry
-            if (w != 0u) unsafeAtomicAdd(&acc[(uint32_t)(x[u] >> 32)], (double)__uint_as_float(w));
-        }
-    }
+    bin_add_entries(acc, bins, b0 + len * j / parts, b0 + len * (j + 1) / parts);
     __syncthreads();
     double* __restrict__ out = part + (int64_t)j * part_stride + (rb << rbits);
     for (int i = threadIdx.x; i < R; i += kTileBlock) out[i] = acc[i];
@@ -1166,6 +1305,15 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         const size_t push_bytes = (size_t)N * sizeof(double);
         SPP_TRY(ctx->acc.reserve(tile_bytes > push_bytes ? tile_bytes : push_bytes));
     }
+    // The push goes through bins where the chunked layout's value memory holds the entries (8 bytes for at most
+    // M / kPushShare edges), the counts and the offsets, and a workgroup per row block fills the chip: graphs of
+    // 4.2M vertices and more.  On 14M vertices it takes 172 us for a first hop of 0.8M edges (atomics: 153 with
+    // the clearing and the finishing pass) and 443 for 13.4M (787).
+    const size_t bin_entries = (size_t)(g->M / kPushShare) + 1;
+    const size_t bin_words = (size_t)kPushGroups * (size_t)g->nrb + 2 * (size_t)g->nrb + 1;
+    const bool binned = g->has_x && parts == 1 && g->nrb <= kBinMaxBlocks &&
+                        bin_entries * sizeof(uint2) + bin_words * sizeof(uint32_t) <= (size_t)g->x_entries * sizeof(float);
+    const size_t bin_lds = (size_t)g->nrb * sizeof(uint32_t), bin_sum_lds = sizeof(double) << kTileRowBits;
     const size_t lds_bytes = (sizeof(double) << g->tile_rbits) + (size_t)(kTileWaves * kTileWin + g->nch + 1) * sizeof(uint32_t);
     const size_t x_lds_expand = (sizeof(float) << kXSrcBits) + sizeof(float);
     static_assert(kXPad == (1u << kXSrcBits), "a padding entry indexes the slot after the chunk's values");
@@ -1183,17 +1331,25 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)x_lds_reduce));
             ctx->x_lds_set = 1;
         }
+        if (binned && ctx->push_lds_set < (int)bin_lds) {
+            for (const void* k : {reinterpret_cast<const void*>(&vip_bin_count_kernel), reinterpret_cast<const void*>(&vip_bin_fill_kernel)})
+                SPP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bin_lds));
+            SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_bin_finish_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bin_sum_lds));
+            ctx->push_lds_set = (int)bin_lds;
+        }
         SPP_TRY(ctx->xvals.reserve((size_t)(g->x_entries > 0 ? g->x_entries : 4) * sizeof(float)));
     }
     // the kernels that write a hop's y run this many workgroups; each leaves the size of the part of
-    // the next frontier it saw (at most kStatBlocks pairs)
+    // the next frontier it saw (at most kStatBlocks pairs, or one per row block)
     const int fill_grid = ctx->num_cu * 8 < kStatBlocks ? ctx->num_cu * 8 : kStatBlocks;
+    const size_t nstat_max = binned && g->nrb > kStatBlocks ? (size_t)g->nrb : (size_t)kStatBlocks;
     const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + 2 * (size_t)kStatBlocks + SPP_MAX_L + 1) * sizeof(unsigned long long)));
+    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + 2 * nstat_max + SPP_MAX_L + 1) * sizeof(unsigned long long)));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));    // [2]: cursor of the list
     unsigned long long* fstat = fcount + 4;
-    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + 2 * kStatBlocks);      // [1 .. L]: how each hop is walked
+    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + 2 * nstat_max);      // [1 .. L]: how each hop is walked
     int64_t* mirror = ctx->h_pinned + kHopMirror;
     float* ycur = ctx->y0.as<float>();
     float* ynext = ctx->y1.as<float>();
@@ -1221,9 +1377,21 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             a.stat = fstat;
             double* acc = ctx->acc.as<double>();
             const uint32_t* how_h = how + h;
-            vip_decide_kernel<<<1, kBlock, 0, st>>>(fstat, fill_grid, g->M, h, how, fcount + 2, mirror);
-            launch_frontier_list(fill_grid, st, ycur, g->rowptr, N, flist, fcount + 2, how_h, acc);
-            vip_push_flat_kernel<<<ctx->num_cu * 8, kBinBlock, 0, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, acc, how_h);
+            vip_decide_kernel<<<1, kBlock, 0, st>>>(fstat, h > 1 && binned ? (int)g->nrb : fill_grid, g->M, h, how, fcount + 2, mirror, d_bad);
+            launch_frontier_list(fill_grid, st, ycur, g->rowptr, N, flist, fcount + 2, how_h, binned ? nullptr : acc);
+            if (binned) {
+                uint2* bins = ctx->xvals.as<uint2>();
+                uint32_t* off = reinterpret_cast<uint32_t*>(bins + bin_entries);
+                uint32_t* total = off + (size_t)kPushGroups * (size_t)g->nrb;
+                uint32_t* base = total + g->nrb;
+                vip_bin_count_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, (int)g->nrb, off, how_h);
+                vip_bin_offsets_kernel<<<(unsigned)((g->nrb + kOffBins - 1) / kOffBins), 1024, 0, st>>>(off, (int)g->nrb, total, how_h);
+                vip_bin_fill_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, (int)g->nrb, off,
+                                                                            total, base, bins, how_h);
+                vip_bin_finish_kernel<<<(unsigned)g->nrb, kTileBlock, bin_sum_lds, st>>>(a, bins, base, N, how_h);
+            } else {
+                vip_push_flat_kernel<<<ctx->num_cu * 8, kBinBlock, 0, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, acc, how_h);
+            }
             int fused = 0;
             if (g->has_x) {
                 const int egrid = g->x_nch < ctx->num_cu * 4 ? g->x_nch : ctx->num_cu * 4;
@@ -1236,7 +1404,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 vip_tile_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, lds_bytes, st>>>(
                     g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, (uint32_t)N, ycur, acc, part_stride, how_h);
             }
-            vip_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N, d_bad, mirror + 2 * SPP_MAX_L);
+            if (!(binned && fused)) vip_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N);
             float* t = ycur; ycur = ynext; ynext = t;
         }
     }

@@ -59,3 +59,54 @@ def test_the_form_of_each_hop(spp, ctx, N, deg, nT, fanouts, want):
         # results are rounded to fp32 at every hop: 6e-8 a hop, well below the 1e-5 the entry point states
         assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.asarray(ref) + 1e-37)
     G.close()
+
+
+# more row blocks than CUs in the chunked layout: pushes go through bins of the row blocks.  256 blocks, the last with one
+# vertex, and 258; frontiers of one vertex, less and more than 64 and 256 vertices for each of 1024 workgroups, in hubs
+# whose rows are walked in pieces, at the rim of every block, and all edges into one vertex.
+@pytest.mark.parametrize("N,kind,nT", [
+    (255 * 16384 + 1, "ring", 1), (255 * 16384 + 1, "ring", 65536), (255 * 16384 + 1, "ring", 65537),
+    (257 * 16384 + 77, "ring", 262145), (257 * 16384 + 77, "rim", 257), (257 * 16384 + 77, "hubs", 9), (257 * 16384 + 77, "star", 70000)])
+def test_pushes_through_bins(spp, ctx, N, kind, nT):
+    print("[case]", N, kind, nT, flush=True)
+    rng = np.random.default_rng(N + nT)
+    rp, col = _ring(N, 2)
+    T = ((np.arange(nT, dtype=np.int64) * 13 + N // 3) % N).astype(np.int32)
+    if kind == "rim":                   # the last and the first vertex of the blocks
+        T = np.unique(np.r_[np.arange(1, 258) * 16384 - 1, np.arange(1, 258) * 16384 - 2, N - 1]).astype(np.int32)
+    if kind == "hubs":
+        T = (np.arange(nT) * 400000 + 5).astype(np.int32)
+        deg = np.full(N, 2)
+        for i, v in enumerate(T):
+            deg[v] = (4095, 4096, 4097, 8192, 8193, 30000, 1, 2, 20000)[i]
+        rp2 = np.zeros(N + 1, dtype=np.int64)
+        np.cumsum(deg, out=rp2[1:])
+        col2 = np.empty(rp2[-1], dtype=np.int32)
+        own = np.repeat(deg == 2, deg)
+        col2[own] = col[np.repeat(deg == 2, 2)]
+        for v in T:
+            if deg[v] != 2:
+                others = rng.choice(N - 1, deg[v], replace=False)
+                col2[rp2[v]:rp2[v + 1]] = np.sort(others + (others >= v))
+        rp, col = rp2, col2
+    if kind == "star":                  # every training vertex points at vertex 7 as well as at its successor
+        c = col.reshape(N, 2)
+        T = T[(T != 7) & (T + 1 < N)]
+        c[T] = np.sort(np.stack([np.full(T.size, 7), np.where(T == 6, 8, T + 1)], 1), axis=1)
+        col = c.ravel()
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True, chunked=True)
+    fanouts, batch = (4000, 2, 2), max(1, T.size // 2)
+    p, ph = spp.vip_propagate(ctx, G, torch.from_numpy(T).to(dev), batch, fanouts, per_hop=True)
+    pushed, edges = spp.vip_last_hops(ctx, len(fanouts))
+    ref_t, ref_h = oracle.vip(rp, col, T, batch, fanouts)
+    deg = np.diff(rp)
+    front = [int(deg[T].sum())] + [int(deg[np.asarray(ref_h[h]) > 0].sum()) for h in range(2)]
+    for h in range(3):
+        assert pushed[h] == (16 * front[h] <= col.size and (h == 0 or pushed[h - 1]))
+        assert edges[h] == (front[h] if h == 0 or pushed[h - 1] else -1)
+    assert pushed[0]
+    for got, ref in ((p, ref_t), (ph, ref_h)):
+        # results are rounded to fp32 at every hop: 6e-8 a hop, well below the 1e-5 the entry point states
+        assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.asarray(ref) + 1e-37)
+    G.close()
