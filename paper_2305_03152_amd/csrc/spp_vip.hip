@@ -46,31 +46,123 @@ struct VipHop {
     unsigned long long* stat;  // per workgroup: vertices and out-edges of the next hop's frontier (unused at the last hop)
 };
 
-// `told` = the running total read beforehand (ignored at a first hop).
-__device__ __forceinline__ void vip_finish_vertex(const VipHop& a, int64_t u, double S, double told,
-                                                  unsigned long long& verts, unsigned long long& edges) {
+// 1 - e^s and log(1 - x) in fp64, to 2 and 4 units in the last place (the library's routines give 1 and
+// take some 300 instructions for the two and a division, which set the pace of the passes that
+// finish vertices: 106 and 181 us for the first two hops on 14M vertices, 70 and 131 with these).  The results are
+// rounded to fp32 afterwards.  s <= 0: e^s = 2^k e^r, |r| <= ln2 / 2, the Taylor series of e^r - 1 up to
+// r^13.  0 <= x <= 1: log(2^e m) = e ln2 + 2 atanh(f / (2 + f)), m = 1 + f between sqrt(1/2) and sqrt(2),
+// the series of atanh up to the 21st power; f = -x itself where e = 0, so that small x lose nothing.
+constexpr double kLn2Hi = 0x1.62e42fefa39efp-1, kLn2Lo = 0x1.abc9e3b39803fp-56;
+__device__ __forceinline__ double one_minus_exp(double s) {
+    s = fmax(s, -64.0);                          // 1 - e^-64 rounds to 1
+    const double k = rint(s * 1.4426950408889634);
+    const double r = fma(-k, kLn2Lo, fma(-k, kLn2Hi, s));
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(r * r, p, r);
+    const double e = ldexp(1.0, (int)k);
+    return fma(-e, p, 1.0 - e);
+}
+// num / den for normal den: a reciprocal refined twice, the quotient once
+__device__ __forceinline__ double quotient(double num, double den) {
+    double r = __builtin_amdgcn_rcp(den);
+    r = fma(fma(-den, r, 1.0), r, r);
+    r = fma(fma(-den, r, 1.0), r, r);
+    const double q = num * r;
+    return fma(fma(-den, q, num), r, q);
+}
+__device__ __forceinline__ double log1p_neg(double x) {
+    const double w = 1.0 - x;
+    const bool near_one = x < 0.2928;
+    double m = __builtin_amdgcn_frexp_mant(w);
+    int ex = __builtin_amdgcn_frexp_exp(w);
+    const bool low = m < 0.70710678;
+    m = low ? 2.0 * m : m;
+    ex -= low ? 1 : 0;
+    const double f = near_one ? -x : m - 1.0, e = near_one ? 0.0 : (double)ex;
+    const double s = quotient(f, 2.0 + f), z = s * s;
+    double p = 1.0 / 21.0;
+    p = fma(p, z, 1.0 / 19.0);
+    p = fma(p, z, 1.0 / 17.0);
+    p = fma(p, z, 1.0 / 15.0);
+    p = fma(p, z, 1.0 / 13.0);
+    p = fma(p, z, 1.0 / 11.0);
+    p = fma(p, z, 1.0 / 9.0);
+    p = fma(p, z, 1.0 / 7.0);
+    p = fma(p, z, 1.0 / 5.0);
+    p = fma(p, z, 1.0 / 3.0);
+    const double t = 2.0 * s;
+    const double l = fma(e, kLn2Hi, fma(e, kLn2Lo, fma(t * z, p, t)));
+    return x >= 1.0 ? -__builtin_inf() : l;
+}
+
+// Finishes vertices u, u + step, ... (U of them, those below N).  S = their sums, told = their running totals (ignored
+// at a first hop).  The loads and the chains of arithmetic of the U vertices are independent.
+template <int U>
+__device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, int64_t step, int64_t N, const double (&S)[U],
+                                                    const double (&told)[U], unsigned long long& verts, unsigned long long& edges) {
     // A vertex that no frontier vertex points at has S = 0 exactly (most vertices, at the early hops):
     // its p^[h] is 0 and it needs no exponential; nor does p^[h] at the last hop when it is not asked for.
-    const bool need_ph = a.p_hop != nullptr || !a.last;
-    const double ph = (need_ph && S != 0.0) ? -expm1(S) : 0.0;
-    if (a.p_hop) a.p_hop[u] = (float)ph;
-    const double T = a.first ? S : told + S;
+    double ph[U];
+    bool some = false;
+#pragma unroll
+    for (int k = 0; k < U; ++k) { ph[k] = 0.0; some |= S[k] != 0.0; }
+    if (some && (a.p_hop != nullptr || !a.last))
+#pragma unroll
+        for (int k = 0; k < U; ++k) ph[k] = one_minus_exp(S[k]);        // 0 for a sum of 0
+    if (a.p_hop)
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (u + k * step < N) a.p_hop[u + k * step] = (float)ph[k];
+    double T[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) T[k] = a.first ? S[k] : told[k] + S[k];
     if (a.last) {
-        a.p_total[u] = T != 0.0 ? (float)(-expm1(T)) : 0.0f;
-    } else {
-        a.tot[u] = T;
-        float yn = 0.f;
-        if (ph > 0.0) {
-            const int64_t d = a.rowptr[u + 1] - a.rowptr[u];
-            if (d > 0) {
-                double t = a.f_next / (double)d;
-                if (t > 1.0) t = 1.0;
-                yn = (float)log1p(-(t * ph));
-                if (yn != 0.0f) { ++verts; edges += (unsigned long long)d; }
-            }
-        }
-        a.y_next[u] = yn;
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < U; ++k) any |= T[k] != 0.0;
+        double p[U] = {};
+        if (any)
+#pragma unroll
+            for (int k = 0; k < U; ++k) p[k] = one_minus_exp(T[k]);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (u + k * step < N) a.p_total[u + k * step] = (float)p[k];
+        return;
     }
+    int64_t d[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        d[k] = 0;
+        if (ph[k] > 0.0 && u + k * step < N) d[k] = a.rowptr[u + k * step + 1] - a.rowptr[u + k * step];
+    }
+    float yn[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) yn[k] = 0.0f;
+    if (some)
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const double dd = (double)d[k];
+            const double t = dd <= a.f_next ? 1.0 : quotient(a.f_next, dd);
+            if (d[k] > 0) yn[k] = (float)log1p_neg(t * ph[k]);
+            if (yn[k] != 0.0f) { ++verts; edges += (unsigned long long)d[k]; }
+        }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+        if (u + k * step < N) {
+            a.tot[u + k * step] = T[k];
+            a.y_next[u + k * step] = yn[k];
+        }
 }
 
 // All vertices, grid-stride, four per thread and round: the four sums and running totals are in
@@ -81,17 +173,14 @@ __device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf
                                                unsigned long long& edges) {
     constexpr int U = 4;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    for (; u + (U - 1) * stride < N; u += U * stride) {
+    for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += U * stride) {
         double S[U], T0[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) S[k] = sum_of(u + k * stride);
+        for (int k = 0; k < U; ++k) S[k] = u + k * stride < N ? sum_of(u + k * stride) : 0.0;
 #pragma unroll
-        for (int k = 0; k < U; ++k) T0[k] = a.first ? 0.0 : a.tot[u + k * stride];
-#pragma unroll
-        for (int k = 0; k < U; ++k) vip_finish_vertex(a, u + k * stride, S[k], T0[k], verts, edges);
+        for (int k = 0; k < U; ++k) T0[k] = a.first || u + k * stride >= N ? 0.0 : a.tot[u + k * stride];
+        vip_finish_vertices<U>(a, u, stride, N, S, T0, verts, edges);
     }
-    for (; u < N; u += stride) vip_finish_vertex(a, u, sum_of(u), a.first ? 0.0 : a.tot[u], verts, edges);
 }
 
 // The R vertices from u0 on whose sums a workgroup of 1024 threads holds in LDS.
@@ -99,13 +188,13 @@ template <int R>
 __device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, int64_t N, const double* acc,
                                                  unsigned long long& verts, unsigned long long& edges) {
     constexpr int U = 4, kThreads = 1024;
-    for (int i0 = threadIdx.x; i0 < R; i0 += U * kThreads) {
-        double T0[U];
+    for (int i = threadIdx.x; i < R && u0 + i < N; i += U * kThreads) {
+        double S[U], T0[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) T0[k] = a.first || u0 + i0 + k * kThreads >= N ? 0.0 : a.tot[u0 + i0 + k * kThreads];
+        for (int k = 0; k < U; ++k) S[k] = acc[i + k * kThreads];
 #pragma unroll
-        for (int k = 0; k < U; ++k)
-            if (u0 + i0 + k * kThreads < N) vip_finish_vertex(a, u0 + i0 + k * kThreads, acc[i0 + k * kThreads], T0[k], verts, edges);
+        for (int k = 0; k < U; ++k) T0[k] = a.first || u0 + i + k * kThreads >= N ? 0.0 : a.tot[u0 + i + k * kThreads];
+        vip_finish_vertices<U>(a, u0 + i, kThreads, N, S, T0, verts, edges);
     }
 }
 

@@ -110,3 +110,27 @@ def test_pushes_through_bins(spp, ctx, N, kind, nT):
         # results are rounded to fp32 at every hop: 6e-8 a hop, well below the 1e-5 the entry point states
         assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.asarray(ref) + 1e-37)
     G.close()
+
+
+@pytest.mark.parametrize("batch", [1, 300, 599, 600])
+def test_probabilities_to_fp32_rounding(spp, ctx, batch):
+    """Chains T -> u -> v of which every u and v has one in-edge: p^[1](u) and p^[2](v) are products of two and
+    three factors over the whole of (0, 1], the library's fp64 exponentials and logarithms invert each other."""
+    nT, deg = 600, np.r_[np.arange(1, 301), np.arange(1, 301) * 40]
+    nu = int(deg.sum())
+    N = nT + 2 * nu
+    rp = np.zeros(N + 1, dtype=np.int64)
+    np.cumsum(np.r_[deg, np.ones(nu, int), np.zeros(nu, int)], out=rp[1:])
+    col = np.r_[nT + np.arange(nu), nT + nu + np.arange(nu)].astype(np.int32)
+    T = np.arange(nT, dtype=np.int32)
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True)
+    for fanouts in ((1, 1), (299, 1), (12000, 2)):
+        print("[case]", batch, fanouts, flush=True)
+        p, ph = spp.vip_propagate(ctx, G, torch.from_numpy(T).to(dev), batch, fanouts, per_hop=True)
+        ref_t, ref_h = oracle.vip(rp, col, T, batch, fanouts)
+        # a hop's logarithms are rounded to fp32 (2^-24, which 1 - e^s does not enlarge), and so is the result
+        for got, ref, roundings in ((ph[0], ref_h[0], 2), (ph[1], ref_h[1], 3), (p, ref_t, 3)):
+            ref = np.asarray(ref)
+            assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= (roundings + 0.01) * 2.0**-24 * ref)
+    G.close()
