@@ -559,15 +559,18 @@ inline int tile_parts(int num_cu, int64_t nrb, int64_t M) {
 // ---- dense hops over the chunked layout -------------------------------------------------------
 // When y does not stay in the caches (10^8 vertices: 444 MB), the gathers of the kernel above fetch
 // a 128-byte line per edge and the hop runs at a tenth of the edge stream's rate.  The chunked
-// layout trades bytes for order.  First pass: one workgroup per chunk of 2^15 sources keeps the
-// chunk's y in LDS (128 KB) and writes y[source] for every entry of the chunk, in entry order:
-// 2 bytes read and 4 written per entry, all of it streamed.  Second pass: one workgroup per row
+// layout trades bytes for order.  First pass: a workgroup keeps the y of a chunk of 2^15 sources
+// in LDS (128 KB) and writes y[source] for entries of the chunk, in entry order: 2 bytes read and 4
+// written per entry, all of it streamed.  The workgroups, one per CU, take equal shares of all entries and go
+// from chunk to chunk inside theirs (a workgroup per chunk left CUs idle in the last round: 428 chunks on 256 CUs
+// took 629 us for 400M entries, shares 569).  Second pass: one workgroup per row
 // block keeps the block's fp64 sums in LDS and adds up the block's pieces, one from every chunk
 // (4 + 2 bytes read per entry in runs of about a hundred entries, found through two tables that are
 // staged in LDS 2048 pieces at a time), then finishes the block's vertices itself.  12 bytes per
 // entry instead of 4, but no line is fetched for four of its bytes.
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 constexpr int kXBlock = 1024;
+constexpr int64_t kExpandShare = 8192;   // fewest vectors per workgroup of the first pass: what a chunk's y costs to load
 constexpr int kXUnroll = 4;              // vectors (four entries) per lane and round of the first pass (2, 4, 8: the same time)
 
 __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __restrict__ x_src,
@@ -575,9 +578,20 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
                                                              const float* __restrict__ y, float* __restrict__ vals,
                                                              const uint32_t* __restrict__ how) {
     extern __shared__ float ych[];
+    __shared__ int c_first;
     if (*how != kPulled) return;
     constexpr int C = 1 << kXSrcBits;
-    for (int c = blockIdx.x; c < nch; c += gridDim.x) {
+    const int64_t nvec = chunk_first[nch] >> 2;
+    const int64_t beg = nvec * blockIdx.x / gridDim.x, end = nvec * (blockIdx.x + 1) / gridDim.x;
+    for (int c = threadIdx.x; c < nch; c += kXBlock)
+        if ((chunk_first[c] >> 2) <= beg && beg < (chunk_first[c + 1] >> 2)) c_first = c;
+    __syncthreads();
+    if (beg >= end) return;
+    for (int c = c_first; c < nch && (chunk_first[c] >> 2) < end; ++c) {
+        int64_t q0 = chunk_first[c] >> 2, q1 = chunk_first[c + 1] >> 2;
+        if (q0 < beg) q0 = beg;
+        if (q1 > end) q1 = end;
+        if (q0 >= q1) continue;          // no entries
         const int64_t v0 = (int64_t)c << kXSrcBits;
         int any = 0;
         if (v0 + C <= N) {               // y is 16-byte aligned and v0 a multiple of C
@@ -599,7 +613,6 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
         }
         if (threadIdx.x == 0) ych[C] = 0.0f;     // what a padding entry (source kXPad = C) looks up
         any = __syncthreads_or(any);
-        const int64_t q0 = chunk_first[c] >> 2, q1 = chunk_first[c + 1] >> 2;
         const u16x4* __restrict__ sv = reinterpret_cast<const u16x4*>(x_src);
         f32x4* __restrict__ out = reinterpret_cast<f32x4*>(vals);
         // The chunk's vectors are cut into tiles of kXTile (32 KB of values); the workgroup's wavefronts
@@ -1483,7 +1496,8 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             }
             int fused = 0;
             if (g->has_x) {
-                const int egrid = g->x_nch < ctx->num_cu * 4 ? g->x_nch : ctx->num_cu * 4;
+                const int64_t evec = g->x_entries / 4, eshare = evec / kExpandShare + 1;
+                const int egrid = eshare < ctx->num_cu ? (int)eshare : ctx->num_cu;
                 vip_expand_kernel<<<egrid, kXBlock, x_lds_expand, st>>>(g->x_src, g->x_chunk_first, g->x_nch, N, ycur,
                                                                         ctx->xvals.as<float>(), how_h);
                 vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(
