@@ -839,21 +839,26 @@ __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __rest
 // counting pass over the hop is needed.  A workgroup takes a portion of the frontier and lays the
 // rows of its vertices end to end (prefix sums of their lengths in LDS; a wavefront takes runs of
 // 64 consecutive edges of that sequence whatever the row lengths, so its loads are contiguous).
-// One walk over col[] counts the portion's entries per bin in LDS, one global atomic per bin
-// reserves their range (reserving per 2048 edges instead serialised on the bins' counters: 59k
-// same-address atomics, 0.9 ms), and a second walk forms the entries and stores them, the slot
-// inside the range coming from an LDS atomic.  (Sorting 2048 entries at a time by bin in LDS, so
-// that neighbouring threads store neighbouring entries, was slower: 1.2 ms against 0.9 ms per
-// dense hop; a thread taking 8 consecutive edges instead of a wavefront taking 64: 1.25 ms.)
-constexpr int kBinBlock = 256;           // threads per workgroup, and most frontier vertices per portion
+// It walks them in rounds of 8192 edges: an LDS atomic per edge counts the round's entries per bin and gives
+// the edge its place among them, one global atomic per bin reserves their range, and the entries, held in
+// registers meanwhile, are stored.  2.4M vertices, 121M edges: 859 us per dense hop (900 with 256 threads
+// that counted a portion in one walk over col[] and stored its entries in a second), 252 and 47 for
+// the sparser hops before it (299 and 92).  What bounds it is the reserving: 15k atomics on each bin's counter at
+// 15 ns each, and the two barriers around them; bytes take 310 us, arithmetic 256.  (Rounds of 2048 edges:
+// 0.9 ms of reserving alone; 4096 and 6144: 884, 852; more registers for half the wavefronts, 1096.  Sorting 2048
+// entries at a time by bin in LDS, so that neighbouring threads store neighbouring entries, was
+// slower: 1.2 ms; a thread taking 8 consecutive edges instead of a wavefront taking 64: 1.25 ms.)
+constexpr int kBinBlock = 256;           // threads per workgroup of the walks below, and most frontier vertices per portion
+constexpr int kFillBlock = 1024;         // the same of the general propagation's
+constexpr int kFillPer = 8;                // and its edges per thread and round
 constexpr int kBinPer = 8;               // edges per thread and round
-constexpr int kBinChunk = kBinBlock * kBinPer;
 constexpr int64_t kBinMaxBlocks = 16384; // row blocks whose two counters each fit the LDS of a workgroup
 
 // Frontier entries per portion: every workgroup gets as many portions as every other, and small
 // frontiers are cut into small portions so that they still spread over the chip.
+template <int kThreads>
 __device__ __forceinline__ int64_t bin_portion_size(int64_t nf) {
-    const int64_t rounds = (nf + (int64_t)gridDim.x * kBinBlock - 1) / ((int64_t)gridDim.x * kBinBlock);
+    const int64_t rounds = (nf + (int64_t)gridDim.x * kThreads - 1) / ((int64_t)gridDim.x * kThreads);
     const int64_t portions = rounds * gridDim.x;
     const int64_t per = portions > 0 ? (nf + portions - 1) / portions : kWave;
     return per < kWave ? kWave : per;
@@ -864,11 +869,12 @@ __device__ __forceinline__ int64_t bin_portion_size(int64_t nf) {
 // different portions; a large one is cut into runs of consecutive entries, whose rows lie
 // side by side in col[] (dealt out entry by entry, the dense hop of the general propagation took
 // 1.00 ms instead of 0.88).
+template <int kThreads>
 struct PortionMap {
     int64_t nf, per, nportions;
     bool dealt;
     __device__ __forceinline__ explicit PortionMap(int64_t nf_) : nf(nf_) {
-        per = bin_portion_size(nf);
+        per = bin_portion_size<kThreads>(nf);
         nportions = (nf + per - 1) / per;
         dealt = nportions <= 2 * (int64_t)gridDim.x;
     }
@@ -882,22 +888,24 @@ struct PortionMap {
     }
 };
 
+template <int kThreads>
 struct BinPortion {
-    uint32_t prefix[kBinBlock + 1];      // edges of the portion before vertex i
-    int64_t  row[kBinBlock];             // where vertex i's row starts in col[] and t[]
-    float    p[kBinBlock];               // p^[h-1] of vertex i
-    uint32_t wave_sum[kBinBlock / kWave];
+    uint32_t prefix[kThreads + 1];       // edges of the portion before vertex i
+    int64_t  row[kThreads];              // where vertex i's row starts in col[] and t[]
+    float    p[kThreads];                // p^[h-1] of vertex i
+    uint32_t wave_sum[kThreads / kWave];
 };
 
-// Exclusive prefix sums over a workgroup of kBinBlock threads; ends with a barrier.
-__device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t* wave_sum, uint32_t& total) {
+// Exclusive prefix sums over a workgroup of kThreads threads; ends with a barrier.
+template <int kThreads>
+__device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t (&wave_sum)[kThreads / kWave], uint32_t& total) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const uint32_t inc = (uint32_t)wave_inclusive_scan((int)v);
     if (lane == kWave - 1) wave_sum[wave] = inc;
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kBinBlock / kWave; ++w) {
+    for (int w = 0; w < kThreads / kWave; ++w) {
         const uint32_t x = wave_sum[w];
         if (w < wave) before += x;
         all += x;
@@ -909,7 +917,8 @@ __device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t* wave_su
 
 // The vertex of the portion whose row holds edge x of the sequence (x < prefix[nv]): the last i
 // with prefix[i] <= x.
-__device__ __forceinline__ int bin_vertex_of(const BinPortion& po, int nv, uint32_t x) {
+template <int kThreads>
+__device__ __forceinline__ int bin_vertex_of(const BinPortion<kThreads>& po, int nv, uint32_t x) {
     int lo = 0, hi = nv;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -920,7 +929,8 @@ __device__ __forceinline__ int bin_vertex_of(const BinPortion& po, int nv, uint3
 
 // Lays the rows of the portion's vertices end to end; returns the number of edges.  Ends with a barrier; the
 // caller puts one between the last use of a portion and the next call.
-__device__ __forceinline__ uint32_t bin_load_portion(BinPortion& po, const PortionMap& pm, int64_t portion,
+template <int kThreads>
+__device__ __forceinline__ uint32_t bin_load_portion(BinPortion<kThreads>& po, const PortionMap<kThreads>& pm, int64_t portion,
                                                      const int32_t* __restrict__ list, const float* __restrict__ p,
                                                      const int64_t* __restrict__ rowptr) {
     const int nv = pm.count(portion);
@@ -932,7 +942,7 @@ __device__ __forceinline__ uint32_t bin_load_portion(BinPortion& po, const Porti
         po.p[threadIdx.x] = p[v];
     }
     uint32_t total;
-    const uint32_t ex = bin_block_scan(deg, po.wave_sum, total);
+    const uint32_t ex = bin_block_scan<kThreads>(deg, po.wave_sum, total);
     if ((int)threadIdx.x < nv) po.prefix[threadIdx.x] = ex;
     if (threadIdx.x == 0) po.prefix[nv] = total;
     __syncthreads();
@@ -942,21 +952,23 @@ __device__ __forceinline__ uint32_t bin_load_portion(BinPortion& po, const Porti
 // A thread's walk over ascending edges of the portion's sequence: where edge x sits in col[] and
 // t[], and the probability of its source.  Rows are entered by comparison with the row's end, so an
 // edge inside the row of the edge before costs an add.
+template <int kThreads>
 struct BinCursor {
+    using Portion = BinPortion<kThreads>;
     int      i;          // vertex of the portion
     uint32_t row_end;    // first x beyond its row
     int64_t  shift;      // position in col[] minus x, inside this row
     float    p;
-    __device__ __forceinline__ void start(const BinPortion& po, int nv, uint32_t x) {
+    __device__ __forceinline__ void start(const Portion& po, int nv, uint32_t x) {
         i = bin_vertex_of(po, nv, x);
         enter(po);
     }
-    __device__ __forceinline__ void enter(const BinPortion& po) {
+    __device__ __forceinline__ void enter(const Portion& po) {
         row_end = po.prefix[i + 1];
         shift = po.row[i] - (int64_t)po.prefix[i];
         p = po.p[i];
     }
-    __device__ __forceinline__ int64_t at(const BinPortion& po, uint32_t x) {     // x < prefix[nv], not below the x before
+    __device__ __forceinline__ int64_t at(const Portion& po, uint32_t x) {     // x < prefix[nv], not below the x before
         if (x >= row_end) {
             do { ++i; } while (x >= po.prefix[i + 1]);
             enter(po);
@@ -965,24 +977,25 @@ struct BinCursor {
     }
 };
 
-// Edge q of a thread in the round that starts at edge c0: a wavefront takes kBinPer runs of 64
+// Edge q of a thread in the round that starts at edge c0: a wavefront takes kPer runs of 64
 // consecutive edges, so that its loads from col[] and t[] are contiguous.
+template <int kPer = kBinPer>
 __device__ __forceinline__ uint32_t bin_edge(uint32_t c0, int q) {
-    return c0 + (threadIdx.x >> 6) * (kWave * kBinPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
+    return c0 + (threadIdx.x >> 6) * (kWave * kPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
 }
 
 // Calls f(u, weight) for every edge of this workgroup's portions.
 template <class F>
-__device__ __forceinline__ void push_walk(BinPortion& po, int64_t nf, const int32_t* __restrict__ list,
+__device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf, const int32_t* __restrict__ list,
                                           const float* __restrict__ y, const int64_t* __restrict__ rowptr,
                                           const int32_t* __restrict__ col, F f) {
-    const PortionMap pm(nf);
+    const PortionMap<kBinBlock> pm(nf);
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
         const uint32_t total = bin_load_portion(po, pm, portion, list, y, rowptr);
-        for (uint32_t c0 = 0; c0 < total; c0 += kBinChunk) {
+        for (uint32_t c0 = 0; c0 < total; c0 += kBinBlock * kBinPer) {
             if (bin_edge(c0, 0) >= total) continue;
-            BinCursor cu;
+            BinCursor<kBinBlock> cu;
             cu.start(po, nv, bin_edge(c0, 0));
             int32_t u[kBinPer];
             float w[kBinPer];
@@ -1029,7 +1042,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t*
                                                                   const int32_t* __restrict__ col,
                                                                   double* __restrict__ acc,
                                                                   const uint32_t* __restrict__ how) {
-    __shared__ BinPortion po;
+    __shared__ BinPortion<kBinBlock> po;
     if (*how != kPushed) return;
     push_walk(po, (int64_t)*nf_ptr, list, y, rowptr, col, [&](uint32_t u, float w) { unsafeAtomicAdd(&acc[u], (double)w); });    // hardware fp64 add
 }
@@ -1055,7 +1068,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_count_kernel(const int32_t*
                                                                   const int32_t* __restrict__ col, int nrb,
                                                                   uint32_t* __restrict__ off,
                                                                   const uint32_t* __restrict__ how) {
-    __shared__ BinPortion po;
+    __shared__ BinPortion<kBinBlock> po;
     extern __shared__ uint32_t bin_lds[];
     if (*how != kPushed) return;
     for (int r = threadIdx.x; r < nrb; r += kBinBlock) bin_lds[r] = 0u;
@@ -1107,7 +1120,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* 
                                                                  const uint32_t* __restrict__ total,
                                                                  uint32_t* __restrict__ base, uint2* __restrict__ bins,
                                                                  const uint32_t* __restrict__ how) {
-    __shared__ BinPortion po;
+    __shared__ BinPortion<kBinBlock> po;
     extern __shared__ uint32_t bin_lds[];        // where this workgroup's next entry of each row block goes
     if (*how != kPushed) return;
     const int per = (nrb + kBinBlock - 1) / kBinBlock;
@@ -1116,7 +1129,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* 
     __syncthreads();
     uint32_t sum = 0, all;
     for (int r = r0; r < r1; ++r) sum += bin_lds[r];
-    uint32_t run = bin_block_scan(sum, po.wave_sum, all);
+    uint32_t run = bin_block_scan<kBinBlock>(sum, po.wave_sum, all);
     for (int r = r0; r < r1; ++r) {
         const uint32_t c = bin_lds[r];
         bin_lds[r] = run;
@@ -1171,25 +1184,23 @@ __device__ __forceinline__ float bin_log1p_neg(float x) {
     return x < 0.25f ? small : large;
 }
 
-__global__ void __launch_bounds__(kBinBlock) vipg_bin_fill_kernel(const int32_t* __restrict__ list,
-                                                                  const unsigned long long* __restrict__ nf_ptr,
-                                                                  const float* __restrict__ pcur,
-                                                                  const int64_t* __restrict__ rowptr,
-                                                                  const int32_t* __restrict__ col,
-                                                                  const float* __restrict__ t, int rbits, int nrb,
-                                                                  const int64_t* __restrict__ first, int nch,
-                                                                  uint32_t* __restrict__ cursor,
-                                                                  uint2* __restrict__ bins, int* __restrict__ bad) {
-    __shared__ BinPortion po;
+__global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int32_t* __restrict__ list,
+                                                                      const unsigned long long* __restrict__ nf_ptr,
+                                                                      const float* __restrict__ pcur,
+                                                                      const int64_t* __restrict__ rowptr,
+                                                                      const int32_t* __restrict__ col,
+                                                                      const float* __restrict__ t, int rbits, int nrb,
+                                                                      const int64_t* __restrict__ first, int nch,
+                                                                      uint32_t* __restrict__ cursor,
+                                                                      uint2* __restrict__ bins, int* __restrict__ bad) {
+    __shared__ BinPortion<kFillBlock> po;
     extern __shared__ uint32_t lds_u32[];
-    uint32_t* base = lds_u32;            // the portion's entries per row block, then the entry (index into bins[], below 2^32) where they start
-    uint32_t* filled = lds_u32 + nrb;    // entries of the block written so far
+    uint32_t* count = lds_u32;           // the round's entries per row block; zero between rounds
+    uint32_t* base = lds_u32 + nrb;      // the entry (index into bins[], below 2^32) where they start
     const int64_t nf = (int64_t)*nf_ptr;
-    const PortionMap pm(nf);
+    const PortionMap<kFillBlock> pm(nf);
     const uint32_t rmask = (1u << rbits) - 1u;
-    const int bins_per_thread = (nrb + kBinBlock - 1) / kBinBlock;
-    const int r0 = threadIdx.x * bins_per_thread;
-    const int r1 = r0 + bins_per_thread < nrb ? r0 + bins_per_thread : nrb;
+    for (int r = threadIdx.x; r < nrb; r += kFillBlock) count[r] = 0u;
     // Portions are handed out through a counter (the slot after the bins' cursors): their sizes
     // differ by the degrees of their vertices, and with fixed shares half of the wavefronts had
     // left before the kernel's end.
@@ -1199,54 +1210,41 @@ __global__ void __launch_bounds__(kBinBlock) vipg_bin_fill_kernel(const int32_t*
         __syncthreads();
         if ((int64_t)portion >= pm.nportions) break;
         const int nv = pm.count(portion);
-        for (int r = threadIdx.x; r < nrb; r += kBinBlock) base[r] = 0u;
         const uint32_t total = bin_load_portion(po, pm, portion, list, pcur, rowptr);
-        // first walk: the portion's entries per bin
-        for (uint32_t c0 = 0; c0 < total; c0 += kBinChunk) {
-            if (bin_edge(c0, 0) >= total) continue;
-            BinCursor cu;
-            cu.start(po, nv, bin_edge(c0, 0));
-            uint32_t u[kBinPer];
+        for (uint32_t c0 = 0; c0 < total; c0 += kFillBlock * kFillPer) {
+            uint32_t key[kFillPer], rank[kFillPer];
+            float x[kFillPer];
 #pragma unroll
-            for (int q = 0; q < kBinPer; ++q) u[q] = bin_edge(c0, q) < total ? (uint32_t)col[cu.at(po, bin_edge(c0, q))] : ~0u;
+            for (int q = 0; q < kFillPer; ++q) key[q] = ~0u;
+            if (bin_edge<kFillPer>(c0, 0) < total) {
+                BinCursor<kFillBlock> cu;
+                cu.start(po, nv, bin_edge<kFillPer>(c0, 0));
 #pragma unroll
-            for (int q = 0; q < kBinPer; ++q)
-                if (u[q] != ~0u) atomicAdd(&base[u[q] >> rbits], 1u);
-        }
-        __syncthreads();
-        for (int r = r0; r < r1; ++r) {
-            const uint32_t c = base[r];
-            base[r] = (uint32_t)first[(int64_t)r * nch] + (c ? atomicAdd(&cursor[r], c) : 0u);
-            filled[r] = 0u;
-        }
-        __syncthreads();
-        // second walk: the entries
-        for (uint32_t c0 = 0; c0 < total; c0 += kBinChunk) {
-            if (bin_edge(c0, 0) >= total) continue;
-            BinCursor cu;
-            cu.start(po, nv, bin_edge(c0, 0));
-            uint32_t key[kBinPer];
-            float pv[kBinPer], tv[kBinPer];
-#pragma unroll
-            for (int q = 0; q < kBinPer; ++q) {
-                key[q] = ~0u;
-                if (bin_edge(c0, q) < total) {
-                    const int64_t k = cu.at(po, bin_edge(c0, q));
-                    key[q] = (uint32_t)col[k];
-                    tv[q] = t[k];
-                    pv[q] = cu.p;
-                }
+                for (int q = 0; q < kFillPer; ++q)
+                    if (bin_edge<kFillPer>(c0, q) < total) {
+                        const int64_t k = cu.at(po, bin_edge<kFillPer>(c0, q));
+                        key[q] = (uint32_t)col[k];
+                        x[q] = unit_or_flag(t[k], bad) * cu.p;
+                    }
             }
 #pragma unroll
-            for (int q = 0; q < kBinPer; ++q) {
+            for (int q = 0; q < kFillPer; ++q)
+                if (key[q] != ~0u) rank[q] = atomicAdd(&count[key[q] >> rbits], 1u);
+            __syncthreads();
+            for (int r = threadIdx.x; r < nrb; r += kFillBlock) {
+                const uint32_t c = count[r];
+                if (c != 0u) {
+                    base[r] = (uint32_t)first[(int64_t)r * nch] + atomicAdd(&cursor[r], c);
+                    count[r] = 0u;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kFillPer; ++q)
                 if (key[q] != ~0u) {
-                    const uint32_t u = key[q];
-                    const float xw = unit_or_flag(tv[q], bad) * pv[q];
-                    const uint32_t rb = u >> rbits;
-                    const uint32_t slot = atomicAdd(&filled[rb], 1u);
-                    bins[base[rb] + slot] = make_uint2(__float_as_uint(xw > 0.0f ? bin_log1p_neg(xw) : 0.0f), u & rmask);
+                    bins[base[key[q] >> rbits] + rank[q]] =
+                        make_uint2(__float_as_uint(x[q] > 0.0f ? bin_log1p_neg(x[q]) : 0.0f), key[q] & rmask);
                 }
-            }
         }
         __syncthreads();
     }
@@ -1353,7 +1351,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
                 fill_f32_kernel<<<(unsigned)((g->nrb + kBlock) / kBlock), kBlock, 0, st>>>(
                     reinterpret_cast<float*>(cursor), g->nrb + 1, 0.f);         // all-zero bits either way
                 // a bin is the range of the edges that end in its row block: block_first, with a stride of one
-                vipg_bin_fill_kernel<<<ctx->num_cu * 8, kBinBlock, fill_lds, st>>>(
+                vipg_bin_fill_kernel<<<ctx->num_cu * 2, kFillBlock, fill_lds, st>>>(
                     flist, fcount + 2, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits, (int)g->nrb,
                     g->block_first, 1, cursor, bins, d_bad);
                 vip_bin_sum_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, sum_lds, st>>>(

@@ -134,3 +134,23 @@ def test_probabilities_to_fp32_rounding(spp, ctx, batch):
             ref = np.asarray(ref)
             assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= (roundings + 0.01) * 2.0**-24 * ref)
     G.close()
+
+
+# rounds of 8192 edges of a workgroup's portion (64 vertices and more): just below, at and above one round, one
+# vertex more than a portion each, more vertices than 1024 for every workgroup, rows longer than a round's share
+@pytest.mark.parametrize("N,deg", [(32768, 127), (32768, 128), (32768, 129), (32769, 1), (525000, 2), (7000, 300)])
+def test_general_probabilities_in_rounds(spp, ctx, N, deg):
+    print("[case]", N, deg, flush=True)
+    rng = np.random.default_rng(N + deg)
+    rp, col = _ring(N, deg)
+    p0 = np.where(rng.random(N) < 0.95, rng.random(N), 0.0).astype(np.float32)
+    t = [(rng.random(col.size) * min(1.0, 8 / deg)).astype(np.float32) for _ in range(2)]
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True)
+    p, ph = spp.vip_propagate_general(ctx, G, torch.from_numpy(p0).to(dev), [torch.from_numpy(a).to(dev) for a in t], 2, per_hop=True)
+    ref_t, ref_h = oracle.vip_general(rp, col, p0, t, 2)
+    for got, ref in ((p, ref_t), (ph, ref_h)):
+        # a term's logarithm carries a few units of fp32 (bin_log1p_neg), all terms have one sign, and the second hop
+        # starts from probabilities rounded to fp32: the 1e-5 that the entry point states
+        assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-5 * np.asarray(ref) + 1e-37)
+    G.close()
