@@ -219,10 +219,6 @@ __device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, un
     }
 }
 
-__global__ void fill_f32_kernel(float* p, int64_t n, float v) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
 __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1269,11 +1265,29 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
     for (int i = threadIdx.x; i < R; i += kTileBlock) out[i] = acc[i];
 }
 
+// What a hop's kernels count with: the frontier list's cursor, and the bins' (none without bins).
+struct HopCounters {
+    unsigned long long* listed;
+    uint32_t* bins;
+    int64_t   nbins;
+    __device__ __forceinline__ void clear(int64_t tid, int64_t stride) const {
+        for (int64_t i = tid; i < nbins; i += stride) bins[i] = 0u;
+        if (tid == 0) *listed = 0ull;
+    }
+};
+
+__global__ void __launch_bounds__(kBlock) vipg_clear_kernel(HopCounters c, int* __restrict__ bad) {
+    c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bad = 0;
+}
+
+// Also empties the counters for the next hop.
 __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __restrict__ acc, double* __restrict__ tot,
                                                              int first, int last, float* __restrict__ p_hop,
                                                              float* __restrict__ p_total, float* __restrict__ pnext,
-                                                             int64_t N, int parts, int64_t part_stride) {
+                                                             int64_t N, int parts, int64_t part_stride, HopCounters c) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
+    c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
     for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += stride) {
         double S = acc[u];
         for (int j = 1; j < parts; ++j) S += acc[(int64_t)j * part_stride + u];
@@ -1341,15 +1355,13 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     }
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
-        fill_f32_kernel<<<1, 64, 0, st>>>(reinterpret_cast<float*>(d_bad), 1, 0.f);
+        const HopCounters counters{fcount + 2, cursor, binned ? g->nrb + 1 : 0};
+        vipg_clear_kernel<<<(unsigned)(counters.nbins / kBlock + 1), kBlock, 0, st>>>(counters, d_bad);
         vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
-            fill_f64_kernel<<<1, 64, 0, st>>>(reinterpret_cast<double*>(fcount), 3, 0.0);
             launch_frontier_list(fill_grid, st, pcur, g->rowptr, N, flist, fcount + 2);
             if (binned) {
-                fill_f32_kernel<<<(unsigned)((g->nrb + kBlock) / kBlock), kBlock, 0, st>>>(
-                    reinterpret_cast<float*>(cursor), g->nrb + 1, 0.f);         // all-zero bits either way
                 // a bin is the range of the edges that end in its row block: block_first, with a stride of one
                 vipg_bin_fill_kernel<<<ctx->num_cu * 2, kFillBlock, fill_lds, st>>>(
                     flist, fcount + 2, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits, (int)g->nrb,
@@ -1363,7 +1375,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
             }
             vipg_finish_kernel<<<fill_grid, kBlock, 0, st>>>(acc, tot, (h == 1 && !include0) ? 1 : 0, h == L ? 1 : 0,
                                                              d_p_hop ? d_p_hop + (int64_t)(h - 1) * N : nullptr,
-                                                             d_p_total, pnext, N, parts, part_stride);
+                                                             d_p_total, pnext, N, parts, part_stride, counters);
             float* tmp = pcur; pcur = pnext; pnext = tmp;
         }
     }
