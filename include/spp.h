@@ -149,7 +149,9 @@ int  spp_cache_lookup(spp_ctx* ctx, const spp_cache* c, const int32_t* d_ids, in
  *     The caller sizes the buffers with spp_mfg_bound and fills the capacities and pointers;
  *     the library fills the buffers and d_counts (device int64[2*(SPP_MAX_L+1)]: n_0..n_L at
  *     [0..L], e_0..e_L at [SPP_MAX_L+1 ..]; e_0 = 0).  With SPP_SYNC it also waits and fills the
- *     host fields n[] and e[].  Capacities below the bounds give SPP_E_CAPACITY before any work. */
+ *     host fields n[] and e[].  Capacities below the bounds give SPP_E_CAPACITY before any work.
+ *     Seeds that are not distinct can reach more than N vertices: what exceeds the bounds is then dropped
+ *     and, with SPP_SYNC, SPP_E_ARG is returned, as for a seed outside [0, N). */
 typedef struct {
     int64_t  n_nodes_cap;               /* in: entries in d_node_ids (>= n_bound[L]) */
     int64_t  n_edges_cap[SPP_MAX_L];    /* in: entries in d_src[h-1] (>= e_bound[h]) */

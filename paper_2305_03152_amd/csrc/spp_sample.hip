@@ -96,6 +96,15 @@ struct SampleArgs {
     int*           ovf;                 // set when a minibatch was abandoned for lack of capacity
 };
 
+// Most members that S_h can have: S_L has the caller's room, the sets before it N, for which the workspaces and
+// the later hops' buffers are sized (the bounds of spp_mfg_bound follow from n_h <= N hop by hop).  Distinct seeds
+// never exceed it; repeated ones do (bad seeds too, which all become vertex 0) once a minibatch reaches nearly the
+// whole graph: what lies beyond is then dropped, so that nothing is written or read out of range, and reported.
+// (With given probabilities every hop has the caller's room, which ids_overflow() has checked.)
+__device__ __forceinline__ int64_t vertex_cap(const BatchDesc& b, int64_t N, int h, int L) {
+    return h < L ? N : (b.ncap < 0x7FFFFFFF ? b.ncap : 0x7FFFFFFF);
+}
+
 __device__ __forceinline__ unsigned long long* tab_of(const SampleArgs& a, int j) { return a.tab + (int64_t)j * a.cap; }
 __device__ __forceinline__ int32_t* flat_of(const SampleArgs& a, int j) { return a.flat + (int64_t)j * a.flat_stride; }
 __device__ __forceinline__ int32_t* gids_of(const SampleArgs& a, int j) { return a.gids + (int64_t)j * a.flat_stride; }
@@ -850,6 +859,7 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
     const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
     const uint64_t* __restrict__ ent = a.ent + (int64_t)jb * a.ent_stride;
     const uint32_t* __restrict__ fsum = a.fsum + (int64_t)jb * kHopGranules;
+    const uint32_t id_cap = (uint32_t)vertex_cap(b, a.N, a.h, a.L);
     int32_t* __restrict__ src = b.src[a.h - 1];
     int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
     int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
@@ -894,13 +904,16 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
                     if (e + u >= n_e) continue;
                     int32_t out;
                     if (w[u] < kRepeat) {
-                        b.S[id] = (int32_t)w[u];
-                        if (a.f_next) {
-                            row0[id] = r0[u];
-                            deg[id] = rlen[u];
-                            atomicAdd(&next_sum[id / kHopTargets - id0 / kHopTargets], (uint32_t)(rlen[u] < a.f_next ? rlen[u] : a.f_next));
+                        if (id < id_cap) {
+                            b.S[id] = (int32_t)w[u];
+                            if (a.f_next) {
+                                row0[id] = r0[u];
+                                deg[id] = rlen[u];
+                                atomicAdd(&next_sum[id / kHopTargets - id0 / kHopTargets], (uint32_t)(rlen[u] < a.f_next ? rlen[u] : a.f_next));
+                            }
                         }
-                        out = (int32_t)id++;
+                        out = (int32_t)(id < id_cap ? id : id_cap - 1);
+                        ++id;
                     } else {
                         // an earlier vertex, or (left for the relabel) a first appearance earlier in this hop
                         const uint32_t first = w[u] & ~kRepeat;
@@ -919,6 +932,7 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
             __syncthreads();                     // the next tile overwrites what[]
         }
         if (g == ngran - 1 && threadIdx.x == 0) {
+            if (id0 > id_cap) { atomicOr(a.bad, 4); id0 = id_cap; }
             b.counts[a.h] = id0;
             if (a.h == a.L) {
                 atomicAdd(&a.totals[1], (unsigned long long)id0);
@@ -926,23 +940,22 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
                 if (a.mirror) {
                     int64_t* m = a.mirror + (int64_t)jb * 2 * kE;
                     for (int q = 0; q < 2 * kE; ++q) m[q] = q == a.h ? (int64_t)id0 : b.counts[q];
-                    if (jb == 0) {
-                        int* fl = reinterpret_cast<int*>(a.mirror + (int64_t)kMaxBatches * 2 * kE);
-                        fl[0] = *a.bad; fl[1] = 0;
-                    }
                 }
             }
         }
     }
 }
 
-// After the last hop: its repeats, and what the next call expects empty.
+// After the last hop: its repeats, the error flags of a call that is waited for, and what the next call expects empty.
 __global__ void __launch_bounds__(kBlock) hop_last_kernel(HopArgs a, const BatchTable* __restrict__ t) {
     const BatchBlock bb = batch_block();
     if (bb.x == 0)
         for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)bb.j * kHopGranules + g] = 0u;
     relabel_repeats(t->b[bb.j], a.h, bb.x, gridDim.x);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.bad_next[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) {
+        if (a.mirror) reinterpret_cast<int*>(a.mirror + (int64_t)kMaxBatches * 2 * kE)[threadIdx.x] = a.bad[threadIdx.x];
+        a.bad_next[threadIdx.x] = 0;
+    }
 }
 
 // ---- steps 1 and 2 with given transition probabilities ----
@@ -1141,9 +1154,10 @@ struct NewOut {
         if (!v || t->b[j].tinfo[2] || ids_overflow(a, t->b[j], total)) return;    // NewFin abandons the minibatch
         // A first appearance gets its local id here; the relabel pass fills in the repeats.
         const int64_t n_prev = t->b[j].counts[a.h - 1];
-        const int64_t id = n_prev + ex;
+        const int64_t id = n_prev + (int64_t)(uint32_t)ex, cap = vertex_cap(t->b[j], a.N, a.h, a.t ? a.h : a.L);
         const int32_t gid = gids_of(a, j)[e];
-        t->b[j].src[a.h - 1][e] = (int32_t)id;
+        t->b[j].src[a.h - 1][e] = (int32_t)(id < cap ? id : cap - 1);
+        if (id >= cap) return;                             // NewFin reports it
         t->b[j].S[id] = gid;
         // a vertex that will be a target of the next hop: its row is looked up here, once
         if (!a.t && a.h < a.L && id < a.node_stride) {
@@ -1159,13 +1173,15 @@ struct NewFin {
         int64_t* c = t->b[j].counts;
         if (a.t) *t->b[j].taken = 0ull;                    // the next hop counts from zero
         if (t->b[j].tinfo[2]) return;
-        const int64_t n = c[a.h - 1] + (int64_t)(uint32_t)total;
+        int64_t n = c[a.h - 1] + (int64_t)(uint32_t)total;
         if (ids_overflow(a, t->b[j], total)) {             // the new ids do not fit the caller's buffer
             t->b[j].tinfo[2] = 1;
             atomicOr(a.ovf, 1);
             c[kE + a.h] = 0;
             return;
         }
+        const int64_t cap = vertex_cap(t->b[j], a.N, a.h, a.t ? a.h : a.L);
+        if (n > cap) { atomicOr(a.bad, 4); n = cap; }
         c[a.h] = n;
         if (a.h == a.L) { atomicAdd(&a.totals[1], (unsigned long long)n); atomicAdd(&a.totals[0], 1ull); }
     }
@@ -1505,6 +1521,7 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
             }
         const int* fl = reinterpret_cast<const int*>(hp + kMaxBatches * 2 * kE);
         SPP_CHECK((fl[0] & 1) == 0, SPP_E_ARG, "spp_sample_mfg: a seed lies outside [0, N)");
+        SPP_CHECK((fl[0] & 4) == 0, SPP_E_ARG, "spp_sample_mfg: a minibatch reached more vertices than its bound: its seeds are not distinct");
         SPP_CHECK((fl[0] & 2) == 0, SPP_E_ARG, "spp_sample_mfg_general: a transition probability lies outside [0, 1]; it was taken as 0");
         SPP_CHECK(fl[1] == 0, SPP_E_CAPACITY, "spp_sample_mfg_general: a minibatch exceeded the capacity of its buffers and was abandoned");
     }

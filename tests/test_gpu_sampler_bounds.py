@@ -1,0 +1,97 @@
+"""GPU: seeds that are not distinct (which is also what seeds outside [0, N) become) let a minibatch reach
+more than N vertices.  Nothing may then be written beyond the bounds, the call reports it, and neither the
+other minibatches of the call nor later calls see any of it."""
+import random
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+SEED = 0x1234567890ABCDEF
+
+
+def test_the_vertex_cap_keeps_every_size_within_its_bound():
+    """Sizes grow by at most n (1 + f) per hop and are cut at N before the last hop: they then stay within the
+    bounds that the workspaces and the caller's buffers are sized by."""
+    import paper_2305_03152_amd as spp
+    rng = random.Random(3)
+    for _ in range(300):
+        N, L = rng.randint(1, 5000), rng.randint(1, 5)
+        f = [rng.randint(1, 20) for _ in range(L)]
+        n = rng.randint(0, N)
+        nb, eb = spp.mfg_bound(n, f, N)
+        for h in range(1, L + 1):
+            e = n * f[h - 1]
+            assert e <= eb[h]
+            n = n + e if rng.random() < 0.7 else n + rng.randint(0, e)
+            n = min(n, N if h < L else max(N, nb[L]))
+            assert n <= nb[h]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("global_table", [False, True])
+@pytest.mark.parametrize("bad", ["outside", "repeated"])
+@pytest.mark.parametrize("fanouts", [(5,), (5, 4), (20, 3, 2), (3, 40)])
+def test_seeds_that_are_not_distinct(bad, fanouts, global_table):
+    import paper_2305_03152_amd as spp
+    dev = torch.device("cuda:0")
+    N = 300
+    rng = np.random.default_rng(1)
+    key = np.unique(np.concatenate([np.arange(N, dtype=np.int64) << 32 | rng.integers(0, N, N) for _ in range(30)]))
+    key = key[(key >> 32) != (key & 0xFFFFFFFF)]
+    rp = np.zeros(N + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key >> 32, minlength=N), out=rp[1:])
+    col = (key & 0xFFFFFFFF).astype(np.int32)
+    ctx = spp.Context(0)
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev))
+    good = np.arange(N, dtype=np.int32)[::-1].copy()
+    wrong = np.full(N, -1 if bad == "outside" else 0, dtype=np.int32)
+    L = len(fanouts)
+
+    def buffers():
+        """All output arrays inside larger ones, so that a write beyond an array's end shows."""
+        m = spp.MFGBuffers(dev, N, fanouts, N)
+        guards = []
+        for name in ("node_ids", "indptr", "src"):
+            arrays = [m.node_ids] if name == "node_ids" else getattr(m, name)
+            out = []
+            for t in arrays:
+                whole = torch.full((t.numel() + 4096,), 777, dtype=t.dtype, device=dev)
+                guards.append(whole[t.numel():])
+                out.append(whole[:t.numel()])
+            if name == "node_ids":
+                m.node_ids = out[0]
+            else:
+                setattr(m, name, out)
+        m._s.d_node_ids = m.node_ids.data_ptr()
+        for h in range(L):
+            m._s.d_indptr[h], m._s.d_src[h] = m.indptr[h].data_ptr(), m.src[h].data_ptr()
+        return m, guards
+
+    items = [(good, *buffers()), (wrong, *buffers()), (good, *buffers())]
+    arg = [(torch.from_numpy(s).to(dev), i, m) for i, (s, m, _) in enumerate(items)]
+    for _ in range(2):
+        with pytest.raises(spp.SppError):
+            spp.sample_mfg_multi(ctx, G, arg, fanouts, SEED, global_table=global_table)
+    for i, (s, m, guards) in enumerate(items):
+        assert all(int((g != 777).sum()) == 0 for g in guards)
+        n = m.counts[:L + 1].cpu().numpy()
+        assert n.max() <= N
+        for h in range(L):
+            e = int(m.counts[9 + h + 1])
+            src = m.src[h][:e].cpu().numpy()
+            assert src.min() >= 0 and src.max() < n[h + 1]
+        if i == 1:
+            continue
+        ref = oracle.sample_mfg(rp, col, s, fanouts, SEED, i)
+        assert list(n) == ref.n and np.array_equal(m.node_ids[:n[-1]].cpu().numpy(), ref.node_ids)
+        for h in range(L):
+            assert np.array_equal(m.indptr[h][:n[h] + 1].cpu().numpy(), ref.indptr[h])
+            assert np.array_equal(m.src[h][:ref.e[h + 1]].cpu().numpy(), ref.src[h])
+    # a later call on the context
+    out = spp.sample_mfg(ctx, G, torch.from_numpy(good[:40].copy()).to(dev), fanouts, SEED, 9, global_table=global_table)
+    ref = oracle.sample_mfg(rp, col, good[:40].copy(), fanouts, SEED, 9)
+    assert out.n == ref.n and np.array_equal(out.node_ids[:out.n[-1]].cpu().numpy(), ref.node_ids)
+    ctx.close()
