@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "spp_edges.h"
+
 namespace spp {
 
 constexpr int kBlock = 256;            // threads per workgroup: 4 wavefronts of 64 lanes
@@ -367,15 +369,8 @@ __device__ __forceinline__ int64_t table_find(const unsigned long long* tab, uin
 }
 
 // ---------------------------------------------------------------------------------------------
-// Edges grouped by blocks of destination rows and sorted by source inside a block, one 32-bit word
-// per edge: (source & (2^18 - 1)) << 14 | row inside the block.  The source's high bits are the
-// index of its "source chunk"; bound[c] is the position inside the block of the first edge whose
-// chunk is >= c (bound[0] = 0, bound[nch] = edges of the block), so the chunk of the edge at
-// position p is the largest c with bound[c] <= p.
+// Row-block layout: see spp_edges.h.
 // ---------------------------------------------------------------------------------------------
-constexpr int kTileSrcLoBits = 18;
-constexpr int kTileRowBits = 14;
-constexpr uint32_t kTileRowMask = (1u << kTileRowBits) - 1u;
 constexpr uint32_t kTileWinBytes = 16 * 448 * 4;    // windows of y in the dense-hop kernel's LDS: 448 values for each of 16 wavefronts
 
 __device__ __forceinline__ int tile_chunk_of(const uint32_t* bound, int nch, uint32_t p) {
@@ -385,9 +380,6 @@ __device__ __forceinline__ int tile_chunk_of(const uint32_t* bound, int nch, uin
         if (bound[mid] <= p) lo = mid; else hi = mid - 1;
     }
     return lo;
-}
-__device__ __forceinline__ uint32_t tile_source(uint32_t word, int chunk) {
-    return ((uint32_t)chunk << kTileSrcLoBits) | (word >> kTileRowBits);
 }
 
 // The chunked layout of the same edges: chunks of 2^kXSrcBits sources, row blocks of 2^kTileRowBits

@@ -10,8 +10,7 @@
 //   and per row block where each chunk's piece lies and how many vectors precede it.
 // The row blocks are one stable partition of the CSR's edges by the block of their destination: the CSR
 // is sorted by source already.  The chunked layout is built by a radix sort of packed edge keys.  Either
-// is built once per graph, then read back and compared with the edges it was built from before
-// anything walks it.
+// is built once per graph, then read back and compared with the edges of the CSR before anything walks it.
 #include "spp_common.h"
 #include "spp_device.h"
 
@@ -47,23 +46,15 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
-// edges: the kernels of a build 9.2 -> 1.0 ms: 0.70 in the placing pass, which issues 137 vector
-// instructions per 64 edges (0.42 ms of it), 0.11 in the counting pass, 0.17 in the read-back.  Tiles of
-// 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
+// edges: the kernels of a build 9.2 -> 1.1 ms: 0.63 in the placing pass, most of it vector instructions,
+// 0.12 in the counting pass, 0.15 in the read-back and 0.19 in the sum over the CSR that it is compared with.
+// Tiles of 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
 constexpr int kPartTile = 4096;
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
 constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
 constexpr int kPartMaxBlocks = 512;                      // 2^23 vertices in blocks of 2^14 rows
 
-// Adds a 64-bit mix of an edge to a sum; the edges of two structures are compared by their sums.  One
-// 32-bit and one 32x32 -> 64 product: the kernels here are bound by their instructions (a wavefront's
-// instruction occupies its SIMD for four clocks, a product for sixteen), and a stronger mix was half
-// of the read-back's time.
-__device__ __forceinline__ void edge_mix(unsigned long long& sum, uint32_t v, uint32_t u) {
-    const uint32_t x = v * 0x9E3779B1u + u;
-    sum += (unsigned long long)(x ^ (x >> 15)) * (u ^ 0x85EBCA77u ^ (v << 7));
-}
 __device__ __forceinline__ void add_mix(unsigned long long mine, unsigned long long* sum) {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
@@ -126,8 +117,7 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
                                                                 const int32_t* __restrict__ col, int rbits,
                                                                 int nrb, int64_t ntiles, const int32_t* __restrict__ tile_row,
                                                                 const uint32_t* __restrict__ offs,
-                                                                uint32_t* __restrict__ t_edge,
-                                                                unsigned long long* __restrict__ mix) {
+                                                                uint32_t* __restrict__ t_edge) {
     __shared__ uint32_t words[kPartTile];        // first: where rows start in the tile; then the edge words by block
     __shared__ uint16_t blk_of[kPartTile];
     __shared__ uint16_t cnt[kPartWaves][kPartMaxBlocks];      // edges, then first place, per wavefront and block
@@ -137,7 +127,6 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
     const int wave = threadIdx.x >> 6, lane = lane_id();
     const uint64_t lt_mask = (1ull << lane) - 1ull;
     const uint32_t rmask = (1u << rbits) - 1u;
-    unsigned long long sum = 0;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t base = tile * kPartTile;
         const int count = M - base < kPartTile ? (int)(M - base) : kPartTile;
@@ -193,7 +182,6 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
             const uint32_t prior = has ? cnt[wave][blk] : 0u;
             if (has && below == 0) cnt[wave][blk] = (uint16_t)(prior + (uint32_t)__popcll(same));
             place[k] = (blk << 16) | (prior + below);
-            if (has) edge_mix(sum, s, u[k]);
             u[k] = ((s & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (u[k] & rmask);
         }
         __syncthreads();
@@ -226,7 +214,6 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
         for (int i = threadIdx.x; i < count; i += kPartBlock) t_edge[gshift[blk_of[i]] + (uint32_t)i] = words[i];
         __syncthreads();                         // the next tile overwrites the LDS arrays
     }
-    add_mix(sum, mix);
 }
 static_assert(kPartMaxBlocks <= kPartBlock, "one block per thread");
 
@@ -249,9 +236,79 @@ __global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const
     if (c == 0 && threadIdx.x == 0) first[(int64_t)nrb * nch] = M;
 }
 
-// Reads the structure back the way the propagation kernel does: every edge must lie in range (so that a
-// kernel that gathers through it never sees a source or a row out of range), and the edges' mixes must
-// add up to those of the CSR's.  `parts` workgroups per row block; the block's chunk bounds sit in LDS.
+// The sum of the mixes of the CSR's edges, each with the row that holds it: what the structure is compared with, found by
+// another way than the one that built it.  A wavefront takes a tile of edges at a time and holds the ends of 64 rows
+// in its lanes, among which an edge finds its own; the first rows are the tile's entry in tile_row[] if that row does
+// hold the tile's first edge (else the structure is bad), later ones follow or, after a long run of empty rows, are found
+// by bisection.  2.4M vertices, 121M edges: 194 us (271 with a bisection for every 2048 edges' first row and one among
+// the 64 rows for every edge).
+__global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
+                                                         const int32_t* __restrict__ col, const int32_t* __restrict__ tile_row,
+                                                         unsigned long long* __restrict__ mix, int* __restrict__ bad) {
+    constexpr int U = 4;                         // batches of 64 edges in flight
+    const int lane = lane_id();
+    const int64_t wave = (int64_t)blockIdx.x * (kBlock / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
+    unsigned long long sum = 0;
+    for (int64_t tile = wave; tile * kPartTile < M; tile += nwaves) {
+        const int64_t base = tile * kPartTile;
+        const uint32_t count = M - base < kPartTile ? (uint32_t)(M - base) : (uint32_t)kPartTile;
+        int64_t lo = tile_row[tile];
+        if (lo < 0 || lo >= N || rowptr[lo] > base || rowptr[lo + 1] <= base) { *bad = 1; continue; }
+        uint32_t done = 0;
+        while (done < count) {
+            if (done > 0) {
+                // the last row that starts at or before the edge (it holds it: rows after an empty one start where that does)
+                int64_t hi = N - 1;
+                lo = 0;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi + 1) >> 1;
+                    if (rowptr[mid] <= base + done) lo = mid; else hi = mid - 1;
+                }
+            }
+            // rows lo .. lo + 63, as long as they hold edges of the tile
+            for (bool more = true; more && done < count; lo += kWave) {
+                const int64_t end64 = (lo + 1 + lane <= N ? rowptr[lo + 1 + lane] : M) - base;
+                const uint32_t end = end64 < (int64_t)count ? (uint32_t)end64 : count;
+                const uint32_t stop = (uint32_t)__shfl((int)end, kWave - 1, kWave);
+                more = stop > done;
+                for (uint32_t p0 = done; p0 < stop; p0 += U * kWave) {
+                    uint32_t u[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        const uint32_t p = p0 + k * kWave + lane;
+                        u[k] = p < stop ? (uint32_t)col[base + p] : 0u;
+                    }
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        const uint32_t p = p0 + k * kWave + lane;
+                        // the rows of the 64 that end at or before the edge: those before the batch, then the few that
+                        // end inside it one by one, many by bisection
+                        const int first = __popcll(__ballot(end <= p0 + k * kWave));
+                        const int last = __popcll(__ballot(end <= p0 + k * kWave + (kWave - 1)));
+                        int r = first;
+                        if (last - first <= 6) {
+                            for (int i = first; i < last; ++i) r += (uint32_t)__builtin_amdgcn_readlane((int)end, i) <= p ? 1 : 0;
+                        } else {
+                            r = 0;               // at most 63 for an edge of the window
+#pragma unroll
+                            for (int s = kWave / 2; s > 0; s >>= 1)
+                                if ((uint32_t)__shfl((int)end, r + s - 1, kWave) <= p) r += s;
+                        }
+                        if (p < stop) edge_mix(sum, (uint32_t)(lo + r), u[k]);
+                    }
+                }
+                done = stop;
+            }
+        }
+    }
+    add_mix(sum, mix);
+}
+
+// Reads the structure back the way the propagation kernel does: every edge must lie in range and the sources of a
+// block must ascend inside a chunk (so that a kernel that gathers through the structure never sees a source, a row or a place
+// in its window of y out of range), and the edges' mixes must add up to those of the CSR's.  `parts` workgroups per
+// row block; the block's chunk bounds sit in LDS.
 __global__ void __launch_bounds__(kBlock) tile_verify_kernel(int rbits, int nch, const uint32_t* __restrict__ t_edge,
                                                              const int64_t* __restrict__ first, int parts, int64_t N, int64_t M,
                                                              unsigned long long* __restrict__ mix, int* __restrict__ bad) {
@@ -276,9 +333,9 @@ __global__ void __launch_bounds__(kBlock) tile_verify_kernel(int rbits, int nch,
         const uint32_t lo = bound[c] > beg ? bound[c] : beg, hi = bound[c + 1] < end ? bound[c + 1] : end;
 #pragma unroll 8
         for (uint32_t p = lo + threadIdx.x; p < hi; p += kBlock) {
-            const uint32_t w = words[p], v = tile_source(w, c), r = w & kTileRowMask;
-            wrong |= v >= (uint32_t)N || r >= rows;
-            edge_mix(sum, v, u0 + r);
+            const uint32_t w = words[p], before = words[p > bound[c] ? p - 1 : p];
+            wrong |= !tile_word_ok(w, before, c, (uint32_t)N, rows);
+            edge_mix(sum, tile_source(w, c), u0 + (w & kTileRowMask));
         }
     }
     if (wrong) *bad = 1;
@@ -323,7 +380,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         const int scan_grid = 1024;
         // one allocation: the counts, the scan's partial sums, the sums of the edges' mixes, a flag,
         // and the tiles' first rows
-        struct { unsigned long long mix[2]; int64_t unused; int bad, unused2; } head = {{0, 0}, 0, 0, 0}, back;
+        struct { unsigned long long mix[2]; int bad, pad; } head = {{0, 0}, 0, 0}, back;
         const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)ntiles * sizeof(int32_t);
         char* tmp = nullptr;
         if (hipMalloc(&tmp, bytes) != hipSuccess) {
@@ -332,7 +389,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             return SPP_E_OOM;
         }
         unsigned long long* mix = reinterpret_cast<unsigned long long*>(tmp);
-        int* d_bad = reinterpret_cast<int*>(tmp + 3 * sizeof(int64_t));
+        int* d_bad = reinterpret_cast<int*>(mix + 2);
         uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(head));
         int* partial = reinterpret_cast<int*>(hist + nhist);
         int32_t* tile_row = partial + scan_grid;
@@ -344,10 +401,11 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(M, g->col, rbits, (int)nrb, ntiles, hist);
             grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
             auto place = [&](auto kernel) {
-                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge, mix);
+                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge);
             };
             if (nrb <= 256) place(part_place_kernel<8>); else place(part_place_kernel<9>);
             part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first);
+            csr_mix_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(N, M, g->rowptr, g->col, tile_row, mix, d_bad);
             const int64_t want = ((int64_t)ctx->num_cu * 8 + nrb - 1) / nrb;
             const int parts = (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
             tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
