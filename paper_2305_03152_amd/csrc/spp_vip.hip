@@ -25,6 +25,7 @@
 // size back cost the host 35 to 60 us per hop, with nothing queued behind it).
 #include "spp_common.h"
 #include "spp_device.h"
+#include "spp_fp64.h"
 
 namespace spp {
 
@@ -46,66 +47,6 @@ struct VipHop {
     int            last;
     unsigned long long* stat;  // per workgroup: vertices and out-edges of the next hop's frontier (unused at the last hop)
 };
-
-// 1 - e^s and log(1 - x) in fp64, to 2 and 4 units in the last place (the library's routines give 1 and
-// take some 300 instructions for the two and a division, which set the pace of the passes that
-// finish vertices: 106 and 181 us for the first two hops on 14M vertices, 70 and 131 with these).  The results are
-// rounded to fp32 afterwards.  s <= 0: e^s = 2^k e^r, |r| <= ln2 / 2, the Taylor series of e^r - 1 up to
-// r^13.  0 <= x <= 1: log(2^e m) = e ln2 + 2 atanh(f / (2 + f)), m = 1 + f between sqrt(1/2) and sqrt(2),
-// the series of atanh up to the 21st power; f = -x itself where e = 0, so that small x lose nothing.
-constexpr double kLn2Hi = 0x1.62e42fefa39efp-1, kLn2Lo = 0x1.abc9e3b39803fp-56;
-__device__ __forceinline__ double one_minus_exp(double s) {
-    s = fmax(s, -64.0);                          // 1 - e^-64 rounds to 1
-    const double k = rint(s * 1.4426950408889634);
-    const double r = fma(-k, kLn2Lo, fma(-k, kLn2Hi, s));
-    double p = 1.0 / 6227020800.0;
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(r * r, p, r);
-    const double e = ldexp(1.0, (int)k);
-    return fma(-e, p, 1.0 - e);
-}
-// num / den for normal den: a reciprocal refined twice, the quotient once
-__device__ __forceinline__ double quotient(double num, double den) {
-    double r = __builtin_amdgcn_rcp(den);
-    r = fma(fma(-den, r, 1.0), r, r);
-    r = fma(fma(-den, r, 1.0), r, r);
-    const double q = num * r;
-    return fma(fma(-den, q, num), r, q);
-}
-__device__ __forceinline__ double log1p_neg(double x) {
-    const double w = 1.0 - x;
-    const bool near_one = x < 0.2928;
-    double m = __builtin_amdgcn_frexp_mant(w);
-    int ex = __builtin_amdgcn_frexp_exp(w);
-    const bool low = m < 0.70710678;
-    m = low ? 2.0 * m : m;
-    ex -= low ? 1 : 0;
-    const double f = near_one ? -x : m - 1.0, e = near_one ? 0.0 : (double)ex;
-    const double s = quotient(f, 2.0 + f), z = s * s;
-    double p = 1.0 / 21.0;
-    p = fma(p, z, 1.0 / 19.0);
-    p = fma(p, z, 1.0 / 17.0);
-    p = fma(p, z, 1.0 / 15.0);
-    p = fma(p, z, 1.0 / 13.0);
-    p = fma(p, z, 1.0 / 11.0);
-    p = fma(p, z, 1.0 / 9.0);
-    p = fma(p, z, 1.0 / 7.0);
-    p = fma(p, z, 1.0 / 5.0);
-    p = fma(p, z, 1.0 / 3.0);
-    const double t = 2.0 * s;
-    const double l = fma(e, kLn2Hi, fma(e, kLn2Lo, fma(t * z, p, t)));
-    return x >= 1.0 ? -__builtin_inf() : l;
-}
 
 // Finishes vertices u, u + step, ... (U of them, those below N).  S = their sums, told = their running totals (ignored
 // at a first hop).  The loads and the chains of arithmetic of the U vertices are independent.
@@ -154,7 +95,7 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const double dd = (double)d[k];
-            const double t = dd <= a.f_next ? 1.0 : quotient(a.f_next, dd);
+            const double t = dd <= a.f_next ? 1.0 : small_quotient(a.f_next, dd);
             if (d[k] > 0) yn[k] = (float)log1p_neg(t * ph[k]);
             if (yn[k] != 0.0f) { ++verts; edges += (unsigned long long)d[k]; }
         }
@@ -1146,7 +1087,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* 
 }
 
 // Sums a row block's entries in LDS and finishes its vertices.  Bound by the finishing arithmetic of 16
-// wavefronts per CU (the sums take the LDS): 14M vertices, 131 us with 13.4M entries, 70 with 0.8M, where the
+// wavefronts per CU (the sums take the LDS): 14M vertices, 133 us with 13.4M entries, 85 with 0.8M, where the
 // bytes take 62 and 27.
 __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, const uint2* __restrict__ bins,
                                                                     const uint32_t* __restrict__ base, int64_t N,
