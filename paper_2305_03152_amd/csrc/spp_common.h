@@ -119,6 +119,8 @@ struct spp_ctx {
     int         sample_flags_clean = 0; // the flags of the next call have been cleared on the stream
     spp::DevBuf hopsums;                // fanout sampling: sums per 256 targets and per granule of edges, all zero between calls
     int         hopsums_clean = 0;      // they are
+    spp::DevBuf hoptab;                 // fanout sampling: id tables of hops too large for LDS, all ones between calls
+    int         hoptab_clean = 0;       // they are
     // gather workspaces
     // two sets, used alternately: the classification of a call may run while the miss copy of the
     // call before still reads its own set

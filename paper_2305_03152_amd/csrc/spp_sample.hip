@@ -12,8 +12,8 @@
 //   5. src of a repeated id = its index in S_{h-1}, or the src of its first appearance
 // Step 3 is where the ids meet.  With fanouts they meet in LDS (the hop_* kernels below: three
 // launches per hop, one after the last hop).  The other form keeps a table in global memory (open
-// addressing, 64-bit entries, six launches per hop: two per prefix sum); it is bound by the rate of
-// global atomics, about 16 G/s, and serves the sampler with given probabilities, whose sizes no
+// addressing, 64-bit entries, six launches per hop: two per prefix sum), as do fanout sampling's hops above
+// kHopLdsKeys ids; it is bound by the rate of global atomics, about 16 G/s, and serves the sampler with given probabilities, whose sizes no
 // fanout bounds, calls that ask for it (SPP_SAMPLE_GLOBAL_TABLE) and calls whose edge bounds would make
 // the LDS form's workspace the larger one by far.  Its table is right-sized per hop on the device: once
 // e_h is known, the hop uses the first 2^k >= 2 (n_{h-1} + e_h) slots of the minibatch's region, clears
@@ -172,12 +172,12 @@ struct CountOut {
     __device__ void operator()(int j, int64_t i, int ex, int, int) const { t->b[j].indptr[a.h - 1][i] = ex; }
 };
 // This hop's table: the smallest power of two >= 2 (n_{h-1} + e_h), at least 1024 slots, never more
-// than the region (the host sized it for the bound, which dominates).
-__device__ __forceinline__ void hop_table(const SampleArgs& a, int64_t n_prev, int e_h, uint32_t& capj, int& shift) {
+// than the region's `cap` slots (the host sized it for the bound, which dominates).
+__device__ __forceinline__ void hop_table(int64_t cap, int64_t n_prev, int e_h, uint32_t& capj, int& shift) {
     const uint64_t want = 2ull * (uint64_t)(n_prev + (int64_t)(uint32_t)e_h);
     capj = 1024;
     shift = 22;
-    while (capj < want && (int64_t)capj < a.cap) { capj <<= 1; --shift; }
+    while (capj < want && (int64_t)capj < cap) { capj <<= 1; --shift; }
 }
 struct CountFin {
     SampleArgs a; const BatchTable* t;
@@ -194,7 +194,7 @@ struct CountFin {
         atomicAdd(&a.totals[2], (unsigned long long)(uint32_t)total);
         uint32_t capj;
         int shift;
-        hop_table(a, c[a.h - 1], total, capj, shift);
+        hop_table(a.cap, c[a.h - 1], total, capj, shift);
         t->b[j].tinfo[0] = capj - 1;
         t->b[j].tinfo[1] = (uint32_t)shift;
     }
@@ -211,7 +211,7 @@ struct TableClear {
         unsigned long long* tab = tab_of(a, j);
         uint32_t capj;
         int shift;
-        hop_table(a, t->b[j].counts[a.h - 1], total, capj, shift);
+        hop_table(a.cap, t->b[j].counts[a.h - 1], total, capj, shift);
         const int64_t stride = (int64_t)gx * kBlock;
         for (int64_t i = (int64_t)x * kBlock + threadIdx.x; i < (int64_t)capj; i += stride) tab[i] = ~0ull;
     }
@@ -308,8 +308,9 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a, const Batc
 // Here
 //   hop_sample_kernel  draws a tile's subsets and leaves the tile's ids already dealt to the
 //                      partitions: a run of (id, position) entries per tile, ordered by partition;
-//   hop_dedup_kernel   walks only the runs of its own partition, whatever the hop's size, and marks the
-//                      entries that repeat an id in place (nothing is scattered by edge);
+//   hop_dedup_kernel   walks only the runs of its own partition and marks the entries that repeat an id in
+//                      place (nothing is scattered by edge); above kHopLdsKeys ids it offers the entries to a
+//                      table in global memory instead, and hop_resolve_kernel marks the repeats;
 //   hop_number_kernel  puts a tile's entries back in edge order in LDS and numbers the first appearances.
 // No launch is spent on prefix sums and nothing ever waits for another workgroup: the sums that a
 // workgroup needs (edges of the targets before its tile, new vertices before its tile) are kept per 256
@@ -320,12 +321,17 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a, const Batc
 // graph (hops of a million ids) 0.86 -> 0.45 ms.
 constexpr int kHopTargets = 256;                 // most targets of a tile, and targets per kept edge sum
 constexpr int kHopEdges = 4096;                  // most edges of a tile
-constexpr int kHopSlots = 8192;                  // slots of a partition's table (64 KB of LDS: two workgroups per CU)
+constexpr int kHopSlots = 8192;                  // slots of a partition's table (64 KB of LDS)
 constexpr int kHopSlotBits = 13;
 constexpr int kHopPartKeys = 7168;               // ids a partition may hold on average, by the hop's bound
 constexpr int kHopMaxPartsLog2 = 8;
 constexpr int kHopGranules = 1024;               // most granules (runs of tiles, one tile as a rule) per hop
 constexpr uint32_t kRepeat = 0x80000000u;        // marks a repeat in an entry's upper half, above the position it repeats
+// Hops above this many ids meet in a table in global memory after all: a partition then has more entries than a
+// workgroup's lanes keep in registers and would be walked twice, 2^(r + 1) times where its ids have to be taken in 2^r
+// parts.  One hop in one minibatch, us in LDS / through the table: 0.5M ids 50 / 83, 1M 64 / 116, 2M 251 / 197,
+// 4M 672 / 359, 8M 1818 / 684, 32M 8704 / 2767.
+constexpr int64_t kHopLdsKeys = (int64_t)kHopPartKeys << kHopMaxPartsLog2;
 constexpr int kDedupBlock = 1024;
 constexpr int kDirectSeeds = 4096;               // up to this many seeds, hop 1 sums the seeds before a tile itself
 
@@ -345,6 +351,8 @@ struct HopArgs {
     uint32_t*      csum;                // per minibatch two arrays of `csum_stride`, used by odd and even hops: edges of the
     int64_t        csum_stride;         //   hop per 256 targets; all zero between calls
     uint32_t*      fsum;                // per minibatch kHopGranules: first appearances per granule of tiles; all zero between calls
+    unsigned long long* tab;            // per minibatch `tab_cap` slots of the id table of hops above kHopLdsKeys ids, all ones
+    int64_t        tab_cap;             //   between such hops; null where the hop's bound is not above
     unsigned long long* totals;
     int*           bad;
     int*           bad_next;
@@ -379,6 +387,20 @@ __host__ __device__ __forceinline__ int hop_granule_log2(uint32_t ntiles) {
     int g = 0;
     while ((ntiles >> g) >= (uint32_t)kHopGranules) ++g;
     return g;
+}
+
+// The hop's table in global memory, if that is where its ids meet.
+struct HopTable {
+    unsigned long long* tab = nullptr;
+    uint32_t slots = 0;
+    int      shift = 0;
+};
+__device__ __forceinline__ HopTable hop_table_of(const HopArgs& a, int j, uint32_t n_prev, uint32_t e_h) {
+    HopTable t;
+    if (a.tab == nullptr || (int64_t)n_prev + e_h <= kHopLdsKeys) return t;
+    t.tab = a.tab + (int64_t)j * a.tab_cap;
+    hop_table(a.tab_cap, n_prev, (int)e_h, t.slots, t.shift);
+    return t;
 }
 
 // The seeds of a call: hop 1 takes them from its argument block.
@@ -711,6 +733,12 @@ __global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const
     const int gshift = hop_granule_log2(ntiles);
     const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
     uint64_t* ent = a.ent + (int64_t)jb * a.ent_stride;
+    const HopTable ht = hop_table_of(a, jb, n_prev, e_h);
+    if (ht.tab) {                                // resolved by the launch that follows
+        for (uint32_t i = blockIdx.y * kDedupBlock + threadIdx.x; i < n_prev + e_h; i += gridDim.y * kDedupBlock)
+            (void)table_insert_min(ht.tab, ht.slots - 1, ht.shift, (uint32_t)(ent[i] >> 32), (uint32_t)ent[i]);
+        return;
+    }
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     auto resolve = [&](uint32_t at, uint32_t tile, uint32_t pos, int slot) {
         if (pos < n_prev) return;
@@ -841,6 +869,39 @@ __global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const
 }
 static_assert(kHopGranules <= kDedupBlock, "one granule per thread");
 
+// The hops whose ids met in the table in global memory: every edge takes the smallest position of its id, a granule of
+// tiles at a time.  Launched only where the hop's bound allows such a hop; leaves at once where it is none.
+__global__ void __launch_bounds__(kBlock) hop_resolve_kernel(HopArgs a, const BatchTable* __restrict__ t) {
+    __shared__ int lds[4];
+    const BatchBlock bb = batch_block();
+    const int jb = bb.j;
+    const BatchDesc& b = t->b[jb];
+    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1], e_h = (uint32_t)b.counts[kE + a.h];
+    const HopTable ht = hop_table_of(a, jb, n_prev, e_h);
+    if (ht.tab == nullptr) return;
+    const uint32_t T = (uint32_t)hop_tile_targets(n_prev, a.n_items, a.f), ntiles = (n_prev + T - 1) / T;      // n_prev > 0 here
+    const int gshift = hop_granule_log2(ntiles);
+    const uint32_t ngran = (ntiles + (1u << gshift) - 1) >> gshift;
+    const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
+    uint64_t* ent = a.ent + (int64_t)jb * a.ent_stride;
+    for (uint32_t g = bb.x; g < ngran; g += gridDim.x) {
+        // the entries of consecutive tiles lie end to end
+        const uint32_t i0 = (g << gshift) * T, i1 = (uint64_t)((g + 1) << gshift) * T < n_prev ? ((g + 1) << gshift) * T : n_prev;
+        const uint32_t x0 = (uint32_t)indptr[i0] + i0, x1 = (uint32_t)indptr[i1] + i1;
+        int firsts = 0;
+        for (uint32_t x = x0 + threadIdx.x; x < x1; x += kBlock) {
+            const uint64_t e = ent[x];
+            uint32_t first = 0;
+            if ((uint32_t)e < n_prev) continue;
+            (void)table_find(ht.tab, ht.slots - 1, ht.shift, (uint32_t)(e >> 32), first);      // it is there
+            if (first == (uint32_t)e) ++firsts;
+            else reinterpret_cast<uint32_t*>(ent + x)[1] = kRepeat | first;
+        }
+        const int all = block_reduce_sum(firsts, lds);
+        if (threadIdx.x == 0) a.fsum[(int64_t)jb * kHopGranules + g] = (uint32_t)all;
+    }
+}
+
 // Numbers the first appearances, a granule of tiles at a time: a tile's entries go back to edge order
 // through LDS, the new vertices are appended to S_h in order, and the row of a vertex that will be a
 // target of the next hop is looked up here, once.
@@ -863,6 +924,12 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
     int32_t* __restrict__ src = b.src[a.h - 1];
     int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
     int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
+    {
+        const HopTable ht = hop_table_of(a, jb, n_prev, (uint32_t)b.counts[kE + a.h]);         // has served
+        typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+        for (uint32_t i = bb.x * kBlock + threadIdx.x; i < ht.slots / 2; i += gridDim.x * kBlock)
+            reinterpret_cast<u64x2*>(ht.tab)[i] = u64x2{~0ull, ~0ull};
+    }
     for (uint32_t g = bb.x; g < ngran; g += gridDim.x) {
         int before = 0;
         for (uint32_t i = threadIdx.x; i < g; i += kBlock) before = uadd(before, (int)fsum[i]);
@@ -1219,8 +1286,8 @@ __global__ void __launch_bounds__(kBlock) batch_table_store_kernel(BatchTableChu
     uint64_t* d = reinterpret_cast<uint64_t*>(&dst->b[first]);
     for (unsigned i = threadIdx.x; i < sizeof(BatchTableChunk) / sizeof(uint64_t); i += kBlock) d[i] = s[i];
 }
-__global__ void __launch_bounds__(kBlock) hop_sums_clear_kernel(uint32_t* p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = 0u;
+__global__ void __launch_bounds__(kBlock) hop_fill_kernel(uint32_t* p, int64_t n, uint32_t v) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = v;
 }
 // [0] error flag, [1] capacity flag of a call
 __global__ void sample_flags_clear_kernel(int* bad) {
@@ -1249,9 +1316,15 @@ extern "C" int spp_mfg_bound(int32_t nseeds, const int32_t* fanouts, int32_t L, 
     return SPP_OK;
 }
 
-// The launches of a fanout-sampling call: three per hop and one after the last (the call on hops of a few
+// Most ids that hop h and S_{h-1} can have.
+static int64_t hop_bound(const int64_t* nb, const int64_t* eb, int h, int64_t g_edges) {
+    return nb[h - 1] + (eb[h] < g_edges ? eb[h] : g_edges);
+}
+
+// The launches of a fanout-sampling call: three per hop (a fourth where a hop's bound exceeds kHopLdsKeys ids) and one after the last (the call on hops of a few
 // thousand edges takes 0.09 ms instead of 0.14 with six per hop).
-static void launch_hops(spp_ctx* ctx, spp::HopArgs a, spp::BatchTable* dt, const spp::BatchDynAll& dyn, const int32_t* fanouts,
+// `g_edges`: edges of the graph, which a hop's distinct targets cannot exceed.
+static void launch_hops(spp_ctx* ctx, spp::HopArgs a, int64_t g_edges, spp::BatchTable* dt, const spp::BatchDynAll& dyn, const int32_t* fanouts,
                         const int64_t* nb, const int64_t* eb, int max_seeds, size_t dedup_lds, hipStream_t st) {
     using namespace spp;
     // workgroups per minibatch: what the bound needs, eight per CU in the whole call at most (they take
@@ -1262,7 +1335,9 @@ static void launch_hops(spp_ctx* ctx, spp::HopArgs a, spp::BatchTable* dt, const
         return dim3((unsigned)((g + 7) & ~(int64_t)7), (unsigned)a.n_items);
     };
     const bool direct = max_seeds <= kDirectSeeds;
+    unsigned long long* const tab = a.tab;
     for (int h = 1; h <= a.L; ++h) {
+        a.tab = hop_bound(nb, eb, h, g_edges) > kHopLdsKeys ? tab : nullptr;
         a.h = h; a.f = fanouts[h - 1]; a.f_next = h < a.L ? fanouts[h] : 0;
         if (h == 1 && !direct) hop_seeds_kernel<<<grid((max_seeds + kHopTargets - 1) / kHopTargets), kBlock, 0, st>>>(a, dt, dyn);
         const int64_t tiles = std::max<int64_t>(std::min<int64_t>(1024 / a.n_items, nb[h - 1] / 16), nb[h - 1] / hop_tile_cap(a.f)) + 1;
@@ -1277,10 +1352,11 @@ static void launch_hops(spp_ctx* ctx, spp::HopArgs a, spp::BatchTable* dt, const
             }
         };
         if (h == 1 && direct) sample(SeedsArg{dyn}); else sample(NoSeedsArg{});
-        // as many partitions as the bound has, two workgroups per CU twice over at most
+        // as many partitions as the bound has, four workgroups per CU in the whole call at most
         const int64_t parts = (int64_t)1 << hop_parts_log2(nb[h - 1], a.n_items, a.f);
         const int64_t most = std::max<int64_t>(1, (int64_t)ctx->num_cu * 4 / a.n_items);
         hop_dedup_kernel<<<dim3((unsigned)a.n_items, (unsigned)std::min(parts, most)), kDedupBlock, dedup_lds, st>>>(a, dt);
+        if (a.tab) hop_resolve_kernel<<<grid(std::min<int64_t>(tiles, kHopGranules)), kBlock, 0, st>>>(a, dt);
         hop_number_kernel<<<grid(std::min<int64_t>(tiles, kHopGranules)), kBlock, 0, st>>>(a, dt);
     }
     hop_last_kernel<<<grid((eb[a.L] + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, dt);
@@ -1450,6 +1526,17 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
         ha.totals = reinterpret_cast<unsigned long long*>(ctx->totals); ha.bad = d_bad; ha.bad_next = d_bad_next;
         ha.mirror = (flags & SPP_SYNC) ? ctx->h_pinned + 64 : nullptr;       // kMaxBatches x 18 counts, then the flags
         ha.n_items = n_items; ha.L = L; ha.seed = seed;
+        // The table of the hops above kHopLdsKeys ids, where a bound allows one: as large as the other form's.  Without the
+        // memory for it such hops take their partitions in parts.
+        ha.tab = nullptr; ha.tab_cap = cap;
+        bool wide = false;
+        for (int h = 1; h <= L; ++h) wide = wide || hop_bound(nb, eb, h, g->M) > kHopLdsKeys;
+        if (wide) {
+            const size_t bytes = (size_t)cap * sizeof(uint64_t) * n_items;
+            if (ctx->hoptab.bytes < bytes) ctx->hoptab_clean = 0;
+            if (ctx->hoptab.reserve(bytes) == SPP_OK) ha.tab = ctx->hoptab.as<unsigned long long>();
+            else (void)hipGetLastError();
+        }
     }
     a.totals = reinterpret_cast<unsigned long long*>(ctx->totals); a.bad = d_bad; a.ovf = d_bad + 1; a.bad_next = d_bad_next;
     a.L = L; a.h = 0; a.f = 0; a.seed = seed;
@@ -1475,10 +1562,14 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
         }
         if (in_lds) {
             if (!ctx->hopsums_clean)
-                hop_sums_clear_kernel<<<ctx->num_cu, kBlock, 0, st>>>(ctx->hopsums.as<uint32_t>(), (int64_t)(ctx->hopsums.bytes / sizeof(uint32_t)));
+                hop_fill_kernel<<<ctx->num_cu, kBlock, 0, st>>>(ctx->hopsums.as<uint32_t>(), (int64_t)(ctx->hopsums.bytes / sizeof(uint32_t)), 0u);
+            if (ha.tab && !ctx->hoptab_clean)
+                hop_fill_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(ctx->hoptab.as<uint32_t>(), (int64_t)(ctx->hoptab.bytes / sizeof(uint32_t)), ~0u);
             ctx->hopsums_clean = 0;         // set again once this call's last kernel is enqueued
-            launch_hops(ctx, ha, dt, dyn, fanouts, nb, eb, max_seeds, dedup_lds, st);
+            if (ha.tab) ctx->hoptab_clean = 0;
+            launch_hops(ctx, ha, g->M, dt, dyn, fanouts, nb, eb, max_seeds, dedup_lds, st);
             ctx->hopsums_clean = 1;
+            if (ha.tab) ctx->hoptab_clean = 1;
         } else {
             seeds_kernel<<<dim3(capped((max_seeds + kBlock - 1) / kBlock, 1 << 20), n_items), kBlock, 0, st>>>(a, dt, dyn);
         }
