@@ -1558,7 +1558,6 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
                 batch_table_store_kernel<<<1, kBlock, 0, st>>>(chunk, dt, first);
             }
             memcpy(&mirror[slot], &ht, sizeof(BatchTable));
-            ctx->btab_n[slot] = n_items;
         }
         if (in_lds) {
             if (!ctx->hopsums_clean)
@@ -1568,8 +1567,6 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
             ctx->hopsums_clean = 0;         // set again once this call's last kernel is enqueued
             if (ha.tab) ctx->hoptab_clean = 0;
             launch_hops(ctx, ha, g->M, dt, dyn, fanouts, nb, eb, max_seeds, dedup_lds, st);
-            ctx->hopsums_clean = 1;
-            if (ha.tab) ctx->hoptab_clean = 1;
         } else {
             seeds_kernel<<<dim3(capped((max_seeds + kBlock - 1) / kBlock, 1 << 20), n_items), kBlock, 0, st>>>(a, dt, dyn);
         }
@@ -1594,9 +1591,13 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
             grid_scan_batched_two(st, scan_grid, n_items, NewIn{a, dt}, NewInKept{a, dt}, NewOut{a, dt}, NewFin{a, dt}, partial);
             relabel_kernel<<<dim3(capped((eb[h] + kBlock - 1) / kBlock, share), n_items), kBlock, 0, st>>>(a, dt);
         }
-        ctx->sample_flags_clean = 1;
     }
     SPP_HIP(hipGetLastError());
+    // what the launches leave behind for the next call, now that all of them have been accepted
+    ctx->btab_n[slot] = n_items;
+    ctx->sample_flags_clean = 1;
+    if (in_lds) ctx->hopsums_clean = 1;
+    if (in_lds && ha.tab) ctx->hoptab_clean = 1;
     if (flags & SPP_SYNC) {
         int64_t* hp = ctx->h_pinned + 64;            // kMaxBatches x 18 counts, then the flags
         if (!in_lds) {                               // else the last hop's numbering has stored them there

@@ -95,3 +95,14 @@ def test_seeds_that_are_not_distinct(bad, fanouts, global_table):
     ref = oracle.sample_mfg(rp, col, good[:40].copy(), fanouts, SEED, 9)
     assert out.n == ref.n and np.array_equal(out.node_ids[:out.n[-1]].cpu().numpy(), ref.node_ids)
     ctx.close()
+
+
+def test_what_a_call_leaves_counts_only_once_its_launches_are_accepted():
+    """A refused launch cannot be produced on purpose; the order in the source is what a later call relies on."""
+    import os
+    text = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2305_03152_amd", "csrc",
+                             "spp_sample.hip")).read()
+    body = text[text.index("static int sample_batches("):]
+    accepted = body.index("SPP_HIP(hipGetLastError());")
+    for mark in ("hopsums_clean = 1", "hoptab_clean = 1", "sample_flags_clean = 1", "btab_n[slot] = n_items"):
+        assert body.index(mark) > accepted, mark
