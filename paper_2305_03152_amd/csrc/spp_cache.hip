@@ -33,8 +33,9 @@ __device__ __forceinline__ uint32_t candidate_bits(const RankArgs& a, int64_t u)
     return s > 0.0f ? __float_as_uint(s) : 0u;
 }
 // The smallest score bits that are kept, as far as the first `passes` histograms decide them: the digit of
-// each pass is the largest bin from which on upward there are enough candidates.  0 if all candidates
-// together are too few.  All threads of a workgroup of 256; `lds` holds 4 ints and `pick` 3 words.
+// each pass is the largest bin from which on upward there are enough candidates.  kTooFew if all candidates
+// together are.  All threads of a workgroup of 256; `lds` holds 4 ints and `pick` 2 words.
+constexpr uint32_t kTooFew = 0xFFFFFFFFu;            // not the bits of a positive score
 __device__ __forceinline__ uint32_t kept_from(const RankArgs& a, int passes, int* lds, unsigned long long* pick) {
     uint64_t want = a.C;
     uint32_t bits = 0;
@@ -47,7 +48,7 @@ __device__ __forceinline__ uint32_t kept_from(const RankArgs& a, int passes, int
         for (int i = 0; i < per; ++i) mine += h[nb - 1 - (int)threadIdx.x * per - i];
         int all;
         uint32_t above = (uint32_t)block_exclusive_scan((int)mine, lds, all);
-        if ((uint64_t)(uint32_t)all < want) return 0u;           // only possible at the first pass
+        if ((uint64_t)(uint32_t)all < want) return kTooFew;      // only possible at the first pass
         if (above < want && above + (uint64_t)mine >= want)      // one thread
             for (int i = 0; i < per; ++i) {
                 const int bin = nb - 1 - (int)threadIdx.x * per - i;
@@ -70,7 +71,7 @@ __global__ void __launch_bounds__(kBlock) rank_hist_kernel(RankArgs a, int pass)
     for (int i = threadIdx.x; i < 2 * 2048; i += kBlock) (&h[0][0])[i] = 0u;
     const uint32_t from = kept_from(a, pass, lds, pick);         // ends with barriers
     if (pass == 0) __syncthreads();
-    if (pass > 0 && from == 0u) return;          // every candidate is kept: nothing to narrow down
+    if (pass > 0 && from == kTooFew) return;          // every candidate is kept: nothing to narrow down
     const int above = pass == 0 ? 32 : kRankShift[pass - 1];     // the bits decided so far must agree
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     constexpr int U = 4;
@@ -94,7 +95,7 @@ __global__ void __launch_bounds__(kBlock) rank_threshold_kernel(RankArgs a, uint
     __shared__ int lds[4];
     __shared__ unsigned long long pick[2];
     const uint32_t bits = kept_from(a, 3, lds, pick);
-    if (threadIdx.x == 0) *from = bits ? bits : 1u;
+    if (threadIdx.x == 0) *from = bits == kTooFew ? 1u : bits;
 }
 struct CandIn {
     RankArgs a; const uint32_t* from;
