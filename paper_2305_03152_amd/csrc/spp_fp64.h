@@ -6,7 +6,7 @@
 // (sums and products whose error is recovered exactly: Dekker, Numer. Math. 18, 1971), so that little more than the
 // final rounding is left.  Largest errors over 4M points against 113-bit arithmetic on gfx950, in units in the last place:
 // 0.71 and 0.56, the library's expm1 and log1p 1.13 and 0.65.  The passes that finish the vertices of a 14M-vertex
-// graph after its first two hops: 106 and 181 us with the library's, 85 and 133 with these, 70 and 131 with the same series
+// graph after its first two hops: 106 and 181 us with the library's, 84 and 131 with these, 70 and 131 with the same series
 // summed plainly (1.2 and 2.9 units).
 #ifndef SPP_FP64_H
 #define SPP_FP64_H

@@ -37,7 +37,6 @@ constexpr uint32_t kPushed = 1, kPulled = 2;
 
 struct VipHop {
     const int64_t* rowptr;     // forward CSR, for d(u)
-    const float*   y;          // this hop's y
     float*         y_next;     // next hop's y (unused at the last hop)
     double*        tot;        // running sum of S over hops
     float*         p_hop;      // p^[h] or null
@@ -45,14 +44,14 @@ struct VipHop {
     double         f_next;     // f_{h+1}
     int            first;      // first hop and hop 0 not included: tot is not read
     int            last;
-    unsigned long long* stat;  // per workgroup: vertices and out-edges of the next hop's frontier (unused at the last hop)
+    unsigned long long* stat;  // per workgroup: out-edges of its part of the next hop's frontier (unused at the last hop)
 };
 
 // Finishes vertices u, u + step, ... (U of them, those below N).  S = their sums, told = their running totals (ignored
 // at a first hop).  The loads and the chains of arithmetic of the U vertices are independent.
 template <int U>
 __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, int64_t step, int64_t N, const double (&S)[U],
-                                                    const double (&told)[U], unsigned long long& verts, unsigned long long& edges) {
+                                                    const double (&told)[U], unsigned long long& edges) {
     // A vertex that no frontier vertex points at has S = 0 exactly (most vertices, at the early hops):
     // its p^[h] is 0 and it needs no exponential; nor does p^[h] at the last hop when it is not asked for.
     double ph[U];
@@ -97,7 +96,7 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
             const double dd = (double)d[k];
             const double t = dd <= a.f_next ? 1.0 : small_quotient(a.f_next, dd);
             if (d[k] > 0) yn[k] = (float)log1p_neg(t * ph[k]);
-            if (yn[k] != 0.0f) { ++verts; edges += (unsigned long long)d[k]; }
+            if (yn[k] != 0.0f) edges += (unsigned long long)d[k];
         }
 #pragma unroll
     for (int k = 0; k < U; ++k)
@@ -111,8 +110,7 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
 // flight together (one vertex per round leaves a pass over 10^8 vertices waiting on its own loads:
 // 0.87 ms where the bytes take 0.55).  sum_of(u) = S_h(u).
 template <class SumOf>
-__device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf sum_of, unsigned long long& verts,
-                                               unsigned long long& edges) {
+__device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf sum_of, unsigned long long& edges) {
     constexpr int U = 4;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += U * stride) {
@@ -121,14 +119,14 @@ __device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf
         for (int k = 0; k < U; ++k) S[k] = u + k * stride < N ? sum_of(u + k * stride) : 0.0;
 #pragma unroll
         for (int k = 0; k < U; ++k) T0[k] = a.first || u + k * stride >= N ? 0.0 : a.tot[u + k * stride];
-        vip_finish_vertices<U>(a, u, stride, N, S, T0, verts, edges);
+        vip_finish_vertices<U>(a, u, stride, N, S, T0, edges);
     }
 }
 
 // The R vertices from u0 on whose sums a workgroup of 1024 threads holds in LDS.
 template <int R>
 __device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, int64_t N, const double* acc,
-                                                 unsigned long long& verts, unsigned long long& edges) {
+                                                 unsigned long long& edges) {
     constexpr int U = 4, kThreads = 1024;
     for (int i = threadIdx.x; i < R && u0 + i < N; i += U * kThreads) {
         double S[U], T0[U];
@@ -136,28 +134,24 @@ __device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, in
         for (int k = 0; k < U; ++k) S[k] = acc[i + k * kThreads];
 #pragma unroll
         for (int k = 0; k < U; ++k) T0[k] = a.first || u0 + i + k * kThreads >= N ? 0.0 : a.tot[u0 + i + k * kThreads];
-        vip_finish_vertices<U>(a, u0 + i, kThreads, N, S, T0, verts, edges);
+        vip_finish_vertices<U>(a, u0 + i, kThreads, N, S, T0, edges);
     }
 }
 
-// The next hop is pushed or pulled depending on the size of its frontier (vertices with y != 0 and
-// their out-edges); the kernel that writes the next hop's y counts both on the way, one pair per
-// workgroup (no atomics: same-address atomics cost about 15 ns each), and vip_decide_kernel adds the pairs.
+// The next hop is pushed or pulled depending on the out-edges of its frontier (the vertices with y != 0); the
+// kernel that writes the next hop's y counts them on the way, one sum per workgroup (no atomics: same-address
+// atomics cost about 15 ns each), and vip_decide_kernel adds the sums.
 template <int kThreads = kBlock>
-__device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long verts,
-                                                    unsigned long long edges) {
-    __shared__ unsigned long long red[2][kThreads / kWave];
+__device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long edges) {
+    __shared__ unsigned long long red[kThreads / kWave];
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        verts += __shfl_down((long long)verts, off, kWave);
-        edges += __shfl_down((long long)edges, off, kWave);
-    }
-    if (lane_id() == 0) { red[0][threadIdx.x >> 6] = verts; red[1][threadIdx.x >> 6] = edges; }
+    for (int off = kWave / 2; off > 0; off >>= 1) edges += __shfl_down((long long)edges, off, kWave);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = edges;
     __syncthreads();
-    if (threadIdx.x < 2) {
+    if (threadIdx.x == 0) {
         unsigned long long all = 0;
-        for (int w = 0; w < kThreads / kWave; ++w) all += red[threadIdx.x][w];
-        stat[2 * blockIdx.x + threadIdx.x] = all;
+        for (int w = 0; w < kThreads / kWave; ++w) all += red[w];
+        stat[blockIdx.x] = all;
     }
 }
 
@@ -285,7 +279,7 @@ __global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long 
                                                             int64_t* __restrict__ mirror, const int* __restrict__ bad) {
     __shared__ unsigned long long red[kBlock / kWave];
     unsigned long long edges = 0;
-    for (int i = threadIdx.x; i < nstat; i += kBlock) edges += stat[2 * i + 1];
+    for (int i = threadIdx.x; i < nstat; i += kBlock) edges += stat[i];
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) edges += __shfl_down((long long)edges, off, kWave);
     if (lane_id() == 0) red[threadIdx.x >> 6] = edges;
@@ -310,13 +304,13 @@ __global__ void __launch_bounds__(kBlock) vip_finish_kernel(VipHop a, const uint
     const bool push = *how == kPushed;
     if (!push && fused_pull) return;
     const int n = push ? 1 : parts;
-    unsigned long long verts = 0, edges = 0;
+    unsigned long long edges = 0;
     vip_finish_all(a, N, [&](int64_t u) {
         double S = acc[u];
         for (int j = 1; j < n; ++j) S += acc[(int64_t)j * part_stride + u];
         return S;
-    }, verts, edges);
-    if (!a.last && push) write_frontier_stat(a.stat, verts, edges);
+    }, edges);
+    if (!a.last && push) write_frontier_stat(a.stat, edges);
 }
 
 // Dense hops, blocked: one workgroup takes the j-th of `parts` shares of the edges that end in one
@@ -691,8 +685,8 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
     __syncthreads();
     const int64_t u0 = rb << kTileRowBits;
     if (parts == 1) {
-        unsigned long long verts = 0, edges = 0;
-        vip_finish_block<R>(a, u0, N, acc, verts, edges);
+        unsigned long long edges = 0;            // not asked for: the hop after a pulled one is pulled
+        vip_finish_block<R>(a, u0, N, acc, edges);
     } else {
         double* __restrict__ out = part + (int64_t)j * part_stride + u0;
         for (int i = threadIdx.x; i < R; i += kXBlock) out[i] = acc[i];
@@ -706,7 +700,7 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
                                                           float* __restrict__ y, double* __restrict__ tot, int include_hop0,
                                                           int* __restrict__ bad, unsigned long long* __restrict__ stat) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    unsigned long long verts = 0, edges = 0;
+    unsigned long long edges = 0;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nT; i += stride) {
         const int64_t v = T[i];
         if (v < 0 || v >= N) { *bad = 1; continue; }
@@ -716,11 +710,11 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
             if (t > 1.0) t = 1.0;
             const float yv = (float)log1p(-(t * p0));
             y[v] = yv;
-            if (yv != 0.0f) { ++verts; edges += (unsigned long long)d; }
+            if (yv != 0.0f) edges += (unsigned long long)d;
         }
         if (include_hop0) tot[v] = log1p(-p0);
     }
-    write_frontier_stat(stat, verts, edges);
+    write_frontier_stat(stat, edges);
 }
 
 // ---- Proposition 1 with arbitrary initial and transition probabilities (Sec. 3.1) -------------
@@ -1087,7 +1081,7 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* 
 }
 
 // Sums a row block's entries in LDS and finishes its vertices.  Bound by the finishing arithmetic of 16
-// wavefronts per CU (the sums take the LDS): 14M vertices, 133 us with 13.4M entries, 85 with 0.8M, where the
+// wavefronts per CU (the sums take the LDS): 14M vertices, 131 us with 13.4M entries, 84 with 0.8M, where the
 // bytes take 62 and 27.
 __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, const uint2* __restrict__ bins,
                                                                     const uint32_t* __restrict__ base, int64_t N,
@@ -1099,9 +1093,9 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
     __syncthreads();
     bin_add_entries(acc, bins, base[blockIdx.x], base[blockIdx.x + 1]);
     __syncthreads();
-    unsigned long long verts = 0, edges = 0;
-    vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, verts, edges);
-    if (!a.last) write_frontier_stat<kTileBlock>(a.stat, verts, edges);
+    unsigned long long edges = 0;
+    vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, edges);
+    if (!a.last) write_frontier_stat<kTileBlock>(a.stat, edges);
 }
 
 // log1p(-x) for 0 < x <= 1 to a few fp32 ulp.  All terms of a vertex's sum have one sign, so the
@@ -1397,15 +1391,15 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         SPP_TRY(ctx->xvals.reserve((size_t)(g->x_entries > 0 ? g->x_entries : 4) * sizeof(float)));
     }
     // the kernels that write a hop's y run this many workgroups; each leaves the size of the part of
-    // the next frontier it saw (at most kStatBlocks pairs, or one per row block)
+    // the next frontier it saw (at most kStatBlocks sums, or one per row block)
     const int fill_grid = ctx->num_cu * 8 < kStatBlocks ? ctx->num_cu * 8 : kStatBlocks;
     const size_t nstat_max = binned && g->nrb > kStatBlocks ? (size_t)g->nrb : (size_t)kStatBlocks;
     const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + 2 * nstat_max + SPP_MAX_L + 1) * sizeof(unsigned long long)));
+    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + nstat_max + SPP_MAX_L + 1) * sizeof(unsigned long long)));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));    // [2]: cursor of the list
     unsigned long long* fstat = fcount + 4;
-    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + 2 * nstat_max);      // [1 .. L]: how each hop is walked
+    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + nstat_max);      // [1 .. L]: how each hop is walked
     int64_t* mirror = ctx->h_pinned + kHopMirror;
     float* ycur = ctx->y0.as<float>();
     float* ynext = ctx->y1.as<float>();
@@ -1424,7 +1418,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
             VipHop a;
             a.rowptr = g->rowptr;
-            a.y = ycur; a.y_next = ynext; a.tot = tot;
+            a.y_next = ynext; a.tot = tot;
             a.p_hop = d_p_hop ? d_p_hop + (int64_t)(h - 1) * N : nullptr;
             a.p_total = d_p_total;
             a.f_next = h < L ? (double)fanouts[h] : 0.0;
