@@ -237,24 +237,29 @@ __global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const
 }
 
 // The sum of the mixes of the CSR's edges, each with the row that holds it: what the structure is compared with, found by
-// another way than the one that built it.  A wavefront takes a tile of edges at a time and holds the ends of 64 rows
-// in its lanes, among which an edge finds its own; the first rows are the tile's entry in tile_row[] if that row does
-// hold the tile's first edge (else the structure is bad), later ones follow or, after a long run of empty rows, are found
-// by bisection.  2.4M vertices, 121M edges: 194 us (271 with a bisection for every 2048 edges' first row and one among
-// the 64 rows for every edge).
+// another way than the one that built it.  A wavefront takes 2^piece_bits edges at a time (a tile, or less where the
+// graph has fewer tiles than the chip wavefronts) and holds the ends of 64 rows in its lanes, among which an edge finds its
+// own; the first row is sought from the tile's entry in tile_row[] on and must hold the first edge (else the structure
+// is bad), later ones follow or, after a long run of empty rows, are found by bisection.  2.4M vertices, 121M edges: 194 us
+// (271 with a bisection over all rows for every 2048 edges' first one and one among the 64 rows for every edge).
 __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
                                                          const int32_t* __restrict__ col, const int32_t* __restrict__ tile_row,
-                                                         unsigned long long* __restrict__ mix, int* __restrict__ bad) {
+                                                         int piece_bits, unsigned long long* __restrict__ mix, int* __restrict__ bad) {
     constexpr int U = 4;                         // batches of 64 edges in flight
     const int lane = lane_id();
     const int64_t wave = (int64_t)blockIdx.x * (kBlock / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
     unsigned long long sum = 0;
-    for (int64_t tile = wave; tile * kPartTile < M; tile += nwaves) {
-        const int64_t base = tile * kPartTile;
-        const uint32_t count = M - base < kPartTile ? (uint32_t)(M - base) : (uint32_t)kPartTile;
-        int64_t lo = tile_row[tile];
-        if (lo < 0 || lo >= N || rowptr[lo] > base || rowptr[lo + 1] <= base) { *bad = 1; continue; }
+    for (int64_t piece = wave; piece << piece_bits < M; piece += nwaves) {
+        const int64_t base = piece << piece_bits, tile = base / kPartTile;
+        const uint32_t count = M - base < (1ll << piece_bits) ? (uint32_t)(M - base) : 1u << piece_bits;
+        int64_t lo = tile_row[tile], up = base == tile * kPartTile ? lo : (tile + 1) * kPartTile < M ? tile_row[tile + 1] : N - 1;
+        if (lo < 0 || lo > up || up >= N) { *bad = 1; continue; }
+        while (lo < up) {
+            const int64_t mid = (lo + up + 1) >> 1;
+            if (rowptr[mid] <= base) lo = mid; else up = mid - 1;
+        }
+        if (rowptr[lo] > base || rowptr[lo + 1] <= base) { *bad = 1; continue; }
         uint32_t done = 0;
         while (done < count) {
             if (done > 0) {
@@ -266,7 +271,7 @@ __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, c
                     if (rowptr[mid] <= base + done) lo = mid; else hi = mid - 1;
                 }
             }
-            // rows lo .. lo + 63, as long as they hold edges of the tile
+            // rows lo .. lo + 63, as long as they hold edges of the piece
             for (bool more = true; more && done < count; lo += kWave) {
                 const int64_t end64 = (lo + 1 + lane <= N ? rowptr[lo + 1 + lane] : M) - base;
                 const uint32_t end = end64 < (int64_t)count ? (uint32_t)end64 : count;
@@ -405,7 +410,9 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             };
             if (nrb <= 256) place(part_place_kernel<8>); else place(part_place_kernel<9>);
             part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first);
-            csr_mix_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(N, M, g->rowptr, g->col, tile_row, mix, d_bad);
+            int piece_bits = 8;
+            while ((1 << piece_bits) < kPartTile && (M >> piece_bits) > (int64_t)ctx->num_cu * 8 * (kBlock / kWave)) ++piece_bits;
+            csr_mix_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(N, M, g->rowptr, g->col, tile_row, piece_bits, mix, d_bad);
             const int64_t want = ((int64_t)ctx->num_cu * 8 + nrb - 1) / nrb;
             const int parts = (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
             tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
