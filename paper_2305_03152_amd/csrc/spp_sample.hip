@@ -356,7 +356,8 @@ struct HopArgs {
     unsigned long long* totals;
     int*           bad;
     int*           bad_next;
-    int64_t*       mirror;              // pinned host memory for the counts and flags of a call that is waited for, or null
+    int64_t*       mirror;              // pinned host memory for the counts and flags of a call that is waited for, or null: 2 * kE counts per
+                                        //   minibatch, the call's two flags, one more per minibatch
     int            n_items;
     int            L, h, f, f_next;     // f_next: fanout of hop h + 1 (0 at the last hop)
     uint64_t       seed;
@@ -712,6 +713,8 @@ __device__ __forceinline__ int hop_find(const uint32_t* ids, uint32_t home, uint
 // 256 partitions of 7168 ids, or ids that share their hash's top bits) is taken in 2^r parts by the next
 // r bits of the hash; at 19 bits in all at most four ids of a part share a bucket, because the hash is
 // a bijection of 32-bit ids: any input fits.
+// kLarge: the hop's bound allows more than kHopLdsKeys ids.
+template <bool kLarge>
 __global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const BatchTable* __restrict__ t) {
     extern __shared__ __align__(16) uint32_t dedup_lds[];
     uint32_t* ids = dedup_lds;                                          // [kHopSlots]
@@ -733,11 +736,13 @@ __global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const
     const int gshift = hop_granule_log2(ntiles);
     const int32_t* __restrict__ indptr = b.indptr[a.h - 1];
     uint64_t* ent = a.ent + (int64_t)jb * a.ent_stride;
-    const HopTable ht = hop_table_of(a, jb, n_prev, e_h);
-    if (ht.tab) {                                // resolved by the launch that follows
-        for (uint32_t i = blockIdx.y * kDedupBlock + threadIdx.x; i < n_prev + e_h; i += gridDim.y * kDedupBlock)
-            (void)table_insert_min(ht.tab, ht.slots - 1, ht.shift, (uint32_t)(ent[i] >> 32), (uint32_t)ent[i]);
-        return;
+    if constexpr (kLarge) {
+        const HopTable ht = hop_table_of(a, jb, n_prev, e_h);
+        if (ht.tab) {                            // resolved by the launch that follows
+            for (uint32_t i = blockIdx.y * kDedupBlock + threadIdx.x; i < n_prev + e_h; i += gridDim.y * kDedupBlock)
+                (void)table_insert_min(ht.tab, ht.slots - 1, ht.shift, (uint32_t)(ent[i] >> 32), (uint32_t)ent[i]);
+            return;
+        }
     }
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     auto resolve = [&](uint32_t at, uint32_t tile, uint32_t pos, int slot) {
@@ -905,6 +910,7 @@ __global__ void __launch_bounds__(kBlock) hop_resolve_kernel(HopArgs a, const Ba
 // Numbers the first appearances, a granule of tiles at a time: a tile's entries go back to edge order
 // through LDS, the new vertices are appended to S_h in order, and the row of a vertex that will be a
 // target of the next hop is looked up here, once.
+template <bool kLarge>
 __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const BatchTable* __restrict__ t) {
     __shared__ uint32_t what[kHopEdges];         // per edge of the tile: the upper half of its entry
     __shared__ int scan_lds[4];
@@ -924,7 +930,7 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
     int32_t* __restrict__ src = b.src[a.h - 1];
     int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
     int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
-    {
+    if constexpr (kLarge) {
         const HopTable ht = hop_table_of(a, jb, n_prev, (uint32_t)b.counts[kE + a.h]);         // has served
         typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
         for (uint32_t i = bb.x * kBlock + threadIdx.x; i < ht.slots / 2; i += gridDim.x * kBlock)
@@ -999,7 +1005,8 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
             __syncthreads();                     // the next tile overwrites what[]
         }
         if (g == ngran - 1 && threadIdx.x == 0) {
-            if (id0 > id_cap) { atomicOr(a.bad, 4); id0 = id_cap; }
+            const bool over = id0 > id_cap;
+            if (over) { atomicOr(a.bad, 4); id0 = id_cap; }
             b.counts[a.h] = id0;
             if (a.h == a.L) {
                 atomicAdd(&a.totals[1], (unsigned long long)id0);
@@ -1007,22 +1014,23 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
                 if (a.mirror) {
                     int64_t* m = a.mirror + (int64_t)jb * 2 * kE;
                     for (int q = 0; q < 2 * kE; ++q) m[q] = q == a.h ? (int64_t)id0 : b.counts[q];
+                    // the flags so far, and this minibatch's own of the last hop (another's may come later)
+                    int* fl = reinterpret_cast<int*>(a.mirror + (int64_t)kMaxBatches * 2 * kE);
+                    if (jb == 0) { fl[0] = *a.bad; fl[1] = 0; }
+                    fl[2 + jb] = over ? 4 : 0;
                 }
             }
         }
     }
 }
 
-// After the last hop: its repeats, the error flags of a call that is waited for, and what the next call expects empty.
+// After the last hop: its repeats, and what the next call expects empty.
 __global__ void __launch_bounds__(kBlock) hop_last_kernel(HopArgs a, const BatchTable* __restrict__ t) {
     const BatchBlock bb = batch_block();
     if (bb.x == 0)
         for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)bb.j * kHopGranules + g] = 0u;
     relabel_repeats(t->b[bb.j], a.h, bb.x, gridDim.x);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) {
-        if (a.mirror) reinterpret_cast<int*>(a.mirror + (int64_t)kMaxBatches * 2 * kE)[threadIdx.x] = a.bad[threadIdx.x];
-        a.bad_next[threadIdx.x] = 0;
-    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.bad_next[threadIdx.x] = 0;
 }
 
 // ---- steps 1 and 2 with given transition probabilities ----
@@ -1355,9 +1363,15 @@ static void launch_hops(spp_ctx* ctx, spp::HopArgs a, int64_t g_edges, spp::Batc
         // as many partitions as the bound has, four workgroups per CU in the whole call at most
         const int64_t parts = (int64_t)1 << hop_parts_log2(nb[h - 1], a.n_items, a.f);
         const int64_t most = std::max<int64_t>(1, (int64_t)ctx->num_cu * 4 / a.n_items);
-        hop_dedup_kernel<<<dim3((unsigned)a.n_items, (unsigned)std::min(parts, most)), kDedupBlock, dedup_lds, st>>>(a, dt);
-        if (a.tab) hop_resolve_kernel<<<grid(std::min<int64_t>(tiles, kHopGranules)), kBlock, 0, st>>>(a, dt);
-        hop_number_kernel<<<grid(std::min<int64_t>(tiles, kHopGranules)), kBlock, 0, st>>>(a, dt);
+        const dim3 dgrid((unsigned)a.n_items, (unsigned)std::min(parts, most)), ngrid = grid(std::min<int64_t>(tiles, kHopGranules));
+        if (a.tab) {
+            hop_dedup_kernel<true><<<dgrid, kDedupBlock, dedup_lds, st>>>(a, dt);
+            hop_resolve_kernel<<<ngrid, kBlock, 0, st>>>(a, dt);
+            hop_number_kernel<true><<<ngrid, kBlock, 0, st>>>(a, dt);
+        } else {
+            hop_dedup_kernel<false><<<dgrid, kDedupBlock, dedup_lds, st>>>(a, dt);
+            hop_number_kernel<false><<<ngrid, kBlock, 0, st>>>(a, dt);
+        }
     }
     hop_last_kernel<<<grid((eb[a.L] + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, dt);
 }
@@ -1509,8 +1523,8 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
     HopArgs ha;
     if (in_lds) {
         if (!ctx->dedup_lds_set) {
-            SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&hop_dedup_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)dedup_lds));
+            for (const void* k : {reinterpret_cast<const void*>(&hop_dedup_kernel<false>), reinterpret_cast<const void*>(&hop_dedup_kernel<true>)})
+                SPP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dedup_lds));
             ctx->dedup_lds_set = 1;
         }
         ha.rowptr = g->rowptr; ha.col = g->col; ha.N = g->N;
@@ -1611,7 +1625,8 @@ static int sample_batches(spp_ctx* ctx, const spp_graph* g, const spp_sample_ite
                 items[j].io->n[k] = hp[j * 2 * kE + k];
                 items[j].io->e[k] = hp[j * 2 * kE + kE + k];
             }
-        const int* fl = reinterpret_cast<const int*>(hp + kMaxBatches * 2 * kE);
+        int* fl = reinterpret_cast<int*>(hp + kMaxBatches * 2 * kE);
+        for (int j = 0; in_lds && j < n_items; ++j) fl[0] |= fl[2 + j];
         SPP_CHECK((fl[0] & 1) == 0, SPP_E_ARG, "spp_sample_mfg: a seed lies outside [0, N)");
         SPP_CHECK((fl[0] & 4) == 0, SPP_E_ARG, "spp_sample_mfg: a minibatch reached more vertices than its bound: its seeds are not distinct");
         SPP_CHECK((fl[0] & 2) == 0, SPP_E_ARG, "spp_sample_mfg_general: a transition probability lies outside [0, 1]; it was taken as 0");
