@@ -30,10 +30,10 @@ PCIE_PEAK_GBS = 64.0           # PCIe Gen5 x16, one direction
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script, scaled by the
 # same counters on the library's plain copy kernel over 1 GiB (`--phase calibrate`); the summaries with
 # their commands are under profiles/.  Keyed by (workload, minibatches per gather launch); other shapes
-# report null.
+# report null.  The sampler's are of a full call: the profiled run's totals less its one small call.
 MEASURED_TRAFFIC = {
-    ("large", 64): {"gather_hit": 1.385e+09, "sampler_call": 5.496e+08, "vip_dense_hop": 4.836e+10},
-    ("mid", 64): {"gather_hit": 2.28e+09, "sampler_call": 6.45e+08, "vip_dense_hop": 8.23e+08},
+    ("large", 64): {"gather_hit": 1.385e+09, "sampler_call": 5.73e+08, "vip_dense_hop": 4.836e+10},
+    ("mid", 64): {"gather_hit": 2.28e+09, "sampler_call": 6.72e+08, "vip_dense_hop": 8.23e+08},
 }
 
 

@@ -89,8 +89,8 @@ int  spp_ctx_sync(spp_ctx* ctx);
 /* Wraps a device CSR (not copied; must outlive the handle).  With SPP_GRAPH_IN_LISTS it also
  * builds, once, the transposed structure (the edges v -> u grouped by blocks of destination
  * vertices u and sorted by v inside a block: who can sample u), which costs about
- * 4*M + N/64 bytes of device memory plus, while it is built, at most M/2 bytes of temporary space
- * (16*M bytes for graphs above 2^23 vertices).
+ * 4*M + N/64 bytes of device memory plus, while it is built, about (M/1024 + 4) * (N/16384 + 2) bytes and a few
+ * KB of temporary space: at most M/2 for large M (16*M bytes for graphs above 2^23 vertices).
  * Synchronous. */
 int  spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_t* d_rowptr,
                       const int32_t* d_col, uint32_t flags, spp_graph** out);

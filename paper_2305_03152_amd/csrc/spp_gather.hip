@@ -7,9 +7,10 @@
 //   hit copy  (main stream)  rows from the local shard or the replica cache, 128-bit vectors,
 //                            outputs walked in order so that stores are dense
 //   miss copy (side stream)  rows read straight from pinned host memory over PCIe (on CUs of
-//                            its own), started after the hit copy and joined before the call
-//                            ends, or (SPP_NO_JOIN) by the next gather, which classifies its own
-//                            ids in the meantime
+//                            its own), started before the hit copy and joined before the call
+//                            ends, or (SPP_NO_JOIN) started after it (unless SPP_HIT_BESIDE_MISS)
+//                            and joined by the next gather, which classifies its own ids in the
+//                            meantime
 // A vertex that several rows of one call miss (several minibatches of a pipeline sampling the same
 // remote vertex) is fetched once: after the classification a pass over the miss list claims every
 // missed vertex in a table that lives for the call (sized for the misses, so a few MB); the row

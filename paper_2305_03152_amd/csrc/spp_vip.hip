@@ -775,8 +775,10 @@ __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __rest
 // the edge its place among them, one global atomic per bin reserves their range, and the entries, held in
 // registers meanwhile, are stored.  2.4M vertices, 121M edges: 859 us per dense hop (900 with 256 threads
 // that counted a portion in one walk over col[] and stored its entries in a second), 252 and 47 for
-// the sparser hops before it (299 and 92).  What bounds it is the reserving: 15k atomics on each bin's counter at
-// 15 ns each, and the two barriers around them; bytes take 310 us, arithmetic 256.  (Rounds of 2048 edges:
+// the sparser hops before it (299 and 92).  Nothing is busy for half of the time (vector units 35 %, LDS 44 %, a third of
+// that bank conflicts; 2.3 GB of traffic, which a copy moves in 360 us): wavefronts wait three quarters of their clocks, for
+// their loads, for the round's reservations (15k atomics on each bin's counter) and at the barriers around those, and the
+// two workgroups of a CU do not fill each other's waits.  (Rounds of 2048 edges:
 // 0.9 ms of reserving alone; 4096 and 6144: 884, 852; more registers for half the wavefronts, 1096.  Sorting 2048
 // entries at a time by bin in LDS, so that neighbouring threads store neighbouring entries, was
 // slower: 1.2 ms; a thread taking 8 consecutive edges instead of a wavefront taking 64: 1.25 ms.)
@@ -1357,8 +1359,8 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     }
     // The push goes through bins where the chunked layout's value memory holds the entries (8 bytes for at most
     // M / kPushShare edges), the counts and the offsets, and a workgroup per row block fills the chip: graphs of
-    // 4.2M vertices and more.  On 14M vertices it takes 172 us for a first hop of 0.8M edges (atomics: 153 with
-    // the clearing and the finishing pass) and 443 for 13.4M (787).
+    // 4.2M vertices and more.  On 14M vertices it takes 396 us for a hop of 13.4M edges (atomics, with the clearing and
+    // the finishing pass: 773) and, as its launches cost what they cost, 156 for one of 0.8M (149).
     const size_t bin_entries = (size_t)(g->M / kPushShare) + 1;
     const size_t bin_words = (size_t)kPushGroups * (size_t)g->nrb + 2 * (size_t)g->nrb + 1;
     const bool binned = g->has_x && parts == 1 && g->nrb <= kBinMaxBlocks &&

@@ -27,7 +27,7 @@ def spp():
 # Every case runs twice: with the transposed edges in row blocks (graphs whose per-vertex vectors stay in
 # the caches) and the sampler's hops deduplicated in LDS (what these sizes get by default), and with the
 # forms that large inputs get, forced here at small sizes: the chunked layout of graphs above 2^23 vertices
-# and the sampler's id table in global memory (hops of more than 131072 ids).
+# and the sampler's id table in global memory.
 _CHUNKED = False
 
 
