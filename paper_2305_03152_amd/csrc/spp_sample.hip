@@ -709,8 +709,8 @@ __device__ __forceinline__ int hop_find(const uint32_t* ids, uint32_t home, uint
 // end to end (a scan of their lengths in LDS), so that every lane has an entry whatever the length of
 // a run; a lane finds its run by bisection.  Entries go into the table, and after a barrier every edge
 // takes the smallest position of its id.  Up to 8192 entries a lane keeps its own in registers between
-// the two; beyond that they are walked twice.  A partition whose ids do not fit the table (a hop beyond
-// 256 partitions of 7168 ids, or ids that share their hash's top bits) is taken in 2^r parts by the next
+// the two; beyond that they are walked twice.  A partition whose ids do not fit the table (ids that share their
+// hash's top bits, or a hop above kHopLdsKeys ids without the memory for its table) is taken in 2^r parts by the next
 // r bits of the hash; at 19 bits in all at most four ids of a part share a bucket, because the hash is
 // a bijection of 32-bit ids: any input fits.
 // kLarge: the hop's bound allows more than kHopLdsKeys ids.
