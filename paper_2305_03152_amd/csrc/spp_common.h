@@ -140,7 +140,7 @@ struct spp_ctx {
     spp::DevBuf sortws, rankws;         // set-up: counts of a radix sort, keys and histograms of a ranking (bounded, see kKeptSortBytes)
     spp::DevBuf xvals;                  // dense hops over the chunked layout: y[source] of every entry
     spp::DevBuf bins;                   // general propagation: per row block the (row, weight) entries of a hop, and the fill counts
-    int         bin_lds_set = 0, sum_lds_set = 0;   // dynamic LDS bytes its two kernels have been allowed
+    int         bin_lds_set = 0, sum_lds_set = 0, prepare_lds_set = 0;   // dynamic LDS its kernels have been allowed
     int         tile_lds_set = 0;       // dynamic LDS bytes the dense-hop kernel has been allowed on this device
     int         dedup_lds_set = 0;      // the LDS dedup kernel of the sampler has been allowed its 76 KB
     int         x_lds_set = 0;          // the two kernels of the chunked layout have been allowed theirs
@@ -175,6 +175,12 @@ struct spp_graph {
     int       tile_rbits = 0;
     int64_t   nrb = 0;                  // row blocks
     int       nch = 0;                  // source chunks (of 2^kTileSrcLoBits vertices)
+    // the partition that laid t_edge out: its tiles of kPartTile edges of the CSR, where a tile's edges of a row block
+    // start in t_edge, and the row that holds a tile's first edge (then: the last row with edges)
+    void*     part_mem = nullptr;       // holds the two
+    uint32_t* tile_off = nullptr;       // uint32[nrb * part_tiles]
+    int32_t*  tile_row = nullptr;       // int32[part_tiles + 1]
+    int64_t   part_tiles = 0;
     int64_t*  block_first = nullptr;    // int64[nrb + 1]: edges that end in row blocks before b (either layout)
     // The second layout of the same edges, built instead of the first for graphs whose per-vertex
     // vector is too large to be gathered from (see spp_vip.hip): the edges sorted by (chunk of 2^15

@@ -14,6 +14,7 @@ namespace spp {
 constexpr int kTileSrcLoBits = 18;
 constexpr int kTileRowBits = 14;
 constexpr uint32_t kTileRowMask = (1u << kTileRowBits) - 1u;
+constexpr int kPartTile = 4096;          // edges of the CSR per tile of the partition that lays the words out
 
 __device__ __forceinline__ uint32_t tile_source(uint32_t word, int chunk) {
     return ((uint32_t)chunk << kTileSrcLoBits) | (word >> kTileRowBits);

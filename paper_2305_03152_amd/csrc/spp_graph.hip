@@ -49,7 +49,6 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // edges: the kernels of a build 9.2 -> 1.1 ms: 0.63 in the placing pass, most of it vector instructions,
 // 0.12 in the counting pass, 0.15 in the read-back and 0.19 in the sum over the CSR that it is compared with.
 // Tiles of 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
-constexpr int kPartTile = 4096;
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
 constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
@@ -75,13 +74,14 @@ __device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// tile_row[t] = the vertex whose row holds the first edge of tile t.
-__global__ void __launch_bounds__(kBlock) part_rows_kernel(int64_t N, const int64_t* __restrict__ rowptr,
+// tile_row[t] = the vertex whose row holds the first edge of tile t; tile_row[ntiles] = the last one with edges.
+__global__ void __launch_bounds__(kBlock) part_rows_kernel(int64_t N, int64_t M, int64_t ntiles, const int64_t* __restrict__ rowptr,
                                                            int32_t* __restrict__ tile_row) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
         const int64_t b = rowptr[v], e = rowptr[v + 1];
         for (int64_t t = (b + kPartTile - 1) / kPartTile; t * kPartTile < e; ++t) tile_row[t] = (int32_t)v;
+        if (b < e && e == M) tile_row[ntiles] = (int32_t)v;
     }
 }
 
@@ -383,10 +383,10 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         const int64_t ntiles = (M + kPartTile - 1) / kPartTile;
         const int64_t nhist = nrb * ntiles;
         const int scan_grid = 1024;
-        // one allocation: the counts, the scan's partial sums, the sums of the edges' mixes, a flag,
-        // and the tiles' first rows
+        // one allocation: the counts (then offsets) and the tiles' first rows, which the graph keeps, the scan's
+        // partial sums, the sums of the edges' mixes and a flag
         struct { unsigned long long mix[2]; int bad, pad; } head = {{0, 0}, 0, 0}, back;
-        const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)ntiles * sizeof(int32_t);
+        const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
         char* tmp = nullptr;
         if (hipMalloc(&tmp, bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -402,7 +402,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         hipError_t e = hipMemcpyAsync(tmp, &head, sizeof(head), hipMemcpyHostToDevice, st);
         if (e == hipSuccess) {
             const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
-            part_rows_kernel<<<grid, kBlock, 0, st>>>(N, g->rowptr, tile_row);
+            part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row);
             part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(M, g->col, rbits, (int)nrb, ntiles, hist);
             grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
             auto place = [&](auto kernel) {
@@ -425,8 +425,9 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         else if (back.bad || back.mix[0] != back.mix[1]) {
             set_error("row blocks: the structure does not read back as the edges it was built from"); rc = SPP_E_HIP;
         }
-        (void)hipFree(tmp);
+        g->part_mem = tmp;               // freed with the graph, also after an error
         SPP_TRY(rc);
+        g->tile_off = hist; g->tile_row = tile_row; g->part_tiles = ntiles;
     }
     SPP_HIP(hipMalloc(&g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
     block_first_from_tiles_kernel<<<(unsigned)((nrb + 1 + kBlock - 1) / kBlock), kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
@@ -801,6 +802,7 @@ extern "C" void spp_graph_destroy(spp_graph* g) {
     (void)hipDeviceSynchronize();      // work that still reads the row blocks may be in flight
     if (g->t_edge) (void)hipFree(g->t_edge);
     if (g->tile_first) (void)hipFree(g->tile_first);
+    if (g->part_mem) (void)hipFree(g->part_mem);
     if (g->block_first) (void)hipFree(g->block_first);
     if (g->x_src) (void)hipFree(g->x_src);
     if (g->x_row) (void)hipFree(g->x_row);

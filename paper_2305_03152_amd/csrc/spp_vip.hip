@@ -27,6 +27,8 @@
 #include "spp_device.h"
 #include "spp_fp64.h"
 
+#include <type_traits>
+
 namespace spp {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -141,18 +143,47 @@ __device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, in
 // The next hop is pushed or pulled depending on the out-edges of its frontier (the vertices with y != 0); the
 // kernel that writes the next hop's y counts them on the way, one sum per workgroup (no atomics: same-address
 // atomics cost about 15 ns each), and vip_decide_kernel adds the sums.
-template <int kThreads = kBlock>
-__device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long edges) {
+template <int kThreads>
+__device__ __forceinline__ unsigned long long workgroup_sum(unsigned long long x) {      // in thread 0
     __shared__ unsigned long long red[kThreads / kWave];
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) edges += __shfl_down((long long)edges, off, kWave);
-    if (lane_id() == 0) red[threadIdx.x >> 6] = edges;
+    for (int off = kWave / 2; off > 0; off >>= 1) x += __shfl_down((long long)x, off, kWave);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long all = 0;
+    unsigned long long all = 0;
+    if (threadIdx.x == 0)
         for (int w = 0; w < kThreads / kWave; ++w) all += red[w];
-        stat[blockIdx.x] = all;
-    }
+    return all;
+}
+template <int kThreads = kBlock>
+__device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long edges) {
+    const unsigned long long all = workgroup_sum<kThreads>(edges);
+    if (threadIdx.x == 0) stat[blockIdx.x] = all;
+}
+
+// Adds up one number per workgroup of a launch without a launch of its own: `slots` holds kTotalSlots words, all zero
+// between uses.  A word counts its arrivals above bit 48 beside their sum, so the arrival that completes it has the
+// sum and nothing has to be fenced; 64 workgroups share a word, the last of each group adds to the first word.  Atomics on
+// one address cost about 15 ns each, and so do those on one 128-byte line: each word has a line of its own (side by side,
+// 2048 workgroups took 9 us).  Called by one thread of every workgroup; true for the one that arrives
+// last, which has the total.  A workgroup's number counts as 2^36 at most.
+constexpr int kTotalMax = 4096;          // most workgroups
+constexpr int kTotalLine = 32;           // 64-bit words from one to the next
+constexpr int kTotalSlots = (1 + kTotalMax / 64) * kTotalLine;
+__device__ __forceinline__ bool grid_total(unsigned long long* slots, unsigned long long mine, unsigned long long& total) {
+    constexpr unsigned long long kOne = 1ull << 48, kMost = 1ull << 36;
+    unsigned long long* s = slots + (1 + blockIdx.x / 64) * kTotalLine;
+    const unsigned first = blockIdx.x & ~63u, members = gridDim.x - first < 64u ? gridDim.x - first : 64u;
+    unsigned long long v = (mine < kMost ? mine : kMost) + kOne;
+    v += atomicAdd(s, v);
+    if ((v >> 48) != members) return false;
+    atomicExch(s, 0ull);
+    v = (v & (kOne - 1)) + kOne;
+    v += atomicAdd(slots, v);
+    if ((v >> 48) != (gridDim.x + 63u) / 64u) return false;
+    atomicExch(slots, 0ull);
+    total = v & (kOne - 1);
+    return true;
 }
 
 __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
@@ -179,6 +210,25 @@ __global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y
     if (tid == 0) *bad = 0;
 }
 
+// Exclusive prefix sums over a workgroup of kThreads threads; ends with a barrier.
+template <int kThreads>
+__device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t (&wave_sum)[kThreads / kWave], uint32_t& total) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t inc = (uint32_t)wave_inclusive_scan((int)v);
+    if (lane == kWave - 1) wave_sum[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) {
+        const uint32_t x = wave_sum[w];
+        if (w < wave) before += x;
+        all += x;
+    }
+    total = all;
+    __syncthreads();
+    return before + inc - v;
+}
+
 // The frontier itself (any order): list[0 .. *cursor) = vertices whose y is not zero and whose row
 // is not empty; a row of more than kPieceEdges entries is listed once per piece of that many
 // entries (adjacent in the list), so that the kernels that walk the frontier's rows can hand the
@@ -192,17 +242,14 @@ constexpr int64_t kPieceEdges = 4096;
 __host__ __device__ inline int64_t frontier_list_capacity(int64_t N, int64_t M) { return N + M / kPieceEdges; }
 
 // With `how`: only if the hop is pushed.  With `acc`: also empties the accumulators of the vertices it looks at.
-template <int kListPer>
-__global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* __restrict__ y,
-                                                                   const int64_t* __restrict__ rowptr, int64_t N,
-                                                                   int32_t* __restrict__ list,
-                                                                   unsigned long long* __restrict__ cursor,
-                                                                   const uint32_t* __restrict__ how,
-                                                                   double* __restrict__ acc) {
-    __shared__ int scan_lds[4];
-    __shared__ unsigned long long start;
-    if (how && *how != kPushed) return;
-    const int64_t round = (int64_t)kBlock * kListPer;
+// `lds`: kThreads / kWave words for a scan, and two more.
+template <int kThreads, int kListPer>
+__device__ __forceinline__ void list_frontier(const float* __restrict__ y, const int64_t* __restrict__ rowptr, int64_t N,
+                                              int32_t* __restrict__ list, unsigned long long* __restrict__ cursor,
+                                              double* __restrict__ acc, uint32_t* lds) {
+    unsigned long long& start = *reinterpret_cast<unsigned long long*>(lds);
+    uint32_t (&wave_sum)[kThreads / kWave] = *reinterpret_cast<uint32_t(*)[kThreads / kWave]>(lds + 2);
+    const int64_t round = (int64_t)kThreads * kListPer;
     auto pieces = [&](int64_t v) { return (int)((rowptr[v + 1] - rowptr[v] + kPieceEdges - 1) / kPieceEdges); };
     for (int64_t r0 = (int64_t)blockIdx.x * round; r0 < N; r0 += (int64_t)gridDim.x * round) {
         // A wavefront covers kWave * kListPer consecutive vertices; lane l takes the 128-bit vectors
@@ -212,7 +259,7 @@ __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* 
         auto vertex = [&](int bit) { return w0 + 4 * ((int64_t)(bit >> 2) * kWave + lane_id()) + (bit & 3); };
         uint64_t nz = 0;
         if (acc)                                 // 16-byte aligned; r0 is even
-            for (int64_t i = r0 + 2 * threadIdx.x; i < r0 + round && i < N; i += 2 * kBlock) {
+            for (int64_t i = r0 + 2 * threadIdx.x; i < r0 + round && i < N; i += 2 * kThreads) {
                 typedef double f64x2 __attribute__((ext_vector_type(2)));
                 if (i + 1 < N) *reinterpret_cast<f64x2*>(acc + i) = f64x2{0.0, 0.0};
                 else acc[i] = 0.0;
@@ -228,10 +275,10 @@ __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* 
                     if (v + c < N && y[v + c] != 0.0f) nz |= 1ull << (4 * k + c);
             }
         }
-        int mine = 0;
-        for (uint64_t m = nz; m; m &= m - 1) mine += pieces(vertex(__builtin_ctzll(m)));
-        int total;
-        int at = block_exclusive_scan(mine, scan_lds, total);
+        uint32_t mine = 0;
+        for (uint64_t m = nz; m; m &= m - 1) mine += (uint32_t)pieces(vertex(__builtin_ctzll(m)));
+        uint32_t total;
+        uint32_t at = bin_block_scan<kThreads>(mine, wave_sum, total);
         if (total == 0) continue;        // uniform over the workgroup: the scan has synchronised it
         if (threadIdx.x == 0) start = atomicAdd(cursor, (unsigned long long)total);
         __syncthreads();
@@ -244,6 +291,15 @@ __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* 
     }
 }
 
+template <int kListPer>
+__global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* __restrict__ y, const int64_t* __restrict__ rowptr,
+                                                                   int64_t N, int32_t* __restrict__ list,
+                                                                   unsigned long long* __restrict__ cursor,
+                                                                   const uint32_t* __restrict__ how, double* __restrict__ acc) {
+    __shared__ __align__(8) uint32_t lds[2 + kBlock / kWave];
+    if (how && *how != kPushed) return;
+    list_frontier<kBlock, kListPer>(y, rowptr, N, list, cursor, acc, lds);
+}
 inline void launch_frontier_list(int grid, hipStream_t st, const float* y, const int64_t* rowptr, int64_t N, int32_t* list,
                                  unsigned long long* cursor, const uint32_t* how = nullptr, double* acc = nullptr) {
     if (N >= (int64_t)1 << 22) vip_frontier_list_kernel<64><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how, acc);
@@ -727,15 +783,40 @@ __device__ __forceinline__ float unit_or_flag(float x, int* bad) {
     return 0.0f;
 }
 
+// How a hop of the general propagation fills its bins: from a list of its frontier, or (kWhole) from the whole CSR, tile
+// by tile, where the frontier's rows hold at least half of the edges.  The kernel that writes a hop's
+// probabilities counts their vertices' out-edges and decides.  2.4M vertices, 121M edges, list, fill and sum: by tiles 640 us
+// whatever the frontier; listed 1075 us with all edges, 345 with 23 % of them.
+constexpr uint32_t kListed = 1, kWhole = 2;
+struct FillRule {
+    const int64_t* rowptr;               // null: always from the list (no tiles to walk)
+    int64_t M;
+    unsigned long long* slots;
+    uint32_t* how;                       // the next hop's
+    __device__ __forceinline__ unsigned long long degree(int64_t v) const {
+        return rowptr ? (unsigned long long)(rowptr[v + 1] - rowptr[v]) : 0ull;
+    }
+    __device__ __forceinline__ void decide(unsigned long long edges) const {      // by whole workgroups of kBlock threads
+        if (!rowptr) return;
+        const unsigned long long mine = workgroup_sum<kBlock>(edges);
+        unsigned long long all;
+        if (threadIdx.x == 0 && grid_total(slots, mine, all)) *how = 2 * all >= (unsigned long long)M ? kWhole : kListed;
+    }
+};
+
 __global__ void __launch_bounds__(kBlock) vipg_init_kernel(const float* __restrict__ p0, int64_t N,
                                                            float* __restrict__ pcur, double* __restrict__ tot,
-                                                           int include_hop0, int* __restrict__ bad) {
+                                                           int include_hop0, int* __restrict__ bad, FillRule rule) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
+    unsigned long long edges = 0;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
+        const unsigned long long deg = rule.degree(v);
         const float p = unit_or_flag(p0[v], bad);
         pcur[v] = p;
+        edges += p > 0.0f ? deg : 0ull;
         if (include_hop0) tot[v] = log1p(-(double)p);
     }
+    rule.decide(edges);
 }
 
 __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __restrict__ list,
@@ -781,7 +862,8 @@ __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __rest
 // two workgroups of a CU do not fill each other's waits.  (Rounds of 2048 edges:
 // 0.9 ms of reserving alone; 4096 and 6144: 884, 852; more registers for half the wavefronts, 1096.  Sorting 2048
 // entries at a time by bin in LDS, so that neighbouring threads store neighbouring entries, was
-// slower: 1.2 ms; a thread taking 8 consecutive edges instead of a wavefront taking 64: 1.25 ms.)
+// slower: 1.2 ms; a thread taking 8 consecutive edges instead of a wavefront taking 64: 1.25 ms.)  Hops whose
+// frontier holds half of the edges and more take vipg_prepare_kernel instead.
 constexpr int kBinBlock = 256;           // threads per workgroup of the walks below, and most frontier vertices per portion
 constexpr int kFillBlock = 1024;         // the same of the general propagation's
 constexpr int kFillPer = 8;                // and its edges per thread and round
@@ -829,25 +911,6 @@ struct BinPortion {
     float    p[kThreads];                // p^[h-1] of vertex i
     uint32_t wave_sum[kThreads / kWave];
 };
-
-// Exclusive prefix sums over a workgroup of kThreads threads; ends with a barrier.
-template <int kThreads>
-__device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t (&wave_sum)[kThreads / kWave], uint32_t& total) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t inc = (uint32_t)wave_inclusive_scan((int)v);
-    if (lane == kWave - 1) wave_sum[wave] = inc;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) {
-        const uint32_t x = wave_sum[w];
-        if (w < wave) before += x;
-        all += x;
-    }
-    total = all;
-    __syncthreads();
-    return before + inc - v;
-}
 
 // The vertex of the portion whose row holds edge x of the sequence (x < prefix[nv]): the last i
 // with prefix[i] <= x.
@@ -1107,7 +1170,10 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
 // of the first); above, the logarithm of 1 - x, whose rounding error is at most 2^-25 against a
 // result of at least 0.28.
 __device__ __forceinline__ float bin_log1p_neg(float x) {
-    const float s = __fdividef(x, 2.0f - x);
+    // x / (2 - x) from the reciprocal's estimate and one correction: to half a unit as the division, four instructions
+    // instead of eleven (2 - x lies in [1, 2])
+    const float d = 2.0f - x, r = __builtin_amdgcn_rcpf(d), s0 = x * r;
+    const float s = __fmaf_rn(__fmaf_rn(-s0, d, x), r, s0);
     const float z = s * s;
     float q = 1.0f / 11.0f;
     q = __fmaf_rn(q, z, 1.0f / 9.0f);
@@ -1115,9 +1181,198 @@ __device__ __forceinline__ float bin_log1p_neg(float x) {
     q = __fmaf_rn(q, z, 1.0f / 5.0f);
     q = __fmaf_rn(q, z, 1.0f / 3.0f);
     q = __fmaf_rn(q, z, 1.0f);
-    const float small = -2.0f * s * q;
+    const float small = __fmaf_rn(-2.0f * s, q, 0.0f);     // +0 for x = 0
     const float large = __logf(1.0f - x);
     return x < 0.25f ? small : large;
+}
+
+// The bins of a hop whose frontier holds most of the edges.  A tile of the CSR (kPartTile edges) puts its edges of a row block
+// where the set-up's partition put them: tile_off[block * ntiles + tile] says where they start and the next word how
+// many they are, so nothing is counted, no range is reserved and no list is read.  A thread reads four consecutive edges
+// (128-bit loads); the rows' probabilities lie at the rows' first edges in LDS, where an edge finds its own by
+// looking back; an LDS atomic on the block's cursor gives the edge its place among the tile's, which are laid out by
+// block in LDS and stored from there as runs.
+// Two barriers per tile: (1) the next tile's rows are marked and its cursors set while the tile before is stored, (2) its
+// edges are weighed and laid out.  A load that is waited for after stores would wait for those too (they complete in
+// order), so a tile's rows and offsets are asked for before the stores of two tiles back, its edges before those of
+// the tile before, and nothing in the loop is loaded conditionally (after a conditional load the compiler waits for all).
+// 2.4M vertices, 121M edges: 419 us, 2.0 GB, where the listed fill took 852; with seven barriers and waits for the stores 535
+// to 780.  What bounds it now: vector instructions half of the time (64 per 64 edges, the logarithm a third of them), LDS a
+// third, and what two workgroups per CU leave uncovered of the two barriers.
+constexpr int kMaxTileBlocks = 512;      // row blocks of a graph that has tiles
+struct PrepareLds {
+    uint2    stage[kPartTile];           // the tile's entries by block: weight, destination
+    uint32_t mark[2][kPartTile];         // p of the row that starts at an edge of the tile
+    uint32_t cnt[kMaxTileBlocks], off[kMaxTileBlocks];           // of the next tile: edges per block and where they go
+    uint32_t cursor[2][kMaxTileBlocks];  // the next entry of a block among the tile's, from its first up and from its last down
+    uint32_t shift[2][kMaxTileBlocks];   // where a block's entries go, less where they start among the tile's
+};
+
+// The launch before the listed fill: lists the frontier or, where the whole CSR is walked, fills the bins itself.
+__global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint32_t* __restrict__ how, const uint32_t* __restrict__ tile_off,
+                                                                     const int32_t* __restrict__ tile_row, int ntiles, int64_t M,
+                                                                     const float* __restrict__ pcur,
+                                                                     const int64_t* __restrict__ rowptr,
+                                                                     const int32_t* __restrict__ col, const float* __restrict__ t,
+                                                                     int rbits, int nrb, uint2* __restrict__ bins,
+                                                                     int* __restrict__ bad, int64_t N, int32_t* __restrict__ list,
+                                                                     unsigned long long* __restrict__ cursor) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) char prepare_lds[];
+    if (*how != kWhole) {
+        list_frontier<kFillBlock, 8>(pcur, rowptr, N, list, cursor, nullptr, reinterpret_cast<uint32_t*>(prepare_lds));
+        return;
+    }
+    PrepareLds& l = *reinterpret_cast<PrepareLds*>(prepare_lds);
+    static_assert(kPartTile == 4 * kFillBlock, "four edges of a tile per thread");
+    constexpr uint32_t kSpan = 4 * kWave;        // edges of a tile per wavefront
+    constexpr uint32_t kNone = 0xFFFFFFFFu;      // no bits of a probability
+    const int lane = lane_id();
+    const uint32_t tid = threadIdx.x, rmask = (1u << rbits) - 1u;
+    const uint32_t blk = (int)tid < nrb ? tid : 0u;
+    const uint32_t* __restrict__ off_b = tile_off + (size_t)blk * (uint32_t)ntiles;
+    // a tile's rows and offsets (the first kFillBlock rows, one per thread; threads beyond take the last one once more)
+    struct { int32_t v0, v1; uint32_t b, e; float p; uint32_t off, off_n; } r;
+    auto load_row = [&](int32_t v) { r.b = (uint32_t)rowptr[v]; r.e = (uint32_t)rowptr[v + 1]; r.p = pcur[v]; };      // below 2^32, like M
+    auto load_rows = [&](int tile) {
+        r.v0 = tile_row[tile]; r.v1 = tile_row[tile + 1];
+        load_row(r.v1 - r.v0 > (int32_t)tid ? r.v0 + (int32_t)tid : r.v1);
+        r.off = off_b[tile];
+        const bool past = (int)blk == nrb - 1 && tile == ntiles - 1;
+        r.off_n = off_b[past ? tile : tile + 1];
+        if (past) r.off_n = (uint32_t)M;
+    };
+    uint32_t u[4];
+    float x[4];
+    auto load_edges = [&](int tile) {            // of a full tile; col and t are 16-byte aligned
+        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(col + (int64_t)tile * kPartTile) + tid);
+        const f32x4 b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(t + (int64_t)tile * kPartTile) + tid);
+        u[0] = a.x; u[1] = a.y; u[2] = a.z; u[3] = a.w;
+        x[0] = b.x; x[1] = b.y; x[2] = b.z; x[3] = b.w;
+    };
+    bool wrong = false;
+    auto mark_rows = [&](int tile, uint32_t n, uint32_t* mark) {
+        const uint32_t base = (uint32_t)tile * (uint32_t)kPartTile, stop = base + n;       // at most M
+        auto one = [&]() {                       // at its first edge, and at the first edge of every wavefront's part that begins inside it
+            const uint32_t b = (r.b > base ? (r.b < stop ? r.b : stop) : base) - base, e = (r.e > base ? (r.e < stop ? r.e : stop) : base) - base;
+            if (b < e) {
+                mark[b] = __float_as_uint(r.p);
+                for (uint32_t k = (b + kSpan) & ~(kSpan - 1); k < e; k += kSpan) mark[k] = __float_as_uint(r.p);
+            }
+        };
+        if (r.v1 - r.v0 >= (int32_t)tid) one();
+        for (int64_t v = (int64_t)r.v0 + kFillBlock + tid; v <= r.v1; v += kFillBlock) { load_row((int32_t)v); one(); }
+    };
+    auto keep_offsets = [&]() {                  // for the wavefront that sets the cursors
+        if ((int)tid < nrb) { l.cnt[tid] = r.off_n - r.off; l.off[tid] = r.off; }
+    };
+    auto set_cursors = [&](uint32_t* shift) {    // by the first wavefront
+        if (tid >= kWave) return;
+        uint32_t before = 0;
+        for (int b0 = 0; b0 < nrb; b0 += kWave) {
+            const int b = b0 + lane;
+            const uint32_t c = b < nrb ? l.cnt[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c), start = before + inc - c;
+            if (b < nrb) { l.cursor[0][b] = start; l.cursor[1][b] = start + c; shift[b] = l.off[b] - start; }
+            before += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        }
+    };
+    auto clear_marks = [&](uint32_t* mark) { reinterpret_cast<u32x4*>(mark)[tid] = u32x4{kNone, kNone, kNone, kNone}; };
+    auto weigh = [&](const uint32_t* mark, auto full, uint32_t n) {
+        // the last mark at or before an edge: among the lane's own four or in the lanes before
+        const u32x4 m4 = reinterpret_cast<const u32x4*>(mark)[tid];
+        uint32_t m[4] = {m4.x, m4.y, m4.z, m4.w};
+        const uint32_t last = m[3] != kNone ? m[3] : m[2] != kNone ? m[2] : m[1] != kNone ? m[1] : m[0];
+        const uint64_t below = __ballot(last != kNone) & ((1ull << lane) - 1ull);
+        const uint32_t before = (uint32_t)__shfl((int)last, 63 - __clzll((long long)(below | 1ull)), kWave);
+        m[0] = m[0] != kNone ? m[0] : before;
+#pragma unroll
+        for (int q = 1; q < 4; ++q) m[q] = m[q] != kNone ? m[q] : m[q - 1];
+        // Rows are sorted, so edges side by side often end in one block: a run of them in the lane takes one atomic.  Even
+        // lanes take a block's places from below, odd ones from above: where a whole wavefront ends in one block (a hub's
+        // row), half as many adds meet on one address.
+        uint32_t blk[4], len[4], place[4];
+        bool run[4] = {};                        // the edge continues the run of the one before
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            blk[q] = u[q] >> rbits;
+            if (q > 0) run[q] = blk[q] == blk[q - 1] && (full || 4 * tid + q < n);
+        }
+        len[3] = 1;
+#pragma unroll
+        for (int q = 2; q >= 0; --q) len[q] = run[q + 1] ? len[q + 1] + 1u : 1u;
+        const bool down = lane & 1;
+        uint32_t* cur = l.cursor[lane & 1];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if ((full || 4 * tid + q < n) && !run[q]) place[q] = atomicAdd(&cur[blk[q]], down ? 0u - len[q] : len[q]) - (down ? len[q] : 0u);
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+            if (run[q]) place[q] = place[q - 1] + 1u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (full || 4 * tid + q < n) {
+                const float p = __uint_as_float(m[q]), c = __builtin_amdgcn_fmed3f(x[q], 0.0f, 1.0f);
+                wrong |= p > 0.0f && !(c == x[q]);
+                l.stage[place[q]] = make_uint2(__float_as_uint(bin_log1p_neg(c == x[q] ? c * p : 0.0f)), u[q]);
+            }
+    };
+    auto store = [&](const uint32_t* shift, auto full, uint32_t n) {
+#pragma unroll
+        for (int k = 0; k < kPartTile / kFillBlock; ++k) {
+            const uint32_t i = tid + k * kFillBlock;
+            if (full || i < n) {
+                const uint2 e = l.stage[i];
+                bins[shift[e.y >> rbits] + i] = make_uint2(e.x, e.y & rmask);
+            }
+        }
+    };
+    // neighbouring tiles store to neighbouring places: an XCD (workgroups go to the eight in turn) takes a run of the full tiles
+    const int nfull = (int)(M / kPartTile), per_xcd = (nfull + 7) / 8, step = (int)(gridDim.x >> 3), x0 = (int)(blockIdx.x & 7) * per_xcd;
+    const int end = x0 + per_xcd < nfull ? x0 + per_xcd : nfull;
+    int tile = x0 + (int)(blockIdx.x >> 3);
+    if (tile < end) {
+        auto at = [&](int tl) { return tl < end ? tl : end - 1; };
+        load_rows(tile);
+        load_edges(tile);
+        clear_marks(l.mark[0]);
+        keep_offsets();
+        __syncthreads();
+        mark_rows(tile, kPartTile, l.mark[0]);
+        set_cursors(l.shift[0]);
+        load_rows(at(tile + step));
+        __syncthreads();
+        for (int k = 0; tile < end; tile += step, k ^= 1) {      // k: which of the two marks and shifts
+            clear_marks(l.mark[k ^ 1]);
+            keep_offsets();
+            weigh(l.mark[k], std::true_type{}, kPartTile);
+            load_edges(at(tile + step));
+            __syncthreads();
+            mark_rows(at(tile + step), kPartTile, l.mark[k ^ 1]);
+            set_cursors(l.shift[k ^ 1]);
+            load_rows(at(tile + 2 * step));
+            store(l.shift[k], std::true_type{}, kPartTile);
+            __syncthreads();
+        }
+    }
+    if (nfull < ntiles && blockIdx.x == gridDim.x - 1) {         // the rest
+        const uint32_t n = (uint32_t)(M - (int64_t)nfull * kPartTile);
+        load_rows(nfull);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u[q] = 4 * tid + q < n ? (uint32_t)col[(int64_t)nfull * kPartTile + 4 * tid + q] : 0u;
+            x[q] = 4 * tid + q < n ? t[(int64_t)nfull * kPartTile + 4 * tid + q] : 0.0f;
+        }
+        clear_marks(l.mark[0]);
+        keep_offsets();
+        __syncthreads();
+        mark_rows(nfull, n, l.mark[0]);
+        set_cursors(l.shift[0]);
+        __syncthreads();
+        weigh(l.mark[0], std::false_type{}, n);
+        __syncthreads();
+        store(l.shift[0], std::false_type{}, n);
+    }
+    if (wrong) *bad = 1;
 }
 
 __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int32_t* __restrict__ list,
@@ -1128,9 +1383,11 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
                                                                       const float* __restrict__ t, int rbits, int nrb,
                                                                       const int64_t* __restrict__ first, int nch,
                                                                       uint32_t* __restrict__ cursor,
-                                                                      uint2* __restrict__ bins, int* __restrict__ bad) {
+                                                                      uint2* __restrict__ bins, int* __restrict__ bad,
+                                                                      const uint32_t* __restrict__ how) {
     __shared__ BinPortion<kFillBlock> po;
     extern __shared__ uint32_t lds_u32[];
+    if (how && *how != kListed) return;
     uint32_t* count = lds_u32;           // the round's entries per row block; zero between rounds
     uint32_t* base = lds_u32 + nrb;      // the entry (index into bins[], below 2^32) where they start
     const int64_t nf = (int64_t)*nf_ptr;
@@ -1191,14 +1448,15 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
 __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __restrict__ bins,
                                                                  const uint32_t* __restrict__ cursor,
                                                                  const int64_t* __restrict__ first, int nch, int parts,
-                                                                 int rbits, double* __restrict__ part, int64_t part_stride) {
+                                                                 int rbits, double* __restrict__ part, int64_t part_stride,
+                                                                 const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
     const int R = 1 << rbits;
     const int64_t rb = blockIdx.x / parts;
     const int j = blockIdx.x % parts;
     for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
     __syncthreads();
-    const int64_t b0 = first[rb * nch], len = (int64_t)cursor[rb];
+    const int64_t b0 = first[rb * nch], len = how && *how == kWhole ? first[(rb + 1) * nch] - b0 : (int64_t)cursor[rb];
     bin_add_entries(acc, bins, b0 + len * j / parts, b0 + len * (j + 1) / parts);
     __syncthreads();
     double* __restrict__ out = part + (int64_t)j * part_stride + (rb << rbits);
@@ -1207,7 +1465,7 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
 
 // What a hop's kernels count with: the frontier list's cursor, and the bins' (none without bins).
 struct HopCounters {
-    unsigned long long* listed;
+    unsigned long long* listed;          // the list's cursor
     uint32_t* bins;
     int64_t   nbins;
     __device__ __forceinline__ void clear(int64_t tid, int64_t stride) const {
@@ -1216,8 +1474,10 @@ struct HopCounters {
     }
 };
 
-__global__ void __launch_bounds__(kBlock) vipg_clear_kernel(HopCounters c, int* __restrict__ bad) {
+__global__ void __launch_bounds__(kBlock) vipg_clear_kernel(HopCounters c, int* __restrict__ bad, unsigned long long* __restrict__ slots) {
     c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < kTotalSlots; i += kBlock) slots[i] = 0ull;
     if (blockIdx.x == 0 && threadIdx.x == 0) *bad = 0;
 }
 
@@ -1225,18 +1485,22 @@ __global__ void __launch_bounds__(kBlock) vipg_clear_kernel(HopCounters c, int* 
 __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __restrict__ acc, double* __restrict__ tot,
                                                              int first, int last, float* __restrict__ p_hop,
                                                              float* __restrict__ p_total, float* __restrict__ pnext,
-                                                             int64_t N, int parts, int64_t part_stride, HopCounters c) {
+                                                             int64_t N, int parts, int64_t part_stride, HopCounters c,
+                                                             FillRule rule) {
+    unsigned long long edges = 0;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
     for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += stride) {
+        const unsigned long long deg = last ? 0ull : rule.degree(u);
         double S = acc[u];
         for (int j = 1; j < parts; ++j) S += acc[(int64_t)j * part_stride + u];
         const double ph = -expm1(S);
         if (p_hop) p_hop[u] = (float)ph;
         const double T = first ? S : tot[u] + S;
         if (last) p_total[u] = (float)(-expm1(T));
-        else { tot[u] = T; pnext[u] = (float)ph; }
+        else { tot[u] = T; pnext[u] = (float)ph; edges += (float)ph > 0.0f ? deg : 0ull; }
     }
+    if (!last) rule.decide(edges);
 }
 
 }  // namespace spp
@@ -1257,22 +1521,28 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double) + sizeof(int)));
     SPP_TRY(ctx->acc.reserve((size_t)N * sizeof(double)));
     const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + 4 * sizeof(unsigned long long)));
+    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + kTotalSlots + SPP_MAX_L + 2) * sizeof(unsigned long long)));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));
+    unsigned long long* slots = fcount + 4;
+    uint32_t* how = reinterpret_cast<uint32_t*>(slots + kTotalSlots);        // [1 .. L]: how each hop fills its bins
     float* pcur = ctx->y0.as<float>();
     float* pnext = ctx->y1.as<float>();
     double* tot = ctx->tot.as<double>();
     double* acc = ctx->acc.as<double>();
     int* d_bad = reinterpret_cast<int*>(tot + N);
     const int include0 = (flags & SPP_VIP_INCLUDE_HOP0) ? 1 : 0;
-    const int fill_grid = ctx->num_cu * 8;
+    const int fill_grid = ctx->num_cu * 8 < kTotalMax ? ctx->num_cu * 8 : kTotalMax;
     // With the row-block structure at hand the push goes through bins (no global fp64 atomics).
     const bool binned = g->has_in && g->nrb > 0 && g->nrb <= kBinMaxBlocks && g->M > 0;
     int parts = 1;
     const int64_t part_stride = binned ? g->nrb << g->tile_rbits : N;
     uint2* bins = nullptr;
     uint32_t* cursor = nullptr;
+    // the tiles are read as 128-bit vectors
+    uintptr_t low = reinterpret_cast<uintptr_t>(g->col);
+    for (int h = 0; h < L; ++h) low |= reinterpret_cast<uintptr_t>(d_t[h]);
+    const bool tiles = binned && g->tile_off != nullptr && (low & 15) == 0;
     const size_t fill_lds = binned ? 2 * (size_t)g->nrb * sizeof(uint32_t) : 0;
     const size_t sum_lds = binned ? sizeof(double) << g->tile_rbits : 0;
     if (binned) {
@@ -1287,6 +1557,11 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)fill_lds));
             ctx->bin_lds_set = (int)fill_lds;
         }
+        if (tiles && !ctx->prepare_lds_set) {
+            SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vipg_prepare_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PrepareLds)));
+            ctx->prepare_lds_set = 1;
+        }
         if (ctx->sum_lds_set < (int)sum_lds) {
             SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_bin_sum_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sum_lds));
@@ -1296,26 +1571,34 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
         const HopCounters counters{fcount + 2, cursor, binned ? g->nrb + 1 : 0};
-        vipg_clear_kernel<<<(unsigned)(counters.nbins / kBlock + 1), kBlock, 0, st>>>(counters, d_bad);
-        vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad);
+        FillRule rule{tiles ? g->rowptr : nullptr, g->M, slots, how + 1};
+        vipg_clear_kernel<<<(unsigned)(counters.nbins / kBlock + 1), kBlock, 0, st>>>(counters, d_bad, slots);
+        vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad, rule);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
-            launch_frontier_list(fill_grid, st, pcur, g->rowptr, N, flist, fcount + 2);
+            const uint32_t* how_h = tiles ? how + h : nullptr;
+            if (tiles)
+                vipg_prepare_kernel<<<ctx->num_cu * 2, kFillBlock, sizeof(PrepareLds), st>>>(
+                    how_h, g->tile_off, g->tile_row, (int)g->part_tiles, g->M, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits,
+                    (int)g->nrb, bins, d_bad, N, flist, fcount + 2);
+            else
+                launch_frontier_list(fill_grid, st, pcur, g->rowptr, N, flist, fcount + 2);
             if (binned) {
                 // a bin is the range of the edges that end in its row block: block_first, with a stride of one
                 vipg_bin_fill_kernel<<<ctx->num_cu * 2, kFillBlock, fill_lds, st>>>(
                     flist, fcount + 2, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits, (int)g->nrb,
-                    g->block_first, 1, cursor, bins, d_bad);
+                    g->block_first, 1, cursor, bins, d_bad, how_h);
                 vip_bin_sum_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, sum_lds, st>>>(
-                    bins, cursor, g->block_first, 1, parts, g->tile_rbits, acc, part_stride);
+                    bins, cursor, g->block_first, 1, parts, g->tile_rbits, acc, part_stride, how_h);
             } else {
                 fill_f64_kernel<<<fill_grid, kBlock, 0, st>>>(acc, N, 0.0);
                 vipg_push_kernel<<<ctx->num_cu * 32, kBlock, 0, st>>>(flist, fcount + 2, pcur, g->rowptr, g->col,
                                                                      d_t[h - 1], acc, d_bad);
             }
+            rule.how = how + h + 1;
             vipg_finish_kernel<<<fill_grid, kBlock, 0, st>>>(acc, tot, (h == 1 && !include0) ? 1 : 0, h == L ? 1 : 0,
                                                              d_p_hop ? d_p_hop + (int64_t)(h - 1) * N : nullptr,
-                                                             d_p_total, pnext, N, parts, part_stride, counters);
+                                                             d_p_total, pnext, N, parts, part_stride, counters, rule);
             float* tmp = pcur; pcur = pnext; pnext = tmp;
         }
     }

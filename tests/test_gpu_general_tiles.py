@@ -1,0 +1,97 @@
+"""GPU: the general propagation's hops that walk the whole CSR tile by tile (frontiers with at least half of the edges),
+where tiles, rows and row blocks end, against the CPU oracle and against the walk over a listed frontier, which
+the same call takes when its probabilities are not aligned for 128-bit loads."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+TILE = 4096
+
+
+@pytest.fixture(scope="module")
+def spp():
+    import paper_2305_03152_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(spp):
+    c = spp.Context(0)
+    yield c
+    c.close()
+
+
+def _graph(rng, N, deg):
+    """Rows of the given lengths, their entries ascending and distinct."""
+    rp = np.zeros(N + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    start = rng.integers(0, N, N)
+    step = rng.integers(1, np.maximum(N // np.maximum(deg, 1), 1) + 1)
+    within = np.arange(rp[-1]) - np.repeat(rp[:-1], deg)
+    col = (np.repeat(start, deg) + within * np.repeat(step, deg)) % N
+    order = np.lexsort((col, np.repeat(np.arange(N), deg)))
+    return rp, col[order].astype(np.int32)
+
+
+def _cases():
+    for M in (1, 3, 255, TILE - 1, TILE, TILE + 1, 9 * TILE - 5, 9 * TILE, 16 * TILE + 257):
+        yield f"spread{M}", 20000, M, None
+    yield "hubs", 40000, 0, {5: 20000, 6: 1, 7: 3 * TILE, 8000: TILE, 39999: TILE + 1}
+    yield "empty", 60000, 0, {0: 10, 30000: 2000, 59000: 7000}           # tens of thousands of empty rows inside a tile
+    yield "single", 70 * 16384 + 3, -1, None                             # one edge per row: 4096 rows a tile, 71 row blocks
+    yield "most_blocks", 1 << 23, -1, None                               # 512 row blocks
+
+
+@pytest.mark.parametrize("name,N,M,rows", list(_cases()), ids=lambda x: x if isinstance(x, str) else "")
+def test_whole_hops(spp, ctx, name, N, M, rows):
+    print("[case]", name, flush=True)
+    rng = np.random.default_rng(N + (M or 0))
+    deg = np.zeros(N, dtype=np.int64)
+    if rows:
+        for v, d in rows.items():
+            deg[v] = d
+    elif M < 0:
+        deg[:] = 1
+    else:
+        deg += np.bincount(rng.integers(0, N, M), minlength=N)
+    rp, col = _graph(rng, N, deg)
+    p0 = rng.random(N).astype(np.float32)
+    p0[rng.random(N) < 0.1] = 0.0
+    p0[rng.random(N) < 0.01] = 1.0
+    p0[deg >= TILE] = 0.5                                                # the hubs are in the frontier
+    t = [(rng.random(col.size) ** 2).astype(np.float32) for _ in range(2)]
+    for a in t:
+        a[rng.random(a.size) < 0.02] = 1.0
+        a[rng.random(a.size) < 0.02] = 0.0
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True)
+    ref_t, ref_h = oracle.vip_general(rp, col, p0, t, 2)
+    for shift in (0, 1):                                                 # 1: from the list
+        td = [torch.zeros(a.size + 4, device=dev)[shift:shift + a.size].copy_(torch.from_numpy(a)) for a in t]
+        p, ph = spp.vip_propagate_general(ctx, G, torch.from_numpy(p0).to(dev), td, 2, per_hop=True)
+        for got, ref in ((p, ref_t), (ph, ref_h)):
+            # a term's logarithm carries a few units of fp32, all terms have one sign, and the second hop starts from
+            # probabilities rounded to fp32: the 1e-5 that the entry point states
+            assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-5 * np.asarray(ref) + 1e-37), (name, shift)
+    G.close()
+
+
+def test_a_probability_that_nothing_uses_is_not_reported(spp, ctx):
+    N = 3 * TILE
+    rp, col = np.arange(N + 1, dtype=np.int64), ((np.arange(N) + 7) % N).astype(np.int32)
+    p0, t = np.full(N, 0.5, np.float32), np.full(N, 0.25, np.float32)
+    p0[100], t[100] = 0.0, 2.0
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True)
+    got = spp.vip_propagate_general(ctx, G, torch.from_numpy(p0).to(dev), torch.from_numpy(t).to(dev), 1).cpu().numpy()
+    want = np.where(np.arange(N) == 107, 0.0, 0.125)
+    assert np.all(np.abs(got - want) <= 1e-6 * want)       # log1p and expm1 of one term: a few units of fp32
+    for wrong in (2.0, -0.5, float("nan")):
+        t[200] = wrong
+        with pytest.raises(spp.SppError):
+            spp.vip_propagate_general(ctx, G, torch.from_numpy(p0).to(dev), torch.from_numpy(t).to(dev), 1)
+    G.close()
