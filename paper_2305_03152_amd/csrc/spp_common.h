@@ -137,6 +137,8 @@ struct spp_ctx {
     int64_t*    totals = nullptr;       // device int64[16], running sums since the last reset (see spp_ctx_totals)
     // vip workspaces
     spp::DevBuf y0, y1, tot, acc, frontier;
+    spp::DevBuf vipstate;               // words for sums over a launch and a flag, all zero between calls
+    int         vip_state_clean = 0;    // they are
     spp::DevBuf sortws, rankws;         // set-up: counts of a radix sort, keys and histograms of a ranking (bounded, see kKeptSortBytes)
     spp::DevBuf xvals;                  // dense hops over the chunked layout: y[source] of every entry
     spp::DevBuf bins;                   // general propagation: per row block the (row, weight) entries of a hop, and the fill counts

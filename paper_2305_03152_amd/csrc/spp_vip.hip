@@ -16,13 +16,13 @@
 // adds the shares and finishes the vertex (p^[h], running total, next hop's y).
 //
 // Early hops touch few edges (hop 1 only the rows of T), so the kernel that writes a hop's y also
-// counts the hop's frontier (vertices with y != 0) and its out-edges; when that is a small share of
-// the graph the frontier is compacted into a list and the hop is done in push form instead: each
-// frontier vertex adds its y to the fp64 accumulator of every member of its row (atomic adds, and one
-// pass finishes all vertices; on large graphs through bins of the row blocks, which finish their
-// vertices).  Which form a hop takes is decided on the device: the launches of both
-// are queued and those of the other form leave at once (a few us each, where reading the frontier's
-// size back cost the host 35 to 60 us per hop, with nothing queued behind it).
+// lists the hop's frontier (vertices with y != 0) and counts its out-edges; when that is a small share of
+// the graph the hop is done in push form instead: each frontier vertex adds its y to the fp64 accumulator of
+// every member of its row (atomic adds, and one pass finishes all vertices; on large graphs through bins of
+// the row blocks, which finish their vertices).  Which form a hop takes is decided on the device, by the last
+// workgroup of the kernel that counts (reading the frontier's size back cost the host 35 to 60 us per hop, with nothing
+// queued behind it); a launch then walks the hop in the form it takes.  A call is two launches and two per hop:
+// on small graphs they set its time.
 #include "spp_common.h"
 #include "spp_device.h"
 #include "spp_fp64.h"
@@ -34,8 +34,30 @@ namespace spp {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int64_t kPushShare = 16;       // push when the frontier's out-edges are at most M/16
-constexpr int kStatBlocks = 2048;        // most workgroups that report a part of the next frontier's size
+constexpr int kSegments = 2048;          // most workgroups of a kernel that lists a frontier: each has a segment of the list
 constexpr uint32_t kPushed = 1, kPulled = 2;
+
+// What the kernel that writes a hop's y leaves for that hop's walk.  The frontier's vertices are listed per workgroup, in any
+// order, in a segment of `seg_cap` entries (no workgroup waits for another's count); rows above kGiantRow entries
+// go to a list of their own, which all workgroups of the walk take together.
+constexpr int64_t kGiantRow = 32768;
+struct HopList {
+    int32_t*  list;
+    uint32_t* seg_count;                 // null: not listed here (large graphs list the frontier in a launch of its own)
+    int64_t   seg_cap;
+    int       nseg;
+    int32_t*  giants;                    // at most M / kGiantRow
+    uint32_t* ngiants;                   // two counters, used by odd and even hops
+};
+struct HopPlan {
+    int       h;                         // the hop whose frontier this is
+    int64_t   M;
+    unsigned long long* slots;           // see grid_total
+    uint32_t* how;                       // [1 .. L]
+    unsigned long long* cursor;          // of the list made in a launch of its own
+    int64_t*  mirror;                    // pinned host memory: per hop pushed?, frontier edges or -1
+    HopList   l;
+};
 
 struct VipHop {
     const int64_t* rowptr;     // forward CSR, for d(u)
@@ -46,14 +68,17 @@ struct VipHop {
     double         f_next;     // f_{h+1}
     int            first;      // first hop and hop 0 not included: tot is not read
     int            last;
-    unsigned long long* stat;  // per workgroup: out-edges of its part of the next hop's frontier (unused at the last hop)
+    HopPlan        next;       // unused at the last hop
+    int*           bad;        // first hop: the flag for bad training ids, emptied again, and where it goes; else null
+    int64_t*       bad_mirror;
 };
 
 // Finishes vertices u, u + step, ... (U of them, those below N).  S = their sums, told = their running totals (ignored
-// at a first hop).  The loads and the chains of arithmetic of the U vertices are independent.
-template <int U>
+// at a first hop).  The loads and the chains of arithmetic of the U vertices are independent.  emit(vertex, degree) is
+// called for the next hop's frontier.
+template <int U, class Emit>
 __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, int64_t step, int64_t N, const double (&S)[U],
-                                                    const double (&told)[U], unsigned long long& edges) {
+                                                    const double (&told)[U], unsigned long long& edges, Emit emit) {
     // A vertex that no frontier vertex points at has S = 0 exactly (most vertices, at the early hops):
     // its p^[h] is 0 and it needs no exponential; nor does p^[h] at the last hop when it is not asked for.
     double ph[U];
@@ -98,7 +123,10 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
             const double dd = (double)d[k];
             const double t = dd <= a.f_next ? 1.0 : small_quotient(a.f_next, dd);
             if (d[k] > 0) yn[k] = (float)log1p_neg(t * ph[k]);
-            if (yn[k] != 0.0f) edges += (unsigned long long)d[k];
+            if (yn[k] != 0.0f) {
+                edges += (unsigned long long)d[k];
+                emit(u + k * step, d[k]);
+            }
         }
 #pragma unroll
     for (int k = 0; k < U; ++k)
@@ -111,8 +139,8 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
 // All vertices, grid-stride, four per thread and round: the four sums and running totals are in
 // flight together (one vertex per round leaves a pass over 10^8 vertices waiting on its own loads:
 // 0.87 ms where the bytes take 0.55).  sum_of(u) = S_h(u).
-template <class SumOf>
-__device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf sum_of, unsigned long long& edges) {
+template <class SumOf, class Emit>
+__device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf sum_of, unsigned long long& edges, Emit emit) {
     constexpr int U = 4;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += U * stride) {
@@ -121,7 +149,7 @@ __device__ __forceinline__ void vip_finish_all(const VipHop& a, int64_t N, SumOf
         for (int k = 0; k < U; ++k) S[k] = u + k * stride < N ? sum_of(u + k * stride) : 0.0;
 #pragma unroll
         for (int k = 0; k < U; ++k) T0[k] = a.first || u + k * stride >= N ? 0.0 : a.tot[u + k * stride];
-        vip_finish_vertices<U>(a, u, stride, N, S, T0, edges);
+        vip_finish_vertices<U>(a, u, stride, N, S, T0, edges, emit);
     }
 }
 
@@ -136,13 +164,10 @@ __device__ __forceinline__ void vip_finish_block(const VipHop& a, int64_t u0, in
         for (int k = 0; k < U; ++k) S[k] = acc[i + k * kThreads];
 #pragma unroll
         for (int k = 0; k < U; ++k) T0[k] = a.first || u0 + i + k * kThreads >= N ? 0.0 : a.tot[u0 + i + k * kThreads];
-        vip_finish_vertices<U>(a, u0 + i, kThreads, N, S, T0, edges);
+        vip_finish_vertices<U>(a, u0 + i, kThreads, N, S, T0, edges, [](int64_t, int64_t) {});
     }
 }
 
-// The next hop is pushed or pulled depending on the out-edges of its frontier (the vertices with y != 0); the
-// kernel that writes the next hop's y counts them on the way, one sum per workgroup (no atomics: same-address
-// atomics cost about 15 ns each), and vip_decide_kernel adds the sums.
 template <int kThreads>
 __device__ __forceinline__ unsigned long long workgroup_sum(unsigned long long x) {      // in thread 0
     __shared__ unsigned long long red[kThreads / kWave];
@@ -155,23 +180,18 @@ __device__ __forceinline__ unsigned long long workgroup_sum(unsigned long long x
         for (int w = 0; w < kThreads / kWave; ++w) all += red[w];
     return all;
 }
-template <int kThreads = kBlock>
-__device__ __forceinline__ void write_frontier_stat(unsigned long long* stat, unsigned long long edges) {
-    const unsigned long long all = workgroup_sum<kThreads>(edges);
-    if (threadIdx.x == 0) stat[blockIdx.x] = all;
-}
 
 // Adds up one number per workgroup of a launch without a launch of its own: `slots` holds kTotalSlots words, all zero
 // between uses.  A word counts its arrivals above bit 48 beside their sum, so the arrival that completes it has the
 // sum and nothing has to be fenced; 64 workgroups share a word, the last of each group adds to the first word.  Atomics on
 // one address cost about 15 ns each, and so do those on one 128-byte line: each word has a line of its own (side by side,
 // 2048 workgroups took 9 us).  Called by one thread of every workgroup; true for the one that arrives
-// last, which has the total.  A workgroup's number counts as 2^36 at most.
-constexpr int kTotalMax = 4096;          // most workgroups
+// last, which has the total.  A workgroup's number counts as 2^33 at most.
+constexpr int kTotalMax = 16384;         // most workgroups
 constexpr int kTotalLine = 32;           // 64-bit words from one to the next
 constexpr int kTotalSlots = (1 + kTotalMax / 64) * kTotalLine;
 __device__ __forceinline__ bool grid_total(unsigned long long* slots, unsigned long long mine, unsigned long long& total) {
-    constexpr unsigned long long kOne = 1ull << 48, kMost = 1ull << 36;
+    constexpr unsigned long long kOne = 1ull << 48, kMost = 1ull << 33;
     unsigned long long* s = slots + (1 + blockIdx.x / 64) * kTotalLine;
     const unsigned first = blockIdx.x & ~63u, members = gridDim.x - first < 64u ? gridDim.x - first : 64u;
     unsigned long long v = (mine < kMost ? mine : kMost) + kOne;
@@ -184,6 +204,32 @@ __device__ __forceinline__ bool grid_total(unsigned long long* slots, unsigned l
     atomicExch(slots, 0ull);
     total = v & (kOne - 1);
     return true;
+}
+
+// How a hop is walked: pushed if its frontier's out-edges are at most M / kPushShare; pulled without looking after a pulled
+// hop (frontiers that have grown large rarely shrink, and either form is correct for any frontier).  Called by all
+// threads of every workgroup of the kernel that counted the edges.
+template <int kThreads>
+__device__ __forceinline__ void plan_hop(const HopPlan& p, unsigned long long edges) {
+    const unsigned long long mine = workgroup_sum<kThreads>(edges);
+    unsigned long long all;
+    if (threadIdx.x == 0 && grid_total(p.slots, mine, all)) {
+        const bool push = all * kPushShare <= (unsigned long long)p.M;
+        p.how[p.h] = push ? kPushed : kPulled;
+        *p.cursor = 0ull;
+        p.l.ngiants[(p.h + 1) & 1] = 0u;         // the hop after next's
+        p.mirror[2 * (p.h - 1)] = push ? 1 : 0;
+        p.mirror[2 * (p.h - 1) + 1] = (int64_t)all;
+    }
+}
+// By one thread of the kernel that finishes a hop's vertices.
+__device__ __forceinline__ void hop_done(const VipHop& a, bool pulled) {
+    if (a.bad) { *a.bad_mirror = *a.bad; *a.bad = 0; }
+    if (!pulled || a.last) return;
+    const HopPlan& p = a.next;
+    p.how[p.h] = kPulled;
+    p.mirror[2 * (p.h - 1)] = 0;
+    p.mirror[2 * (p.h - 1) + 1] = -1;
 }
 
 __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
@@ -200,14 +246,20 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
     for (int64_t i = tid; i < n; i += stride) p[i] = v;
 }
 
-// What a propagation starts from: no weights, no totals (if hop 0 counts), no bad id seen.
-__global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y, double* __restrict__ tot, int64_t N, int* bad) {
+// What a propagation starts from: no weights, no totals (if hop 0 counts), empty accumulators (if hops add to them
+// directly), no long rows listed.
+__global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y, double* __restrict__ tot, double* __restrict__ acc, int64_t N,
+                                                           uint32_t* __restrict__ ngiants) {
     const int64_t stride = (int64_t)gridDim.x * kBlock, tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     for (int64_t i = tid; i < (N + 3) / 4; i += stride) reinterpret_cast<f32x4*>(y)[i] = z;      // y holds a vector more than N
     if (tot)
         for (int64_t i = tid; i < N; i += stride) tot[i] = 0.0;
-    if (tid == 0) *bad = 0;
+    if (acc) {                                   // holds an even number
+        typedef double f64x2 __attribute__((ext_vector_type(2)));
+        for (int64_t i = tid; i < (N + 1) / 2; i += stride) reinterpret_cast<f64x2*>(acc)[i] = f64x2{0.0, 0.0};
+    }
+    if (tid == 0) ngiants[0] = ngiants[1] = 0u;
 }
 
 // Exclusive prefix sums over a workgroup of kThreads threads; ends with a barrier.
@@ -241,12 +293,12 @@ __device__ __forceinline__ uint32_t bin_block_scan(uint32_t v, uint32_t (&wave_s
 constexpr int64_t kPieceEdges = 4096;
 __host__ __device__ inline int64_t frontier_list_capacity(int64_t N, int64_t M) { return N + M / kPieceEdges; }
 
-// With `how`: only if the hop is pushed.  With `acc`: also empties the accumulators of the vertices it looks at.
+// With `how`: only if the hop is pushed.
 // `lds`: kThreads / kWave words for a scan, and two more.
 template <int kThreads, int kListPer>
 __device__ __forceinline__ void list_frontier(const float* __restrict__ y, const int64_t* __restrict__ rowptr, int64_t N,
                                               int32_t* __restrict__ list, unsigned long long* __restrict__ cursor,
-                                              double* __restrict__ acc, uint32_t* lds) {
+                                              uint32_t* lds) {
     unsigned long long& start = *reinterpret_cast<unsigned long long*>(lds);
     uint32_t (&wave_sum)[kThreads / kWave] = *reinterpret_cast<uint32_t(*)[kThreads / kWave]>(lds + 2);
     const int64_t round = (int64_t)kThreads * kListPer;
@@ -258,12 +310,6 @@ __device__ __forceinline__ void list_frontier(const float* __restrict__ y, const
         const int64_t w0 = r0 + (int64_t)(threadIdx.x >> 6) * (kWave * kListPer);
         auto vertex = [&](int bit) { return w0 + 4 * ((int64_t)(bit >> 2) * kWave + lane_id()) + (bit & 3); };
         uint64_t nz = 0;
-        if (acc)                                 // 16-byte aligned; r0 is even
-            for (int64_t i = r0 + 2 * threadIdx.x; i < r0 + round && i < N; i += 2 * kThreads) {
-                typedef double f64x2 __attribute__((ext_vector_type(2)));
-                if (i + 1 < N) *reinterpret_cast<f64x2*>(acc + i) = f64x2{0.0, 0.0};
-                else acc[i] = 0.0;
-            }
 #pragma unroll
         for (int k = 0; k < kListPer / 4; ++k) {
             const int64_t v = vertex(4 * k);
@@ -295,15 +341,15 @@ template <int kListPer>
 __global__ void __launch_bounds__(kBlock) vip_frontier_list_kernel(const float* __restrict__ y, const int64_t* __restrict__ rowptr,
                                                                    int64_t N, int32_t* __restrict__ list,
                                                                    unsigned long long* __restrict__ cursor,
-                                                                   const uint32_t* __restrict__ how, double* __restrict__ acc) {
+                                                                   const uint32_t* __restrict__ how) {
     __shared__ __align__(8) uint32_t lds[2 + kBlock / kWave];
     if (how && *how != kPushed) return;
-    list_frontier<kBlock, kListPer>(y, rowptr, N, list, cursor, acc, lds);
+    list_frontier<kBlock, kListPer>(y, rowptr, N, list, cursor, lds);
 }
 inline void launch_frontier_list(int grid, hipStream_t st, const float* y, const int64_t* rowptr, int64_t N, int32_t* list,
-                                 unsigned long long* cursor, const uint32_t* how = nullptr, double* acc = nullptr) {
-    if (N >= (int64_t)1 << 22) vip_frontier_list_kernel<64><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how, acc);
-    else vip_frontier_list_kernel<8><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how, acc);
+                                 unsigned long long* cursor, const uint32_t* how = nullptr) {
+    if (N >= (int64_t)1 << 22) vip_frontier_list_kernel<64><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how);
+    else vip_frontier_list_kernel<8><<<grid, kBlock, 0, st>>>(y, rowptr, N, list, cursor, how);
 }
 
 // Entry i of that list: where its piece of the row starts in col[] and how many entries it has.
@@ -325,48 +371,40 @@ __device__ __forceinline__ int32_t frontier_entry(const int32_t* __restrict__ li
     return v;
 }
 
-// How a hop is walked: pushed if its frontier's out-edges are at most M / kPushShare, as counted by the
-// kernel that wrote its y; pulled without looking after a pulled hop (frontiers that have grown large
-// rarely shrink, and either form is correct for any frontier).  One workgroup; also empties the
-// list's cursor.
-__global__ void __launch_bounds__(kBlock) vip_decide_kernel(const unsigned long long* __restrict__ stat, int nstat, int64_t M,
-                                                            int h, uint32_t* __restrict__ how,
-                                                            unsigned long long* __restrict__ cursor,
-                                                            int64_t* __restrict__ mirror, const int* __restrict__ bad) {
-    __shared__ unsigned long long red[kBlock / kWave];
-    unsigned long long edges = 0;
-    for (int i = threadIdx.x; i < nstat; i += kBlock) edges += stat[i];
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) edges += __shfl_down((long long)edges, off, kWave);
-    if (lane_id() == 0) red[threadIdx.x >> 6] = edges;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        edges = red[0] + red[1] + red[2] + red[3];
-        const bool asked = h == 1 || how[h - 1] == kPushed;
-        const bool push = asked && (int64_t)edges * kPushShare <= M;
-        how[h] = push ? kPushed : kPulled;
-        *cursor = 0ull;
-        mirror[2 * (h - 1)] = push ? 1 : 0;
-        mirror[2 * (h - 1) + 1] = asked ? (int64_t)edges : -1;
-        if (h == 1) mirror[2 * SPP_MAX_L] = *bad;
-    }
+// Puts a vertex of the next frontier on this workgroup's list; `n`: a counter in LDS.
+__device__ __forceinline__ void list_vertex(const HopList& l, int h, uint32_t* n, int64_t v, int64_t d) {
+    if (d > kGiantRow) l.giants[atomicAdd(&l.ngiants[h & 1], 1u)] = (int32_t)v;
+    else l.list[(int64_t)blockIdx.x * l.seg_cap + atomicAdd(n, 1u)] = (int32_t)v;
 }
 
-// Finishes all vertices: after a push from the accumulators, after a pull from the shares' sums (unless the
-// pull has finished its vertices itself).
+// Finishes all vertices: after a push from the accumulators, which it empties again, after a pull from the shares' sums
+// (unless the pull has finished its vertices itself).
 __global__ void __launch_bounds__(kBlock) vip_finish_kernel(VipHop a, const uint32_t* __restrict__ how, int fused_pull,
-                                                            const double* __restrict__ acc, int parts, int64_t part_stride,
+                                                            double* __restrict__ acc, int parts, int64_t part_stride,
                                                             int64_t N) {
+    __shared__ uint32_t listed;
     const bool push = *how == kPushed;
-    if (!push && fused_pull) return;
-    const int n = push ? 1 : parts;
+    if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, !push);
     unsigned long long edges = 0;
+    if (push) {
+        if (threadIdx.x == 0) listed = 0u;
+        __syncthreads();
+        vip_finish_all(a, N, [&](int64_t u) {
+            const double S = acc[u];
+            if (S != 0.0) acc[u] = 0.0;
+            return S;
+        }, edges, [&](int64_t v, int64_t d) { list_vertex(a.next.l, a.next.h, &listed, v, d); });
+        if (a.last) return;
+        plan_hop<kBlock>(a.next, edges);         // its barrier: everything is listed
+        if (threadIdx.x == 0) a.next.l.seg_count[blockIdx.x] = listed;
+        return;
+    }
+    if (fused_pull) return;
     vip_finish_all(a, N, [&](int64_t u) {
         double S = acc[u];
-        for (int j = 1; j < n; ++j) S += acc[(int64_t)j * part_stride + u];
+        for (int j = 1; j < parts; ++j) S += acc[(int64_t)j * part_stride + u];
         return S;
-    }, edges);
-    if (!a.last && push) write_frontier_stat(a.stat, edges);
+    }, edges, [](int64_t, int64_t) {});
 }
 
 // Dense hops, blocked: one workgroup takes the j-th of `parts` shares of the edges that end in one
@@ -397,19 +435,16 @@ constexpr int kTileRound = kTileUnroll * kWave;      // vectors of a wavefront's
 constexpr uint32_t kTileWin = 448;      // what 160 KB of LDS leave per wavefront beside the block's sums (16384 in fp64)
 constexpr uint32_t kTileSpan = kTileWin - 4;
 static_assert(kTileWaves * kTileWin * sizeof(float) == kTileWinBytes, "the layout was built for this much LDS beside the sums");
-__global__ void __launch_bounds__(kTileBlock) vip_tile_kernel(const uint32_t* __restrict__ t_edge,
-                                                              const int64_t* __restrict__ first, int nch, int parts,
-                                                              int rbits, uint32_t N, const float* __restrict__ y,
-                                                              double* __restrict__ part, int64_t part_stride,
-                                                              const uint32_t* __restrict__ how) {
-    extern __shared__ double acc[];
-    if (*how != kPulled) return;
+__device__ __forceinline__ void pull_tiles(double* acc, const uint32_t* __restrict__ t_edge,
+                                           const int64_t* __restrict__ first, int nch, int64_t nrb, int parts,
+                                           int rbits, uint32_t N, const float* __restrict__ y,
+                                           double* __restrict__ part, int64_t part_stride) {
     const int R = 1 << rbits;
     float* win = reinterpret_cast<float*>(acc + R) + (threadIdx.x >> 6) * kTileWin;      // this wavefront's
     uint32_t* bound = reinterpret_cast<uint32_t*>(acc + R) + kTileWaves * kTileWin;
     // share-major order: the workgroups that run at the same time take the same share of different
     // blocks, i.e. the same parts of y
-    const int64_t nrb = gridDim.x / parts;
+    if ((int64_t)blockIdx.x >= nrb * parts) return;
     const int64_t rb = blockIdx.x % nrb;
     const int j = (int)(blockIdx.x / nrb);
     const int64_t b0 = first[rb * nch], len = first[(rb + 1) * nch] - b0;
@@ -659,7 +694,7 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
                                                              const uint32_t* __restrict__ x_start,
                                                              const uint32_t* __restrict__ x_prefix, int nch, int parts,
                                                              int64_t N, double* __restrict__ part, int64_t part_stride,
-                                                             VipHop a, const uint32_t* __restrict__ how) {
+                                                             VipHop a, int alone, const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
     if (*how != kPulled) return;
     constexpr int R = 1 << kTileRowBits;
@@ -741,6 +776,7 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
     __syncthreads();
     const int64_t u0 = rb << kTileRowBits;
     if (parts == 1) {
+        if (alone && blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, true);
         unsigned long long edges = 0;            // not asked for: the hop after a pulled one is pulled
         vip_finish_block<R>(a, u0, N, acc, edges);
     } else {
@@ -750,11 +786,14 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
 }
 
 // y_1(v) for the training vertices (p^[0] = min(1, B/|T|), Sec. 3.1); optionally hop 0 into the
-// total; counts hop 1's frontier on the way.
+// total; lists and counts hop 1's frontier on the way (a vertex that T names twice is listed once and counted twice).
 __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restrict__ T, int64_t nT, int64_t N, double p0,
                                                           double f1, const int64_t* __restrict__ rowptr,
                                                           float* __restrict__ y, double* __restrict__ tot, int include_hop0,
-                                                          int* __restrict__ bad, unsigned long long* __restrict__ stat) {
+                                                          int* __restrict__ bad, HopPlan plan) {
+    __shared__ uint32_t listed;
+    if (threadIdx.x == 0) listed = 0u;
+    __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     unsigned long long edges = 0;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nT; i += stride) {
@@ -765,12 +804,16 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
             double t = f1 / (double)d;
             if (t > 1.0) t = 1.0;
             const float yv = (float)log1p(-(t * p0));
-            y[v] = yv;
-            if (yv != 0.0f) edges += (unsigned long long)d;
+            if (yv != 0.0f) {
+                edges += (unsigned long long)d;
+                if (plan.l.seg_count == nullptr) y[v] = yv;
+                else if (atomicCAS(reinterpret_cast<uint32_t*>(&y[v]), 0u, __float_as_uint(yv)) == 0u) list_vertex(plan.l, plan.h, &listed, v, d);
+            }
         }
         if (include_hop0) tot[v] = log1p(-p0);
     }
-    write_frontier_stat(stat, edges);
+    plan_hop<kBlock>(plan, edges);               // its barrier: everything is listed
+    if (plan.l.seg_count && threadIdx.x == 0) plan.l.seg_count[blockIdx.x] = listed;
 }
 
 // ---- Proposition 1 with arbitrary initial and transition probabilities (Sec. 3.1) -------------
@@ -804,10 +847,22 @@ struct FillRule {
     }
 };
 
+// What a hop's kernels count with: the frontier list's cursor, and the bins' (none without bins).
+struct HopCounters {
+    unsigned long long* listed;          // the list's cursor
+    uint32_t* bins;
+    int64_t   nbins;
+    __device__ __forceinline__ void clear(int64_t tid, int64_t stride) const {
+        for (int64_t i = tid; i < nbins; i += stride) bins[i] = 0u;
+        if (tid == 0) *listed = 0ull;
+    }
+};
+
 __global__ void __launch_bounds__(kBlock) vipg_init_kernel(const float* __restrict__ p0, int64_t N,
                                                            float* __restrict__ pcur, double* __restrict__ tot,
-                                                           int include_hop0, int* __restrict__ bad, FillRule rule) {
+                                                           int include_hop0, int* __restrict__ bad, FillRule rule, HopCounters c) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
+    c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
     unsigned long long edges = 0;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
         const unsigned long long deg = rule.degree(v);
@@ -924,17 +979,14 @@ __device__ __forceinline__ int bin_vertex_of(const BinPortion<kThreads>& po, int
     return lo;
 }
 
-// Lays the rows of the portion's vertices end to end; returns the number of edges.  Ends with a barrier; the
-// caller puts one between the last use of a portion and the next call.
-template <int kThreads>
-__device__ __forceinline__ uint32_t bin_load_portion(BinPortion<kThreads>& po, const PortionMap<kThreads>& pm, int64_t portion,
-                                                     const int32_t* __restrict__ list, const float* __restrict__ p,
-                                                     const int64_t* __restrict__ rowptr) {
-    const int nv = pm.count(portion);
+// Lays the rows of the portion's nv vertices end to end; row_of(t, start, length) = the t-th of them.  Returns the number of
+// edges.  Ends with a barrier; the caller puts one between the last use of a portion and the next call.
+template <int kThreads, class RowOf>
+__device__ __forceinline__ uint32_t bin_load_portion(BinPortion<kThreads>& po, int nv, const float* __restrict__ p, RowOf row_of) {
     uint32_t deg = 0;
     if ((int)threadIdx.x < nv) {
         int64_t b;
-        const int32_t v = frontier_entry(list, pm.entry(portion, threadIdx.x), rowptr, b, deg);
+        const int32_t v = row_of((int)threadIdx.x, b, deg);
         po.row[threadIdx.x] = b;
         po.p[threadIdx.x] = p[v];
     }
@@ -981,18 +1033,17 @@ __device__ __forceinline__ uint32_t bin_edge(uint32_t c0, int q) {
     return c0 + (threadIdx.x >> 6) * (kWave * kPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
 }
 
-// Calls f(u, weight) for every edge of this workgroup's portions.
-template <class F>
-__device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf, const int32_t* __restrict__ list,
-                                          const float* __restrict__ y, const int64_t* __restrict__ rowptr,
-                                          const int32_t* __restrict__ col, F f) {
-    const PortionMap<kBinBlock> pm(nf);
+// Calls f(u, weight) for every edge of this workgroup's portions of a frontier of nf entries.
+template <int kThreads, class RowOf, class F>
+__device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t nf, const float* __restrict__ y,
+                                              const int32_t* __restrict__ col, RowOf row_of, F f) {
+    const PortionMap<kThreads> pm(nf);
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
-        const uint32_t total = bin_load_portion(po, pm, portion, list, y, rowptr);
-        for (uint32_t c0 = 0; c0 < total; c0 += kBinBlock * kBinPer) {
+        const uint32_t total = bin_load_portion(po, nv, y, [&](int i, int64_t& b, uint32_t& deg) { return row_of(pm.entry(portion, i), b, deg); });
+        for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) {
             if (bin_edge(c0, 0) >= total) continue;
-            BinCursor<kBinBlock> cu;
+            BinCursor<kThreads> cu;
             cu.start(po, nv, bin_edge(c0, 0));
             int32_t u[kBinPer];
             float w[kBinPer];
@@ -1010,6 +1061,12 @@ __device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf,
         }
         __syncthreads();
     }
+}
+template <class F>
+__device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf, const int32_t* __restrict__ list,
+                                          const float* __restrict__ y, const int64_t* __restrict__ rowptr,
+                                          const int32_t* __restrict__ col, F f) {
+    push_portions(po, nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return frontier_entry(list, i, rowptr, b, deg); }, f);
 }
 
 // Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.
@@ -1029,19 +1086,60 @@ __device__ __forceinline__ void bin_add_entries(double* acc, const uint2* __rest
 }
 
 // Push form of eq. (2) for the uniform weights: every frontier vertex adds y(v) into the
-// accumulator of every member of adj(v) (fp64 global atomics).  Portions of `per` frontier vertices
-// walked as one edge sequence, as above: with one wavefront per vertex the longest row set the
-// kernel's duration (138 us for the 1.2M out-edges of 24k training vertices, degrees up to 20k).
-__global__ void __launch_bounds__(kBinBlock) vip_push_flat_kernel(const int32_t* __restrict__ list,
-                                                                  const unsigned long long* __restrict__ nf_ptr,
-                                                                  const float* __restrict__ y,
-                                                                  const int64_t* __restrict__ rowptr,
-                                                                  const int32_t* __restrict__ col,
-                                                                  double* __restrict__ acc,
-                                                                  const uint32_t* __restrict__ how) {
-    __shared__ BinPortion<kBinBlock> po;
-    if (*how != kPushed) return;
-    push_walk(po, (int64_t)*nf_ptr, list, y, rowptr, col, [&](uint32_t u, float w) { unsafeAtomicAdd(&acc[u], (double)w); });    // hardware fp64 add
+// accumulator of every member of adj(v) (fp64 global atomics).  Portions of frontier vertices walked as one
+// edge sequence, as above: with one wavefront per vertex the longest row set the
+// kernel's duration (138 us for the 1.2M out-edges of 24k training vertices, degrees up to 20k).  The frontier lies in
+// segments; where each starts in the whole is summed up by every workgroup for itself.
+struct PushLds {
+    BinPortion<kTileBlock> po;
+    uint32_t seg_first[kSegments];
+};
+__device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, int h, const float* __restrict__ y,
+                                              const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                              double* __restrict__ acc) {
+    auto add = [&](uint32_t u, float w) { unsafeAtomicAdd(&acc[u], (double)w); };        // hardware fp64 add
+    constexpr int kPer = kSegments / kTileBlock;
+    uint32_t c[kPer], mine = 0, nf;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = (int)threadIdx.x * kPer + k;
+        c[k] = i < l.nseg ? l.seg_count[i] : 0u;
+        mine += c[k];
+    }
+    const uint32_t ng = l.ngiants[h & 1];
+    uint32_t run = bin_block_scan<kTileBlock>(mine, lds.po.wave_sum, nf);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) { lds.seg_first[threadIdx.x * kPer + k] = run; run += c[k]; }
+    __syncthreads();
+    push_portions(lds.po, (int64_t)nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) {
+        int s = 0;                               // the last segment that starts at or before entry i (empty ones start where the next does)
+#pragma unroll
+        for (int step = kSegments / 2; step > 0; step >>= 1)
+            if (lds.seg_first[s + step] <= (uint32_t)i) s += step;
+        const int32_t v = l.list[(int64_t)s * l.seg_cap + ((uint32_t)i - lds.seg_first[s])];
+        b = rowptr[v];
+        deg = (uint32_t)(rowptr[v + 1] - b);
+        return v;
+    }, add);
+    for (uint32_t g = 0; g < ng; ++g) {          // long rows, by all workgroups together
+        const int32_t v = l.giants[g];
+        const float w = y[v];
+        const int64_t e = rowptr[v + 1];
+        for (int64_t k = rowptr[v] + (int64_t)blockIdx.x * kTileBlock + threadIdx.x; k < e; k += (int64_t)gridDim.x * kTileBlock) add((uint32_t)col[k], w);
+    }
+}
+
+// A hop in the form it takes: one launch, whose workgroups push the frontier or pull row blocks.  (A launch for each form,
+// one of which leaves at once, cost a hop 5 us, and listing the frontier in a third the same again.)
+__global__ void __launch_bounds__(kTileBlock) vip_hop_kernel(HopList l, int h, const int64_t* __restrict__ rowptr,
+                                                             const int32_t* __restrict__ col, const uint32_t* __restrict__ t_edge,
+                                                             const int64_t* __restrict__ first, int nch, int64_t nrb, int parts,
+                                                             int rbits, uint32_t N, const float* __restrict__ y,
+                                                             double* __restrict__ acc, int64_t part_stride,
+                                                             const uint32_t* __restrict__ how) {
+    extern __shared__ double hop_lds[];
+    if (*how == kPushed) push_frontier(*reinterpret_cast<PushLds*>(hop_lds), l, h, y, rowptr, col, acc);
+    else if (t_edge) pull_tiles(hop_lds, t_edge, first, nch, nrb, parts, rbits, N, y, acc, part_stride);
 }
 
 // The same push through bins, for graphs in the chunked layout.  The atomics above run at 21 G/s whatever
@@ -1158,9 +1256,10 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
     __syncthreads();
     bin_add_entries(acc, bins, base[blockIdx.x], base[blockIdx.x + 1]);
     __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, false);
     unsigned long long edges = 0;
     vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, edges);
-    if (!a.last) write_frontier_stat<kTileBlock>(a.stat, edges);
+    if (!a.last) plan_hop<kTileBlock>(a.next, edges);
 }
 
 // log1p(-x) for 0 < x <= 1 to a few fp32 ulp.  All terms of a vertex's sum have one sign, so the
@@ -1220,7 +1319,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) char prepare_lds[];
     if (*how != kWhole) {
-        list_frontier<kFillBlock, 8>(pcur, rowptr, N, list, cursor, nullptr, reinterpret_cast<uint32_t*>(prepare_lds));
+        list_frontier<kFillBlock, 8>(pcur, rowptr, N, list, cursor, reinterpret_cast<uint32_t*>(prepare_lds));
         return;
     }
     PrepareLds& l = *reinterpret_cast<PrepareLds*>(prepare_lds);
@@ -1403,7 +1502,9 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
         __syncthreads();
         if ((int64_t)portion >= pm.nportions) break;
         const int nv = pm.count(portion);
-        const uint32_t total = bin_load_portion(po, pm, portion, list, pcur, rowptr);
+        const uint32_t total = bin_load_portion(po, nv, pcur, [&](int i, int64_t& b, uint32_t& deg) {
+            return frontier_entry(list, pm.entry(portion, i), rowptr, b, deg);
+        });
         for (uint32_t c0 = 0; c0 < total; c0 += kFillBlock * kFillPer) {
             uint32_t key[kFillPer], rank[kFillPer];
             float x[kFillPer];
@@ -1444,7 +1545,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
 }
 
 // Adds the entries of one share of one bin into the block's fp64 sums (LDS) and writes them to
-// part[j][row], like vip_tile_kernel but with the weights already in place.
+// part[j][row], like pull_tiles but with the weights already in place.
 __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __restrict__ bins,
                                                                  const uint32_t* __restrict__ cursor,
                                                                  const int64_t* __restrict__ first, int nch, int parts,
@@ -1463,30 +1564,19 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
     for (int i = threadIdx.x; i < R; i += kTileBlock) out[i] = acc[i];
 }
 
-// What a hop's kernels count with: the frontier list's cursor, and the bins' (none without bins).
-struct HopCounters {
-    unsigned long long* listed;          // the list's cursor
-    uint32_t* bins;
-    int64_t   nbins;
-    __device__ __forceinline__ void clear(int64_t tid, int64_t stride) const {
-        for (int64_t i = tid; i < nbins; i += stride) bins[i] = 0u;
-        if (tid == 0) *listed = 0ull;
-    }
-};
-
-__global__ void __launch_bounds__(kBlock) vipg_clear_kernel(HopCounters c, int* __restrict__ bad, unsigned long long* __restrict__ slots) {
-    c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < kTotalSlots; i += kBlock) slots[i] = 0ull;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *bad = 0;
+// The state that a call leaves clean for the next, where it may not be.
+__global__ void __launch_bounds__(kBlock) vip_state_clear_kernel(unsigned long long* __restrict__ slots, int* __restrict__ bad) {
+    for (int i = threadIdx.x; i < kTotalSlots; i += kBlock) slots[i] = 0ull;
+    if (threadIdx.x == 0) *bad = 0;
 }
 
-// Also empties the counters for the next hop.
+// Also empties the counters for the next hop; the last one leaves the flag where the host reads it, and empties it.
 __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __restrict__ acc, double* __restrict__ tot,
                                                              int first, int last, float* __restrict__ p_hop,
                                                              float* __restrict__ p_total, float* __restrict__ pnext,
                                                              int64_t N, int parts, int64_t part_stride, HopCounters c,
-                                                             FillRule rule) {
+                                                             FillRule rule, int* __restrict__ bad, int64_t* __restrict__ bad_mirror) {
+    if (last && blockIdx.x == 0 && threadIdx.x == 0) { *bad_mirror = *bad; *bad = 0; }
     unsigned long long edges = 0;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
@@ -1501,6 +1591,19 @@ __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __res
         else { tot[u] = T; pnext[u] = (float)ph; edges += (float)ph > 0.0f ? deg : 0ull; }
     }
     if (!last) rule.decide(edges);
+}
+
+// The context's words for grid_total and the flag for bad input, emptied here where the call before may not have left them
+// empty: it counts as one that has not until its launches have been accepted.
+static int vip_state(spp_ctx* ctx, unsigned long long** slots, int** bad) {
+    const size_t bytes = kTotalSlots * sizeof(unsigned long long) + sizeof(int);
+    if (ctx->vipstate.bytes < bytes) ctx->vip_state_clean = 0;
+    SPP_TRY(ctx->vipstate.reserve(bytes));
+    *slots = ctx->vipstate.as<unsigned long long>();
+    *bad = reinterpret_cast<int*>(*slots + kTotalSlots);
+    if (!ctx->vip_state_clean) vip_state_clear_kernel<<<1, kBlock, 0, ctx->stream>>>(*slots, *bad);
+    ctx->vip_state_clean = 0;
+    return SPP_OK;
 }
 
 }  // namespace spp
@@ -1518,21 +1621,26 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     const int64_t N = g->N;
     SPP_TRY(ctx->y0.reserve((size_t)N * sizeof(float)));
     SPP_TRY(ctx->y1.reserve((size_t)N * sizeof(float)));
-    SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double) + sizeof(int)));
+    SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double)));
     SPP_TRY(ctx->acc.reserve((size_t)N * sizeof(double)));
     const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + kTotalSlots + SPP_MAX_L + 2) * sizeof(unsigned long long)));
+    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + SPP_MAX_L + 2) * sizeof(unsigned long long)));
+    unsigned long long* slots;
+    int* d_bad;
+    SPP_TRY(vip_state(ctx, &slots, &d_bad));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));
-    unsigned long long* slots = fcount + 4;
-    uint32_t* how = reinterpret_cast<uint32_t*>(slots + kTotalSlots);        // [1 .. L]: how each hop fills its bins
+    uint32_t* how = reinterpret_cast<uint32_t*>(fcount + 4);                 // [1 .. L]: how each hop fills its bins
     float* pcur = ctx->y0.as<float>();
     float* pnext = ctx->y1.as<float>();
     double* tot = ctx->tot.as<double>();
     double* acc = ctx->acc.as<double>();
-    int* d_bad = reinterpret_cast<int*>(tot + N);
+    int64_t* bad_mirror = ctx->h_pinned + kHopMirror + 2 * SPP_MAX_L;
     const int include0 = (flags & SPP_VIP_INCLUDE_HOP0) ? 1 : 0;
-    const int fill_grid = ctx->num_cu * 8 < kTotalMax ? ctx->num_cu * 8 : kTotalMax;
+    // a workgroup per 256 vertices, up to eight per CU: launching and counting 2048 of them cost a 10k-vertex graph more than
+    // its vertices (122 us a call; 97 with forty)
+    int fill_grid = ctx->num_cu * 8 < kTotalMax ? ctx->num_cu * 8 : kTotalMax;
+    if ((N + kBlock - 1) / kBlock < fill_grid) fill_grid = (int)((N + kBlock - 1) / kBlock);
     // With the row-block structure at hand the push goes through bins (no global fp64 atomics).
     const bool binned = g->has_in && g->nrb > 0 && g->nrb <= kBinMaxBlocks && g->M > 0;
     int parts = 1;
@@ -1543,6 +1651,9 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     uintptr_t low = reinterpret_cast<uintptr_t>(g->col);
     for (int h = 0; h < L; ++h) low |= reinterpret_cast<uintptr_t>(d_t[h]);
     const bool tiles = binned && g->tile_off != nullptr && (low & 15) == 0;
+    // two workgroups per CU, fewer where neither the tiles nor the rounds of the list need them; a multiple of eight
+    const int64_t prepare_most = g->part_tiles > N / (8 * kFillBlock) ? g->part_tiles : N / (8 * kFillBlock) + 1;
+    const int prepare_grid = prepare_most < ctx->num_cu * 2 ? (int)((prepare_most + 7) / 8 * 8) : ctx->num_cu * 2 / 8 * 8;
     const size_t fill_lds = binned ? 2 * (size_t)g->nrb * sizeof(uint32_t) : 0;
     const size_t sum_lds = binned ? sizeof(double) << g->tile_rbits : 0;
     if (binned) {
@@ -1572,13 +1683,12 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
         const HopCounters counters{fcount + 2, cursor, binned ? g->nrb + 1 : 0};
         FillRule rule{tiles ? g->rowptr : nullptr, g->M, slots, how + 1};
-        vipg_clear_kernel<<<(unsigned)(counters.nbins / kBlock + 1), kBlock, 0, st>>>(counters, d_bad, slots);
-        vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad, rule);
+        vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad, rule, counters);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
             const uint32_t* how_h = tiles ? how + h : nullptr;
             if (tiles)
-                vipg_prepare_kernel<<<ctx->num_cu * 2, kFillBlock, sizeof(PrepareLds), st>>>(
+                vipg_prepare_kernel<<<prepare_grid, kFillBlock, sizeof(PrepareLds), st>>>(
                     how_h, g->tile_off, g->tile_row, (int)g->part_tiles, g->M, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits,
                     (int)g->nrb, bins, d_bad, N, flist, fcount + 2);
             else
@@ -1598,17 +1708,16 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
             rule.how = how + h + 1;
             vipg_finish_kernel<<<fill_grid, kBlock, 0, st>>>(acc, tot, (h == 1 && !include0) ? 1 : 0, h == L ? 1 : 0,
                                                              d_p_hop ? d_p_hop + (int64_t)(h - 1) * N : nullptr,
-                                                             d_p_total, pnext, N, parts, part_stride, counters, rule);
+                                                             d_p_total, pnext, N, parts, part_stride, counters, rule, d_bad, bad_mirror);
             float* tmp = pcur; pcur = pnext; pnext = tmp;
         }
     }
     SPP_HIP(hipGetLastError());
+    ctx->vip_state_clean = 1;
     ctx->vip_hops = -L;
     if (flags & SPP_SYNC) {
-        int bad = 0;
-        SPP_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
         SPP_HIP(hipStreamSynchronize(st));
-        SPP_CHECK(bad == 0, SPP_E_ARG, "spp_vip_propagate_general: a probability lies outside [0, 1]; it was taken as 0");
+        SPP_CHECK(*bad_mirror == 0, SPP_E_ARG, "spp_vip_propagate_general: a probability lies outside [0, 1]; it was taken as 0");
     }
     return SPP_OK;
 }
@@ -1629,7 +1738,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     SPP_TRY(ctx->y0.reserve((size_t)(N + 4) * sizeof(float)));       // dense hops read y as whole vectors of four
     SPP_TRY(ctx->y1.reserve((size_t)(N + 4) * sizeof(float)));
     static_assert(2 * SPP_MAX_L + 1 <= 64, "fits the mirror");
-    SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double) + sizeof(int)));
+    SPP_TRY(ctx->tot.reserve((size_t)N * sizeof(double)));
     int parts = tile_parts(ctx->num_cu, g->nrb, g->M);
     // the chunked layout: with a row block per CU or more, one workgroup takes a whole block and
     // finishes its vertices itself (no partial sums leave the chip)
@@ -1637,7 +1746,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     const int64_t part_stride = g->nrb << g->tile_rbits;
     {
         const size_t tile_bytes = (size_t)parts * (size_t)part_stride * sizeof(double);
-        const size_t push_bytes = (size_t)N * sizeof(double);
+        const size_t push_bytes = (size_t)(N + 1) * sizeof(double);
         SPP_TRY(ctx->acc.reserve(tile_bytes > push_bytes ? tile_bytes : push_bytes));
     }
     // The push goes through bins where the chunked layout's value memory holds the entries (8 bytes for at most
@@ -1653,10 +1762,11 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     const size_t x_lds_expand = (sizeof(float) << kXSrcBits) + sizeof(float);
     static_assert(kXPad == (1u << kXSrcBits), "a padding entry indexes the slot after the chunk's values");
     const size_t x_lds_reduce = (sizeof(double) << kTileRowBits) + (2 * kXGroup + 1) * sizeof(uint32_t);
-    if (!g->has_x && ctx->tile_lds_set < (int)lds_bytes) {        // more than the 64 KB a launch may ask for by default
-        SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_tile_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
-        ctx->tile_lds_set = (int)lds_bytes;
+    const size_t hop_lds = g->has_x || lds_bytes < sizeof(PushLds) ? sizeof(PushLds) : lds_bytes;
+    if (!binned && ctx->tile_lds_set < (int)hop_lds) {        // more than the 64 KB a launch may ask for by default
+        SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_hop_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)hop_lds));
+        ctx->tile_lds_set = (int)hop_lds;
     }
     if (g->has_x) {
         if (!ctx->x_lds_set) {
@@ -1675,32 +1785,45 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         }
         SPP_TRY(ctx->xvals.reserve((size_t)(g->x_entries > 0 ? g->x_entries : 4) * sizeof(float)));
     }
-    // the kernels that write a hop's y run this many workgroups; each leaves the size of the part of
-    // the next frontier it saw (at most kStatBlocks sums, or one per row block)
-    const int fill_grid = ctx->num_cu * 8 < kStatBlocks ? ctx->num_cu * 8 : kStatBlocks;
-    const size_t nstat_max = binned && g->nrb > kStatBlocks ? (size_t)g->nrb : (size_t)kStatBlocks;
-    const int64_t lcap = frontier_list_capacity(N, g->M);
-    SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + nstat_max + SPP_MAX_L + 1) * sizeof(unsigned long long)));
+    // A workgroup per 256 vertices, up to eight per CU (the finishing pass takes four vertices per thread and round: its
+    // workgroups see no more than a round's vertices in kSegments segments, or ceil of their share).
+    const int most = ctx->num_cu * 8 < kSegments ? ctx->num_cu * 8 : kSegments;
+    auto groups = [&](int64_t n) { const int64_t w = (n + kBlock - 1) / kBlock; return (int)(w < 1 ? 1 : w < most ? w : most); };
+    auto per_group = [&](int64_t n) { return (n + (int64_t)groups(n) * kBlock - 1) / ((int64_t)groups(n) * kBlock) * kBlock; };
+    const int vgrid = groups(N), tgrid = groups(nT);
+    // the frontier: in segments of the workgroups that list it, or (bins) as one list with the pieces of long rows
+    const int64_t seg_all = vgrid * per_group(N) > tgrid * per_group(nT) ? vgrid * per_group(N) : tgrid * per_group(nT);
+    int64_t lcap = binned ? frontier_list_capacity(N, g->M) : seg_all + g->M / kGiantRow + kSegments + 2;
+    lcap += lcap & 1;
+    SPP_TRY(ctx->frontier.reserve((size_t)lcap * sizeof(int32_t) + (1 + SPP_MAX_L + 2) * sizeof(unsigned long long)));
+    unsigned long long* slots;
+    int* d_bad;
+    SPP_TRY(vip_state(ctx, &slots, &d_bad));
     int32_t* flist = ctx->frontier.as<int32_t>();
-    unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));    // [2]: cursor of the list
-    unsigned long long* fstat = fcount + 4;
-    uint32_t* how = reinterpret_cast<uint32_t*>(fstat + nstat_max);      // [1 .. L]: how each hop is walked
+    uint32_t* seg_count = reinterpret_cast<uint32_t*>(flist + seg_all);
+    int32_t* giants = reinterpret_cast<int32_t*>(seg_count + kSegments);
+    unsigned long long* fcursor = reinterpret_cast<unsigned long long*>(flist + lcap);       // of the one list
+    uint32_t* how = reinterpret_cast<uint32_t*>(fcursor + 1);            // [1 .. L]: how each hop is walked
+    uint32_t* ngiants = how + SPP_MAX_L + 1;
     int64_t* mirror = ctx->h_pinned + kHopMirror;
     float* ycur = ctx->y0.as<float>();
     float* ynext = ctx->y1.as<float>();
     double* tot = ctx->tot.as<double>();
-    int* d_bad = reinterpret_cast<int*>(tot + N);
     const int include0 = (flags & SPP_VIP_INCLUDE_HOP0) ? 1 : 0;
     double p0 = (double)B / (double)nT;
     if (p0 > 1.0) p0 = 1.0;
 
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
-        vip_clear_kernel<<<fill_grid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, N, d_bad);
-        vip_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_T, nT, N, p0, (double)fanouts[0], g->rowptr, ycur, tot, include0,
-                                                      d_bad, fstat);
+        double* acc = ctx->acc.as<double>();
+        HopPlan plan{1, g->M, slots, how, fcursor, mirror, {flist, binned ? nullptr : seg_count, per_group(nT), tgrid, giants, ngiants}};
+        vip_clear_kernel<<<vgrid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, binned ? nullptr : acc, N, ngiants);
+        vip_init_kernel<<<tgrid, kBlock, 0, st>>>(d_T, nT, N, p0, (double)fanouts[0], g->rowptr, ycur, tot, include0, d_bad, plan);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
+            const HopList walked = plan.l;
+            plan.h = h + 1;
+            plan.l.seg_cap = per_group(N); plan.l.nseg = vgrid;
             VipHop a;
             a.rowptr = g->rowptr;
             a.y_next = ynext; a.tot = tot;
@@ -1709,23 +1832,27 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             a.f_next = h < L ? (double)fanouts[h] : 0.0;
             a.first = (h == 1 && !include0) ? 1 : 0;
             a.last = (h == L) ? 1 : 0;
-            a.stat = fstat;
-            double* acc = ctx->acc.as<double>();
+            a.next = plan;
+            a.bad = h == 1 ? d_bad : nullptr;
+            a.bad_mirror = mirror + 2 * SPP_MAX_L;
             const uint32_t* how_h = how + h;
-            vip_decide_kernel<<<1, kBlock, 0, st>>>(fstat, h > 1 && binned ? (int)g->nrb : fill_grid, g->M, h, how, fcount + 2, mirror, d_bad);
-            launch_frontier_list(fill_grid, st, ycur, g->rowptr, N, flist, fcount + 2, how_h, binned ? nullptr : acc);
             if (binned) {
                 uint2* bins = ctx->xvals.as<uint2>();
                 uint32_t* off = reinterpret_cast<uint32_t*>(bins + bin_entries);
                 uint32_t* total = off + (size_t)kPushGroups * (size_t)g->nrb;
                 uint32_t* base = total + g->nrb;
-                vip_bin_count_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, (int)g->nrb, off, how_h);
+                launch_frontier_list(most, st, ycur, g->rowptr, N, flist, fcursor, how_h);
+                vip_bin_count_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcursor, ycur, g->rowptr, g->col, (int)g->nrb, off, how_h);
                 vip_bin_offsets_kernel<<<(unsigned)((g->nrb + kOffBins - 1) / kOffBins), 1024, 0, st>>>(off, (int)g->nrb, total, how_h);
-                vip_bin_fill_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, (int)g->nrb, off,
+                vip_bin_fill_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcursor, ycur, g->rowptr, g->col, (int)g->nrb, off,
                                                                             total, base, bins, how_h);
                 vip_bin_finish_kernel<<<(unsigned)g->nrb, kTileBlock, bin_sum_lds, st>>>(a, bins, base, N, how_h);
             } else {
-                vip_push_flat_kernel<<<ctx->num_cu * 8, kBinBlock, 0, st>>>(flist, fcount + 2, ycur, g->rowptr, g->col, acc, how_h);
+                // as many workgroups as there are shares of row blocks, and one per CU at least for a push
+                const int64_t shares = g->has_x ? 0 : g->nrb * parts;
+                vip_hop_kernel<<<(unsigned)(shares > ctx->num_cu ? shares : ctx->num_cu), kTileBlock, hop_lds, st>>>(
+                    walked, h, g->rowptr, g->col, g->t_edge, g->tile_first, g->nch, g->nrb, parts, g->tile_rbits, (uint32_t)N, ycur, acc,
+                    part_stride, how_h);
             }
             int fused = 0;
             if (g->has_x) {
@@ -1734,17 +1861,15 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 vip_expand_kernel<<<egrid, kXBlock, x_lds_expand, st>>>(g->x_src, g->x_chunk_first, g->x_nch, N, ycur,
                                                                         ctx->xvals.as<float>(), how_h);
                 vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(
-                    ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, a, how_h);
+                    ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, a, binned, how_h);
                 fused = parts == 1;
-            } else {
-                vip_tile_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, lds_bytes, st>>>(
-                    g->t_edge, g->tile_first, g->nch, parts, g->tile_rbits, (uint32_t)N, ycur, acc, part_stride, how_h);
             }
-            if (!(binned && fused)) vip_finish_kernel<<<fill_grid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N);
+            if (!binned) vip_finish_kernel<<<vgrid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N);
             float* t = ycur; ycur = ynext; ynext = t;
         }
     }
     SPP_HIP(hipGetLastError());
+    ctx->vip_state_clean = 1;
     ctx->vip_hops = L;
     // training ids are checked on the device; the flag is read when the caller asks to wait
     if (flags & SPP_SYNC) {

@@ -1,0 +1,75 @@
+"""GPU: the frontier that a hop's writer lists for the next hop's push -- segments of one and of several rounds of
+vertices, ids that the training set names more than once, rows long enough for the list that all workgroups walk
+together (more than 32768 entries), at the first hop and reached by it -- against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def spp():
+    import paper_2305_03152_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(spp):
+    c = spp.Context(0)
+    yield c
+    c.close()
+
+
+def _graph(deg):
+    """Vertex v points at v+1 .. v+deg[v] (mod N)."""
+    N = deg.size
+    rp = np.zeros(N + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    row = np.repeat(np.arange(N), deg)
+    col = (row + 1 + np.arange(rp[-1]) - rp[row]) % N
+    wrap = np.flatnonzero(np.arange(N) + deg >= N)
+    for v in wrap:
+        col[rp[v]:rp[v + 1]].sort()
+    return rp, col.astype(np.int32)
+
+
+def _case(name):
+    if name == "giants":                 # the first is in T, the second is reached by vertex 10, the third by the first
+        deg = np.full(220_000, 16)
+        deg[50], deg[11], deg[20_000], deg[99_000] = 32769, 70_000, 32768, 33_000
+        return deg, np.array([10, 50, 150_000, 219_990], np.int32)
+    if name == "named_twice":
+        deg = np.full(60_000, 9)
+        T = np.arange(1500, dtype=np.int32) * 17
+        return deg, np.concatenate([T, T[:700], T[:1]])
+    if name == "rounds":                 # more training vertices than 2048 workgroups take in a round, all with one edge
+        deg = np.full(1_400_000, 14)
+        T = (np.arange(600_000, dtype=np.int64) * 2).astype(np.int32)
+        deg[T] = 1
+        return deg, T
+    deg = np.full(300, 20)               # "one": a single training vertex, the last
+    return deg, np.array([299], np.int32)
+
+
+@pytest.mark.parametrize("name", ["giants", "named_twice", "rounds", "one"])
+@pytest.mark.parametrize("chunked", [False, True])
+def test_listed_frontiers(spp, ctx, name, chunked):
+    print("[case]", name, chunked, flush=True)
+    deg, T = _case(name)
+    rp, col = _graph(deg)
+    dev = torch.device("cuda:0")
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True, chunked=chunked)
+    fanouts, batch = (3, 40_000, 5), max(1, T.size // 3)
+    for _ in range(2):                   # a call leaves its counters and accumulators as the next one expects them
+        p, ph = spp.vip_propagate(ctx, G, torch.from_numpy(T).to(dev), batch, fanouts, per_hop=True)
+        pushed, edges = spp.vip_last_hops(ctx, len(fanouts))
+        assert pushed[0] and edges[0] == int(deg[T].sum())
+        ref_t, ref_h = oracle.vip(rp, col, T, batch, fanouts)
+        for got, ref in ((p, ref_t), (ph, ref_h)):
+            # results are rounded to fp32 at every hop: 6e-8 a hop, well below the 1e-5 the entry point states
+            assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.asarray(ref) + 1e-37)
+    G.close()
