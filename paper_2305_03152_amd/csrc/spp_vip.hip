@@ -586,7 +586,7 @@ inline int tile_parts(int num_cu, int64_t nrb, int64_t M) {
 // in LDS (128 KB) and writes y[source] for entries of the chunk, in entry order: 2 bytes read and 4
 // written per entry, all of it streamed.  The workgroups, one per CU, take equal shares of all entries and go
 // from chunk to chunk inside theirs (a workgroup per chunk left CUs idle in the last round: 428 chunks on 256 CUs
-// took 629 us for 400M entries, shares 569).  Second pass: one workgroup per row
+// took 629 us for 400M entries, shares 569; 546 now).  Second pass: one workgroup per row
 // block keeps the block's fp64 sums in LDS and adds up the block's pieces, one from every chunk
 // (4 + 2 bytes read per entry in runs of about a hundred entries, found through two tables that are
 // staged in LDS 2048 pieces at a time), then finishes the block's vertices itself.  12 bytes per
@@ -653,31 +653,38 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
                 for (int64_t q = wq0 + (threadIdx.x & (kWave - 1)); q < wq1; q += kWave) __builtin_nontemporal_store(z, out + q);
                 continue;
             }
-            // the next round's entries are in flight while this round's values are looked up and stored
+            // The next round's entries are in flight while this round's values are looked up and stored.  They are asked for
+            // before the stores, which a later load would wait for, and unconditionally (past the end the tile's last
+            // vector once more): after a conditional load the compiler waits for all that is in flight.  400M entries: 546 us
+            // instead of 572.
             constexpr int64_t kRound = (int64_t)kWave * kXUnroll;
-            u16x4 s[kXUnroll];
+            struct Sources { u16x4 v[kXUnroll]; };
+            auto load = [&](int64_t q) {
+                Sources s;
+#pragma unroll
+                for (int u = 0; u < kXUnroll; ++u) s.v[u] = __builtin_nontemporal_load(sv + (q + u * kWave < wq1 ? q + u * kWave : wq1 - 1));
+                return s;
+            };
+            auto store = [&](const u16x4& s, int64_t q) {
+                f32x4 w;
+                w.x = ych[s.x];
+                w.y = ych[s.y];
+                w.z = ych[s.z];
+                w.w = ych[s.w];
+                __builtin_nontemporal_store(w, out + q);
+            };
             int64_t q = wq0 + (threadIdx.x & (kWave - 1));
+            Sources s = load(q);
+            for (int64_t r = wq0; r + kRound <= wq1; r += kRound, q += kRound) {
+                const Sources n = load(q + kRound);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < kXUnroll; ++u) store(s.v[u], q + u * kWave);
+                s = n;
+            }
 #pragma unroll
             for (int u = 0; u < kXUnroll; ++u)
-                if (q + u * kWave < wq1) s[u] = __builtin_nontemporal_load(sv + q + u * kWave);
-            for (; q < wq1; q += kRound) {
-                u16x4 n[kXUnroll];
-#pragma unroll
-                for (int u = 0; u < kXUnroll; ++u)
-                    if (q + kRound + u * kWave < wq1) n[u] = __builtin_nontemporal_load(sv + q + kRound + u * kWave);
-#pragma unroll
-                for (int u = 0; u < kXUnroll; ++u)
-                    if (q + u * kWave < wq1) {
-                        f32x4 w;
-                        w.x = ych[s[u].x];
-                        w.y = ych[s[u].y];
-                        w.z = ych[s[u].z];
-                        w.w = ych[s[u].w];
-                        __builtin_nontemporal_store(w, out + q + u * kWave);
-                    }
-#pragma unroll
-                for (int u = 0; u < kXUnroll; ++u) s[u] = n[u];
-            }
+                if (q + u * kWave < wq1) store(s.v[u], q + u * kWave);
         }
         __syncthreads();                 // the next chunk overwrites ych
     }
