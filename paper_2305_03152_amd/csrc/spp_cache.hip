@@ -315,14 +315,14 @@ extern "C" int spp_build_vip_cache(spp_ctx* ctx, const float* d_score, int64_t N
         int shift = 32;
         for (uint32_t t = cap; t > 1; t >>= 1) --shift;
         c->table_mask = cap - 1; c->table_shift = shift;
-        if (hipMalloc(&c->table, (size_t)cap * sizeof(uint64_t)) != hipSuccess) {
+        if (pool_take(c->device, &c->table, (size_t)cap * sizeof(uint64_t)) != hipSuccess) {
             set_error("spp_build_vip_cache: out of device memory for the id table"); fail(SPP_E_OOM); break;
         }
         fill_table_kernel<<<ctx->num_cu * 4, kBlock, 0, st>>>(reinterpret_cast<unsigned long long*>(c->table), cap, ~0ull);
         cache_fill_kernel<<<(unsigned)((keep + kBlock - 1) / kBlock), kBlock, 0, st>>>(
             sorted, keep, lo, hi, d_cache_ids, rowidx, reinterpret_cast<unsigned long long*>(c->table), c->table_mask, shift);
         if (remote) {
-            if (hipMalloc(&c->rows, (size_t)keep * (size_t)c->row_bytes) != hipSuccess) {
+            if (pool_take(c->device, &c->rows, (size_t)keep * (size_t)c->row_bytes) != hipSuccess) {
                 set_error("spp_build_vip_cache: out of device memory for %lld cached rows", (long long)keep); fail(SPP_E_OOM); break;
             }
             rc = copy_rows_indexed(st, remote, rowidx, keep, c->row_bytes, c->rows, ctx->num_cu);
@@ -343,8 +343,8 @@ extern "C" void spp_cache_destroy(spp_cache* c) {
     if (!c) return;
     if (hipSetDevice(c->device) != hipSuccess) { (void)hipGetLastError(); delete c; return; }   // runtime already shut down
     (void)hipDeviceSynchronize();      // a gather that still reads the cache may be in flight
-    if (c->table) (void)hipFree(c->table);
-    if (c->rows) (void)hipFree(c->rows);
+    spp::pool_give(c->device, c->table);
+    spp::pool_give(c->device, c->rows);
     delete c;
 }
 

@@ -19,9 +19,14 @@
 namespace spp {
 
 // Every kernel of the library indexes with these arrays, so they are checked once here: offsets
-// monotone inside [0, M], column ids inside [0, N).
+// monotone inside [0, M], column ids inside [0, N).  Nothing is read of col[] unless the CSR says that it has M entries.
+// found: rowptr[0], rowptr[N], whether something is wrong (zero before).
 __global__ void __launch_bounds__(kBlock) validate_csr_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
-                                                              const int32_t* __restrict__ col, int* __restrict__ bad) {
+                                                              const int32_t* __restrict__ col, int64_t* __restrict__ found) {
+    const int64_t first = rowptr[0], last = rowptr[N];
+    if (blockIdx.x == 0 && threadIdx.x == 0) { found[0] = first; found[1] = last; }
+    if (first != 0 || last != M) return;
+    int64_t* __restrict__ bad = found + 2;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     for (int64_t v = t; v < N; v += stride) {
@@ -376,30 +381,31 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
     static_assert(kPartMaxBlocks <= 512, "nine bits name a block");
     g->tile_rbits = rbits; g->nrb = nrb; g->nch = nch;
     const int64_t nfirst = nrb * nch + 1;
-    SPP_HIP(hipMalloc(&g->tile_first, (size_t)nfirst * sizeof(int64_t)));
-    SPP_HIP(hipMalloc(&g->t_edge, (size_t)(M > 0 ? M : 1) * sizeof(uint32_t)));
-    fill_i64_kernel<<<grid, kBlock, 0, st>>>(g->tile_first, nfirst, M);
+    SPP_HIP(pool_take(g->device, &g->tile_first, (size_t)nfirst * sizeof(int64_t)));
+    SPP_HIP(pool_take(g->device, &g->t_edge, (size_t)(M > 0 ? M : 1) * sizeof(uint32_t)));
+    SPP_HIP(pool_take(g->device, &g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
+    const unsigned bf_grid = (unsigned)((nrb + 1 + kBlock - 1) / kBlock);
     if (M > 0) {
         const int64_t ntiles = (M + kPartTile - 1) / kPartTile;
         const int64_t nhist = nrb * ntiles;
         const int scan_grid = 1024;
         // one allocation: the counts (then offsets) and the tiles' first rows, which the graph keeps, the scan's
         // partial sums, the sums of the edges' mixes and a flag
-        struct { unsigned long long mix[2]; int bad, pad; } head = {{0, 0}, 0, 0}, back;
-        const size_t bytes = sizeof(head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
+        struct Head { unsigned long long mix[2]; int bad, pad; } back;
+        const size_t bytes = sizeof(Head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
         char* tmp = nullptr;
-        if (hipMalloc(&tmp, bytes) != hipSuccess) {
+        if (pool_take(g->device, &tmp, bytes) != hipSuccess) {
             (void)hipGetLastError();
             set_error("row blocks: out of device memory for %zu bytes of counts", bytes);
             return SPP_E_OOM;
         }
         unsigned long long* mix = reinterpret_cast<unsigned long long*>(tmp);
         int* d_bad = reinterpret_cast<int*>(mix + 2);
-        uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(head));
+        uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(Head));
         int* partial = reinterpret_cast<int*>(hist + nhist);
         int32_t* tile_row = partial + scan_grid;
         int rc = SPP_OK;
-        hipError_t e = hipMemcpyAsync(tmp, &head, sizeof(head), hipMemcpyHostToDevice, st);
+        hipError_t e = hipMemsetAsync(tmp, 0, sizeof(Head), st);
         if (e == hipSuccess) {
             const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
             part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row);
@@ -417,9 +423,11 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             const int parts = (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
             tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
                                                                                      mix + 1, d_bad);
-            e = hipMemcpyAsync(&back, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
+            block_first_from_tiles_kernel<<<bf_grid, kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
+            e = hipMemcpyAsync(ctx->h_pinned, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(st);
+        memcpy(&back, ctx->h_pinned, sizeof(back));
         if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) { set_error("row blocks: %s", hipGetErrorString(e)); rc = SPP_E_HIP; }
         else if (back.bad || back.mix[0] != back.mix[1]) {
@@ -429,9 +437,11 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         SPP_TRY(rc);
         g->tile_off = hist; g->tile_row = tile_row; g->part_tiles = ntiles;
     }
-    SPP_HIP(hipMalloc(&g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
-    block_first_from_tiles_kernel<<<(unsigned)((nrb + 1 + kBlock - 1) / kBlock), kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
-    SPP_HIP(hipStreamSynchronize(st));
+    if (M == 0) {
+        fill_i64_kernel<<<grid, kBlock, 0, st>>>(g->tile_first, nfirst, M);
+        block_first_from_tiles_kernel<<<bf_grid, kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
+        SPP_HIP(hipStreamSynchronize(st));
+    }
     return SPP_OK;
 }
 
@@ -693,10 +703,10 @@ static int build_chunked(spp_ctx* ctx, spp_graph* g) {
     SPP_CHECK(M + 3 * npieces < ((int64_t)1 << 34), SPP_E_ARG, "chunked layout: %lld edges in %lld pieces exceed 2^32 vectors",
               (long long)M, (long long)npieces);
     g->tile_rbits = kTileRowBits; g->nrb = nrb; g->x_nch = nch;
-    SPP_HIP(hipMalloc(&g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
-    SPP_HIP(hipMalloc(&g->x_chunk_first, (size_t)(nch + 1) * sizeof(int64_t)));
-    SPP_HIP(hipMalloc(&g->x_start, (size_t)npieces * sizeof(uint32_t)));
-    SPP_HIP(hipMalloc(&g->x_prefix, (size_t)nrb * (nch + 1) * sizeof(uint32_t)));
+    SPP_HIP(pool_take(g->device, &g->block_first, (size_t)(nrb + 1) * sizeof(int64_t)));
+    SPP_HIP(pool_take(g->device, &g->x_chunk_first, (size_t)(nch + 1) * sizeof(int64_t)));
+    SPP_HIP(pool_take(g->device, &g->x_start, (size_t)npieces * sizeof(uint32_t)));
+    SPP_HIP(pool_take(g->device, &g->x_prefix, (size_t)nrb * (nch + 1) * sizeof(uint32_t)));
     XBuild t;
     SPP_HIP(hipMalloc(&t.first, (size_t)(npieces + 1) * sizeof(int64_t)));
     SPP_HIP(hipMalloc(&t.padded, (size_t)(npieces + 1) * sizeof(int64_t)));
@@ -723,8 +733,8 @@ static int build_chunked(spp_ctx* ctx, spp_graph* g) {
     SPP_CHECK(entries >= M && entries <= M + 3 * npieces && (entries & 3) == 0, SPP_E_HIP,
               "chunked layout: %lld entries for %lld edges in %lld pieces", (long long)entries, (long long)M, (long long)npieces);
     g->x_entries = entries;
-    SPP_HIP(hipMalloc(&g->x_src, (size_t)(entries > 0 ? entries : 4) * sizeof(uint16_t)));
-    SPP_HIP(hipMalloc(&g->x_row, (size_t)(entries > 0 ? entries : 4) * sizeof(uint16_t)));
+    SPP_HIP(pool_take(g->device, &g->x_src, (size_t)(entries > 0 ? entries : 4) * sizeof(uint16_t)));
+    SPP_HIP(pool_take(g->device, &g->x_row, (size_t)(entries > 0 ? entries : 4) * sizeof(uint16_t)));
     if (M > 0) x_entries_kernel<<<grid, kBlock, 0, st>>>(sorted, M, bbits, nrb, t.first, t.padded, g->x_src, g->x_row);
     x_padding_kernel<<<grid, kBlock, 0, st>>>(npieces, t.first, t.padded, g->x_src, g->x_row);
     x_tables_kernel<<<(unsigned)((nrb + kBlock - 1) / kBlock), kBlock, 0, st>>>(nrb, nch, t.first, t.padded, g->x_start,
@@ -757,28 +767,27 @@ extern "C" int spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_
     SPP_CHECK(M >= 0 && M < 0xFFFFFFFFll, SPP_E_ARG, "spp_graph_create: M = %lld out of range", (long long)M);
     SPP_CHECK(d_rowptr && (d_col || M == 0), SPP_E_ARG, "spp_graph_create: null CSR array");
     SPP_HIP(hipSetDevice(ctx->device));
-    // the CSR must really describe M edges
-    int64_t ends[2] = {-1, -1};
-    SPP_HIP(hipMemcpy(&ends[0], d_rowptr, sizeof(int64_t), hipMemcpyDeviceToHost));
-    SPP_HIP(hipMemcpy(&ends[1], d_rowptr + N, sizeof(int64_t), hipMemcpyDeviceToHost));
-    SPP_CHECK(ends[0] == 0 && ends[1] == M, SPP_E_ARG, "spp_graph_create: rowptr[0] = %lld, rowptr[N] = %lld, M = %lld",
-              (long long)ends[0], (long long)ends[1], (long long)M);
     spp_graph* g = new (std::nothrow) spp_graph();
     SPP_CHECK(g != nullptr, SPP_E_OOM, "spp_graph_create: out of host memory");
     g->device = ctx->device; g->N = N; g->M = M; g->rowptr = d_rowptr; g->col = d_col;
     {
-        int* d_bad = nullptr;
-        int bad = 0;
-        hipError_t e = hipMalloc(&d_bad, sizeof(int));
-        if (e == hipSuccess) e = hipMemsetAsync(d_bad, 0, sizeof(int), ctx->stream);
+        // the CSR must really describe M edges
+        int64_t* d_found = nullptr;
+        int64_t* found = ctx->h_pinned;
+        // the arrays may come from the default stream, which a context's stream need not wait for
+        hipError_t e = ctx->stream ? hipStreamSynchronize(nullptr) : hipSuccess;
+        if (e == hipSuccess) e = spp::pool_take(g->device, &d_found, 3 * sizeof(int64_t));
+        if (e == hipSuccess) e = hipMemsetAsync(d_found, 0, 3 * sizeof(int64_t), ctx->stream);
         if (e == hipSuccess) {
-            spp::validate_csr_kernel<<<ctx->num_cu * 8, spp::kBlock, 0, ctx->stream>>>(N, M, d_rowptr, d_col, d_bad);
-            e = hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream);
+            spp::validate_csr_kernel<<<ctx->num_cu * 8, spp::kBlock, 0, ctx->stream>>>(N, M, d_rowptr, d_col, d_found);
+            e = hipMemcpyAsync(found, d_found, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (d_bad) (void)hipFree(d_bad);
-        if (e != hipSuccess || bad) {
+        if (d_found) { if (e == hipSuccess) spp::pool_give(g->device, d_found); else (void)hipFree(d_found); }
+        const bool ends = e == hipSuccess && found[0] == 0 && found[1] == M;
+        if (e != hipSuccess || !ends || found[2]) {
             if (e != hipSuccess) spp::set_error("spp_graph_create: %s", hipGetErrorString(e));
+            else if (!ends) spp::set_error("spp_graph_create: rowptr[0] = %lld, rowptr[N] = %lld, M = %lld", (long long)found[0], (long long)found[1], (long long)M);
             else spp::set_error("spp_graph_create: rowptr is not monotone within [0, M] or a column id lies outside [0, N)");
             delete g;
             return e != hipSuccess ? SPP_E_HIP : SPP_E_ARG;
@@ -800,14 +809,8 @@ extern "C" void spp_graph_destroy(spp_graph* g) {
     if (!g) return;
     if (hipSetDevice(g->device) != hipSuccess) { (void)hipGetLastError(); delete g; return; }   // runtime already shut down
     (void)hipDeviceSynchronize();      // work that still reads the row blocks may be in flight
-    if (g->t_edge) (void)hipFree(g->t_edge);
-    if (g->tile_first) (void)hipFree(g->tile_first);
-    if (g->part_mem) (void)hipFree(g->part_mem);
-    if (g->block_first) (void)hipFree(g->block_first);
-    if (g->x_src) (void)hipFree(g->x_src);
-    if (g->x_row) (void)hipFree(g->x_row);
-    if (g->x_chunk_first) (void)hipFree(g->x_chunk_first);
-    if (g->x_start) (void)hipFree(g->x_start);
-    if (g->x_prefix) (void)hipFree(g->x_prefix);
+    for (void* p : {(void*)g->t_edge, (void*)g->tile_first, g->part_mem, (void*)g->block_first, (void*)g->x_src, (void*)g->x_row,
+                    (void*)g->x_chunk_first, (void*)g->x_start, (void*)g->x_prefix})
+        spp::pool_give(g->device, p);
     delete g;
 }
