@@ -20,13 +20,16 @@ namespace spp {
 
 // Every kernel of the library indexes with these arrays, so they are checked once here: offsets
 // monotone inside [0, M], column ids inside [0, N).  Nothing is read of col[] unless the CSR says that it has M entries.
-// found: rowptr[0], rowptr[N], whether something is wrong (zero before).
-__global__ void __launch_bounds__(kBlock) validate_csr_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
-                                                              const int32_t* __restrict__ col, int64_t* __restrict__ found) {
+struct CsrFound { int64_t first, last, bad; };   // rowptr[0], rowptr[N], whether something is wrong (zero before)
+__device__ __forceinline__ bool csr_ends(int64_t N, int64_t M, const int64_t* __restrict__ rowptr, CsrFound* __restrict__ found) {
     const int64_t first = rowptr[0], last = rowptr[N];
-    if (blockIdx.x == 0 && threadIdx.x == 0) { found[0] = first; found[1] = last; }
-    if (first != 0 || last != M) return;
-    int64_t* __restrict__ bad = found + 2;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { found->first = first; found->last = last; }
+    return first == 0 && last == M;
+}
+__global__ void __launch_bounds__(kBlock) validate_csr_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
+                                                              const int32_t* __restrict__ col, CsrFound* __restrict__ found) {
+    if (!csr_ends(N, M, rowptr, found)) return;
+    int64_t* __restrict__ bad = &found->bad;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     for (int64_t v = t; v < N; v += stride) {
@@ -52,7 +55,7 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
 // edges: the kernels of a build 9.2 -> 1.1 ms: 0.63 in the placing pass, most of it vector instructions,
-// 0.12 in the counting pass, 0.15 in the read-back and 0.19 in the sum over the CSR that it is compared with.
+// 0.12 in the counting pass, 0.15 in the read-back and 0.19 in the sum over the CSR that it is compared with (1.1 ms in all).
 // Tiles of 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
@@ -79,21 +82,31 @@ __device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// The passes that build the row blocks validate the CSR on the way: this one its offsets, the counting pass its ids, each
+// before it uses them; the passes after those two do nothing if either found something wrong.  (A pass of its own cost a
+// build of 121M edges 141 us.)
+__device__ __forceinline__ bool csr_bad(const CsrFound* found, int64_t M) { return found->first != 0 || found->last != M || found->bad != 0; }
+
 // tile_row[t] = the vertex whose row holds the first edge of tile t; tile_row[ntiles] = the last one with edges.
 __global__ void __launch_bounds__(kBlock) part_rows_kernel(int64_t N, int64_t M, int64_t ntiles, const int64_t* __restrict__ rowptr,
-                                                           int32_t* __restrict__ tile_row) {
+                                                           int32_t* __restrict__ tile_row, CsrFound* __restrict__ found) {
+    if (!csr_ends(N, M, rowptr, found)) return;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
         const int64_t b = rowptr[v], e = rowptr[v + 1];
+        if (b < 0 || e > M || b > e) { found->bad = 1; continue; }
         for (int64_t t = (b + kPartTile - 1) / kPartTile; t * kPartTile < e; ++t) tile_row[t] = (int32_t)v;
         if (b < e && e == M) tile_row[ntiles] = (int32_t)v;
     }
 }
 
 // hist[block * ntiles + tile] = edges of the tile that end in the block.
-__global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t M, const int32_t* __restrict__ col, int rbits,
+__global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
+                                                                const int32_t* __restrict__ col, int rbits,
                                                                 int nrb, int64_t ntiles,
-                                                                uint32_t* __restrict__ hist) {
+                                                                uint32_t* __restrict__ hist, CsrFound* __restrict__ found) {
+    if (rowptr[0] != 0 || rowptr[N] != M) return;        // then col[] need not hold M ids
+    bool wrong = false;
     constexpr int kCopies = 8;                   // a lane adds to one of eight copies: most edges of a tile end in few blocks
     __shared__ uint32_t cnt[kPartMaxBlocks][kCopies];
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -105,7 +118,10 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t M, const
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k)
-            if (e0 + k * kPartBlock < M) atomicAdd(&cnt[u[k] >> rbits][threadIdx.x & (kCopies - 1)], 1u);
+            if (e0 + k * kPartBlock < M) {
+                if (u[k] < (uint32_t)N) atomicAdd(&cnt[u[k] >> rbits][threadIdx.x & (kCopies - 1)], 1u);
+                else wrong = true;
+            }
         __syncthreads();
         if ((int)threadIdx.x < nrb) {
             uint32_t c = 0;
@@ -115,6 +131,7 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t M, const
         }
         __syncthreads();
     }
+    if (wrong) found->bad = 1;
 }
 
 template <int BITS>
@@ -122,7 +139,8 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
                                                                 const int32_t* __restrict__ col, int rbits,
                                                                 int nrb, int64_t ntiles, const int32_t* __restrict__ tile_row,
                                                                 const uint32_t* __restrict__ offs,
-                                                                uint32_t* __restrict__ t_edge) {
+                                                                uint32_t* __restrict__ t_edge, const CsrFound* __restrict__ found) {
+    if (csr_bad(found, M)) return;
     __shared__ uint32_t words[kPartTile];        // first: where rows start in the tile; then the edge words by block
     __shared__ uint16_t blk_of[kPartTile];
     __shared__ uint16_t cnt[kPartWaves][kPartMaxBlocks];      // edges, then first place, per wavefront and block
@@ -228,7 +246,8 @@ static_assert(kPartMaxBlocks <= kPartBlock, "one block per thread");
 __global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const int64_t* __restrict__ rowptr,
                                                                 const int32_t* __restrict__ col, int rbits, int nrb, int nch,
                                                                 int64_t ntiles, const uint32_t* __restrict__ offs,
-                                                                int64_t* __restrict__ first) {
+                                                                int64_t* __restrict__ first, const CsrFound* __restrict__ found) {
+    if (csr_bad(found, M)) return;
     __shared__ uint32_t cnt[kPartMaxBlocks];
     const int c = blockIdx.x;
     const int64_t at = rowptr[(int64_t)c << kTileSrcLoBits];             // at most M
@@ -249,7 +268,9 @@ __global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const
 // (271 with a bisection over all rows for every 2048 edges' first one and one among the 64 rows for every edge).
 __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
                                                          const int32_t* __restrict__ col, const int32_t* __restrict__ tile_row,
-                                                         int piece_bits, unsigned long long* __restrict__ mix, int* __restrict__ bad) {
+                                                         int piece_bits, unsigned long long* __restrict__ mix, int* __restrict__ bad,
+                                                         const CsrFound* __restrict__ found) {
+    if (csr_bad(found, M)) return;
     constexpr int U = 4;                         // batches of 64 edges in flight
     const int lane = lane_id();
     const int64_t wave = (int64_t)blockIdx.x * (kBlock / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -321,8 +342,10 @@ __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, c
 // row block; the block's chunk bounds sit in LDS.
 __global__ void __launch_bounds__(kBlock) tile_verify_kernel(int rbits, int nch, const uint32_t* __restrict__ t_edge,
                                                              const int64_t* __restrict__ first, int parts, int64_t N, int64_t M,
-                                                             unsigned long long* __restrict__ mix, int* __restrict__ bad) {
+                                                             unsigned long long* __restrict__ mix, int* __restrict__ bad,
+                                                             const CsrFound* __restrict__ found) {
     extern __shared__ uint32_t bound[];
+    if (csr_bad(found, M)) return;
     const int64_t rb = blockIdx.x / parts;
     const int j = blockIdx.x % parts;
     const int64_t b0 = first[rb * nch], len = first[(rb + 1) * nch] - b0;
@@ -357,12 +380,23 @@ struct PartOut { uint32_t* h; __device__ void operator()(int64_t i, int ex, int)
 struct PartFin { __device__ void operator()(int) const {} };
 
 __global__ void block_first_from_tiles_kernel(const int64_t* __restrict__ tile_first, int nch, int64_t nrb,
-                                              int64_t* __restrict__ block_first) {
+                                              int64_t* __restrict__ block_first) {      // copies whatever tile_first[] holds
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b <= nrb) block_first[b] = tile_first[b * nch];
 }
 
-// The edges grouped by destination row block and sorted by source inside a block.
+// Says what is wrong with the CSR, if anything is.
+static bool csr_error(const CsrFound& f, int64_t M) {
+    if (f.first != 0 || f.last != M)
+        set_error("spp_graph_create: rowptr[0] = %lld, rowptr[N] = %lld, M = %lld", (long long)f.first, (long long)f.last, (long long)M);
+    else if (f.bad)
+        set_error("spp_graph_create: rowptr is not monotone within [0, M] or a column id lies outside [0, N)");
+    else
+        return false;
+    return true;
+}
+
+// The edges grouped by destination row block and sorted by source inside a block.  Validates the CSR if M > 0.
 static int build_tiles(spp_ctx* ctx, spp_graph* g) {
     hipStream_t st = ctx->stream;
     const int64_t N = g->N, M = g->M;
@@ -391,7 +425,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         const int scan_grid = 1024;
         // one allocation: the counts (then offsets) and the tiles' first rows, which the graph keeps, the scan's
         // partial sums, the sums of the edges' mixes and a flag
-        struct Head { unsigned long long mix[2]; int bad, pad; } back;
+        struct Head { unsigned long long mix[2]; int bad, pad; CsrFound csr; } back;
         const size_t bytes = sizeof(Head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
         char* tmp = nullptr;
         if (pool_take(g->device, &tmp, bytes) != hipSuccess) {
@@ -401,6 +435,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         }
         unsigned long long* mix = reinterpret_cast<unsigned long long*>(tmp);
         int* d_bad = reinterpret_cast<int*>(mix + 2);
+        CsrFound* found = &reinterpret_cast<Head*>(tmp)->csr;
         uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(Head));
         int* partial = reinterpret_cast<int*>(hist + nhist);
         int32_t* tile_row = partial + scan_grid;
@@ -408,21 +443,21 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         hipError_t e = hipMemsetAsync(tmp, 0, sizeof(Head), st);
         if (e == hipSuccess) {
             const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
-            part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row);
-            part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(M, g->col, rbits, (int)nrb, ntiles, hist);
+            part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row, found);
+            part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, hist, found);
             grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
             auto place = [&](auto kernel) {
-                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge);
+                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge, found);
             };
             if (nrb <= 256) place(part_place_kernel<8>); else place(part_place_kernel<9>);
-            part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first);
+            part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first, found);
             int piece_bits = 8;
             while ((1 << piece_bits) < kPartTile && (M >> piece_bits) > (int64_t)ctx->num_cu * 8 * (kBlock / kWave)) ++piece_bits;
-            csr_mix_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(N, M, g->rowptr, g->col, tile_row, piece_bits, mix, d_bad);
+            csr_mix_kernel<<<ctx->num_cu * 8, kBlock, 0, st>>>(N, M, g->rowptr, g->col, tile_row, piece_bits, mix, d_bad, found);
             const int64_t want = ((int64_t)ctx->num_cu * 8 + nrb - 1) / nrb;
             const int parts = (int)(want < 1 ? 1 : (want > 256 ? 256 : want));
             tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
-                                                                                     mix + 1, d_bad);
+                                                                                     mix + 1, d_bad, found);
             block_first_from_tiles_kernel<<<bf_grid, kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
             e = hipMemcpyAsync(ctx->h_pinned, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
         }
@@ -430,6 +465,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         memcpy(&back, ctx->h_pinned, sizeof(back));
         if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) { set_error("row blocks: %s", hipGetErrorString(e)); rc = SPP_E_HIP; }
+        else if (csr_error(back.csr, M)) rc = SPP_E_ARG;
         else if (back.bad || back.mix[0] != back.mix[1]) {
             set_error("row blocks: the structure does not read back as the edges it was built from"); rc = SPP_E_HIP;
         }
@@ -770,32 +806,26 @@ extern "C" int spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_
     spp_graph* g = new (std::nothrow) spp_graph();
     SPP_CHECK(g != nullptr, SPP_E_OOM, "spp_graph_create: out of host memory");
     g->device = ctx->device; g->N = N; g->M = M; g->rowptr = d_rowptr; g->col = d_col;
-    {
-        // the CSR must really describe M edges
-        int64_t* d_found = nullptr;
-        int64_t* found = ctx->h_pinned;
-        // the arrays may come from the default stream, which a context's stream need not wait for
-        hipError_t e = ctx->stream ? hipStreamSynchronize(nullptr) : hipSuccess;
-        if (e == hipSuccess) e = spp::pool_take(g->device, &d_found, 3 * sizeof(int64_t));
-        if (e == hipSuccess) e = hipMemsetAsync(d_found, 0, 3 * sizeof(int64_t), ctx->stream);
+    // which layout: gathering y per edge pays while y stays in the caches (see spp_vip.hip)
+    const bool lists = (flags & SPP_GRAPH_IN_LISTS) != 0;
+    const bool chunked = lists && ((flags & SPP_GRAPH_CHUNKED) != 0 || N > spp::kChunkedAboveVertices);
+    // the arrays may come from the default stream, which a context's stream need not wait for
+    hipError_t e = ctx->stream ? hipStreamSynchronize(nullptr) : hipSuccess;
+    if (e == hipSuccess && !(lists && !chunked && M > 0)) {          // the row blocks' build does it on the way
+        spp::CsrFound* d_found = nullptr;
+        spp::CsrFound* found = reinterpret_cast<spp::CsrFound*>(ctx->h_pinned);
+        e = spp::pool_take(g->device, &d_found, sizeof(*found));
+        if (e == hipSuccess) e = hipMemsetAsync(d_found, 0, sizeof(*found), ctx->stream);
         if (e == hipSuccess) {
             spp::validate_csr_kernel<<<ctx->num_cu * 8, spp::kBlock, 0, ctx->stream>>>(N, M, d_rowptr, d_col, d_found);
-            e = hipMemcpyAsync(found, d_found, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream);
+            e = hipMemcpyAsync(found, d_found, sizeof(*found), hipMemcpyDeviceToHost, ctx->stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (d_found) { if (e == hipSuccess) spp::pool_give(g->device, d_found); else (void)hipFree(d_found); }
-        const bool ends = e == hipSuccess && found[0] == 0 && found[1] == M;
-        if (e != hipSuccess || !ends || found[2]) {
-            if (e != hipSuccess) spp::set_error("spp_graph_create: %s", hipGetErrorString(e));
-            else if (!ends) spp::set_error("spp_graph_create: rowptr[0] = %lld, rowptr[N] = %lld, M = %lld", (long long)found[0], (long long)found[1], (long long)M);
-            else spp::set_error("spp_graph_create: rowptr is not monotone within [0, M] or a column id lies outside [0, N)");
-            delete g;
-            return e != hipSuccess ? SPP_E_HIP : SPP_E_ARG;
-        }
+        if (e == hipSuccess && spp::csr_error(*found, M)) { delete g; return SPP_E_ARG; }
     }
+    if (e != hipSuccess) { spp::set_error("spp_graph_create: %s", hipGetErrorString(e)); delete g; return SPP_E_HIP; }
     if (flags & SPP_GRAPH_IN_LISTS) {
-        // which layout: gathering y per edge pays while y stays in the caches (see spp_vip.hip)
-        const bool chunked = (flags & SPP_GRAPH_CHUNKED) != 0 || N > spp::kChunkedAboveVertices;
         int rc = chunked ? spp::build_chunked(ctx, g) : spp::build_tiles(ctx, g);
         if (rc != SPP_OK) { spp_graph_destroy(g); return rc; }
         g->has_in = true;
