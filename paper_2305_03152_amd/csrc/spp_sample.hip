@@ -52,8 +52,14 @@ struct BatchDesc {
     int32_t        nseeds;
     uint32_t       batch_lo;
 };
+// Fanout sampling in LDS: the counts once more, written and read by the device only.  A kernel asks for them together with
+// the pointers; behind the pointer `counts` they were one more trip to memory at the head of each of a call's ten launches.
+struct BatchCounts {
+    uint32_t n[SPP_MAX_L + 1], e[SPP_MAX_L + 1];
+};
 struct BatchTable {
-    BatchDesc b[kMaxBatches];
+    BatchDesc   b[kMaxBatches];
+    BatchCounts c[kMaxBatches];
 };
 // What changes from call to call even when the caller reuses its buffers: the seeds and the number
 // of the minibatch.  It rides in the argument block of the call's first launch, which stores it
@@ -407,11 +413,11 @@ __device__ __forceinline__ HopTable hop_table_of(const HopArgs& a, int j, uint32
 // The seeds of a call: hop 1 takes them from its argument block.
 struct SeedsArg {
     BatchDynAll dyn;
-    __device__ __forceinline__ int64_t n(const BatchDesc&, int j, int) const { return dyn.d[j].nseeds; }
+    __device__ __forceinline__ int64_t n(const BatchCounts&, int j, int) const { return dyn.d[j].nseeds; }
     __device__ __forceinline__ uint32_t batch_lo(const BatchDesc&, int j) const { return dyn.d[j].batch_lo; }
 };
 struct NoSeedsArg {
-    __device__ __forceinline__ int64_t n(const BatchDesc& b, int, int h) const { return b.counts[h - 1]; }
+    __device__ __forceinline__ int64_t n(const BatchCounts& c, int, int h) const { return c.n[h - 1]; }
     __device__ __forceinline__ uint32_t batch_lo(const BatchDesc& b, int) const { return b.batch_lo; }
 };
 __device__ __forceinline__ int32_t checked_seed(const HopArgs& a, int32_t v) {
@@ -419,12 +425,13 @@ __device__ __forceinline__ int32_t checked_seed(const HopArgs& a, int32_t v) {
     atomicOr(a.bad, 1);                          // reported; vertex 0 keeps later row reads in range
     return 0;
 }
-__device__ __forceinline__ void start_counts(BatchDesc& b, const BatchDyn& dyn) {
+__device__ __forceinline__ void start_counts(BatchDesc& b, BatchCounts& k, const BatchDyn& dyn) {
     int64_t* c = b.counts;
-    for (int k = 1; k <= SPP_MAX_L; ++k) c[k] = 0;
-    for (int k = 0; k <= SPP_MAX_L; ++k)
-        if (k != 1) c[kE + k] = 0;               // e_1 is written by the tile that ends hop 1
+    for (int i = 1; i <= SPP_MAX_L; ++i) c[i] = 0;
+    for (int i = 0; i <= SPP_MAX_L; ++i)
+        if (i != 1) c[kE + i] = 0;               // e_1 is written by the tile that ends hop 1
     c[0] = dyn.nseeds;
+    k.n[0] = (uint32_t)dyn.nseeds;
     b.batch_lo = dyn.batch_lo;
 }
 
@@ -434,7 +441,7 @@ __global__ void __launch_bounds__(kBlock) hop_seeds_kernel(HopArgs a, BatchTable
     const BatchBlock bb = batch_block();
     const int j = bb.j;
     const BatchDyn& d = dyn.d[j];
-    if (bb.x == 0 && threadIdx.x == 0) start_counts(t->b[j], d);
+    if (bb.x == 0 && threadIdx.x == 0) start_counts(t->b[j], t->c[j], d);
     for (int64_t base = (int64_t)bb.x * kHopTargets; base < d.nseeds; base += (int64_t)gridDim.x * kHopTargets) {
         const int64_t i = base + threadIdx.x;
         int c = 0;
@@ -453,8 +460,8 @@ __global__ void __launch_bounds__(kBlock) hop_seeds_kernel(HopArgs a, BatchTable
 
 // A repeated id takes the local id of its first appearance (an earlier edge of the same hop, final
 // since the launch that numbered it), which the numbering left as a negative edge index.
-__device__ __forceinline__ void relabel_repeats(const BatchDesc& b, int h, unsigned x, unsigned gx) {
-    const int64_t e_h = b.counts[kE + h];
+__device__ __forceinline__ void relabel_repeats(const BatchDesc& b, const BatchCounts& c, int h, unsigned x, unsigned gx) {
+    const int64_t e_h = c.e[h];
     int32_t* src = b.src[h - 1];
     for (int64_t e = (int64_t)x * kBlock + threadIdx.x; e < e_h; e += (int64_t)gx * kBlock) {
         const int32_t v = src[e];
@@ -506,7 +513,7 @@ __global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchT
     const BatchBlock bb = batch_block();
     const int jb = bb.j;
     BatchDesc& b = t->b[jb];
-    const int64_t n_prev = seeds.n(b, jb, a.h);
+    const int64_t n_prev = seeds.n(t->c[jb], jb, a.h);
     const uint32_t batch_lo = seeds.batch_lo(b, jb);
     const int f = a.f;
     const int T = hop_tile_targets(n_prev, a.n_items, f);
@@ -523,7 +530,7 @@ __global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchT
     const uint64_t lt_mask = (1ull << lane) - 1ull;
 
     if constexpr (kFirst) {
-        if (bb.x == 0 && threadIdx.x == 0) start_counts(b, seeds.dyn.d[jb]);
+        if (bb.x == 0 && threadIdx.x == 0) start_counts(b, t->c[jb], seeds.dyn.d[jb]);
     }
     for (int64_t tile = bb.x; tile < ntiles; tile += gridDim.x) {
         const int64_t i0 = tile * T;
@@ -573,6 +580,7 @@ __global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchT
         if (tile == ntiles - 1 && threadIdx.x == 0) {
             indptr[n_prev] = (int32_t)(ebase + n_e);
             b.counts[kE + a.h] = ebase + n_e;
+            t->c[jb].e[a.h] = (uint32_t)(ebase + n_e);
             atomicAdd(&a.totals[2], (unsigned long long)(ebase + n_e));
         }
         // the draws
@@ -667,7 +675,7 @@ __global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchT
         // what the hop before left: its granules' sums, and the repeats of its ids
         if (bb.x == 0)
             for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)jb * kHopGranules + g] = 0u;
-        if (a.h > 1) relabel_repeats(b, a.h - 1, bb.x, gridDim.x);
+        if (a.h > 1) relabel_repeats(b, t->c[jb], a.h - 1, bb.x, gridDim.x);
     }
 }
 
@@ -725,7 +733,7 @@ __global__ void __launch_bounds__(kDedupBlock) hop_dedup_kernel(HopArgs a, const
     uint32_t* wsum = adr + kDedupBlock;                                 // [kDedupBlock / kWave]
     const int jb = blockIdx.x;                   // partitions are the slow index: workgroups without one come last
     const BatchDesc& b = t->b[jb];
-    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1], e_h = (uint32_t)b.counts[kE + a.h];     // below 2^30 each
+    const uint32_t n_prev = t->c[jb].n[a.h - 1], e_h = t->c[jb].e[a.h];      // below 2^30 each
     const int T = hop_tile_targets(n_prev, a.n_items, a.f);
     const int k = hop_parts_log2(n_prev, a.n_items, a.f);
     const uint32_t ntiles = n_prev > 0 ? (n_prev + T - 1) / T : 1;
@@ -881,7 +889,7 @@ __global__ void __launch_bounds__(kBlock) hop_resolve_kernel(HopArgs a, const Ba
     const BatchBlock bb = batch_block();
     const int jb = bb.j;
     const BatchDesc& b = t->b[jb];
-    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1], e_h = (uint32_t)b.counts[kE + a.h];
+    const uint32_t n_prev = t->c[jb].n[a.h - 1], e_h = t->c[jb].e[a.h];
     const HopTable ht = hop_table_of(a, jb, n_prev, e_h);
     if (ht.tab == nullptr) return;
     const uint32_t T = (uint32_t)hop_tile_targets(n_prev, a.n_items, a.f), ntiles = (n_prev + T - 1) / T;      // n_prev > 0 here
@@ -911,14 +919,14 @@ __global__ void __launch_bounds__(kBlock) hop_resolve_kernel(HopArgs a, const Ba
 // through LDS, the new vertices are appended to S_h in order, and the row of a vertex that will be a
 // target of the next hop is looked up here, once.
 template <bool kLarge>
-__global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const BatchTable* __restrict__ t) {
+__global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, BatchTable* __restrict__ t) {
     __shared__ uint32_t what[kHopEdges];         // per edge of the tile: the upper half of its entry
     __shared__ int scan_lds[4];
     __shared__ uint32_t next_sum[1024 / kHopTargets + 2];
     const BatchBlock bb = batch_block();
     const int jb = bb.j;
     const BatchDesc& b = t->b[jb];
-    const uint32_t n_prev = (uint32_t)b.counts[a.h - 1];
+    const uint32_t n_prev = t->c[jb].n[a.h - 1];
     const int T = hop_tile_targets(n_prev, a.n_items, a.f);
     const uint32_t ntiles = n_prev > 0 ? (n_prev + T - 1) / T : 1;
     const int gshift = hop_granule_log2(ntiles);
@@ -931,7 +939,7 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
     int64_t* __restrict__ row0 = a.row0 + (int64_t)jb * a.node_stride;
     int32_t* __restrict__ deg = a.deg + (int64_t)jb * a.node_stride;
     if constexpr (kLarge) {
-        const HopTable ht = hop_table_of(a, jb, n_prev, (uint32_t)b.counts[kE + a.h]);         // has served
+        const HopTable ht = hop_table_of(a, jb, n_prev, t->c[jb].e[a.h]);  // has served
         typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
         for (uint32_t i = bb.x * kBlock + threadIdx.x; i < ht.slots / 2; i += gridDim.x * kBlock)
             reinterpret_cast<u64x2*>(ht.tab)[i] = u64x2{~0ull, ~0ull};
@@ -1008,6 +1016,7 @@ __global__ void __launch_bounds__(kBlock) hop_number_kernel(HopArgs a, const Bat
             const bool over = id0 > id_cap;
             if (over) { atomicOr(a.bad, 4); id0 = id_cap; }
             b.counts[a.h] = id0;
+            t->c[jb].n[a.h] = id0;
             if (a.h == a.L) {
                 atomicAdd(&a.totals[1], (unsigned long long)id0);
                 atomicAdd(&a.totals[0], 1ull);
@@ -1029,7 +1038,7 @@ __global__ void __launch_bounds__(kBlock) hop_last_kernel(HopArgs a, const Batch
     const BatchBlock bb = batch_block();
     if (bb.x == 0)
         for (int g = threadIdx.x; g < kHopGranules; g += kBlock) a.fsum[(int64_t)bb.j * kHopGranules + g] = 0u;
-    relabel_repeats(t->b[bb.j], a.h, bb.x, gridDim.x);
+    relabel_repeats(t->b[bb.j], t->c[bb.j], a.h, bb.x, gridDim.x);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.bad_next[threadIdx.x] = 0;
 }
 
