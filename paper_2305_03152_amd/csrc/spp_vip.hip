@@ -498,8 +498,9 @@ __device__ __forceinline__ void pull_tiles(double* acc, const uint32_t* __restri
         if (hi - lo >= kTileSpan) return (int)kGather;
         w0 = lo & ~3u;
         const uint32_t v = (w0 >> 2) + lane;
-        if (4 * v < N) y0 = y4[v];
-        if (lane < (kTileWin - 256) / 4 && 4 * (v + kWave) < N) y1 = y4[v + kWave];
+        const uint32_t vhi = hi >> 2;            // nothing past the stretch (hi < N) is read: half of a window as a rule (2 % of a hop)
+        if (v <= vhi) y0 = y4[v];
+        if (lane < (kTileWin - 256) / 4 && v + kWave <= vhi) y1 = y4[v + kWave];
         return (int)kWindow;
     };
     uint32_t q0 = 0;
