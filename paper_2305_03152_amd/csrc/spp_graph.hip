@@ -14,7 +14,10 @@
 #include "spp_common.h"
 #include "spp_device.h"
 
+#include <stddef.h>
+
 #include <new>
+#include <type_traits>
 
 namespace spp {
 
@@ -54,9 +57,8 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
-// edges: the kernels of a build 9.2 -> 1.1 ms: 0.63 in the placing pass, most of it vector instructions,
-// 0.12 in the counting pass, 0.15 in the read-back and 0.19 in the sum over the CSR that it is compared with (1.1 ms in all).
-// Tiles of 4096 or 8192 edges and 8 or 16 edges per thread take the same time.
+// edges: the kernels of a build 9.2 -> 1.0 ms: 0.54 in the placing pass, most of it vector instructions,
+// 0.12 in the counting pass, 0.15 in the read-back and 0.20 in the sum over the CSR that it is compared with.
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
 constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
@@ -134,108 +136,191 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64
     if (wrong) found->bad = 1;
 }
 
+// Places a tile's edge words by block, in CSR order, and stores them as runs.  How many edges of each block the tile has follows
+// from the offsets, so that the blocks' places in the tile are known before an edge is looked at; left to find are an
+// edge's source (the rows leave their numbers at their first edges, and at the first edge of every 64 they reach into) and its
+// rank among its wavefront's edges of the block.  Four barriers per tile: (1) sources and ranks; (2) per block, the
+// wavefronts' places; (3) the words; (4) they are stored while the next tile's rows are marked.  All loads of a
+// tile are asked for before the stores of the tile before, unconditionally: a load that is waited for after stores waits for those too.
+// 2.4M vertices, 121M edges: 544 us (628 with nine barriers and the loads at the head of a tile; 1.0 GB, which a copy moves
+// in 150): vector instructions two thirds of the time, the ballots that rank the edges a third of them.  (Asking first
+// whether 64 edges end in one block, as those of a hub's row do: 663, it spills registers.)
+struct PlaceLds {
+    uint32_t words[kPartTile];           // the tile's words by block
+    uint16_t blk_of[kPartTile];
+    uint32_t mark[2][kPartTile];         // per edge: the row that starts there, less the tile's first
+    uint32_t num[kPartMaxBlocks], off[kPartMaxBlocks];        // of the next tile: edges per block and where they go
+    uint32_t start[kPartMaxBlocks];      // where a block's words start among the tile's
+    uint32_t shift[2][kPartMaxBlocks];   // where they go in t_edge, less that
+    uint4    cnt[1];                     // per block 16 numbers of 16 bits: edges, then first place, per wavefront
+};
 template <int BITS>
 __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
                                                                 const int32_t* __restrict__ col, int rbits,
-                                                                int nrb, int64_t ntiles, const int32_t* __restrict__ tile_row,
+                                                                int nrb, int ntiles, const int32_t* __restrict__ tile_row,
                                                                 const uint32_t* __restrict__ offs,
                                                                 uint32_t* __restrict__ t_edge, const CsrFound* __restrict__ found) {
+    extern __shared__ __align__(16) char place_lds[];
     if (csr_bad(found, M)) return;
-    __shared__ uint32_t words[kPartTile];        // first: where rows start in the tile; then the edge words by block
-    __shared__ uint16_t blk_of[kPartTile];
-    __shared__ uint16_t cnt[kPartWaves][kPartMaxBlocks];      // edges, then first place, per wavefront and block
-    __shared__ uint32_t gshift[kPartMaxBlocks];  // where the block's run goes in t_edge, less where it starts in words[]
-    __shared__ uint32_t wave_top[kPartWaves];
-    __shared__ uint32_t wsum[kPartWaves];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    PlaceLds& l = *reinterpret_cast<PlaceLds*>(place_lds);
+    uint16_t* cnt = reinterpret_cast<uint16_t*>(l.cnt);
+    static_assert(kPartWaves == 16, "a block's counts are two 128-bit words");
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    const int lane = lane_id();
+    const uint32_t tid = threadIdx.x, wave = tid >> 6, rmask = (1u << rbits) - 1u;
+    const uint32_t we0 = wave * (kPartTile / kPartWaves) + lane;
     const uint64_t lt_mask = (1ull << lane) - 1ull;
-    const uint32_t rmask = (1u << rbits) - 1u;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t base = tile * kPartTile;
-        const int count = M - base < kPartTile ? (int)(M - base) : kPartTile;
-        const uint32_t we0 = wave * (kPartTile / kPartWaves) + lane;
-        const int32_t* __restrict__ tcol = col + base;
-        // all that the tile reads is asked for before the first barrier
-        const int64_t v0 = tile_row[tile], v1 = tile + 1 < ntiles ? tile_row[tile + 1] : N - 1;
-        uint32_t u[kPartPer];
+    const uint32_t last_off = (uint32_t)nrb * (uint32_t)ntiles - 1u, off0 = ((int)tid < nrb ? tid : 0u) * (uint32_t)ntiles;      // below 2^30
+    const uint32_t* __restrict__ row32 = reinterpret_cast<const uint32_t*>(rowptr);      // the lower halves: offsets are below 2^32, like M
+    // a tile's rows (the first kPartBlock of them, one per thread; threads beyond take the last one once more) and offsets
+    struct { int32_t v0, v1; uint32_t b, e, off, off_n; } r;
+    auto load_row = [&](uint32_t v) { r.b = row32[2u * v]; r.e = row32[2u * v + 2u]; };
+    auto load_rows = [&](int tile) {
+        r.v0 = tile_row[tile]; r.v1 = tile_row[tile + 1];
+        load_row((uint32_t)(r.v1 - r.v0 > (int32_t)tid ? r.v0 + (int32_t)tid : r.v1));
+        const uint32_t at = off0 + (uint32_t)tile;
+        r.off = offs[at];
+        r.off_n = offs[at < last_off ? at + 1u : at];
+        if (at == last_off) r.off_n = (uint32_t)M;
+    };
+    uint32_t u[kPartPer];
+    auto load_edges = [&](int tile) {            // of a full tile
+        const int32_t* __restrict__ c = col + (int64_t)tile * kPartTile;
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k) u[k] = we0 + k * kWave < (uint32_t)count ? (uint32_t)tcol[we0 + k * kWave] : 0u;
-        const uint32_t goff = (int)threadIdx.x < nrb ? offs[(int64_t)threadIdx.x * ntiles + tile] : 0u;
-        int64_t v = v0 + 1 + threadIdx.x;
-        int64_t p = v <= v1 ? rowptr[v] - base : count;
-        for (int i = threadIdx.x; i < kPartWaves * kPartMaxBlocks / 2; i += kPartBlock) reinterpret_cast<uint32_t*>(&cnt[0][0])[i] = 0u;
-        for (int i = threadIdx.x; i < kPartTile; i += kPartBlock) words[i] = 0u;
-        __syncthreads();
-        // a row that starts inside the tile leaves its number (less the first row's) at its first edge; of
-        // empty rows that start at the same edge the last one counts
-        while (v <= v1) {
-            if (p < count) atomicMax(&words[p], (uint32_t)(v - v0));
-            v += kPartBlock;
-            if (v <= v1) p = rowptr[v] - base;
+        for (int k = 0; k < kPartPer; ++k) u[k] = (uint32_t)__builtin_nontemporal_load(c + (we0 + k * kWave));
+    };
+    auto mark_rows = [&](int tile, uint32_t n, uint32_t* mark) {
+        const uint32_t base = (uint32_t)tile * (uint32_t)kPartTile, stop = base + n;       // at most M
+        auto one = [&](int32_t v) {
+            const uint32_t b = (r.b > base ? (r.b < stop ? r.b : stop) : base) - base, e = (r.e > base ? (r.e < stop ? r.e : stop) : base) - base;
+            if (b < e) {
+                mark[b] = (uint32_t)(v - r.v0);
+                for (uint32_t k = (b + kWave) & ~(uint32_t)(kWave - 1); k < e; k += kWave) mark[k] = (uint32_t)(v - r.v0);
+            }
+        };
+        if (r.v1 - r.v0 >= (int32_t)tid) one(r.v0 + (int32_t)tid);
+        for (int64_t v = (int64_t)r.v0 + kPartBlock + tid; v <= r.v1; v += kPartBlock) { load_row((uint32_t)v); one((int32_t)v); }
+    };
+    auto clear_marks = [&](uint32_t* mark) { reinterpret_cast<u32x4*>(mark)[tid] = u32x4{kNone, kNone, kNone, kNone}; };
+    auto clear_counts = [&]() { for (int i = tid; i < 2 * nrb; i += kPartBlock) l.cnt[i] = uint4{0u, 0u, 0u, 0u}; };
+    auto keep_offsets = [&]() { if ((int)tid < nrb) { l.num[tid] = r.off_n - r.off; l.off[tid] = r.off; } };
+    auto set_starts = [&](uint32_t* shift) {     // by the first wavefront
+        if (tid >= kWave) return;
+        uint32_t before = 0;
+        for (int b0 = 0; b0 < nrb; b0 += kWave) {
+            const int b = b0 + lane;
+            const uint32_t c = b < nrb ? l.num[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c), st = before + inc - c;
+            if (b < nrb) { l.start[b] = st; shift[b] = l.off[b] - st; }
+            before += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
         }
-        __syncthreads();
-        // an edge's source: the last number at or before it, in this wavefront's part of the tile ...
-        uint32_t top = 0;
-        for (int k = kPartPer - 1; k >= 0 && top == 0; --k) {
-            const uint32_t m = words[we0 + k * kWave];
-            const uint64_t marks = __ballot(m != 0u);
-            if (marks) top = (uint32_t)__shfl((int)m, 63 - __clzll((long long)marks), kWave);
-        }
-        if (lane == 0) wave_top[wave] = top;
-        __syncthreads();
-        top = 0;                                 // ... or before it
-        for (int w = 0; w < wave; ++w) top = wave_top[w] ? wave_top[w] : top;
-        uint32_t place[kPartPer];                // block << 16 | rank among the wavefront's edges of the block
+    };
+    uint32_t place[kPartPer];                    // block << 16 | rank among the wavefront's edges of the block
+    auto rank = [&](const uint32_t* mark, int32_t v0, auto full, uint32_t n) {
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k) {
-            const bool has = we0 + k * kWave < (uint32_t)count;
-            const uint32_t m = words[we0 + k * kWave];
-            const uint64_t marks = __ballot(m != 0u);
-            uint32_t s = top;
-            if (marks) {
-                const uint64_t upto = marks & (lt_mask | (1ull << lane));
-                const uint32_t t = (uint32_t)__shfl((int)m, upto ? 63 - __clzll((long long)upto) : 0, kWave);
-                if (upto) s = t;
-                top = (uint32_t)__shfl((int)m, 63 - __clzll((long long)marks), kWave);
-            }
-            s += (uint32_t)v0;
+            const uint32_t e = we0 + k * kWave;
+            const bool has = full || e < n;
+            const uint32_t m = mark[e];
+            const uint64_t upto = __ballot(m != kNone) & (lt_mask | (1ull << lane));
+            const uint32_t src = (uint32_t)v0 + (uint32_t)__shfl((int)m, 63 - __clzll((long long)(upto | 1ull)), kWave);
             const uint32_t blk = u[k] >> rbits;
             const uint64_t same = lanes_alike<BITS>(has, blk);
             const uint32_t below = (uint32_t)__popcll(same & lt_mask);
-            const uint32_t prior = has ? cnt[wave][blk] : 0u;
-            if (has && below == 0) cnt[wave][blk] = (uint16_t)(prior + (uint32_t)__popcll(same));
+            uint16_t* c = cnt + (has ? blk * kPartWaves + wave : 0u);
+            const uint32_t prior = *c;
+            if (has && below == 0) *c = (uint16_t)(prior + (uint32_t)__popcll(same));
             place[k] = (blk << 16) | (prior + below);
-            u[k] = ((s & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (u[k] & rmask);
+            u[k] = ((src & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (u[k] & rmask);
         }
-        __syncthreads();
-        {   // per block: where its run starts in the tile, and each wavefront's part of it
-            const int blk = threadIdx.x;
-            uint32_t all = 0;
-            if (blk < kPartMaxBlocks)
-                for (int w = 0; w < kPartWaves; ++w) all += cnt[w][blk];
-            const uint32_t inc = (uint32_t)wave_inclusive_scan((int)all);
-            if (lane == kWave - 1) wsum[wave] = inc;
-            __syncthreads();
-            uint32_t st = inc - all;
-            for (int w = 0; w < wave; ++w) st += wsum[w];
-            if (blk < kPartMaxBlocks) {
-                gshift[blk] = goff - st;
-#pragma unroll 1
-                for (int w = 0; w < kPartWaves; ++w) { const uint32_t c = cnt[w][blk]; cnt[w][blk] = (uint16_t)st; st += c; }
+    };
+    auto wave_places = [&]() {
+        if ((int)tid >= nrb) return;
+        uint32_t run = l.start[tid];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint4 c = l.cnt[2 * tid + h];
+            uint32_t x[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t mid = run + (x[q] & 0xFFFFu), next = mid + (x[q] >> 16);
+                x[q] = run | (mid << 16);        // places are below 4097
+                run = next;
             }
+            l.cnt[2 * tid + h] = uint4{x[0], x[1], x[2], x[3]};
         }
-        __syncthreads();
+    };
+    auto put = [&](auto full, uint32_t n) {
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k)
-            if (we0 + k * kWave < (uint32_t)count) {
-                const uint32_t at = cnt[wave][place[k] >> 16] + (place[k] & 0xFFFFu);
-                words[at] = u[k];
-                blk_of[at] = (uint16_t)(place[k] >> 16);
+            if (full || we0 + k * kWave < n) {
+                const uint32_t at = cnt[(place[k] >> 16) * kPartWaves + wave] + (place[k] & 0xFFFFu);
+                l.words[at] = u[k];
+                l.blk_of[at] = (uint16_t)(place[k] >> 16);
             }
+    };
+    auto store = [&](const uint32_t* shift, auto full, uint32_t n) {
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) {
+            const uint32_t i = tid + k * kPartBlock;
+            if (full || i < n) t_edge[shift[l.blk_of[i]] + i] = l.words[i];
+        }
+    };
+    // neighbouring tiles store to neighbouring places: an XCD (workgroups go to the eight in turn) takes a run of the full tiles
+    const int nfull = (int)(M / kPartTile), per_xcd = (nfull + 7) / 8, step = (int)(gridDim.x >> 3), x0 = (int)(blockIdx.x & 7) * per_xcd;
+    const int end = x0 + per_xcd < nfull ? x0 + per_xcd : nfull;
+    int tile = x0 + (int)(blockIdx.x >> 3);
+    if (tile < end) {
+        auto at = [&](int tl) { return tl < end ? tl : end - 1; };
+        load_rows(tile);
+        load_edges(tile);
+        clear_marks(l.mark[0]);
+        clear_counts();
+        keep_offsets();
         __syncthreads();
-#pragma unroll 4
-        for (int i = threadIdx.x; i < count; i += kPartBlock) t_edge[gshift[blk_of[i]] + (uint32_t)i] = words[i];
-        __syncthreads();                         // the next tile overwrites the LDS arrays
+        mark_rows(tile, kPartTile, l.mark[0]);
+        set_starts(l.shift[0]);
+        int32_t v0 = r.v0;
+        load_rows(at(tile + step));
+        __syncthreads();
+        for (int k = 0; tile < end; tile += step, k ^= 1) {      // k: which of the two marks and shifts
+            rank(l.mark[k], v0, std::true_type{}, kPartTile);
+            clear_marks(l.mark[k ^ 1]);
+            __syncthreads();
+            wave_places();
+            __syncthreads();
+            put(std::true_type{}, kPartTile);
+            keep_offsets();
+            v0 = r.v0;
+            load_edges(at(tile + step));
+            __syncthreads();
+            clear_counts();
+            mark_rows(at(tile + step), kPartTile, l.mark[k ^ 1]);
+            set_starts(l.shift[k ^ 1]);
+            load_rows(at(tile + 2 * step));
+            store(l.shift[k], std::true_type{}, kPartTile);
+            __syncthreads();
+        }
+    }
+    if (nfull < ntiles && blockIdx.x == gridDim.x - 1) {         // the rest
+        const uint32_t n = (uint32_t)(M - (int64_t)nfull * kPartTile);
+        load_rows(nfull);
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) u[k] = we0 + k * kWave < n ? (uint32_t)col[(int64_t)nfull * kPartTile + we0 + k * kWave] : 0u;
+        clear_marks(l.mark[0]);
+        clear_counts();
+        keep_offsets();
+        __syncthreads();
+        mark_rows(nfull, n, l.mark[0]);
+        set_starts(l.shift[0]);
+        __syncthreads();
+        rank(l.mark[0], r.v0, std::false_type{}, n);
+        __syncthreads();
+        wave_places();
+        __syncthreads();
+        put(std::false_type{}, n);
+        __syncthreads();
+        store(l.shift[0], std::false_type{}, n);
     }
 }
 static_assert(kPartMaxBlocks <= kPartBlock, "one block per thread");
@@ -446,8 +531,14 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row, found);
             part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, hist, found);
             grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
+            // two workgroups per CU, fewer where there are fewer tiles; a multiple of eight
+            const int64_t want_place = (ntiles + 7) / 8 * 8, most_place = ctx->num_cu * 2 / 8 * 8;
+            const size_t place_lds = offsetof(PlaceLds, cnt) + (size_t)nrb * kPartWaves * sizeof(uint16_t);
             auto place = [&](auto kernel) {
-                kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, tile_row, hist, g->t_edge, found);
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)place_lds);
+                if (e != hipSuccess) return;
+                kernel<<<(unsigned)(want_place < most_place ? want_place : most_place), kPartBlock, place_lds, st>>>(
+                    N, M, g->rowptr, g->col, rbits, (int)nrb, (int)ntiles, tile_row, hist, g->t_edge, found);
             };
             if (nrb <= 256) place(part_place_kernel<8>); else place(part_place_kernel<9>);
             part_first_kernel<<<nch, kPartBlock, 0, st>>>(M, g->rowptr, g->col, rbits, (int)nrb, nch, ntiles, hist, g->tile_first, found);
@@ -459,7 +550,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             tile_verify_kernel<<<(unsigned)(nrb * parts), kBlock, bound_bytes, st>>>(rbits, nch, g->t_edge, g->tile_first, parts, N, M,
                                                                                      mix + 1, d_bad, found);
             block_first_from_tiles_kernel<<<bf_grid, kBlock, 0, st>>>(g->tile_first, nch, nrb, g->block_first);
-            e = hipMemcpyAsync(ctx->h_pinned, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipMemcpyAsync(ctx->h_pinned, tmp, sizeof(back), hipMemcpyDeviceToHost, st);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         memcpy(&back, ctx->h_pinned, sizeof(back));
