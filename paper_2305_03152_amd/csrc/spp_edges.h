@@ -15,6 +15,10 @@ constexpr int kTileSrcLoBits = 18;
 constexpr int kTileRowBits = 14;
 constexpr uint32_t kTileRowMask = (1u << kTileRowBits) - 1u;
 constexpr int kPartTile = 4096;          // edges of the CSR per tile of the partition that lays the words out
+// The kernels that walk such tiles look at all rows between a tile's first edge and the next tile's, empty ones included; beyond
+// this many (isolated vertices side by side) every edge bisects for its row instead: some twenty dependent reads, where 4M
+// empty rows would be 4000 rounds of a workgroup.
+constexpr int kTileManyRows = 16384;
 
 __device__ __forceinline__ uint32_t tile_source(uint32_t word, int chunk) {
     return ((uint32_t)chunk << kTileSrcLoBits) | (word >> kTileRowBits);

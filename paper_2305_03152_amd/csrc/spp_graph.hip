@@ -199,6 +199,12 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
                 for (uint32_t k = (b + kWave) & ~(uint32_t)(kWave - 1); k < e; k += kWave) mark[k] = (uint32_t)(v - r.v0);
             }
         };
+        if (r.v1 - r.v0 > kTileManyRows) {       // the same for all threads
+#pragma unroll 1
+            for (int k = 0; k < kPartPer; ++k)
+                if (we0 + k * kWave < n) mark[we0 + k * kWave] = (uint32_t)(row_of_edge(rowptr, r.v0, r.v1, base + we0 + k * kWave) - r.v0);
+            return;
+        }
         if (r.v1 - r.v0 >= (int32_t)tid) one(r.v0 + (int32_t)tid);
         for (int64_t v = (int64_t)r.v0 + kPartBlock + tid; v <= r.v1; v += kPartBlock) { load_row((uint32_t)v); one((int32_t)v); }
     };

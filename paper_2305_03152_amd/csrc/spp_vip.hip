@@ -1367,6 +1367,11 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
                 for (uint32_t k = (b + kSpan) & ~(kSpan - 1); k < e; k += kSpan) mark[k] = __float_as_uint(r.p);
             }
         };
+        if (r.v1 - r.v0 > kTileManyRows) {       // the same for all threads
+#pragma unroll 1
+            for (uint32_t e = 4 * tid; e < 4 * tid + 4 && e < n; ++e) mark[e] = __float_as_uint(pcur[row_of_edge(rowptr, r.v0, r.v1, base + e)]);
+            return;
+        }
         if (r.v1 - r.v0 >= (int32_t)tid) one();
         for (int64_t v = (int64_t)r.v0 + kFillBlock + tid; v <= r.v1; v += kFillBlock) { load_row((int32_t)v); one(); }
     };
