@@ -89,8 +89,9 @@ int  spp_ctx_sync(spp_ctx* ctx);
 /* Wraps a device CSR (not copied; must outlive the handle).  With SPP_GRAPH_IN_LISTS it also
  * builds, once, the transposed structure (the edges v -> u grouped by blocks of destination
  * vertices u and sorted by v inside a block: who can sample u), which costs about
- * 4*M + N/64 bytes of device memory plus, while it is built, about (M/1024 + 4) * (N/16384 + 2) bytes and a few
- * KB of temporary space: at most M/2 for large M (16*M bytes for graphs above 2^23 vertices).
+ * 4*M + N/64 bytes of device memory and about (M/1024 + 4) * (N/16384 + 2) bytes, at most M/2 for large M, that say where
+ * the edges lie (graphs above 2^23 vertices: 16*M bytes of temporary space instead).  Destroyed graphs and caches leave at
+ * most 1 GiB per device to later ones; it is given back with the device's last context, or when memory runs out.
  * Synchronous. */
 int  spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_t* d_rowptr,
                       const int32_t* d_col, uint32_t flags, spp_graph** out);
