@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspp.so")
-SOURCES = ["spp_api.hip", "spp_radix.hip", "spp_graph.hip", "spp_vip.hip", "spp_sample.hip",
+SOURCES = ["spp_api.hip", "spp_pool.hip", "spp_radix.hip", "spp_graph.hip", "spp_vip.hip", "spp_sample.hip",
            "spp_gather.hip", "spp_cache.hip", "spp_local.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-Wall",

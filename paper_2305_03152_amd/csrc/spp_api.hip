@@ -3,9 +3,7 @@
 #include <cstdlib>
 
 #include <algorithm>
-#include <mutex>
 #include <new>
-#include <unordered_map>
 #include <vector>
 
 namespace spp {
@@ -17,96 +15,6 @@ void set_error(const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
-}
-
-struct MemoryPool {
-    std::mutex lock;
-    std::vector<std::pair<void*, size_t>> kept;
-    std::unordered_map<void*, size_t> lent;      // what pool_take has handed out
-    size_t kept_bytes = 0;
-    int contexts = 0;
-    void trim() {
-        for (auto& k : kept) (void)hipFree(k.first);
-        kept.clear();
-        kept_bytes = 0;
-    }
-};
-static MemoryPool* pool_of(int device) {         // never destroyed: handles may outlive everything static
-    constexpr int kDevices = 64;
-    static MemoryPool* pools = new (std::nothrow) MemoryPool[kDevices];
-    return pools && device >= 0 && device < kDevices ? &pools[device] : nullptr;
-}
-
-hipError_t device_malloc(void** out, size_t bytes) {
-    hipError_t e = hipMalloc(out, bytes);
-    int device = 0;
-    if (e != hipErrorOutOfMemory || hipGetDevice(&device) != hipSuccess) return e;
-    MemoryPool* p = pool_of(device);
-    if (!p) return e;
-    {
-        std::lock_guard<std::mutex> hold(p->lock);
-        if (p->kept.empty()) return e;
-        p->trim();
-    }
-    (void)hipGetLastError();
-    return hipMalloc(out, bytes);
-}
-
-hipError_t pool_take(int device, void** out, size_t bytes) {
-    *out = nullptr;
-    MemoryPool* p = pool_of(device);
-    if (p) {
-        std::lock_guard<std::mutex> hold(p->lock);
-        size_t best = p->kept.size();
-        for (size_t i = 0; i < p->kept.size(); ++i) {
-            const size_t have = p->kept[i].second;
-            if (have >= bytes && have <= bytes + bytes / 4 + 65536 && (best == p->kept.size() || have < p->kept[best].second)) best = i;
-        }
-        if (best < p->kept.size()) {
-            const auto block = p->kept[best];
-            try { p->lent[block.first] = block.second; } catch (...) { return hipErrorOutOfMemory; }
-            p->kept[best] = p->kept.back();
-            p->kept.pop_back();
-            p->kept_bytes -= block.second;
-            *out = block.first;
-            return hipSuccess;
-        }
-    }
-    const hipError_t e = device_malloc(out, bytes);
-    if (e == hipSuccess && p) {
-        std::lock_guard<std::mutex> hold(p->lock);
-        try { p->lent[*out] = bytes; } catch (...) {}        // not known to the pool: freed when it is given back
-    }
-    return e;
-}
-
-void pool_give(int device, void* q) {
-    if (!q) return;
-    MemoryPool* p = pool_of(device);
-    if (p) {
-        std::lock_guard<std::mutex> hold(p->lock);
-        const auto it = p->lent.find(q);
-        if (it != p->lent.end()) {
-            const size_t bytes = it->second;
-            p->lent.erase(it);
-            if (p->contexts > 0 && p->kept_bytes + bytes <= kPoolBytes) {
-                try {
-                    p->kept.emplace_back(q, bytes);
-                    p->kept_bytes += bytes;
-                    return;
-                } catch (...) {}
-            }
-        }
-    }
-    (void)hipFree(q);
-}
-
-void pool_context(int device, int change) {
-    MemoryPool* p = pool_of(device);
-    if (!p) return;
-    std::lock_guard<std::mutex> hold(p->lock);
-    p->contexts += change;
-    if (p->contexts == 0) p->trim();
 }
 
 }  // namespace spp

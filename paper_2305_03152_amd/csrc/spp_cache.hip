@@ -342,9 +342,7 @@ extern "C" int spp_build_vip_cache(spp_ctx* ctx, const float* d_score, int64_t N
 extern "C" void spp_cache_destroy(spp_cache* c) {
     if (!c) return;
     if (hipSetDevice(c->device) != hipSuccess) { (void)hipGetLastError(); delete c; return; }   // runtime already shut down
-    (void)hipDeviceSynchronize();      // a gather that still reads the cache may be in flight
-    spp::pool_give(c->device, c->table);
-    spp::pool_give(c->device, c->rows);
+    spp::pool_retire(c->device, {c->table, c->rows});        // a gather that still reads the cache may be in flight
     delete c;
 }
 

@@ -918,7 +918,7 @@ extern "C" int spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_
             e = hipMemcpyAsync(found, d_found, sizeof(*found), hipMemcpyDeviceToHost, ctx->stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (d_found) { if (e == hipSuccess) spp::pool_give(g->device, d_found); else (void)hipFree(d_found); }
+        if (e == hipSuccess) spp::pool_give(g->device, d_found); else spp::pool_retire(g->device, {d_found});
         if (e == hipSuccess && spp::csr_error(*found, M)) { delete g; return SPP_E_ARG; }
     }
     if (e != hipSuccess) { spp::set_error("spp_graph_create: %s", hipGetErrorString(e)); delete g; return SPP_E_HIP; }
@@ -935,9 +935,8 @@ extern "C" int spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_
 extern "C" void spp_graph_destroy(spp_graph* g) {
     if (!g) return;
     if (hipSetDevice(g->device) != hipSuccess) { (void)hipGetLastError(); delete g; return; }   // runtime already shut down
-    (void)hipDeviceSynchronize();      // work that still reads the row blocks may be in flight
-    for (void* p : {(void*)g->t_edge, (void*)g->tile_first, g->part_mem, (void*)g->block_first, (void*)g->x_src, (void*)g->x_row,
-                    (void*)g->x_chunk_first, (void*)g->x_start, (void*)g->x_prefix})
-        spp::pool_give(g->device, p);
+    // work that still reads the row blocks may be in flight
+    spp::pool_retire(g->device, {g->t_edge, g->tile_first, g->part_mem, g->block_first, g->x_src, g->x_row, g->x_chunk_first, g->x_start,
+                                 g->x_prefix});
     delete g;
 }
