@@ -91,11 +91,14 @@ int  spp_ctx_sync(spp_ctx* ctx);
  * vertices u and sorted by v inside a block: who can sample u), which costs about
  * 4*M + N/64 bytes of device memory and about (M/1024 + 4) * (N/16384 + 2) bytes, at most M/2 for large M, that say where
  * the edges lie (graphs above 2^23 vertices: 16*M bytes of temporary space instead).  Destroyed graphs and caches leave at
- * most 1 GiB per device to later ones; it is given back with the device's last context, or when memory runs out.
- * Synchronous. */
+ * most 1 GiB per device to later ones; it is given back with the device's last context, to any other allocation of this
+ * library that would fail without it, and by spp_memory_trim.  Synchronous. */
 int  spp_graph_create(spp_ctx* ctx, int64_t N, int64_t M, const int64_t* d_rowptr,
                       const int32_t* d_col, uint32_t flags, spp_graph** out);
 void spp_graph_destroy(spp_graph* g);
+/* Gives the memory that destroyed graphs and caches have left on `device` back to the system: for a program whose own
+ * allocations (a framework's allocator among them) need it while a context is open. */
+int  spp_memory_trim(int device);
 
 /* (1) Vertex-inclusion probabilities, Proposition 1 with the uniform instantiation of Sec. 3.1:
  *       p^[0](u) = min(1, B/nT) for u in T, else 0

@@ -35,7 +35,7 @@ SPP_T_GATHER_HIT, SPP_T_GATHER_MISS, SPP_T_GATHER_CLASSIFY, SPP_T_COUNT = 10, 11
 
 EXPORTS = [
     "spp_last_error", "spp_ctx_create", "spp_ctx_destroy", "spp_ctx_sync", "spp_graph_create",
-    "spp_graph_destroy", "spp_vip_propagate", "spp_vip_last_hops", "spp_build_vip_cache", "spp_cache_destroy",
+    "spp_graph_destroy", "spp_memory_trim", "spp_vip_propagate", "spp_vip_last_hops", "spp_build_vip_cache", "spp_cache_destroy",
     "spp_cache_set_limit", "spp_cache_lookup", "spp_mfg_bound", "spp_sample_mfg", "spp_sample_mfg_multi",
     "spp_gather_features", "spp_gather_features_multi", "spp_gather_last_stats", "spp_gather_join", "spp_ctx_timing", "spp_ctx_times", "spp_ctx_time_stats", "spp_ctx_totals",
     "spp_build_local_store", "spp_local_store_destroy", "spp_local_store_set_limit", "spp_local_store_rank",
@@ -103,6 +103,7 @@ def load_library():
     lib.spp_graph_create.argtypes = [C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p, C.c_uint32,
                                      C.POINTER(C.c_void_p)]
     lib.spp_graph_destroy.argtypes = [C.c_void_p]
+    lib.spp_memory_trim.argtypes = [C.c_int]
     lib.spp_vip_propagate.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int32,
                                       C.POINTER(C.c_int32), C.c_int32, C.c_void_p, C.c_void_p, C.c_uint32]
     lib.spp_vip_last_hops.argtypes = [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.c_int32]
@@ -295,6 +296,12 @@ class Graph(_Handle):
         _check(load_library().spp_graph_create(ctx._h, self.N, self.M, _ptr(rowptr), _ptr(col), flags,
                                                C.byref(self._h)))
         ctx._adopt(self)
+
+
+def release_memory(device: int = 0):
+    """Gives back the device memory (at most 1 GiB) that closed graphs and caches have left to later ones; torch's
+    allocator cannot ask for it by itself."""
+    _check(load_library().spp_memory_trim(device))
 
 
 def vip_propagate(ctx: Context, graph: Graph, T: torch.Tensor, B: int, fanouts: Sequence[int],

@@ -44,7 +44,7 @@ extern "C" int spp_ctx_create(spp_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join[1], hipEventDisableTiming);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), 8192 * sizeof(int64_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->totals), 16 * sizeof(int64_t));
+    if (e == hipSuccess) e = spp::device_malloc(&c->totals, 16 * sizeof(int64_t));
     if (e == hipSuccess) e = hipMemset(c->totals, 0, 16 * sizeof(int64_t));
     if (e != hipSuccess) {
         spp::set_error("spp_ctx_create: %s", hipGetErrorString(e));
@@ -77,6 +77,12 @@ extern "C" void spp_ctx_destroy(spp_ctx* c) {
     c->sortws.release(); c->rankws.release();
     spp::pool_context(c->device, -1);
     delete c;
+}
+
+extern "C" int spp_memory_trim(int device) {
+    SPP_CHECK(device >= 0 && device < spp::kPoolDevices, SPP_E_ARG, "spp_memory_trim: device %d", device);
+    spp::pool_trim(device);
+    return SPP_OK;
 }
 
 extern "C" int spp_ctx_sync(spp_ctx* c) {

@@ -841,14 +841,14 @@ static int build_chunked(spp_ctx* ctx, spp_graph* g) {
     SPP_HIP(pool_take(g->device, &g->x_start, (size_t)npieces * sizeof(uint32_t)));
     SPP_HIP(pool_take(g->device, &g->x_prefix, (size_t)nrb * (nch + 1) * sizeof(uint32_t)));
     XBuild t;
-    SPP_HIP(hipMalloc(&t.first, (size_t)(npieces + 1) * sizeof(int64_t)));
-    SPP_HIP(hipMalloc(&t.padded, (size_t)(npieces + 1) * sizeof(int64_t)));
+    SPP_HIP(device_malloc(&t.first, (size_t)(npieces + 1) * sizeof(int64_t)));
+    SPP_HIP(device_malloc(&t.padded, (size_t)(npieces + 1) * sizeof(int64_t)));
     const int64_t nsum = (npieces + (int64_t)kBlock * kXScanPer - 1) / ((int64_t)kBlock * kXScanPer);
-    SPP_HIP(hipMalloc(&t.sums, (size_t)(nsum + 1) * sizeof(int64_t)));
-    SPP_HIP(hipMalloc(&t.real, sizeof(unsigned long long)));
-    SPP_HIP(hipMalloc(&t.bad, sizeof(int)));
-    SPP_HIP(hipMalloc(&t.ka, (size_t)(M > 0 ? M : 1) * sizeof(uint64_t)));
-    SPP_HIP(hipMalloc(&t.kb, (size_t)(M > 0 ? M : 1) * sizeof(uint64_t)));
+    SPP_HIP(device_malloc(&t.sums, (size_t)(nsum + 1) * sizeof(int64_t)));
+    SPP_HIP(device_malloc(&t.real, sizeof(unsigned long long)));
+    SPP_HIP(device_malloc(&t.bad, sizeof(int)));
+    SPP_HIP(device_malloc(&t.ka, (size_t)(M > 0 ? M : 1) * sizeof(uint64_t)));
+    SPP_HIP(device_malloc(&t.kb, (size_t)(M > 0 ? M : 1) * sizeof(uint64_t)));
     uint64_t* sorted = t.ka;
     fill_i64_kernel<<<grid, kBlock, 0, st>>>(t.first, npieces + 1, M);
     if (M > 0) {

@@ -81,10 +81,10 @@ extern "C" int spp_build_local_store(spp_ctx* ctx, const float* d_score, int64_t
         if (n == 0) break;
         rc = device_view(local_rows, &s->host_rows);
         if (rc != SPP_OK) break;
-        if (hipMalloc(&ka, (size_t)n * sizeof(uint64_t)) != hipSuccess ||
-            hipMalloc(&kb, (size_t)n * sizeof(uint64_t)) != hipSuccess ||
-            hipMalloc(&s->rank, (size_t)n * sizeof(int32_t)) != hipSuccess ||
-            hipMalloc(&rowidx, (size_t)(keep > 0 ? keep : 1) * sizeof(int64_t)) != hipSuccess) {
+        if (device_malloc(&ka, (size_t)n * sizeof(uint64_t)) != hipSuccess ||
+            device_malloc(&kb, (size_t)n * sizeof(uint64_t)) != hipSuccess ||
+            device_malloc(&s->rank, (size_t)n * sizeof(int32_t)) != hipSuccess ||
+            device_malloc(&rowidx, (size_t)(keep > 0 ? keep : 1) * sizeof(int64_t)) != hipSuccess) {
             set_error("spp_build_local_store: out of device memory for %lld local vertices", (long long)n);
             rc = SPP_E_OOM; break;
         }
@@ -95,7 +95,7 @@ extern "C" int spp_build_local_store(spp_ctx* ctx, const float* d_score, int64_t
         if (rc != SPP_OK) break;
         local_rank_kernel<<<grid, kBlock, 0, st>>>(sorted, n, keep, s->rank, rowidx);
         if (keep > 0) {
-            if (hipMalloc(&s->rows, (size_t)keep * (size_t)s->row_bytes) != hipSuccess) {
+            if (device_malloc(&s->rows, (size_t)keep * (size_t)s->row_bytes) != hipSuccess) {
                 set_error("spp_build_local_store: out of device memory for %lld local rows", (long long)keep);
                 rc = SPP_E_OOM; break;
             }

@@ -22,9 +22,8 @@ struct MemoryPool {
     }
 };
 static MemoryPool* pool_of(int device) {         // never destroyed: handles may outlive everything static
-    constexpr int kDevices = 64;
-    static MemoryPool* pools = new (std::nothrow) MemoryPool[kDevices];
-    return pools && device >= 0 && device < kDevices ? &pools[device] : nullptr;
+    static MemoryPool* pools = new (std::nothrow) MemoryPool[kPoolDevices];
+    return pools && device >= 0 && device < kPoolDevices ? &pools[device] : nullptr;
 }
 
 hipError_t device_malloc(void** out, size_t bytes) {
@@ -98,6 +97,13 @@ void pool_retire(int device, std::initializer_list<void*> blocks) {
     // such memory goes to hipFree, which does not hand it on before that work has ended.
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     for (void* q : blocks) give_back(device, q, idle);
+}
+
+void pool_trim(int device) {
+    MemoryPool* p = pool_of(device);
+    if (!p) return;
+    std::lock_guard<std::mutex> hold(p->lock);
+    p->trim();
 }
 
 void pool_context(int device, int change) {

@@ -87,3 +87,20 @@ def test_what_is_kept_is_bounded(spp):
     torch.cuda.empty_cache()
     assert before - torch.cuda.mem_get_info()[0] < (1 << 30) + (256 << 20)  # the bound, and what the context's buffers hold
     ctx.close()
+
+
+def test_what_is_kept_is_given_back_on_request(spp):
+    ctx = spp.Context(0)
+    N, deg = 1_000_000, 30
+    rp = torch.arange(N + 1, dtype=torch.int64, device="cuda") * deg
+    col = ((torch.arange(N, device="cuda").unsqueeze(1) + torch.arange(1, deg + 1, device="cuda")) % N).sort(1).values.to(torch.int32).reshape(-1)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    spp.Graph(ctx, rp, col, in_lists=True).close()
+    assert before - torch.cuda.mem_get_info()[0] > 4 * N * deg          # the edges' words are kept
+    spp.release_memory(0)
+    assert before - torch.cuda.mem_get_info()[0] < 2 * N * deg
+    ctx.close()
+    with pytest.raises(spp.SppError):
+        spp.release_memory(-1)

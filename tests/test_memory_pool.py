@@ -1,6 +1,8 @@
 """The device memory pool without a GPU: compiled for the host over an allocator of its own that counts, runs out of
 memory and refuses to wait on demand."""
+import glob
 import os
+import re
 import subprocess
 
 import pytest
@@ -68,6 +70,13 @@ int main(int, char** argv) {
         CHECK(pool_take(0, &a, 500 * MB) == hipSuccess && held == 1000 * MB);      // also to its own, of another size
         pool_retire(0, {a});
         hipFree(b);
+    } else if (!strcmp(argv[1], "trimmed")) {
+        CHECK(pool_take(0, &a, 600 * MB) == hipSuccess && pool_take(0, &b, 10 * MB) == hipSuccess);
+        pool_retire(0, {a});
+        pool_trim(0);
+        CHECK(held == 10 * MB);                          // what is in use stays
+        pool_retire(0, {b});
+        CHECK(held == 10 * MB);
     } else {
         return 3;
     }
@@ -91,7 +100,15 @@ def program(tmp_path_factory):
     return str(d / "pool")
 
 
-@pytest.mark.parametrize("case", ["kept", "refused wait", "bound", "runs out"])
+@pytest.mark.parametrize("case", ["kept", "refused wait", "bound", "runs out", "trimmed"])
 def test_pool(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_every_allocation_can_empty_the_pool():
+    """No file of the library but the pool's own calls hipMalloc, which would fail while the pool holds the memory."""
+    for path in glob.glob(os.path.join(CSRC, "*")):
+        if os.path.basename(path) != "spp_pool.hip":
+            code = re.sub(r"//.*|\"[^\"\n]*\"", "", open(path).read())
+            assert not re.search(r"\bhipMalloc\w*\s*\(", code), path
