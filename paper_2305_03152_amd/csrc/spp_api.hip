@@ -44,8 +44,8 @@ extern "C" int spp_ctx_create(spp_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join[1], hipEventDisableTiming);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), 8192 * sizeof(int64_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = spp::device_malloc(&c->totals, 16 * sizeof(int64_t));
-    if (e == hipSuccess) e = hipMemset(c->totals, 0, 16 * sizeof(int64_t));
+    if (e == hipSuccess) e = spp::device_malloc(&c->totals, spp::kTotalsBytes);
+    if (e == hipSuccess) e = hipMemset(c->totals, 0, spp::kTotalsBytes);
     if (e != hipSuccess) {
         spp::set_error("spp_ctx_create: %s", hipGetErrorString(e));
         spp_ctx_destroy(c);
@@ -73,7 +73,7 @@ extern "C" void spp_ctx_destroy(spp_ctx* c) {
     c->btab.release(); c->hopsums.release(); c->hoptab.release(); free(c->btab_mirror);
     c->gtable.release(); c->gfirst.release();
     for (int k = 0; k < 2; ++k) { c->srcdesc[k].release(); c->misslist[k].release(); c->gcount[k].release(); c->hititems[k].release(); }
-    c->y0.release(); c->y1.release(); c->tot.release(); c->acc.release(); c->frontier.release(); c->vipstate.release(); c->bins.release(); c->xvals.release();
+    c->y0.release(); c->y1.release(); c->tot.release(); c->acc.release(); c->frontier.release(); c->bins.release(); c->xvals.release();
     c->sortws.release(); c->rankws.release();
     spp::pool_context(c->device, -1);
     delete c;

@@ -63,6 +63,11 @@ struct DevBuf {
 };
 
 constexpr int kNumTimers = SPP_T_COUNT;
+constexpr int kTotalsWords = 16;
+constexpr int kTotalMax = 16384;         // grid_total (spp_vip.hip): most workgroups,
+constexpr int kTotalLine = 32;           // 64-bit words from one of its words to the next,
+constexpr int kTotalSlots = (1 + kTotalMax / 64) * kTotalLine;           // and all of them
+constexpr size_t kTotalsBytes = (kTotalsWords + kTotalSlots) * sizeof(int64_t) + sizeof(int);
 constexpr int kHopMirror = 2048;         // where a VIP propagation leaves, in the context's pinned mirror (int64 index), per hop
                                          //   pushed?, frontier edges (or -1); then the flag for bad training ids
 constexpr size_t kKeptSortBytes = (size_t)32 << 20;      // set-up workspaces up to this size stay with the context, larger ones do not
@@ -135,11 +140,11 @@ struct spp_ctx {
     spp::DevBuf gfirst;                 // the same per row of the remote store (SPP_STORE_ORDER): first row that misses it
     int64_t*    h_pinned = nullptr;     // pinned host mirror (8192 int64): gather counters from 40, sampler counts from 64,
                                         // how the last VIP propagation walked its hops from kHopMirror
-    int64_t*    totals = nullptr;       // device int64[16], running sums since the last reset (see spp_ctx_totals)
+    int64_t*    totals = nullptr;       // device int64[16], running sums since the last reset (see spp_ctx_totals); behind them
+                                        // what a vip propagation adds up over its launches with and a flag, all zero between calls
+    int         vip_state_clean = 1;    // they are
     // vip workspaces
     spp::DevBuf y0, y1, tot, acc, frontier;
-    spp::DevBuf vipstate;               // words for sums over a launch and a flag, all zero between calls
-    int         vip_state_clean = 0;    // they are
     spp::DevBuf sortws, rankws;         // set-up: counts of a radix sort, keys and histograms of a ranking (bounded, see kKeptSortBytes)
     spp::DevBuf xvals;                  // dense hops over the chunked layout: y[source] of every entry
     spp::DevBuf bins;                   // general propagation: per row block the (row, weight) entries of a hop, and the fill counts

@@ -187,9 +187,6 @@ __device__ __forceinline__ unsigned long long workgroup_sum(unsigned long long x
 // one address cost about 15 ns each, and so do those on one 128-byte line: each word has a line of its own (side by side,
 // 2048 workgroups took 9 us).  Called by one thread of every workgroup; true for the one that arrives
 // last, which has the total.  A workgroup's number counts as 2^33 at most.
-constexpr int kTotalMax = 16384;         // most workgroups
-constexpr int kTotalLine = 32;           // 64-bit words from one to the next
-constexpr int kTotalSlots = (1 + kTotalMax / 64) * kTotalLine;
 __device__ __forceinline__ bool grid_total(unsigned long long* slots, unsigned long long mine, unsigned long long& total) {
     constexpr unsigned long long kOne = 1ull << 48, kMost = 1ull << 33;
     unsigned long long* s = slots + (1 + blockIdx.x / 64) * kTotalLine;
@@ -1606,16 +1603,18 @@ __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __res
     if (!last) rule.decide(edges);
 }
 
-// The context's words for grid_total and the flag for bad input, emptied here where the call before may not have left them
-// empty: it counts as one that has not until its launches have been accepted.
-static int vip_state(spp_ctx* ctx, unsigned long long** slots, int** bad) {
-    const size_t bytes = kTotalSlots * sizeof(unsigned long long) + sizeof(int);
-    if (ctx->vipstate.bytes < bytes) ctx->vip_state_clean = 0;
-    SPP_TRY(ctx->vipstate.reserve(bytes));
-    *slots = ctx->vipstate.as<unsigned long long>();
+// The context's words for grid_total and the flag for bad input.  They are empty from the context's creation on, whether calls
+// run or are only recorded, and each call leaves them so; only after one whose launches were refused they are emptied here.
+static int vip_state(spp_ctx* ctx, unsigned long long** slots, int** bad, int* left_clean) {
+    *slots = reinterpret_cast<unsigned long long*>(ctx->totals + kTotalsWords);
     *bad = reinterpret_cast<int*>(*slots + kTotalSlots);
-    if (!ctx->vip_state_clean) vip_state_clear_kernel<<<1, kBlock, 0, ctx->stream>>>(*slots, *bad);
+    hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+    if (!ctx->vip_state_clean) {
+        SPP_HIP(hipStreamIsCapturing(ctx->stream, &recording));
+        vip_state_clear_kernel<<<1, kBlock, 0, ctx->stream>>>(*slots, *bad);
+    }
     ctx->vip_state_clean = 0;
+    *left_clean = recording == hipStreamCaptureStatusNone;           // what is only recorded empties nothing now
     return SPP_OK;
 }
 
@@ -1639,8 +1638,8 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     const int64_t lcap = frontier_list_capacity(N, g->M);
     SPP_TRY(ctx->frontier.reserve((size_t)(lcap + 2) * sizeof(int32_t) + (4 + SPP_MAX_L + 2) * sizeof(unsigned long long)));
     unsigned long long* slots;
-    int* d_bad;
-    SPP_TRY(vip_state(ctx, &slots, &d_bad));
+    int *d_bad, left_clean;
+    SPP_TRY(vip_state(ctx, &slots, &d_bad, &left_clean));
     int32_t* flist = ctx->frontier.as<int32_t>();
     unsigned long long* fcount = reinterpret_cast<unsigned long long*>(flist + (lcap + (lcap & 1)));
     uint32_t* how = reinterpret_cast<uint32_t*>(fcount + 4);                 // [1 .. L]: how each hop fills its bins
@@ -1726,7 +1725,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
         }
     }
     SPP_HIP(hipGetLastError());
-    ctx->vip_state_clean = 1;
+    ctx->vip_state_clean = left_clean;
     ctx->vip_hops = -L;
     if (flags & SPP_SYNC) {
         SPP_HIP(hipStreamSynchronize(st));
@@ -1810,8 +1809,8 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     lcap += lcap & 1;
     SPP_TRY(ctx->frontier.reserve((size_t)lcap * sizeof(int32_t) + (1 + SPP_MAX_L + 2) * sizeof(unsigned long long)));
     unsigned long long* slots;
-    int* d_bad;
-    SPP_TRY(vip_state(ctx, &slots, &d_bad));
+    int *d_bad, left_clean;
+    SPP_TRY(vip_state(ctx, &slots, &d_bad, &left_clean));
     int32_t* flist = ctx->frontier.as<int32_t>();
     uint32_t* seg_count = reinterpret_cast<uint32_t*>(flist + seg_all);
     int32_t* giants = reinterpret_cast<int32_t*>(seg_count + kSegments);
@@ -1882,7 +1881,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         }
     }
     SPP_HIP(hipGetLastError());
-    ctx->vip_state_clean = 1;
+    ctx->vip_state_clean = left_clean;
     ctx->vip_hops = L;
     // training ids are checked on the device; the flag is read when the caller asks to wait
     if (flags & SPP_SYNC) {
