@@ -38,16 +38,18 @@ constexpr int kSegments = 2048;          // most workgroups of a kernel that lis
 constexpr uint32_t kPushed = 1, kPulled = 2;
 
 // What the kernel that writes a hop's y leaves for that hop's walk.  The frontier's vertices are listed per workgroup, in any
-// order, in a segment of `seg_cap` entries (no workgroup waits for another's count); rows above kGiantRow entries
-// go to a list of their own, which all workgroups of the walk take together.
-constexpr int64_t kGiantRow = 32768;
+// order, in a segment of `seg_cap` entries (no workgroup waits for another's count): from its start on, and those with more
+// than kLongRow entries from its end back: those are shared out edge by edge (see push_frontier), which costs every workgroup
+// the look at all of them.  Hop 1 of 2.4M vertices: 1000 rows of 4000 entries 200 us shared out, 468 in portions of 64 rows;
+// 2000 of 2000, 200 and 258; 10000 of 400, 229 and 200; the 24k training vertices of a power law (up to 20000 entries), 81 for
+// limits of 1024 to 4096, 84 below.
+constexpr int64_t kLongRow = 1024;
 struct HopList {
     int32_t*  list;
-    uint32_t* seg_count;                 // null: not listed here (large graphs list the frontier in a launch of its own)
+    uint32_t* seg_count;                 // per segment how many from its start, and from its end; null: not listed here (large
+                                         // graphs list the frontier in a launch of its own)
     int64_t   seg_cap;
     int       nseg;
-    int32_t*  giants;                    // at most M / kGiantRow
-    uint32_t* ngiants;                   // two counters, used by odd and even hops
 };
 struct HopPlan {
     int       h;                         // the hop whose frontier this is
@@ -214,7 +216,6 @@ __device__ __forceinline__ void plan_hop(const HopPlan& p, unsigned long long ed
         const bool push = all * kPushShare <= (unsigned long long)p.M;
         p.how[p.h] = push ? kPushed : kPulled;
         *p.cursor = 0ull;
-        p.l.ngiants[(p.h + 1) & 1] = 0u;         // the hop after next's
         p.mirror[2 * (p.h - 1)] = push ? 1 : 0;
         p.mirror[2 * (p.h - 1) + 1] = (int64_t)all;
     }
@@ -244,9 +245,8 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
 }
 
 // What a propagation starts from: no weights, no totals (if hop 0 counts), empty accumulators (if hops add to them
-// directly), no long rows listed.
-__global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y, double* __restrict__ tot, double* __restrict__ acc, int64_t N,
-                                                           uint32_t* __restrict__ ngiants) {
+// directly).
+__global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y, double* __restrict__ tot, double* __restrict__ acc, int64_t N) {
     const int64_t stride = (int64_t)gridDim.x * kBlock, tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     for (int64_t i = tid; i < (N + 3) / 4; i += stride) reinterpret_cast<f32x4*>(y)[i] = z;      // y holds a vector more than N
@@ -256,7 +256,6 @@ __global__ void __launch_bounds__(kBlock) vip_clear_kernel(float* __restrict__ y
         typedef double f64x2 __attribute__((ext_vector_type(2)));
         for (int64_t i = tid; i < (N + 1) / 2; i += stride) reinterpret_cast<f64x2*>(acc)[i] = f64x2{0.0, 0.0};
     }
-    if (tid == 0) ngiants[0] = ngiants[1] = 0u;
 }
 
 // Exclusive prefix sums over a workgroup of kThreads threads; ends with a barrier.
@@ -368,10 +367,11 @@ __device__ __forceinline__ int32_t frontier_entry(const int32_t* __restrict__ li
     return v;
 }
 
-// Puts a vertex of the next frontier on this workgroup's list; `n`: a counter in LDS.
-__device__ __forceinline__ void list_vertex(const HopList& l, int h, uint32_t* n, int64_t v, int64_t d) {
-    if (d > kGiantRow) l.giants[atomicAdd(&l.ngiants[h & 1], 1u)] = (int32_t)v;
-    else l.list[(int64_t)blockIdx.x * l.seg_cap + atomicAdd(n, 1u)] = (int32_t)v;
+// Puts a vertex of the next frontier on this workgroup's list; `n`: its two counters, in LDS.
+__device__ __forceinline__ void list_vertex(const HopList& l, uint32_t (&n)[2], int64_t v, int64_t d) {
+    int32_t* segment = l.list + (int64_t)blockIdx.x * l.seg_cap;
+    if (d > kLongRow) segment[l.seg_cap - 1 - atomicAdd(&n[1], 1u)] = (int32_t)v;
+    else segment[atomicAdd(&n[0], 1u)] = (int32_t)v;
 }
 
 // Finishes all vertices: after a push from the accumulators, which it empties again, after a pull from the shares' sums
@@ -379,21 +379,21 @@ __device__ __forceinline__ void list_vertex(const HopList& l, int h, uint32_t* n
 __global__ void __launch_bounds__(kBlock) vip_finish_kernel(VipHop a, const uint32_t* __restrict__ how, int fused_pull,
                                                             double* __restrict__ acc, int parts, int64_t part_stride,
                                                             int64_t N) {
-    __shared__ uint32_t listed;
+    __shared__ uint32_t listed[2];
     const bool push = *how == kPushed;
     if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, !push);
     unsigned long long edges = 0;
     if (push) {
-        if (threadIdx.x == 0) listed = 0u;
+        if (threadIdx.x < 2) listed[threadIdx.x] = 0u;
         __syncthreads();
         vip_finish_all(a, N, [&](int64_t u) {
             const double S = acc[u];
             if (S != 0.0) acc[u] = 0.0;
             return S;
-        }, edges, [&](int64_t v, int64_t d) { list_vertex(a.next.l, a.next.h, &listed, v, d); });
+        }, edges, [&](int64_t v, int64_t d) { list_vertex(a.next.l, listed, v, d); });
         if (a.last) return;
         plan_hop<kBlock>(a.next, edges);         // its barrier: everything is listed
-        if (threadIdx.x == 0) a.next.l.seg_count[blockIdx.x] = listed;
+        if (threadIdx.x < 2) a.next.l.seg_count[2 * blockIdx.x + threadIdx.x] = listed[threadIdx.x];
         return;
     }
     if (fused_pull) return;
@@ -796,8 +796,8 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
                                                           double f1, const int64_t* __restrict__ rowptr,
                                                           float* __restrict__ y, double* __restrict__ tot, int include_hop0,
                                                           int* __restrict__ bad, HopPlan plan) {
-    __shared__ uint32_t listed;
-    if (threadIdx.x == 0) listed = 0u;
+    __shared__ uint32_t listed[2];
+    if (threadIdx.x < 2) listed[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     unsigned long long edges = 0;
@@ -812,13 +812,13 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
             if (yv != 0.0f) {
                 edges += (unsigned long long)d;
                 if (plan.l.seg_count == nullptr) y[v] = yv;
-                else if (atomicCAS(reinterpret_cast<uint32_t*>(&y[v]), 0u, __float_as_uint(yv)) == 0u) list_vertex(plan.l, plan.h, &listed, v, d);
+                else if (atomicCAS(reinterpret_cast<uint32_t*>(&y[v]), 0u, __float_as_uint(yv)) == 0u) list_vertex(plan.l, listed, v, d);
             }
         }
         if (include_hop0) tot[v] = log1p(-p0);
     }
     plan_hop<kBlock>(plan, edges);               // its barrier: everything is listed
-    if (plan.l.seg_count && threadIdx.x == 0) plan.l.seg_count[blockIdx.x] = listed;
+    if (plan.l.seg_count && threadIdx.x < 2) plan.l.seg_count[2 * blockIdx.x + threadIdx.x] = listed[threadIdx.x];
 }
 
 // ---- Proposition 1 with arbitrary initial and transition probabilities (Sec. 3.1) -------------
@@ -1038,6 +1038,28 @@ __device__ __forceinline__ uint32_t bin_edge(uint32_t c0, int q) {
     return c0 + (threadIdx.x >> 6) * (kWave * kPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
 }
 
+// Calls f(u, weight) for the portion's edges x, x + 64, ... (kBinPer of them, those below `total`): all of a thread's loads in
+// flight, a wavefront's contiguous.
+template <int kThreads, class F>
+__device__ __forceinline__ void push_run(const BinPortion<kThreads>& po, int nv, uint32_t total, uint32_t x, const int32_t* __restrict__ col, F f) {
+    if (x >= total) return;
+    BinCursor<kThreads> cu;
+    cu.start(po, nv, x);
+    int32_t u[kBinPer];
+    float w[kBinPer];
+#pragma unroll
+    for (int q = 0; q < kBinPer; ++q) {
+        u[q] = -1;
+        if (x + q * kWave < total) {
+            u[q] = col[cu.at(po, x + q * kWave)];
+            w[q] = cu.p;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kBinPer; ++q)
+        if (u[q] >= 0) f((uint32_t)u[q], w[q]);
+}
+
 // Calls f(u, weight) for every edge of this workgroup's portions of a frontier of nf entries.
 template <int kThreads, class RowOf, class F>
 __device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t nf, const float* __restrict__ y,
@@ -1046,24 +1068,7 @@ __device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t 
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
         const uint32_t total = bin_load_portion(po, nv, y, [&](int i, int64_t& b, uint32_t& deg) { return row_of(pm.entry(portion, i), b, deg); });
-        for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) {
-            if (bin_edge(c0, 0) >= total) continue;
-            BinCursor<kThreads> cu;
-            cu.start(po, nv, bin_edge(c0, 0));
-            int32_t u[kBinPer];
-            float w[kBinPer];
-#pragma unroll
-            for (int q = 0; q < kBinPer; ++q) {
-                u[q] = -1;
-                if (bin_edge(c0, q) < total) {
-                    u[q] = col[cu.at(po, bin_edge(c0, q))];
-                    w[q] = cu.p;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < kBinPer; ++q)
-                if (u[q] >= 0) f((uint32_t)u[q], w[q]);
-        }
+        for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) push_run(po, nv, total, bin_edge(c0, 0), col, f);
         __syncthreads();
     }
 }
@@ -1094,56 +1099,74 @@ __device__ __forceinline__ void bin_add_entries(double* acc, const uint2* __rest
 // accumulator of every member of adj(v) (fp64 global atomics).  Portions of frontier vertices walked as one
 // edge sequence, as above: with one wavefront per vertex the longest row set the
 // kernel's duration (138 us for the 1.2M out-edges of 24k training vertices, degrees up to 20k).  The frontier lies in
-// segments; where each starts in the whole is summed up by every workgroup for itself.
+// segments; where each starts in the whole is summed up by every workgroup for itself.  A portion of a workgroup's own has at
+// least 64 rows; one CU adds 0.5 G/s and forty reach the 21 G/s of all, so rows that are too long for that are walked by all
+// workgroups: each lays (up to 1024 of) them end to end for itself and the wavefronts of the launch take 512 edges in turn.
 struct PushLds {
     BinPortion<kTileBlock> po;
     uint32_t seg_first[kSegments];
 };
-__device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, int h, const float* __restrict__ y,
+__device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, const float* __restrict__ y,
                                               const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
                                               double* __restrict__ acc) {
+    static_assert(kSegments % kTileBlock == 0 && kWave * kBinPer == 512, "a thread's segments; a wavefront's edges");
     auto add = [&](uint32_t u, float w) { unsafeAtomicAdd(&acc[u], (double)w); };        // hardware fp64 add
     constexpr int kPer = kSegments / kTileBlock;
-    uint32_t c[kPer], mine = 0, nf;
+    uint32_t rows[kPer], longs[kPer], any = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         const int i = (int)threadIdx.x * kPer + k;
-        c[k] = i < l.nseg ? l.seg_count[i] : 0u;
-        mine += c[k];
+        rows[k] = i < l.nseg ? l.seg_count[2 * i] : 0u;
+        longs[k] = i < l.nseg ? l.seg_count[2 * i + 1] : 0u;
+        any |= longs[k];
     }
-    const uint32_t ng = l.ngiants[h & 1];
-    uint32_t run = bin_block_scan<kTileBlock>(mine, lds.po.wave_sum, nf);
+    auto lay_out = [&](const uint32_t (&c)[kPer]) {      // the segments' parts end to end; returns the number of entries
+        uint32_t mine = 0, all;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) { lds.seg_first[threadIdx.x * kPer + k] = run; run += c[k]; }
-    __syncthreads();
-    push_portions(lds.po, (int64_t)nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) {
+        for (int k = 0; k < kPer; ++k) mine += c[k];
+        uint32_t run = bin_block_scan<kTileBlock>(mine, lds.po.wave_sum, all);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) { lds.seg_first[threadIdx.x * kPer + k] = run; run += c[k]; }
+        __syncthreads();
+        return all;
+    };
+    auto row_of = [&](bool is_long, uint32_t i, int64_t& b, uint32_t& deg) {
         int s = 0;                               // the last segment that starts at or before entry i (empty ones start where the next does)
 #pragma unroll
         for (int step = kSegments / 2; step > 0; step >>= 1)
-            if (lds.seg_first[s + step] <= (uint32_t)i) s += step;
-        const int32_t v = l.list[(int64_t)s * l.seg_cap + ((uint32_t)i - lds.seg_first[s])];
+            if (lds.seg_first[s + step] <= i) s += step;
+        const int64_t at = i - lds.seg_first[s];
+        const int32_t v = l.list[(int64_t)s * l.seg_cap + (is_long ? l.seg_cap - 1 - at : at)];
         b = rowptr[v];
         deg = (uint32_t)(rowptr[v + 1] - b);
         return v;
-    }, add);
-    for (uint32_t g = 0; g < ng; ++g) {          // long rows, by all workgroups together
-        const int32_t v = l.giants[g];
-        const float w = y[v];
-        const int64_t e = rowptr[v + 1];
-        for (int64_t k = rowptr[v] + (int64_t)blockIdx.x * kTileBlock + threadIdx.x; k < e; k += (int64_t)gridDim.x * kTileBlock) add((uint32_t)col[k], w);
+    };
+    const uint32_t nf = lay_out(rows);
+    push_portions(lds.po, (int64_t)nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return row_of(false, (uint32_t)i, b, deg); }, add);
+    if (!__syncthreads_or((int)any)) return;
+    const uint32_t nlong = lay_out(longs);
+    for (uint32_t f0 = 0; f0 < nlong; f0 += kTileBlock) {
+        const int nv = (int)(nlong - f0 < kTileBlock ? nlong - f0 : kTileBlock);
+        // below 2^28 edges: the frontier of a pushed hop has M / kPushShare at most
+        const uint32_t total = bin_load_portion(lds.po, nv, y, [&](int t, int64_t& b, uint32_t& deg) { return row_of(true, f0 + (uint32_t)t, b, deg); });
+        // a wavefront of every workgroup before a second one of any
+        const uint32_t wave = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+        for (uint32_t x0 = wave * 512u; x0 < total; x0 += gridDim.x * (kTileBlock / kWave) * 512u)
+            push_run(lds.po, nv, total, x0 + (threadIdx.x & (kWave - 1)), col, add);
+        __syncthreads();
     }
 }
 
 // A hop in the form it takes: one launch, whose workgroups push the frontier or pull row blocks.  (A launch for each form,
 // one of which leaves at once, cost a hop 5 us, and listing the frontier in a third the same again.)
-__global__ void __launch_bounds__(kTileBlock) vip_hop_kernel(HopList l, int h, const int64_t* __restrict__ rowptr,
+__global__ void __launch_bounds__(kTileBlock) vip_hop_kernel(HopList l, const int64_t* __restrict__ rowptr,
                                                              const int32_t* __restrict__ col, const uint32_t* __restrict__ t_edge,
                                                              const int64_t* __restrict__ first, int nch, int64_t nrb, int parts,
                                                              int rbits, uint32_t N, const float* __restrict__ y,
                                                              double* __restrict__ acc, int64_t part_stride,
                                                              const uint32_t* __restrict__ how) {
     extern __shared__ double hop_lds[];
-    if (*how == kPushed) push_frontier(*reinterpret_cast<PushLds*>(hop_lds), l, h, y, rowptr, col, acc);
+    if (*how == kPushed) push_frontier(*reinterpret_cast<PushLds*>(hop_lds), l, y, rowptr, col, acc);
     else if (t_edge) pull_tiles(hop_lds, t_edge, first, nch, nrb, parts, rbits, N, y, acc, part_stride);
 }
 
@@ -1805,7 +1828,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     const int vgrid = groups(N), tgrid = groups(nT);
     // the frontier: in segments of the workgroups that list it, or (bins) as one list with the pieces of long rows
     const int64_t seg_all = vgrid * per_group(N) > tgrid * per_group(nT) ? vgrid * per_group(N) : tgrid * per_group(nT);
-    int64_t lcap = binned ? frontier_list_capacity(N, g->M) : seg_all + g->M / kGiantRow + kSegments + 2;
+    int64_t lcap = binned ? frontier_list_capacity(N, g->M) : seg_all + 2 * kSegments;
     lcap += lcap & 1;
     SPP_TRY(ctx->frontier.reserve((size_t)lcap * sizeof(int32_t) + (1 + SPP_MAX_L + 2) * sizeof(unsigned long long)));
     unsigned long long* slots;
@@ -1813,10 +1836,8 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     SPP_TRY(vip_state(ctx, &slots, &d_bad, &left_clean));
     int32_t* flist = ctx->frontier.as<int32_t>();
     uint32_t* seg_count = reinterpret_cast<uint32_t*>(flist + seg_all);
-    int32_t* giants = reinterpret_cast<int32_t*>(seg_count + kSegments);
     unsigned long long* fcursor = reinterpret_cast<unsigned long long*>(flist + lcap);       // of the one list
     uint32_t* how = reinterpret_cast<uint32_t*>(fcursor + 1);            // [1 .. L]: how each hop is walked
-    uint32_t* ngiants = how + SPP_MAX_L + 1;
     int64_t* mirror = ctx->h_pinned + kHopMirror;
     float* ycur = ctx->y0.as<float>();
     float* ynext = ctx->y1.as<float>();
@@ -1828,8 +1849,8 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
         double* acc = ctx->acc.as<double>();
-        HopPlan plan{1, g->M, slots, how, fcursor, mirror, {flist, binned ? nullptr : seg_count, per_group(nT), tgrid, giants, ngiants}};
-        vip_clear_kernel<<<vgrid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, binned ? nullptr : acc, N, ngiants);
+        HopPlan plan{1, g->M, slots, how, fcursor, mirror, {flist, binned ? nullptr : seg_count, per_group(nT), tgrid}};
+        vip_clear_kernel<<<vgrid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, binned ? nullptr : acc, N);
         vip_init_kernel<<<tgrid, kBlock, 0, st>>>(d_T, nT, N, p0, (double)fanouts[0], g->rowptr, ycur, tot, include0, d_bad, plan);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
@@ -1863,7 +1884,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 // as many workgroups as there are shares of row blocks, and one per CU at least for a push
                 const int64_t shares = g->has_x ? 0 : g->nrb * parts;
                 vip_hop_kernel<<<(unsigned)(shares > ctx->num_cu ? shares : ctx->num_cu), kTileBlock, hop_lds, st>>>(
-                    walked, h, g->rowptr, g->col, g->t_edge, g->tile_first, g->nch, g->nrb, parts, g->tile_rbits, (uint32_t)N, ycur, acc,
+                    walked, g->rowptr, g->col, g->t_edge, g->tile_first, g->nch, g->nrb, parts, g->tile_rbits, (uint32_t)N, ycur, acc,
                     part_stride, how_h);
             }
             int fused = 0;

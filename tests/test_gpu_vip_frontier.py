@@ -1,6 +1,7 @@
 """GPU: the frontier that a hop's writer lists for the next hop's push -- segments of one and of several rounds of
-vertices, ids that the training set names more than once, rows long enough for the list that all workgroups walk
-together (more than 32768 entries), at the first hop and reached by it -- against the CPU oracle."""
+vertices, ids that the training set names more than once, rows long enough to be walked by all workgroups together (more
+than 1024 entries), at the first hop and reached by it -- against the CPU oracle; and that a push of few long rows takes
+no longer than one of many short ones."""
 import numpy as np
 import pytest
 import torch
@@ -46,6 +47,12 @@ def _case(name):
         deg = np.full(60_000, 9)
         T = np.arange(1500, dtype=np.int32) * 17
         return deg, np.concatenate([T, T[:700], T[:1]])
+    if name == "long_rows":              # 1100 rows above 1024 entries, which a workgroup lays out in two rounds, 1100 below
+        deg = np.full(1_200_000, 30)
+        T = (np.arange(2200, dtype=np.int64) * 500).astype(np.int32)
+        deg[T] = 1025 + np.arange(2200) % 3
+        deg[T[::2]] = 1022 + np.arange(1100) % 3
+        return deg, T
     if name == "rounds":                 # more training vertices than 2048 workgroups take in a round, all with one edge
         deg = np.full(1_400_000, 14)
         T = (np.arange(600_000, dtype=np.int64) * 2).astype(np.int32)
@@ -55,7 +62,7 @@ def _case(name):
     return deg, np.array([299], np.int32)
 
 
-@pytest.mark.parametrize("name", ["giants", "named_twice", "rounds", "one"])
+@pytest.mark.parametrize("name", ["giants", "long_rows", "named_twice", "rounds", "one"])
 @pytest.mark.parametrize("chunked", [False, True])
 def test_listed_frontiers(spp, ctx, name, chunked):
     print("[case]", name, chunked, flush=True)
@@ -73,3 +80,26 @@ def test_listed_frontiers(spp, ctx, name, chunked):
             # results are rounded to fp32 at every hop: 6e-8 a hop, well below the 1e-5 the entry point states
             assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 1e-6 * np.asarray(ref) + 1e-37)
     G.close()
+
+
+def test_long_rows_are_shared_out(spp):
+    """1,024,000 edges in 64 rows and in 20480: the same adds, by all CUs either way (eight times as long, 241 and 31 us,
+    where one workgroup walks the 64 rows; three times leaves room for noise)."""
+    deg = np.full(1_200_000, 30)
+    deg[:64], deg[64:64 + 20480] = 16000, 50
+    rp, col = _graph(deg)
+    dev = torch.device("cuda:0")
+    ctx = spp.Context(0)
+    G = spp.Graph(ctx, torch.from_numpy(rp).to(dev), torch.from_numpy(col).to(dev), in_lists=True)
+    took = []
+    for T in (torch.arange(64, dtype=torch.int32), torch.arange(64, 64 + 20480, dtype=torch.int32)):
+        T = T.to(dev)
+        spp.vip_propagate(ctx, G, T, 32, (3,))
+        ctx.timing(True)
+        for _ in range(8):
+            spp.vip_propagate(ctx, G, T, 32, (3,))
+        took.append(ctx.time_stats()[2][1])                 # SPP_T_VIP_HOP_FIRST, the shortest
+        assert spp.vip_last_hops(ctx, 1) == ([True], [1_024_000])
+        ctx.timing(False)
+    ctx.close()
+    assert took[0] < 3 * took[1], took
