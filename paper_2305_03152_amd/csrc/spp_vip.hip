@@ -1038,10 +1038,10 @@ __device__ __forceinline__ uint32_t bin_edge(uint32_t c0, int q) {
     return c0 + (threadIdx.x >> 6) * (kWave * kPer) + (uint32_t)q * kWave + (threadIdx.x & (kWave - 1));
 }
 
-// Calls f(u, weight) for the portion's edges x, x + 64, ... (kBinPer of them, those below `total`): all of a thread's loads in
-// flight, a wavefront's contiguous.
+// Calls f(u, weight) for the portion's edges x, x + 64, ... (`runs` of them, at most kBinPer, those below `total`): all of a
+// thread's loads in flight, a wavefront's contiguous.
 template <int kThreads, class F>
-__device__ __forceinline__ void push_run(const BinPortion<kThreads>& po, int nv, uint32_t total, uint32_t x, const int32_t* __restrict__ col, F f) {
+__device__ __forceinline__ void push_run(const BinPortion<kThreads>& po, int nv, uint32_t total, uint32_t x, int runs, const int32_t* __restrict__ col, F f) {
     if (x >= total) return;
     BinCursor<kThreads> cu;
     cu.start(po, nv, x);
@@ -1050,7 +1050,7 @@ __device__ __forceinline__ void push_run(const BinPortion<kThreads>& po, int nv,
 #pragma unroll
     for (int q = 0; q < kBinPer; ++q) {
         u[q] = -1;
-        if (x + q * kWave < total) {
+        if (q < runs && x + q * kWave < total) {
             u[q] = col[cu.at(po, x + q * kWave)];
             w[q] = cu.p;
         }
@@ -1068,7 +1068,11 @@ __device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t 
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
         const uint32_t total = bin_load_portion(po, nv, y, [&](int i, int64_t& b, uint32_t& deg) { return row_of(pm.entry(portion, i), b, deg); });
-        for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) push_run(po, nv, total, bin_edge(c0, 0), col, f);
+        for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) {
+            // of few edges every wavefront gets some (a hop from 200k rows of one edge: 49 us; 83 with 512 edges to a wavefront)
+            const uint32_t runs = total - c0 < kThreads * kBinPer ? (total - c0 + kThreads - 1) / kThreads : kBinPer;
+            push_run(po, nv, total, c0 + ((threadIdx.x >> 6) * runs << 6) + (threadIdx.x & (kWave - 1)), (int)runs, col, f);
+        }
         __syncthreads();
     }
 }
@@ -1152,7 +1156,7 @@ __device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, co
         // a wavefront of every workgroup before a second one of any
         const uint32_t wave = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
         for (uint32_t x0 = wave * 512u; x0 < total; x0 += gridDim.x * (kTileBlock / kWave) * 512u)
-            push_run(lds.po, nv, total, x0 + (threadIdx.x & (kWave - 1)), col, add);
+            push_run(lds.po, nv, total, x0 + (threadIdx.x & (kWave - 1)), kBinPer, col, add);
         __syncthreads();
     }
 }
