@@ -791,7 +791,9 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
 }
 
 // y_1(v) for the training vertices (p^[0] = min(1, B/|T|), Sec. 3.1); optionally hop 0 into the
-// total; lists and counts hop 1's frontier on the way (a vertex that T names twice is listed once and counted twice).
+// total; lists and counts hop 1's frontier on the way.  A vertex that T names twice is counted twice, and listed twice unless
+// its row is long, which every workgroup of the walk reads the weight of: a compare-and-swap for every vertex cost calls
+// with large sets, whose hops are all pulled, 95 us of 870 (8M vertices, all in T).
 __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restrict__ T, int64_t nT, int64_t N, double p0,
                                                           double f1, const int64_t* __restrict__ rowptr,
                                                           float* __restrict__ y, double* __restrict__ tot, int include_hop0,
@@ -811,8 +813,10 @@ __global__ void __launch_bounds__(kBlock) vip_init_kernel(const int32_t* __restr
             const float yv = (float)log1p(-(t * p0));
             if (yv != 0.0f) {
                 edges += (unsigned long long)d;
-                if (plan.l.seg_count == nullptr) y[v] = yv;
-                else if (atomicCAS(reinterpret_cast<uint32_t*>(&y[v]), 0u, __float_as_uint(yv)) == 0u) list_vertex(plan.l, listed, v, d);
+                const bool once = plan.l.seg_count && d > kLongRow;
+                if (!once) y[v] = yv;
+                if (plan.l.seg_count && (!once || atomicCAS(reinterpret_cast<uint32_t*>(&y[v]), 0u, __float_as_uint(yv)) == 0u))
+                    list_vertex(plan.l, listed, v, d);
             }
         }
         if (include_hop0) tot[v] = log1p(-p0);
@@ -984,16 +988,15 @@ __device__ __forceinline__ int bin_vertex_of(const BinPortion<kThreads>& po, int
     return lo;
 }
 
-// Lays the rows of the portion's nv vertices end to end; row_of(t, start, length) = the t-th of them.  Returns the number of
+// Lays the rows of the portion's nv vertices end to end; row_of(t, start, length) = the t-th one's weight.  Returns the number of
 // edges.  Ends with a barrier; the caller puts one between the last use of a portion and the next call.
 template <int kThreads, class RowOf>
-__device__ __forceinline__ uint32_t bin_load_portion(BinPortion<kThreads>& po, int nv, const float* __restrict__ p, RowOf row_of) {
+__device__ __forceinline__ uint32_t bin_load_portion(BinPortion<kThreads>& po, int nv, RowOf row_of) {
     uint32_t deg = 0;
     if ((int)threadIdx.x < nv) {
         int64_t b;
-        const int32_t v = row_of((int)threadIdx.x, b, deg);
+        po.p[threadIdx.x] = row_of((int)threadIdx.x, b, deg);
         po.row[threadIdx.x] = b;
-        po.p[threadIdx.x] = p[v];
     }
     uint32_t total;
     const uint32_t ex = bin_block_scan<kThreads>(deg, po.wave_sum, total);
@@ -1062,12 +1065,12 @@ __device__ __forceinline__ void push_run(const BinPortion<kThreads>& po, int nv,
 
 // Calls f(u, weight) for every edge of this workgroup's portions of a frontier of nf entries.
 template <int kThreads, class RowOf, class F>
-__device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t nf, const float* __restrict__ y,
+__device__ __forceinline__ void push_portions(BinPortion<kThreads>& po, int64_t nf,
                                               const int32_t* __restrict__ col, RowOf row_of, F f) {
     const PortionMap<kThreads> pm(nf);
     for (int64_t portion = blockIdx.x; portion < pm.nportions; portion += gridDim.x) {
         const int nv = pm.count(portion);
-        const uint32_t total = bin_load_portion(po, nv, y, [&](int i, int64_t& b, uint32_t& deg) { return row_of(pm.entry(portion, i), b, deg); });
+        const uint32_t total = bin_load_portion(po, nv, [&](int i, int64_t& b, uint32_t& deg) { return row_of(pm.entry(portion, i), b, deg); });
         for (uint32_t c0 = 0; c0 < total; c0 += kThreads * kBinPer) {
             // of few edges every wavefront gets some (a hop from 200k rows of one edge: 49 us; 83 with 512 edges to a wavefront)
             const uint32_t runs = total - c0 < kThreads * kBinPer ? (total - c0 + kThreads - 1) / kThreads : kBinPer;
@@ -1080,7 +1083,7 @@ template <class F>
 __device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf, const int32_t* __restrict__ list,
                                           const float* __restrict__ y, const int64_t* __restrict__ rowptr,
                                           const int32_t* __restrict__ col, F f) {
-    push_portions(po, nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return frontier_entry(list, i, rowptr, b, deg); }, f);
+    push_portions(po, nf, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return y[frontier_entry(list, i, rowptr, b, deg)]; }, f);
 }
 
 // Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.
@@ -1110,7 +1113,7 @@ struct PushLds {
     BinPortion<kTileBlock> po;
     uint32_t seg_first[kSegments];
 };
-__device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, const float* __restrict__ y,
+__device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, int h, float* __restrict__ y,
                                               const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
                                               double* __restrict__ acc) {
     static_assert(kSegments % kTileBlock == 0 && kWave * kBinPer == 512, "a thread's segments; a wavefront's edges");
@@ -1143,16 +1146,18 @@ __device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, co
         const int32_t v = l.list[(int64_t)s * l.seg_cap + (is_long ? l.seg_cap - 1 - at : at)];
         b = rowptr[v];
         deg = (uint32_t)(rowptr[v + 1] - b);
-        return v;
+        // a vertex that the training set names twice is listed twice (see vip_init_kernel): one of the entries takes the weight,
+        // and nothing reads y after a push
+        return h == 1 && !is_long ? __uint_as_float(atomicExch(reinterpret_cast<uint32_t*>(y) + v, 0u)) : y[v];
     };
     const uint32_t nf = lay_out(rows);
-    push_portions(lds.po, (int64_t)nf, y, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return row_of(false, (uint32_t)i, b, deg); }, add);
+    push_portions(lds.po, (int64_t)nf, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return row_of(false, (uint32_t)i, b, deg); }, add);
     if (!__syncthreads_or((int)any)) return;
     const uint32_t nlong = lay_out(longs);
     for (uint32_t f0 = 0; f0 < nlong; f0 += kTileBlock) {
         const int nv = (int)(nlong - f0 < kTileBlock ? nlong - f0 : kTileBlock);
         // below 2^28 edges: the frontier of a pushed hop has M / kPushShare at most
-        const uint32_t total = bin_load_portion(lds.po, nv, y, [&](int t, int64_t& b, uint32_t& deg) { return row_of(true, f0 + (uint32_t)t, b, deg); });
+        const uint32_t total = bin_load_portion(lds.po, nv, [&](int t, int64_t& b, uint32_t& deg) { return row_of(true, f0 + (uint32_t)t, b, deg); });
         // a wavefront of every workgroup before a second one of any
         const uint32_t wave = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
         for (uint32_t x0 = wave * 512u; x0 < total; x0 += gridDim.x * (kTileBlock / kWave) * 512u)
@@ -1163,14 +1168,14 @@ __device__ __forceinline__ void push_frontier(PushLds& lds, const HopList& l, co
 
 // A hop in the form it takes: one launch, whose workgroups push the frontier or pull row blocks.  (A launch for each form,
 // one of which leaves at once, cost a hop 5 us, and listing the frontier in a third the same again.)
-__global__ void __launch_bounds__(kTileBlock) vip_hop_kernel(HopList l, const int64_t* __restrict__ rowptr,
+__global__ void __launch_bounds__(kTileBlock) vip_hop_kernel(HopList l, int h, const int64_t* __restrict__ rowptr,
                                                              const int32_t* __restrict__ col, const uint32_t* __restrict__ t_edge,
                                                              const int64_t* __restrict__ first, int nch, int64_t nrb, int parts,
-                                                             int rbits, uint32_t N, const float* __restrict__ y,
+                                                             int rbits, uint32_t N, float* __restrict__ y,
                                                              double* __restrict__ acc, int64_t part_stride,
                                                              const uint32_t* __restrict__ how) {
     extern __shared__ double hop_lds[];
-    if (*how == kPushed) push_frontier(*reinterpret_cast<PushLds*>(hop_lds), l, y, rowptr, col, acc);
+    if (*how == kPushed) push_frontier(*reinterpret_cast<PushLds*>(hop_lds), l, h, y, rowptr, col, acc);
     else if (t_edge) pull_tiles(hop_lds, t_edge, first, nch, nrb, parts, rbits, N, y, acc, part_stride);
 }
 
@@ -1539,8 +1544,8 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
         __syncthreads();
         if ((int64_t)portion >= pm.nportions) break;
         const int nv = pm.count(portion);
-        const uint32_t total = bin_load_portion(po, nv, pcur, [&](int i, int64_t& b, uint32_t& deg) {
-            return frontier_entry(list, pm.entry(portion, i), rowptr, b, deg);
+        const uint32_t total = bin_load_portion(po, nv, [&](int i, int64_t& b, uint32_t& deg) {
+            return pcur[frontier_entry(list, pm.entry(portion, i), rowptr, b, deg)];
         });
         for (uint32_t c0 = 0; c0 < total; c0 += kFillBlock * kFillPer) {
             uint32_t key[kFillPer], rank[kFillPer];
@@ -1888,7 +1893,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 // as many workgroups as there are shares of row blocks, and one per CU at least for a push
                 const int64_t shares = g->has_x ? 0 : g->nrb * parts;
                 vip_hop_kernel<<<(unsigned)(shares > ctx->num_cu ? shares : ctx->num_cu), kTileBlock, hop_lds, st>>>(
-                    walked, g->rowptr, g->col, g->t_edge, g->tile_first, g->nch, g->nrb, parts, g->tile_rbits, (uint32_t)N, ycur, acc,
+                    walked, h, g->rowptr, g->col, g->t_edge, g->tile_first, g->nch, g->nrb, parts, g->tile_rbits, (uint32_t)N, ycur, acc,
                     part_stride, how_h);
             }
             int fused = 0;

@@ -47,6 +47,11 @@ def _case(name):
         deg = np.full(60_000, 9)
         T = np.arange(1500, dtype=np.int32) * 17
         return deg, np.concatenate([T, T[:700], T[:1]])
+    if name == "long_twice":             # rows above the limit and below, each named up to three times
+        deg = np.full(600_000, 20)
+        T = (np.arange(300, dtype=np.int64) * 1700).astype(np.int32)
+        deg[T] = 1000 + np.arange(300) % 3 * 20
+        return deg, np.concatenate([T, T[::-1], T[100:200]])
     if name == "long_rows":              # 1100 rows above 1024 entries, which a workgroup lays out in two rounds, 1100 below
         deg = np.full(1_200_000, 30)
         T = (np.arange(2200, dtype=np.int64) * 500).astype(np.int32)
@@ -62,7 +67,7 @@ def _case(name):
     return deg, np.array([299], np.int32)
 
 
-@pytest.mark.parametrize("name", ["giants", "long_rows", "named_twice", "rounds", "one"])
+@pytest.mark.parametrize("name", ["giants", "long_rows", "long_twice", "named_twice", "rounds", "one"])
 @pytest.mark.parametrize("chunked", [False, True])
 def test_listed_frontiers(spp, ctx, name, chunked):
     print("[case]", name, chunked, flush=True)
