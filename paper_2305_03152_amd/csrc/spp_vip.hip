@@ -837,7 +837,8 @@ __device__ __forceinline__ float unit_or_flag(float x, int* bad) {
 
 // How a hop of the general propagation fills its bins: from a list of its frontier, or (kWhole) from the whole CSR, tile
 // by tile, where the frontier's rows hold at least half of the edges.  The kernel that writes a hop's
-// probabilities counts their vertices' out-edges and decides.  2.4M vertices, 121M edges, list, fill and sum: by tiles 640 us
+// probabilities counts their vertices' out-edges and decides; on large graphs it counts a part of them (either form is correct
+// for any frontier).  2.4M vertices, 121M edges, list, fill and sum: by tiles 640 us
 // whatever the frontier; listed 1075 us with all edges, 345 with 23 % of them.
 constexpr uint32_t kListed = 1, kWhole = 2;
 struct FillRule {
@@ -845,14 +846,21 @@ struct FillRule {
     int64_t M;
     unsigned long long* slots;
     uint32_t* how;                       // the next hop's
-    __device__ __forceinline__ unsigned long long degree(int64_t v) const {
-        return rowptr ? (unsigned long long)(rowptr[v + 1] - rowptr[v]) : 0ull;
-    }
-    __device__ __forceinline__ void decide(unsigned long long edges) const {      // by whole workgroups of kBlock threads
+    int sample;                          // looks at the vertices of one in so many rounds of a wavefront: a power of two
+    // By whole workgroups of kBlock threads, whose threads have written the next hop's p[v], p[v + stride], ...; in a loop of its
+    // own, after the one that writes them.  (Every vertex's degree, read in that loop: a call of three sparse hops on 8M vertices
+    // 389 us, where it takes 350; only the frontier's, 381: a load under a condition keeps the loop's others from overlapping.)
+    __device__ __forceinline__ void decide(const float* p, int64_t N) const {
         if (!rowptr) return;
+        const int64_t stride = (int64_t)gridDim.x * kBlock, tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+        unsigned long long edges = 0;
+        for (int64_t v = tid + ((tid >> 6) & (sample - 1)) * stride; v < N; v += sample * stride) {
+            const unsigned long long deg = (unsigned long long)(rowptr[v + 1] - rowptr[v]);
+            edges += p[v] > 0.0f ? deg : 0ull;
+        }
         const unsigned long long mine = workgroup_sum<kBlock>(edges);
         unsigned long long all;
-        if (threadIdx.x == 0 && grid_total(slots, mine, all)) *how = 2 * all >= (unsigned long long)M ? kWhole : kListed;
+        if (threadIdx.x == 0 && grid_total(slots, mine, all)) *how = 2 * all * sample >= (unsigned long long)M ? kWhole : kListed;
     }
 };
 
@@ -872,15 +880,12 @@ __global__ void __launch_bounds__(kBlock) vipg_init_kernel(const float* __restri
                                                            int include_hop0, int* __restrict__ bad, FillRule rule, HopCounters c) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
-    unsigned long long edges = 0;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < N; v += stride) {
-        const unsigned long long deg = rule.degree(v);
         const float p = unit_or_flag(p0[v], bad);
         pcur[v] = p;
-        edges += p > 0.0f ? deg : 0ull;
         if (include_hop0) tot[v] = log1p(-(double)p);
     }
-    rule.decide(edges);
+    rule.decide(pcur, N);
 }
 
 __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __restrict__ list,
@@ -1356,7 +1361,10 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) char prepare_lds[];
     if (*how != kWhole) {
-        list_frontier<kFillBlock, 8>(pcur, rowptr, N, list, cursor, reinterpret_cast<uint32_t*>(prepare_lds));
+        uint32_t* lds = reinterpret_cast<uint32_t*>(prepare_lds);
+        // a sparse frontier among 8M vertices 16 us instead of 20; small graphs and denser frontiers the other way round
+        if (N >= (int64_t)1 << 22) list_frontier<kFillBlock, 16>(pcur, rowptr, N, list, cursor, lds);
+        else list_frontier<kFillBlock, 8>(pcur, rowptr, N, list, cursor, lds);
         return;
     }
     PrepareLds& l = *reinterpret_cast<PrepareLds*>(prepare_lds);
@@ -1619,20 +1627,18 @@ __global__ void __launch_bounds__(kBlock) vipg_finish_kernel(const double* __res
                                                              int64_t N, int parts, int64_t part_stride, HopCounters c,
                                                              FillRule rule, int* __restrict__ bad, int64_t* __restrict__ bad_mirror) {
     if (last && blockIdx.x == 0 && threadIdx.x == 0) { *bad_mirror = *bad; *bad = 0; }
-    unsigned long long edges = 0;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     c.clear((int64_t)blockIdx.x * kBlock + threadIdx.x, stride);
     for (int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x; u < N; u += stride) {
-        const unsigned long long deg = last ? 0ull : rule.degree(u);
         double S = acc[u];
         for (int j = 1; j < parts; ++j) S += acc[(int64_t)j * part_stride + u];
         const double ph = -expm1(S);
         if (p_hop) p_hop[u] = (float)ph;
         const double T = first ? S : tot[u] + S;
         if (last) p_total[u] = (float)(-expm1(T));
-        else { tot[u] = T; pnext[u] = (float)ph; edges += (float)ph > 0.0f ? deg : 0ull; }
+        else { tot[u] = T; pnext[u] = (float)ph; }
     }
-    if (!last) rule.decide(edges);
+    if (!last) rule.decide(pnext, N);
 }
 
 // The context's words for grid_total and the flag for bad input.  They are empty from the context's creation on, whether calls
@@ -1726,7 +1732,9 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
     {
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
         const HopCounters counters{fcount + 2, cursor, binned ? g->nrb + 1 : 0};
-        FillRule rule{tiles ? g->rowptr : nullptr, g->M, slots, how + 1};
+        int sample = 1;                          // of a graph of up to 8M vertices, one to two rounds of the launch are looked at
+        while (sample < 8 && N >= 2 * sample * (int64_t)fill_grid * kBlock) sample *= 2;
+        FillRule rule{tiles ? g->rowptr : nullptr, g->M, slots, how + 1, sample};
         vipg_init_kernel<<<fill_grid, kBlock, 0, st>>>(d_p0, N, pcur, tot, include0, d_bad, rule, counters);
         for (int h = 1; h <= L; ++h) {
             ScopedTimer th(ctx, SPP_T_VIP_HOP_FIRST + h - 1, st);
