@@ -368,7 +368,6 @@ __device__ __forceinline__ int64_t table_find(const unsigned long long* tab, uin
     }
 }
 
-// ---------------------------------------------------------------------------------------------
 // The row among lo .. hi that holds edge e of the CSR (row lo starts at or before it, row hi ends after it): the last one that
 // starts at or before it.
 __device__ __forceinline__ int32_t row_of_edge(const int64_t* __restrict__ rowptr, int32_t lo, int32_t hi, int64_t e) {
@@ -379,6 +378,7 @@ __device__ __forceinline__ int32_t row_of_edge(const int64_t* __restrict__ rowpt
     return lo;
 }
 
+// ---------------------------------------------------------------------------------------------
 // Row-block layout: see spp_edges.h.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kTileWinBytes = 16 * 448 * 4;    // windows of y in the dense-hop kernel's LDS: 448 values for each of 16 wavefronts

@@ -17,8 +17,9 @@ constexpr uint32_t kTileRowMask = (1u << kTileRowBits) - 1u;
 constexpr int kPartTile = 4096;          // edges of the CSR per tile of the partition that lays the words out
 // The kernels that walk such tiles look at all rows between a tile's first edge and the next tile's, empty ones included; beyond
 // this many (isolated vertices side by side) every edge bisects for its row instead: some twenty dependent reads, where 4M
-// empty rows would be 4000 rounds of a workgroup.
-constexpr int kTileManyRows = 16384;
+// empty rows would be 4000 rounds of a workgroup.  Rows per tile, placing pass and general fill in us, all rows and bisected:
+// 8000 (1029 tiles) 75 + 42, 106 + 76; 16000 (516) 65 + 39, 78 + 59; 32000 (258) 66 + 40, 61 + 48; 64000 (129) 58 + 52, 35 + 32.
+constexpr int kTileManyRows = 32768;
 
 __device__ __forceinline__ uint32_t tile_source(uint32_t word, int chunk) {
     return ((uint32_t)chunk << kTileSrcLoBits) | (word >> kTileRowBits);

@@ -42,6 +42,7 @@ def _cases():
         yield f"spread{M}", 20000, M, None
     yield "hubs", 40000, 0, {5: 20000, 6: 1, 7: 3 * TILE, 8000: TILE, 39999: TILE + 1}
     yield "empty", 60000, 0, {0: 10, 30000: 2000, 59000: 7000}           # tens of thousands of empty rows inside a tile
+    yield "gaps", 60000, 0, {0: 3000, 25000: 3000, 50000: 3000}          # fewer, which are looked at one by one
     yield "single", 70 * 16384 + 3, -1, None                             # one edge per row: 4096 rows a tile, 71 row blocks
     yield "most_blocks", 1 << 23, -1, None                               # 512 row blocks
 
