@@ -25,6 +25,7 @@
 // on small graphs they set its time.
 #include "spp_common.h"
 #include "spp_device.h"
+#include "spp_fp32.h"
 #include "spp_fp64.h"
 
 #include <type_traits>
@@ -1302,29 +1303,6 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
     unsigned long long edges = 0;
     vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, edges);
     if (!a.last) plan_hop<kTileBlock>(a.next, edges);
-}
-
-// log1p(-x) for 0 < x <= 1 to a few fp32 ulp.  All terms of a vertex's sum have one sign, so the
-// sum's relative error is at most the largest of its terms'; the library's fp32 and fp64 routines
-// carry extended precision that is of no use here and were 90 and 117 of the walk's instructions per
-// edge.  Below 1/4 the atanh series in s = x / (2 - x) <= 1/7 (six terms: the next is below 2^-33
-// of the first); above, the logarithm of 1 - x, whose rounding error is at most 2^-25 against a
-// result of at least 0.28.
-__device__ __forceinline__ float bin_log1p_neg(float x) {
-    // x / (2 - x) from the reciprocal's estimate and one correction: to half a unit as the division, four instructions
-    // instead of eleven (2 - x lies in [1, 2])
-    const float d = 2.0f - x, r = __builtin_amdgcn_rcpf(d), s0 = x * r;
-    const float s = __fmaf_rn(__fmaf_rn(-s0, d, x), r, s0);
-    const float z = s * s;
-    float q = 1.0f / 11.0f;
-    q = __fmaf_rn(q, z, 1.0f / 9.0f);
-    q = __fmaf_rn(q, z, 1.0f / 7.0f);
-    q = __fmaf_rn(q, z, 1.0f / 5.0f);
-    q = __fmaf_rn(q, z, 1.0f / 3.0f);
-    q = __fmaf_rn(q, z, 1.0f);
-    const float small = __fmaf_rn(-2.0f * s, q, 0.0f);     // +0 for x = 0
-    const float large = __logf(1.0f - x);
-    return x < 0.25f ? small : large;
 }
 
 // The bins of a hop whose frontier holds most of the edges.  A tile of the CSR (kPartTile edges) puts its edges of a row block
