@@ -1,5 +1,7 @@
 """GPU: graphs and caches built from memory that closed ones left behind -- other sizes, several threads with a context
-and a stream each -- give what freshly allocated ones give, and what is kept stays within its bound."""
+and a stream each -- give what freshly allocated ones give; what is kept serves the next build, stays within its bound
+and goes back with the last context or on request."""
+import gc
 import threading
 
 import numpy as np
@@ -73,19 +75,45 @@ def test_threads(spp):
     assert not errors, errors
 
 
+def _free():
+    """Bytes the device reports free, without what torch and handles that nothing refers to any more keep."""
+    gc.collect()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_what_is_kept_serves_the_next_build(spp):
+    N, deg = 2_000_000, 30
+    rp = torch.arange(N + 1, dtype=torch.int64, device="cuda") * deg
+    col = ((torch.arange(N, device="cuda").unsqueeze(1) + torch.arange(1, deg + 1, device="cuda")) % N).sort(1).values.to(torch.int32).reshape(-1)
+    ctx = spp.Context(0)
+    spp.release_memory(0)
+    before = _free()
+    g = spp.Graph(ctx, rp, col, in_lists=True)
+    built = _free()
+    assert before - built >= 4 * N * deg                                    # a word per edge, and what goes with it
+    for _ in range(2):
+        g.close()
+        assert _free() == built                                             # nothing went back ...
+        g = spp.Graph(ctx, rp, col, in_lists=True)
+        assert _free() == built                                             # ... and nothing more was taken
+    g.close()
+    ctx.close()
+    assert _free() >= before                                                # the last context's own buffers went with it
+
+
 def test_what_is_kept_is_bounded(spp):
     ctx = spp.Context(0)
-    torch.cuda.synchronize()
-    before = torch.cuda.mem_get_info()[0]
+    spp.release_memory(0)
+    before = _free()
     for N in (3_000_000, 4_000_000, 5_000_000, 6_000_000, 7_000_000):       # 30 edges a vertex: 360 to 840 MB, 3 GB in all
         rp = torch.arange(N + 1, dtype=torch.int64, device="cuda") * 30
         col = ((torch.arange(N, device="cuda").unsqueeze(1) + torch.arange(1, 31, device="cuda")) % N).sort(1).values.to(torch.int32).reshape(-1)
         g = spp.Graph(ctx, rp, col, in_lists=True)
         g.close()
         del rp, col, g
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    assert before - torch.cuda.mem_get_info()[0] < (1 << 30) + (256 << 20)  # the bound, and what the context's buffers hold
+    assert 360 << 20 < before - _free() < (1 << 30) + (256 << 20)            # something; the bound and what the context's buffers hold
     ctx.close()
 
 
@@ -94,13 +122,11 @@ def test_what_is_kept_is_given_back_on_request(spp):
     N, deg = 1_000_000, 30
     rp = torch.arange(N + 1, dtype=torch.int64, device="cuda") * deg
     col = ((torch.arange(N, device="cuda").unsqueeze(1) + torch.arange(1, deg + 1, device="cuda")) % N).sort(1).values.to(torch.int32).reshape(-1)
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    before = torch.cuda.mem_get_info()[0]
+    before = _free()
     spp.Graph(ctx, rp, col, in_lists=True).close()
-    assert before - torch.cuda.mem_get_info()[0] > 4 * N * deg          # the edges' words are kept
+    assert before - _free() > 4 * N * deg                               # the edges' words are kept
     spp.release_memory(0)
-    assert before - torch.cuda.mem_get_info()[0] < 2 * N * deg
+    assert before - _free() < 2 * N * deg
     ctx.close()
     with pytest.raises(spp.SppError):
         spp.release_memory(-1)
