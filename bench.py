@@ -33,7 +33,7 @@ PCIE_PEAK_GBS = 64.0           # PCIe Gen5 x16, one direction
 # report null.  The sampler's are of a full call: the profiled run's totals less its one small call.
 MEASURED_TRAFFIC = {
     ("large", 64): {"gather_hit": 1.385e+09, "sampler_call": 5.73e+08, "vip_dense_hop": 4.836e+10},
-    ("mid", 64): {"gather_hit": 2.28e+09, "sampler_call": 6.72e+08, "vip_dense_hop": 8.23e+08},
+    ("mid", 64): {"gather_hit": 2.28e+09, "sampler_call": 6.72e+08, "vip_dense_hop": 8.2e+08},
 }
 
 

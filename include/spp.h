@@ -57,7 +57,7 @@ enum {
 #define SPP_SYNC              0x1u   /* wait for the stream before returning and fill host outputs */
 #define SPP_VIP_INCLUDE_HOP0  0x2u   /* also multiply (1 - p^[0]) into eq. (1); default: as printed, h = 1..L */
 #define SPP_GRAPH_IN_LISTS    0x4u   /* spp_graph_create: also build the transposed edge structure (who can sample u)
-                                        that vip_propagate needs: 4 bytes per edge of device memory */
+                                        that vip_propagate needs: 4 to 4.5 bytes per edge of device memory (see there) */
 #define SPP_GRAPH_CHUNKED     0x20u  /* spp_graph_create, with SPP_GRAPH_IN_LISTS: build the layout for graphs whose
                                         per-vertex vectors exceed the caches (two passes per dense hop) whatever N is;
                                         by default graphs above 2^23 vertices get it */

@@ -57,7 +57,7 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
-// edges: the kernels of a build 9.2 -> 1.0 ms: 0.54 in the placing pass, most of it vector instructions,
+// edges: the kernels of a build 9.2 -> 1.0 ms: 0.55 in the placing pass, most of it vector instructions,
 // 0.12 in the counting pass, 0.15 in the read-back and 0.20 in the sum over the CSR that it is compared with.
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
@@ -142,7 +142,7 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64
 // rank among its wavefront's edges of the block.  Four barriers per tile: (1) sources and ranks; (2) per block, the
 // wavefronts' places; (3) the words; (4) they are stored while the next tile's rows are marked.  All loads of a
 // tile are asked for before the stores of the tile before, unconditionally: a load that is waited for after stores waits for those too.
-// 2.4M vertices, 121M edges: 544 us (628 with nine barriers and the loads at the head of a tile; 1.0 GB, which a copy moves
+// 2.4M vertices, 121M edges: 530 to 570 us by box (630 on the fastest with nine barriers and the loads at the head of a tile; 1.0 GB, which a copy moves
 // in 150): vector instructions two thirds of the time, the ballots that rank the edges a third of them.  (Asking first
 // whether 64 edges end in one block, as those of a hub's row do: 663, it spills registers.)
 struct PlaceLds {
