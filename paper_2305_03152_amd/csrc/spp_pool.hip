@@ -30,15 +30,9 @@ hipError_t device_malloc(void** out, size_t bytes) {
     hipError_t e = hipMalloc(out, bytes);
     int device = 0;
     if (e != hipErrorOutOfMemory || hipGetDevice(&device) != hipSuccess) return e;
-    MemoryPool* p = pool_of(device);
-    if (!p) return e;
-    {
-        std::lock_guard<std::mutex> hold(p->lock);
-        if (p->kept.empty()) return e;
-        p->trim();
-    }
+    pool_trim(device);
     (void)hipGetLastError();
-    return hipMalloc(out, bytes);
+    return hipMalloc(out, bytes);        // also where there was nothing to give: another thread may just have emptied the pool
 }
 
 hipError_t pool_take(int device, void** out, size_t bytes) {

@@ -17,8 +17,13 @@ SOURCE = r"""
 static std::map<void*, size_t> live;
 static size_t held = 0, limit = (size_t)1 << 40;
 static hipError_t waits = hipSuccess;
+static int refuse = 0;                   // allocations that fail although there is room: another thread is about to make it
 hipError_t hipMalloc(void** p, size_t n) {
-    if (held + n > limit) { *p = nullptr; return hipErrorOutOfMemory; }
+    if (refuse > 0 || held + n > limit) {
+        if (refuse > 0) --refuse;
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
     *p = malloc(1);
     live[*p] = n;
     held += n;
@@ -70,6 +75,10 @@ int main(int, char** argv) {
         CHECK(pool_take(0, &a, 500 * MB) == hipSuccess && held == 1000 * MB);      // also to its own, of another size
         pool_retire(0, {a});
         hipFree(b);
+    } else if (!strcmp(argv[1], "emptied by another")) {         // between the allocation that fails and the look at the pool
+        refuse = 1;
+        CHECK(device_malloc(&a, 500 * MB) == hipSuccess);
+        hipFree(a);
     } else if (!strcmp(argv[1], "trimmed")) {
         CHECK(pool_take(0, &a, 600 * MB) == hipSuccess && pool_take(0, &b, 10 * MB) == hipSuccess);
         pool_retire(0, {a});
@@ -100,7 +109,7 @@ def program(tmp_path_factory):
     return str(d / "pool")
 
 
-@pytest.mark.parametrize("case", ["kept", "refused wait", "bound", "runs out", "trimmed"])
+@pytest.mark.parametrize("case", ["kept", "refused wait", "bound", "runs out", "emptied by another", "trimmed"])
 def test_pool(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
