@@ -186,7 +186,7 @@ struct spp_graph {
     // the partition that laid t_edge out: its tiles of kPartTile edges of the CSR, where a tile's edges of a row block
     // start in t_edge, and the row that holds a tile's first edge (then: the last row with edges)
     void*     part_mem = nullptr;       // holds the two
-    uint32_t* tile_off = nullptr;       // uint32[nrb * part_tiles]
+    uint32_t* tile_off = nullptr;       // uint32[nrb * part_tiles + 1], the last one M
     int32_t*  tile_row = nullptr;       // int32[part_tiles + 1]
     int64_t   part_tiles = 0;
     int64_t*  block_first = nullptr;    // int64[nrb + 1]: edges that end in row blocks before b (either layout)

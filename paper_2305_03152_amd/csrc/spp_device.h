@@ -15,6 +15,14 @@ constexpr int kWave = 64;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
+// A value that the compiler takes for a new one: what is computed from it is computed where it is used.  Kept over a loop in
+// registers that the loop has not got, such values go to memory and back, and a load of one of them waits for all loads before it.
+template <class T>
+__device__ __forceinline__ T here(T x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Prefix sums are formed modulo 2^32 (counts up to 2^32 - 1 pass through int unchanged).
 __device__ __forceinline__ int uadd(int a, int b) { return (int)((unsigned)a + (unsigned)b); }
 
@@ -36,6 +44,16 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
     v += dpp_or_zero<0x142, 0xA>(v);             // lane 15 of rows 0 and 2 to rows 1 and 3
     v += dpp_or_zero<0x143, 0xC>(v);             // lane 31 to rows 2 and 3
     return (int)v;
+}
+__device__ __forceinline__ unsigned wave_inclusive_max(unsigned v) {
+    auto up = [&](unsigned x) { v = v > x ? v : x; };
+    up(dpp_or_zero<0x111>(v));
+    up(dpp_or_zero<0x112>(v));
+    up(dpp_or_zero<0x114>(v));
+    up(dpp_or_zero<0x118>(v));
+    up(dpp_or_zero<0x142, 0xA>(v));
+    up(dpp_or_zero<0x143, 0xC>(v));
+    return v;
 }
 __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 

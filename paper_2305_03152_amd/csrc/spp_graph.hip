@@ -57,11 +57,12 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
-// edges: the kernels of a build 9.2 -> 1.0 ms: 0.55 in the placing pass, most of it vector instructions,
+// edges: the kernels of a build 9.2 -> 0.85 ms: 0.35 in the placing pass, most of it vector instructions,
 // 0.12 in the counting pass, 0.15 in the read-back and 0.20 in the sum over the CSR that it is compared with.
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
 constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
+constexpr int kPartRows = 4;                             // most rows that begin among 64 edges to be looked at one by one
 constexpr int kPartMaxBlocks = 512;                      // 2^23 vertices in blocks of 2^14 rows
 
 __device__ __forceinline__ void add_mix(unsigned long long mine, unsigned long long* sum) {
@@ -69,17 +70,19 @@ __device__ __forceinline__ void add_mix(unsigned long long mine, unsigned long l
     for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
     if (lane_id() == 0 && mine) atomicAdd(sum, mine);
 }
-// The wavefront's lanes whose value agrees with this lane's in the low BITS bits.
+// The wavefront's lanes whose value agrees with this lane's in the low BITS bits: four instructions a bit (the bit spread over a
+// word, its ballot, and one three-input operation for each half of the lanes).
 template <int BITS>
 __device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
     const uint64_t all = __ballot(has);
     uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
 #pragma unroll
     for (int bit = 0; bit < BITS; ++bit) {
-        const uint32_t m = (uint32_t)((int32_t)(value << (31 - bit)) >> 31);      // all ones where the bit is set
+        uint32_t m = (uint32_t)((int32_t)(value << (31 - bit)) >> 31);            // all ones where the bit is set
+        asm("" : "+v"(m));                       // else the ballot is of the shifted value, one instruction more
         const uint64_t bm = __ballot(m != 0u);
-        lo &= ~((uint32_t)bm ^ m);
-        hi &= ~((uint32_t)(bm >> 32) ^ m);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bm, m, 0x90);              // lo & ~(bm ^ m)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bm >> 32), m, 0x90);
     }
     return ((uint64_t)hi << 32) | lo;
 }
@@ -138,17 +141,21 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64
 
 // Places a tile's edge words by block, in CSR order, and stores them as runs.  How many edges of each block the tile has follows
 // from the offsets, so that the blocks' places in the tile are known before an edge is looked at; left to find are an
-// edge's source (the rows leave their numbers at their first edges, and at the first edge of every 64 they reach into) and its
-// rank among its wavefront's edges of the block.  Four barriers per tile: (1) sources and ranks; (2) per block, the
-// wavefronts' places; (3) the words; (4) they are stored while the next tile's rows are marked.  All loads of a
-// tile are asked for before the stores of the tile before, unconditionally: a load that is waited for after stores waits for those too.
-// 2.4M vertices, 121M edges: 530 to 570 us by box (630 on the fastest with nine barriers and the loads at the head of a tile; 1.0 GB, which a copy moves
-// in 150): vector instructions two thirds of the time, the ballots that rank the edges a third of them.  (Asking first
-// whether 64 edges end in one block, as those of a hub's row do: 663, it spills registers.)
+// edge's source (the rows leave their numbers at their first edges; an edge takes the last one before it among its 64, or the
+// last row to start in the 64s before) and its rank among its wavefront's edges of the block.  Four barriers per tile: (1) sources
+// and ranks; (2) per block, the wavefronts' places; (3) the words; (4) they are stored while the next tile's rows are marked.  All
+// loads of a tile are asked for before the stores of the tile before, unconditionally: a load that is waited for after stores waits
+// for those too.
+// 2.4M vertices, 121M edges: 352 us, 1.04 GB.  It took 554: a lane wrote a long row's number at every 64th of its edges one
+// by one and the first wavefront scanned the blocks' counts by shuffles (half of a tile's time, the other wavefronts waiting), values
+// kept over the loop went to memory and back (see here()), and a ballot's bit cost six instructions (four: 427 -> 368).  What
+// bounds it now: the ranks' vector instructions, a third of the time, and the four barriers.  (Ranks by LDS atomics, row by row
+// as the lanes of one row may come in any order: 513, they wait for each other.)
 struct PlaceLds {
     uint32_t words[kPartTile];           // the tile's words by block
     uint16_t blk_of[kPartTile];
     uint32_t mark[2][kPartTile];         // per edge: the row that starts there, less the tile's first
+    uint32_t last[2][kPartTile / kWave]; // per 64 edges: the last row that starts among them, less the tile's first, plus one
     uint32_t num[kPartMaxBlocks], off[kPartMaxBlocks];        // of the next tile: edges per block and where they go
     uint32_t start[kPartMaxBlocks];      // where a block's words start among the tile's
     uint32_t shift[2][kPartMaxBlocks];   // where they go in t_edge, less that
@@ -169,20 +176,23 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
     constexpr uint32_t kNone = 0xFFFFFFFFu;
     const int lane = lane_id();
     const uint32_t tid = threadIdx.x, wave = tid >> 6, rmask = (1u << rbits) - 1u;
+    const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
     const uint32_t we0 = wave * (kPartTile / kPartWaves) + lane;
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
-    const uint32_t last_off = (uint32_t)nrb * (uint32_t)ntiles - 1u, off0 = ((int)tid < nrb ? tid : 0u) * (uint32_t)ntiles;      // below 2^30
+    const uint32_t off0 = ((int)tid < nrb ? tid : 0u) * (uint32_t)ntiles;      // below 2^30
     const uint32_t* __restrict__ row32 = reinterpret_cast<const uint32_t*>(rowptr);      // the lower halves: offsets are below 2^32, like M
     // a tile's rows (the first kPartBlock of them, one per thread; threads beyond take the last one once more) and offsets
     struct { int32_t v0, v1; uint32_t b, e, off, off_n; } r;
     auto load_row = [&](uint32_t v) { r.b = row32[2u * v]; r.e = row32[2u * v + 2u]; };
+    // where a tile's rows begin and end, in even and odd lanes, is asked for a tile before they are: by a vector load, as a scalar
+    // one is waited for at the next read of LDS
+    int32_t ends;
+    auto load_ends = [&](int tile) { ends = tile_row[tile + (lane & 1)]; };
     auto load_rows = [&](int tile) {
-        r.v0 = tile_row[tile]; r.v1 = tile_row[tile + 1];
+        r.v0 = __builtin_amdgcn_readlane(ends, 0); r.v1 = __builtin_amdgcn_readlane(ends, 1);
         load_row((uint32_t)(r.v1 - r.v0 > (int32_t)tid ? r.v0 + (int32_t)tid : r.v1));
         const uint32_t at = off0 + (uint32_t)tile;
         r.off = offs[at];
-        r.off_n = offs[at < last_off ? at + 1u : at];
-        if (at == last_off) r.off_n = (uint32_t)M;
+        r.off_n = offs[at + 1u];                 // behind the last one stands M
     };
     uint32_t u[kPartPer];
     auto load_edges = [&](int tile) {            // of a full tile
@@ -190,13 +200,13 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k) u[k] = (uint32_t)__builtin_nontemporal_load(c + (we0 + k * kWave));
     };
-    auto mark_rows = [&](int tile, uint32_t n, uint32_t* mark) {
+    auto mark_rows = [&](int tile, uint32_t n, uint32_t* mark, uint32_t* last) {
         const uint32_t base = (uint32_t)tile * (uint32_t)kPartTile, stop = base + n;       // at most M
         auto one = [&](int32_t v) {
             const uint32_t b = (r.b > base ? (r.b < stop ? r.b : stop) : base) - base, e = (r.e > base ? (r.e < stop ? r.e : stop) : base) - base;
             if (b < e) {
                 mark[b] = (uint32_t)(v - r.v0);
-                for (uint32_t k = (b + kWave) & ~(uint32_t)(kWave - 1); k < e; k += kWave) mark[k] = (uint32_t)(v - r.v0);
+                atomicMax(&last[b / kWave], (uint32_t)(v - r.v0) + 1u);
             }
         };
         if (r.v1 - r.v0 > kTileManyRows) {       // the same for all threads
@@ -208,31 +218,48 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
         if (r.v1 - r.v0 >= (int32_t)tid) one(r.v0 + (int32_t)tid);
         for (int64_t v = (int64_t)r.v0 + kPartBlock + tid; v <= r.v1; v += kPartBlock) { load_row((uint32_t)v); one((int32_t)v); }
     };
-    auto clear_marks = [&](uint32_t* mark) { reinterpret_cast<u32x4*>(mark)[tid] = u32x4{kNone, kNone, kNone, kNone}; };
-    auto clear_counts = [&]() { for (int i = tid; i < 2 * nrb; i += kPartBlock) l.cnt[i] = uint4{0u, 0u, 0u, 0u}; };
+    auto clear_marks = [&](uint32_t* mark, uint32_t* last) {
+        const uint32_t none = here(kNone);
+        reinterpret_cast<u32x4*>(mark)[here(tid)] = u32x4{none, none, none, none};
+        if (tid < kPartTile / kWave) last[tid] = 0u;
+    };
+    auto clear_counts = [&]() { const uint32_t z = here(0u); for (int i = here(tid); i < 2 * nrb; i += kPartBlock) l.cnt[i] = uint4{z, z, z, z}; };
     auto keep_offsets = [&]() { if ((int)tid < nrb) { l.num[tid] = r.off_n - r.off; l.off[tid] = r.off; } };
-    auto set_starts = [&](uint32_t* shift) {     // by the first wavefront
-        if (tid >= kWave) return;
+    auto set_starts = [&](uint32_t* shift) {     // 64 blocks to a wavefront, from the third on: the first ones have the rows to mark,
+                                                 // the last ones are the last to get through what all do
+        const int b0 = ((int)wave_u - 2) * kWave, b = b0 + lane;
+        if (b0 < 0 || b0 >= nrb) return;
         uint32_t before = 0;
-        for (int b0 = 0; b0 < nrb; b0 += kWave) {
-            const int b = b0 + lane;
-            const uint32_t c = b < nrb ? l.num[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c), st = before + inc - c;
-            if (b < nrb) { l.start[b] = st; shift[b] = l.off[b] - st; }
-            before += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-        }
+        for (int q = lane; q < b0; q += kWave) before += l.num[q];
+        const uint32_t c = b < nrb ? l.num[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c), st = (uint32_t)wave_sum((int)before) + inc - c;
+        if (b < nrb) { l.start[b] = st; shift[b] = l.off[b] - st; }
     };
     uint32_t place[kPartPer];                    // block << 16 | rank among the wavefront's edges of the block
-    auto rank = [&](const uint32_t* mark, int32_t v0, auto full, uint32_t n) {
+    auto rank = [&](const uint32_t* mark, const uint32_t* last, int32_t v0, auto full, uint32_t n) {
+        // the row that an edge of a 64 lies in, if none starts at or before it there: the last one to start in those before
+        const uint32_t rows_before = wave_inclusive_max(last[lane]);
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k) {
-            const uint32_t e = we0 + k * kWave;
+            const uint32_t e = here(we0) + k * kWave;
             const bool has = full || e < n;
             const uint32_t m = mark[e];
-            const uint64_t upto = __ballot(m != kNone) & (lt_mask | (1ull << lane));
-            const uint32_t src = (uint32_t)v0 + (uint32_t)__shfl((int)m, 63 - __clzll((long long)(upto | 1ull)), kWave);
+            const uint64_t starts = __ballot(m != kNone);
+            const int batch = (int)(wave_u * kPartPer) + k;      // the first edge of a tile is marked
+            uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)rows_before, batch > 0 ? batch - 1 : 0) - 1u;
+            if (__popcll(starts) <= kPartRows) { // one after the other: two instructions each, where looking back takes eleven
+                for (uint64_t rest = starts; rest; rest &= rest - 1) {
+                    const int at = __builtin_ctzll(rest);
+                    src = __builtin_amdgcn_inverse_ballot_w64(~0ull << at) ? (uint32_t)__builtin_amdgcn_readlane((int)m, at) : src;
+                }
+            } else {
+                const uint64_t upto = starts & ((2ull << here(lane)) - 1ull);
+                const uint32_t found = (uint32_t)__shfl((int)m, 63 - __clzll((long long)(upto | 1ull)), kWave);
+                src = upto ? found : src;
+            }
+            src += (uint32_t)v0;
             const uint32_t blk = u[k] >> rbits;
             const uint64_t same = lanes_alike<BITS>(has, blk);
-            const uint32_t below = (uint32_t)__popcll(same & lt_mask);
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
             uint16_t* c = cnt + (has ? blk * kPartWaves + wave : 0u);
             const uint32_t prior = *c;
             if (has && below == 0) *c = (uint16_t)(prior + (uint32_t)__popcll(same));
@@ -268,7 +295,7 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
     auto store = [&](const uint32_t* shift, auto full, uint32_t n) {
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k) {
-            const uint32_t i = tid + k * kPartBlock;
+            const uint32_t i = here(tid) + k * kPartBlock;
             if (full || i < n) t_edge[shift[l.blk_of[i]] + i] = l.words[i];
         }
     };
@@ -278,20 +305,23 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
     int tile = x0 + (int)(blockIdx.x >> 3);
     if (tile < end) {
         auto at = [&](int tl) { return tl < end ? tl : end - 1; };
+        load_ends(tile);
         load_rows(tile);
+        load_ends(at(tile + step));
         load_edges(tile);
-        clear_marks(l.mark[0]);
+        clear_marks(l.mark[0], l.last[0]);
         clear_counts();
         keep_offsets();
         __syncthreads();
-        mark_rows(tile, kPartTile, l.mark[0]);
+        mark_rows(tile, kPartTile, l.mark[0], l.last[0]);
         set_starts(l.shift[0]);
         int32_t v0 = r.v0;
         load_rows(at(tile + step));
+        load_ends(at(tile + 2 * step));
         __syncthreads();
         for (int k = 0; tile < end; tile += step, k ^= 1) {      // k: which of the two marks and shifts
-            rank(l.mark[k], v0, std::true_type{}, kPartTile);
-            clear_marks(l.mark[k ^ 1]);
+            rank(l.mark[k], l.last[k], v0, std::true_type{}, kPartTile);
+            clear_marks(l.mark[k ^ 1], l.last[k ^ 1]);
             __syncthreads();
             wave_places();
             __syncthreads();
@@ -301,26 +331,28 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
             load_edges(at(tile + step));
             __syncthreads();
             clear_counts();
-            mark_rows(at(tile + step), kPartTile, l.mark[k ^ 1]);
+            mark_rows(at(tile + step), kPartTile, l.mark[k ^ 1], l.last[k ^ 1]);
             set_starts(l.shift[k ^ 1]);
             load_rows(at(tile + 2 * step));
+            load_ends(at(tile + 3 * step));
             store(l.shift[k], std::true_type{}, kPartTile);
             __syncthreads();
         }
     }
     if (nfull < ntiles && blockIdx.x == gridDim.x - 1) {         // the rest
         const uint32_t n = (uint32_t)(M - (int64_t)nfull * kPartTile);
+        load_ends(nfull);
         load_rows(nfull);
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k) u[k] = we0 + k * kWave < n ? (uint32_t)col[(int64_t)nfull * kPartTile + we0 + k * kWave] : 0u;
-        clear_marks(l.mark[0]);
+        clear_marks(l.mark[0], l.last[0]);
         clear_counts();
         keep_offsets();
         __syncthreads();
-        mark_rows(nfull, n, l.mark[0]);
+        mark_rows(nfull, n, l.mark[0], l.last[0]);
         set_starts(l.shift[0]);
         __syncthreads();
-        rank(l.mark[0], r.v0, std::false_type{}, n);
+        rank(l.mark[0], l.last[0], r.v0, std::false_type{}, n);
         __syncthreads();
         wave_places();
         __syncthreads();
@@ -468,7 +500,7 @@ __global__ void __launch_bounds__(kBlock) tile_verify_kernel(int rbits, int nch,
 
 struct PartIn  { const uint32_t* h; __device__ int operator()(int64_t i) const { return (int)h[i]; } };
 struct PartOut { uint32_t* h; __device__ void operator()(int64_t i, int ex, int) const { h[i] = (uint32_t)ex; } };
-struct PartFin { __device__ void operator()(int) const {} };
+struct PartFin { uint32_t* end; __device__ void operator()(int total) const { *end = (uint32_t)total; } };
 
 __global__ void block_first_from_tiles_kernel(const int64_t* __restrict__ tile_first, int nch, int64_t nrb,
                                               int64_t* __restrict__ block_first) {      // copies whatever tile_first[] holds
@@ -517,7 +549,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         // one allocation: the counts (then offsets) and the tiles' first rows, which the graph keeps, the scan's
         // partial sums, the sums of the edges' mixes and a flag
         struct Head { unsigned long long mix[2]; int bad, pad; CsrFound csr; } back;
-        const size_t bytes = sizeof(Head) + (size_t)(nhist + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
+        const size_t bytes = sizeof(Head) + (size_t)(nhist + 1 + scan_grid) * sizeof(int) + (size_t)(ntiles + 1) * sizeof(int32_t);
         char* tmp = nullptr;
         if (pool_take(g->device, &tmp, bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -528,7 +560,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
         int* d_bad = reinterpret_cast<int*>(mix + 2);
         CsrFound* found = &reinterpret_cast<Head*>(tmp)->csr;
         uint32_t* hist = reinterpret_cast<uint32_t*>(tmp + sizeof(Head));
-        int* partial = reinterpret_cast<int*>(hist + nhist);
+        int* partial = reinterpret_cast<int*>(hist + nhist + 1);
         int32_t* tile_row = partial + scan_grid;
         int rc = SPP_OK;
         hipError_t e = hipMemsetAsync(tmp, 0, sizeof(Head), st);
@@ -536,7 +568,7 @@ static int build_tiles(spp_ctx* ctx, spp_graph* g) {
             const int pgrid = (int)(ntiles < (int64_t)ctx->num_cu * 8 ? ntiles : (int64_t)ctx->num_cu * 8);
             part_rows_kernel<<<grid, kBlock, 0, st>>>(N, M, ntiles, g->rowptr, tile_row, found);
             part_count_kernel<<<pgrid, kPartBlock, 0, st>>>(N, M, g->rowptr, g->col, rbits, (int)nrb, ntiles, hist, found);
-            grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{}, partial);
+            grid_scan(st, scan_grid, nhist, PartIn{hist}, PartOut{hist}, PartFin{hist + nhist}, partial);
             // two workgroups per CU, fewer where there are fewer tiles; a multiple of eight
             const int64_t want_place = (ntiles + 7) / 8 * 8, most_place = ctx->num_cu * 2 / 8 * 8;
             const size_t place_lds = offsetof(PlaceLds, cnt) + (size_t)nrb * kPartWaves * sizeof(uint16_t);
