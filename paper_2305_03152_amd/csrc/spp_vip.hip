@@ -839,7 +839,7 @@ __device__ __forceinline__ float unit_or_flag(float x, int* bad) {
 // How a hop of the general propagation fills its bins: from a list of its frontier, or (kWhole) from the whole CSR, tile
 // by tile, where the frontier's rows hold at least half of the edges.  The kernel that writes a hop's
 // probabilities counts their vertices' out-edges and decides; on large graphs it counts a part of them (either form is correct
-// for any frontier).  2.4M vertices, 121M edges, list, fill and sum: by tiles 640 us
+// for any frontier).  2.4M vertices, 121M edges, list, fill and sum: by tiles 558 us
 // whatever the frontier; listed 1075 us with all edges, 345 with 23 % of them.
 constexpr uint32_t kListed = 1, kWhole = 2;
 struct FillRule {
@@ -1092,19 +1092,77 @@ __device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf,
     push_portions(po, nf, col, [&](int64_t i, int64_t& b, uint32_t& deg) { return y[frontier_entry(list, i, rowptr, b, deg)]; }, f);
 }
 
-// Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.
+// Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.  A thread asks for its next vectors
+// before it adds those it has: 121M entries 224 -> 209 us (one 8-byte load at a time: 325).
 __device__ __forceinline__ void bin_add_entries(double* acc, const uint2* __restrict__ bins, int64_t beg, int64_t end) {
-    constexpr int U = 8;                       // entries in flight per thread (one: 325 us for 121M entries, eight: 208)
-    for (int64_t e0 = beg + threadIdx.x; e0 < end; e0 += U * kTileBlock) {
-        unsigned long long x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            x[u] = e0 + u * kTileBlock < end ? __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(bins) + e0 + u * kTileBlock) : 0ull;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int U = 4;                       // vectors of two entries per thread and round
+    auto add = [&](uint32_t w, uint32_t row) { if (w != 0u) unsafeAtomicAdd(&acc[row], (double)__uint_as_float(w)); };
+    if (threadIdx.x < 2) {                     // entries that share their vector with a neighbour's
+        const int64_t e = threadIdx.x == 0 ? beg : end - 1;
+        if (beg < end && ((e & 1) == 1) == (threadIdx.x == 0)) add(bins[e].x, bins[e].y);
+    }
+    const u32x4* __restrict__ pairs = reinterpret_cast<const u32x4*>(bins) + (beg + 1) / 2;
+    const int n = (int)(end / 2 - (beg + 1) / 2);        // below 2^31: M is below 2^32
+    if (n <= 0) return;
+    u32x4 x[U], next[U];
+    auto load = [&](u32x4 (&v)[U], int i0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t w = (uint32_t)x[u];             // .x of the entry
-            if (w != 0u) unsafeAtomicAdd(&acc[(uint32_t)(x[u] >> 32)], (double)__uint_as_float(w));
+            const int i = i0 + u * kTileBlock;
+            v[u] = __builtin_nontemporal_load(pairs + (i < n ? i : n - 1));
         }
+    };
+    load(x, (int)threadIdx.x);
+    for (int64_t i0 = threadIdx.x; i0 < n; i0 += U * kTileBlock) {
+        load(next, (int)(i0 + U * kTileBlock < n ? i0 + U * kTileBlock : n - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kTileBlock < n) { add(x[u].x, x[u].y); add(x[u].z, x[u].w); }
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = next[u];
+    }
+}
+
+// The same with the entries' weights and rows in arrays of their own, as a fill by tiles leaves them: 121M entries 172 us.
+struct SplitBins {
+    float*    w;
+    uint16_t* row;
+    __host__ __device__ SplitBins(void* mem, int64_t M) : w(reinterpret_cast<float*>(mem)), row(reinterpret_cast<uint16_t*>(w + ((M + 3) & ~3ll))) {}
+};
+__device__ __forceinline__ void bin_add_split(double* acc, const SplitBins& bins, int64_t beg, int64_t end) {
+    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+    constexpr int U = 4;                       // vectors of four entries per thread and round
+    auto add = [&](float w, uint32_t row) { if (w != 0.0f) unsafeAtomicAdd(&acc[row], (double)w); };
+    const int64_t v0 = (beg + 3) / 4, v1 = end / 4;
+    // the entries before the first whole vector and behind the last (all, if there is no whole one)
+    const int64_t head = v0 * 4 < end ? v0 * 4 : end, tail = v1 > v0 ? v1 * 4 : head;
+    if (beg + threadIdx.x < head) add(bins.w[beg + threadIdx.x], bins.row[beg + threadIdx.x]);
+    if (tail + threadIdx.x < end) add(bins.w[tail + threadIdx.x], bins.row[tail + threadIdx.x]);
+    if (v1 <= v0) return;
+    const f32x4* __restrict__ w4 = reinterpret_cast<const f32x4*>(bins.w) + v0;
+    const u16x4* __restrict__ r4 = reinterpret_cast<const u16x4*>(bins.row) + v0;
+    const int n = (int)(v1 - v0);              // below 2^30: M is below 2^32
+    f32x4 w[U], wn[U];
+    u16x4 r[U], rn[U];
+    auto load = [&](f32x4 (&a)[U], u16x4 (&b)[U], int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kTileBlock < n ? i0 + u * kTileBlock : n - 1;
+            a[u] = __builtin_nontemporal_load(w4 + i);
+            b[u] = __builtin_nontemporal_load(r4 + i);
+        }
+    };
+    load(w, r, (int)threadIdx.x);
+    for (int i0 = (int)threadIdx.x; i0 < n; i0 += U * kTileBlock) {
+        load(wn, rn, i0 + U * kTileBlock);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kTileBlock < n)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) add(w[u][c], r[u][c]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) { w[u] = wn[u]; r[u] = rn[u]; }
     }
 }
 
@@ -1315,9 +1373,12 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
 // edges are weighed and laid out.  A load that is waited for after stores would wait for those too (they complete in
 // order), so a tile's rows and offsets are asked for before the stores of two tiles back, its edges before those of
 // the tile before, and nothing in the loop is loaded conditionally (after a conditional load the compiler waits for all).
-// 2.4M vertices, 121M edges: 419 us, 2.0 GB, where the listed fill took 852; with seven barriers and waits for the stores 535
-// to 780.  What bounds it now: vector instructions half of the time (64 per 64 edges, the logarithm a third of them), LDS a
-// third, and what two workgroups per CU leave uncovered of the two barriers.
+// The entries' weights and rows go to arrays of their own: 6 bytes per entry where a pair of words takes 8.  (Not so the listed
+// fill's, whose stores are scattered: it would store twice as often.)
+// 2.4M vertices, 121M edges: 381 us, 1.7 GB (pairs: 424, 2.0 GB), where the listed fill took 852; with seven barriers and waits
+// for the stores 535 to 780.  What bounds it now: vector instructions half of the time (64 per 64 edges, the logarithm a third
+// of them), LDS a third, and what two workgroups per CU leave uncovered of the two barriers.  (That a tile's rows are waited for
+// together with most stores of the tile before costs nothing: 391 with a wait for the loads alone.)
 constexpr int kMaxTileBlocks = 512;      // row blocks of a graph that has tiles
 struct PrepareLds {
     uint2    stage[kPartTile];           // the tile's entries by block: weight, destination
@@ -1333,7 +1394,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
                                                                      const float* __restrict__ pcur,
                                                                      const int64_t* __restrict__ rowptr,
                                                                      const int32_t* __restrict__ col, const float* __restrict__ t,
-                                                                     int rbits, int nrb, uint2* __restrict__ bins,
+                                                                     int rbits, int nrb, SplitBins bins,
                                                                      int* __restrict__ bad, int64_t N, int32_t* __restrict__ list,
                                                                      unsigned long long* __restrict__ cursor) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1351,18 +1412,22 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
     constexpr uint32_t kNone = 0xFFFFFFFFu;      // no bits of a probability
     const int lane = lane_id();
     const uint32_t tid = threadIdx.x, rmask = (1u << rbits) - 1u;
-    const uint32_t blk = (int)tid < nrb ? tid : 0u;
-    const uint32_t* __restrict__ off_b = tile_off + (size_t)blk * (uint32_t)ntiles;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t off0 = ((int)tid < nrb ? tid : 0u) * (uint32_t)ntiles;       // below 2^30
     // a tile's rows and offsets (the first kFillBlock rows, one per thread; threads beyond take the last one once more)
     struct { int32_t v0, v1; uint32_t b, e; float p; uint32_t off, off_n; } r;
-    auto load_row = [&](int32_t v) { r.b = (uint32_t)rowptr[v]; r.e = (uint32_t)rowptr[v + 1]; r.p = pcur[v]; };      // below 2^32, like M
+    const uint32_t* __restrict__ row32 = reinterpret_cast<const uint32_t*>(rowptr);      // the lower halves: offsets are below 2^32, like M
+    auto load_row = [&](uint32_t v) { r.b = row32[2u * v]; r.e = row32[2u * v + 2u]; r.p = pcur[v]; };
+    // where a tile's rows begin and end, in even and odd lanes, is asked for a tile before they are: by a vector load, as a scalar
+    // one is waited for at the next read of LDS
+    int32_t ends;
+    auto load_ends = [&](int tile) { ends = tile_row[tile + (lane & 1)]; };
     auto load_rows = [&](int tile) {
-        r.v0 = tile_row[tile]; r.v1 = tile_row[tile + 1];
-        load_row(r.v1 - r.v0 > (int32_t)tid ? r.v0 + (int32_t)tid : r.v1);
-        r.off = off_b[tile];
-        const bool past = (int)blk == nrb - 1 && tile == ntiles - 1;
-        r.off_n = off_b[past ? tile : tile + 1];
-        if (past) r.off_n = (uint32_t)M;
+        r.v0 = __builtin_amdgcn_readlane(ends, 0); r.v1 = __builtin_amdgcn_readlane(ends, 1);
+        load_row((uint32_t)(r.v1 - r.v0 > (int32_t)tid ? r.v0 + (int32_t)tid : r.v1));
+        const uint32_t at = off0 + (uint32_t)tile;
+        r.off = tile_off[at];
+        r.off_n = tile_off[at + 1u];             // behind the last one stands M
     };
     uint32_t u[4];
     float x[4];
@@ -1388,22 +1453,24 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
             return;
         }
         if (r.v1 - r.v0 >= (int32_t)tid) one();
-        for (int64_t v = (int64_t)r.v0 + kFillBlock + tid; v <= r.v1; v += kFillBlock) { load_row((int32_t)v); one(); }
+        for (int64_t v = (int64_t)r.v0 + kFillBlock + tid; v <= r.v1; v += kFillBlock) { load_row((uint32_t)v); one(); }
     };
     auto keep_offsets = [&]() {                  // for the wavefront that sets the cursors
         if ((int)tid < nrb) { l.cnt[tid] = r.off_n - r.off; l.off[tid] = r.off; }
     };
-    auto set_cursors = [&](uint32_t* shift) {    // by the first wavefront
-        if (tid >= kWave) return;
+    auto set_cursors = [&](uint32_t* shift) {    // 64 blocks to a wavefront, from the third on: the first ones have rows to mark
+        const int b0 = (wave - 2) * kWave, b = b0 + lane;
+        if (b0 < 0 || b0 >= nrb) return;
         uint32_t before = 0;
-        for (int b0 = 0; b0 < nrb; b0 += kWave) {
-            const int b = b0 + lane;
-            const uint32_t c = b < nrb ? l.cnt[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c), start = before + inc - c;
-            if (b < nrb) { l.cursor[0][b] = start; l.cursor[1][b] = start + c; shift[b] = l.off[b] - start; }
-            before += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-        }
+        for (int q = lane; q < b0; q += kWave) before += l.cnt[q];
+        const uint32_t c = b < nrb ? l.cnt[b] : 0u, inc = (uint32_t)wave_inclusive_scan((int)c);
+        const uint32_t start = (uint32_t)wave_sum((int)before) + inc - c;
+        if (b < nrb) { l.cursor[0][b] = start; l.cursor[1][b] = start + c; shift[b] = l.off[b] - start; }
     };
-    auto clear_marks = [&](uint32_t* mark) { reinterpret_cast<u32x4*>(mark)[tid] = u32x4{kNone, kNone, kNone, kNone}; };
+    auto clear_marks = [&](uint32_t* mark) {
+        const uint32_t none = here(kNone);
+        reinterpret_cast<u32x4*>(mark)[here(tid)] = u32x4{none, none, none, none};
+    };
     auto weigh = [&](const uint32_t* mark, auto full, uint32_t n) {
         // the last mark at or before an edge: among the lane's own four or in the lanes before
         const u32x4 m4 = reinterpret_cast<const u32x4*>(mark)[tid];
@@ -1446,10 +1513,12 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
     auto store = [&](const uint32_t* shift, auto full, uint32_t n) {
 #pragma unroll
         for (int k = 0; k < kPartTile / kFillBlock; ++k) {
-            const uint32_t i = tid + k * kFillBlock;
+            const uint32_t i = here(tid) + k * kFillBlock;
             if (full || i < n) {
                 const uint2 e = l.stage[i];
-                bins[shift[e.y >> rbits] + i] = make_uint2(e.x, e.y & rmask);
+                const uint32_t to = shift[e.y >> rbits] + i;
+                bins.w[to] = __uint_as_float(e.x);
+                bins.row[to] = (uint16_t)(e.y & rmask);
             }
         }
     };
@@ -1459,7 +1528,9 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
     int tile = x0 + (int)(blockIdx.x >> 3);
     if (tile < end) {
         auto at = [&](int tl) { return tl < end ? tl : end - 1; };
+        load_ends(tile);
         load_rows(tile);
+        load_ends(at(tile + step));
         load_edges(tile);
         clear_marks(l.mark[0]);
         keep_offsets();
@@ -1467,6 +1538,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
         mark_rows(tile, kPartTile, l.mark[0]);
         set_cursors(l.shift[0]);
         load_rows(at(tile + step));
+        load_ends(at(tile + 2 * step));
         __syncthreads();
         for (int k = 0; tile < end; tile += step, k ^= 1) {      // k: which of the two marks and shifts
             clear_marks(l.mark[k ^ 1]);
@@ -1477,12 +1549,14 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
             mark_rows(at(tile + step), kPartTile, l.mark[k ^ 1]);
             set_cursors(l.shift[k ^ 1]);
             load_rows(at(tile + 2 * step));
+            load_ends(at(tile + 3 * step));
             store(l.shift[k], std::true_type{}, kPartTile);
             __syncthreads();
         }
     }
     if (nfull < ntiles && blockIdx.x == gridDim.x - 1) {         // the rest
         const uint32_t n = (uint32_t)(M - (int64_t)nfull * kPartTile);
+        load_ends(nfull);
         load_rows(nfull);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1574,7 +1648,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
 
 // Adds the entries of one share of one bin into the block's fp64 sums (LDS) and writes them to
 // part[j][row], like pull_tiles but with the weights already in place.
-__global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __restrict__ bins,
+__global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(uint2* __restrict__ bins, int64_t M,
                                                                  const uint32_t* __restrict__ cursor,
                                                                  const int64_t* __restrict__ first, int nch, int parts,
                                                                  int rbits, double* __restrict__ part, int64_t part_stride,
@@ -1586,7 +1660,9 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_sum_kernel(const uint2* __
     for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
     __syncthreads();
     const int64_t b0 = first[rb * nch], len = how && *how == kWhole ? first[(rb + 1) * nch] - b0 : (int64_t)cursor[rb];
-    bin_add_entries(acc, bins, b0 + len * j / parts, b0 + len * (j + 1) / parts);
+    const int64_t beg = b0 + len * j / parts, end = b0 + len * (j + 1) / parts;
+    if (how && *how == kWhole) bin_add_split(acc, SplitBins(bins, M), beg, end);
+    else bin_add_entries(acc, bins, beg, end);
     __syncthreads();
     double* __restrict__ out = part + (int64_t)j * part_stride + (rb << rbits);
     for (int i = threadIdx.x; i < R; i += kTileBlock) out[i] = acc[i];
@@ -1688,9 +1764,10 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
         parts = tile_parts(ctx->num_cu, g->nrb, g->M);
         SPP_TRY(ctx->acc.reserve((size_t)parts * (size_t)part_stride * sizeof(double)));
         acc = ctx->acc.as<double>();
-        SPP_TRY(ctx->bins.reserve(((size_t)g->M + (size_t)g->nrb + 1) * sizeof(uint2)));
+        const int64_t room = g->M > 8 ? g->M : 8;        // entries, or as many weights, rounded up, and rows
+        SPP_TRY(ctx->bins.reserve(((size_t)room + (size_t)g->nrb + 1) * sizeof(uint2)));
         bins = ctx->bins.as<uint2>();
-        cursor = reinterpret_cast<uint32_t*>(bins + g->M);
+        cursor = reinterpret_cast<uint32_t*>(bins + room);
         if (ctx->bin_lds_set < (int)fill_lds) {
             SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vipg_bin_fill_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)fill_lds));
@@ -1720,7 +1797,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
             if (tiles)
                 vipg_prepare_kernel<<<prepare_grid, kFillBlock, sizeof(PrepareLds), st>>>(
                     how_h, g->tile_off, g->tile_row, (int)g->part_tiles, g->M, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits,
-                    (int)g->nrb, bins, d_bad, N, flist, fcount + 2);
+                    (int)g->nrb, SplitBins(bins, g->M), d_bad, N, flist, fcount + 2);
             else
                 launch_frontier_list(fill_grid, st, pcur, g->rowptr, N, flist, fcount + 2);
             if (binned) {
@@ -1729,7 +1806,7 @@ extern "C" int spp_vip_propagate_general(spp_ctx* ctx, const spp_graph* g, const
                     flist, fcount + 2, pcur, g->rowptr, g->col, d_t[h - 1], g->tile_rbits, (int)g->nrb,
                     g->block_first, 1, cursor, bins, d_bad, how_h);
                 vip_bin_sum_kernel<<<(unsigned)(g->nrb * parts), kTileBlock, sum_lds, st>>>(
-                    bins, cursor, g->block_first, 1, parts, g->tile_rbits, acc, part_stride, how_h);
+                    bins, g->M, cursor, g->block_first, 1, parts, g->tile_rbits, acc, part_stride, how_h);
             } else {
                 fill_f64_kernel<<<fill_grid, kBlock, 0, st>>>(acc, N, 0.0);
                 vipg_push_kernel<<<ctx->num_cu * 32, kBlock, 0, st>>>(flist, fcount + 2, pcur, g->rowptr, g->col,
