@@ -3,12 +3,13 @@
 //
 // Of all candidates (remote, score > 0) only those that can be kept are ranked: positive floats order
 // like their bit patterns, so three histogram passes over the scores (11, 10 and 10 bits) find the C-th
-// largest score exactly.  The candidates at or above it are compacted in ascending id order by a grid
-// scan, packed as (~score bits) << 32 | id, and sorted: in one workgroup up to 8192 of them, else
+// largest score exactly.  The candidates at or above it are compacted in ascending id order (one launch counts
+// a workgroup's, one places them), packed as (~score bits) << 32 | id, and sorted: in one workgroup up to 4096 of them, else
 // stably by radix on the score bits only (the complement turns ascending into descending score, and
 // stability keeps ascending id among equal scores).  Before, all candidates were sorted, in buffers of
-// 16 bytes per candidate that each call allocated.  8M scores, cache of 320k rows: 2.88 -> 2.07 ms, of
-// which the rows take 1.5 over PCIe; a cache of 200 rows out of 18k scores 253 -> 100 us.
+// 16 bytes per candidate that each call allocated.  A call with 8-byte rows in device memory, 320k kept of 8M scores: 281 -> 167 us
+// with a workgroup per CU in the passes over the scores and two launches per pass of the sort; 60k of 1M 201 -> 114, 10k of 60k
+// 166 -> 112, 1.5M of 8M 477 -> 395.  Rows from the host add what the link takes: 8M scores, 320k rows of 256 bytes 1.70 ms, 1.53 of it.
 #include "spp_common.h"
 #include "spp_device.h"
 #include "spp_rowcopy.h"
@@ -27,94 +28,172 @@ struct RankArgs {
     uint64_t     C;                  // candidates wanted
     uint32_t*    hist;               // kRankHistWords counts
 };
-__device__ __forceinline__ uint32_t candidate_bits(const RankArgs& a, int64_t u) {      // 0: not a candidate
-    if (u >= a.lo && u < a.hi) return 0u;
-    const float s = a.score[u];
-    return s > 0.0f ? __float_as_uint(s) : 0u;
+__device__ __forceinline__ uint32_t candidate_bits(const RankArgs& a, int64_t u) {      // 0: not a candidate, or beyond the last id
+    const float s = a.score[u < a.N ? u : a.N - 1];              // whatever u: a load under a condition is waited for by itself
+    return s > 0.0f && u < a.N && !(u >= a.lo && u < a.hi) ? __float_as_uint(s) : 0u;
 }
 // The smallest score bits that are kept, as far as the first `passes` histograms decide them: the digit of
 // each pass is the largest bin from which on upward there are enough candidates.  kTooFew if all candidates
-// together are.  All threads of a workgroup of 256; `lds` holds 4 ints and `pick` 2 words.
+// together are.  All threads of a workgroup of kRankBlock; after all three passes `kept` is how many candidates
+// reach them, ties at the threshold included.
 constexpr uint32_t kTooFew = 0xFFFFFFFFu;            // not the bits of a positive score
-__device__ __forceinline__ uint32_t kept_from(const RankArgs& a, int passes, int* lds, unsigned long long* pick) {
+constexpr int kRankBlock = 1024, kRankWaves = kRankBlock / kWave;
+struct RankLds { uint32_t sums[kRankWaves]; unsigned long long bin, want, holds; };
+__device__ __forceinline__ uint32_t kept_from(const RankArgs& a, int passes, RankLds& l, uint64_t& kept) {
     uint64_t want = a.C;
     uint32_t bits = 0;
     const uint32_t* h = a.hist;
+    const int wave = threadIdx.x >> 6;
+    kept = 0;
     for (int p = 0; p < passes; ++p) {
-        const int nb = kRankBins[p], per = nb / kBlock;
-        // thread t adds up the t-th run of bins from the top; block_exclusive_scan adds modulo 2^32, which
-        // the at most 2^31 candidates fit
+        const int nb = kRankBins[p], per = nb / kRankBlock;
+        // thread t adds up the t-th run of bins from the top, modulo 2^32, which the at most 2^31 candidates fit
         uint32_t mine = 0;
         for (int i = 0; i < per; ++i) mine += h[nb - 1 - (int)threadIdx.x * per - i];
-        int all;
-        uint32_t above = (uint32_t)block_exclusive_scan((int)mine, lds, all);
-        if ((uint64_t)(uint32_t)all < want) return kTooFew;      // only possible at the first pass
+        const uint32_t inc = (uint32_t)wave_inclusive_scan((int)mine);
+        if (lane_id() == kWave - 1) l.sums[wave] = inc;
+        __syncthreads();
+        uint32_t above = inc - mine, all = 0;
+        for (int w = 0; w < kRankWaves; ++w) {
+            const uint32_t x = l.sums[w];
+            above += w < wave ? x : 0u;
+            all += x;
+        }
+        if ((uint64_t)all < want) { kept = all; return kTooFew; }        // only possible at the first pass
         if (above < want && above + (uint64_t)mine >= want)      // one thread
             for (int i = 0; i < per; ++i) {
                 const int bin = nb - 1 - (int)threadIdx.x * per - i;
-                if (above + (uint64_t)h[bin] >= want) { pick[0] = (unsigned long long)bin; pick[1] = want - above; break; }
-                above += h[bin];
+                const uint32_t c = h[bin];
+                if (above + (uint64_t)c >= want) { l.bin = (unsigned long long)bin; l.want = want - above; l.holds = c; break; }
+                above += c;
             }
         __syncthreads();
-        bits |= (uint32_t)pick[0] << kRankShift[p];
-        want = pick[1];
+        bits |= (uint32_t)l.bin << kRankShift[p];
+        want = l.want;
+        kept = a.C - want + l.holds;
         __syncthreads();
         h += nb;
     }
     return bits;
 }
-__global__ void __launch_bounds__(kBlock) rank_hist_kernel(RankArgs a, int pass) {
-    __shared__ uint32_t h[2][2048];              // two copies: scores cluster
-    __shared__ int lds[4];
-    __shared__ unsigned long long pick[2];
+// One workgroup per CU: each adds what it has counted to the same few bins (scores cluster), at 15 ns an add.  8M scores, the three
+// passes: 31, 17 and 15 us with four workgroups of 256 threads per CU.
+__global__ void __launch_bounds__(kRankBlock) rank_hist_kernel(RankArgs a, int pass) {
+    constexpr int kCopies = 4, U = 8;            // scores in flight per thread
+    __shared__ uint32_t h[kCopies][2048];
+    __shared__ RankLds l;
     const int nb = kRankBins[pass], shift = kRankShift[pass];
-    for (int i = threadIdx.x; i < 2 * 2048; i += kBlock) (&h[0][0])[i] = 0u;
-    const uint32_t from = kept_from(a, pass, lds, pick);         // ends with barriers
-    if (pass == 0) __syncthreads();
+    for (int i = threadIdx.x; i < kCopies * 2048; i += kRankBlock) (&h[0][0])[i] = 0u;
+    uint64_t kept;
+    const uint32_t from = kept_from(a, pass, l, kept);
     if (pass > 0 && from == kTooFew) return;          // every candidate is kept: nothing to narrow down
+    __syncthreads();
     const int above = pass == 0 ? 32 : kRankShift[pass - 1];     // the bits decided so far must agree
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    constexpr int U = 4;
-    for (int64_t u0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; u0 < a.N; u0 += U * stride) {
+    for (int64_t base = (int64_t)blockIdx.x * (U * kRankBlock); base < a.N; base += (int64_t)gridDim.x * (U * kRankBlock)) {
         uint32_t b[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) b[k] = u0 + k * stride < a.N ? candidate_bits(a, u0 + k * stride) : 0u;
+        for (int k = 0; k < U; ++k) b[k] = candidate_bits(a, base + k * kRankBlock + threadIdx.x);
 #pragma unroll
         for (int k = 0; k < U; ++k)
             if (b[k] != 0u && (pass == 0 || (b[k] >> above) == (from >> above)))
-                atomicAdd(&h[threadIdx.x & 1][(b[k] >> shift) & (uint32_t)(nb - 1)], 1u);
+                atomicAdd(&h[threadIdx.x % kCopies][(b[k] >> shift) & (uint32_t)(nb - 1)], 1u);
     }
     __syncthreads();
     uint32_t* out = a.hist + (pass == 0 ? 0 : pass == 1 ? 2048 : 3072);
-    for (int i = threadIdx.x; i < nb; i += kBlock) {
-        const uint32_t c = h[0][i] + h[1][i];
+    for (int i = threadIdx.x; i < nb; i += kRankBlock) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int k = 0; k < kCopies; ++k) c += h[k][i];
         if (c) atomicAdd(&out[i], c);
     }
 }
-__global__ void __launch_bounds__(kBlock) rank_threshold_kernel(RankArgs a, uint32_t* from) {
-    __shared__ int lds[4];
-    __shared__ unsigned long long pick[2];
-    const uint32_t bits = kept_from(a, 3, lds, pick);
-    if (threadIdx.x == 0) *from = bits == kTooFew ? 1u : bits;
-}
-struct CandIn {
-    RankArgs a; const uint32_t* from;
-    __device__ int operator()(int64_t u) const { return candidate_bits(a, u) >= *from ? 1 : 0; }
-};
-struct CandOut {
-    RankArgs a; uint64_t* keys;
-    __device__ void operator()(int64_t u, int ex, int v) const {
-        if (v) keys[(uint32_t)ex] = ((uint64_t)(~__float_as_uint(a.score[u])) << 32) | (uint32_t)u;
+
+// The candidates that are kept, in ascending id order: a workgroup takes a run of whole tiles of kRankTile ids, first to count
+// its own (and to leave the threshold, and for the host their number), then to place them behind those of the workgroups before it.
+// 8M scores, 320k of them kept: 14 + 4 + 24 us as a scan by a general grid scan, which asked for one score per thread at a time.
+constexpr int kRankPer = 8, kRankTile = kRankPer * kRankBlock, kRankGroups = 256;
+struct RankRun {
+    int64_t beg, end;
+    __device__ __forceinline__ explicit RankRun(int64_t N) {
+        const int64_t tiles = (N + kRankTile - 1) / kRankTile, per = (tiles + gridDim.x - 1) / gridDim.x * kRankTile;
+        beg = (int64_t)blockIdx.x * per;
+        end = beg + per < N ? beg + per : N;
     }
 };
-struct CandFin {
-    int64_t* total;                      // pinned host memory
-    __device__ void operator()(int t) const { *total = (int64_t)(uint32_t)t; }
-};
+__global__ void __launch_bounds__(kRankBlock) rank_count_kernel(RankArgs a, uint32_t* __restrict__ from, uint32_t* __restrict__ count,
+                                                                int64_t* __restrict__ total) {
+    __shared__ RankLds l;
+    uint64_t kept;
+    uint32_t bits = kept_from(a, 3, l, kept);
+    if (bits == kTooFew) bits = 1u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { *from = bits; *total = (int64_t)kept; }
+    const RankRun run(a.N);
+    uint32_t mine = 0;
+    for (int64_t base = run.beg; base < run.end; base += kRankTile) {
+        uint32_t b[kRankPer];
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) b[k] = candidate_bits(a, base + k * kRankBlock + threadIdx.x);
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) mine += b[k] >= bits ? 1u : 0u;
+    }
+    mine = (uint32_t)wave_sum((int)mine);
+    __syncthreads();
+    if (lane_id() == 0) l.sums[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kRankWaves; ++w) mine += l.sums[w];
+        count[blockIdx.x] = mine;
+    }
+}
+__global__ void __launch_bounds__(kRankBlock) rank_place_kernel(RankArgs a, const uint32_t* __restrict__ from,
+                                                                const uint32_t* __restrict__ count, uint64_t* __restrict__ keys) {
+    __shared__ uint32_t sums[2][kRankWaves];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t bits = *from;
+    uint32_t at = 0;                             // where the workgroup's next one goes
+    {
+        const uint32_t x = (int)threadIdx.x < (int)blockIdx.x ? count[threadIdx.x] : 0u;     // at most kRankGroups of them
+        const uint32_t s = (uint32_t)wave_sum((int)x);
+        if (lane == 0) sums[0][wave] = s;
+        __syncthreads();
+        for (int w = 0; w < kRankWaves; ++w) at += sums[0][w];
+    }
+    const RankRun run(a.N);
+    for (int64_t base = run.beg; base < run.end; base += kRankTile) {
+        // a wavefront takes kRankPer times 64 consecutive ids
+        const int64_t u0 = base + wave * (kWave * kRankPer) + lane;
+        uint32_t b[kRankPer];
+        uint64_t has[kRankPer];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) b[k] = candidate_bits(a, u0 + k * kWave);
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            has[k] = __ballot(b[k] >= bits);
+            mine += (uint32_t)__popcll(has[k]);
+        }
+        __syncthreads();                         // the sums of the tile before have been read
+        if (lane == 0) sums[1][wave] = mine;
+        __syncthreads();
+        uint32_t to = at;
+        for (int w = 0; w < kRankWaves; ++w) {
+            const uint32_t x = sums[1][w];
+            to += w < wave ? x : 0u;
+            at += x;
+        }
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(has[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has[k], 0u));
+            if (b[k] >= bits) keys[to + below] = ((uint64_t)~b[k] << 32) | (uint32_t)(u0 + k * kWave);
+            to += (uint32_t)__popcll(has[k]);
+        }
+    }
+}
 
 // Up to kSmallRank keys in one workgroup: a bitonic network in LDS over the whole keys (ids make them
-// distinct), padded with all ones.
-constexpr int kSmallRank = 8192;
+// distinct), padded with all ones.  A ranking of 4000 keys out of 20k 104 us, as by the eight launches of the radix sort; of 8000
+// out of 40k 141, and 111 by radix.
+constexpr int kSmallRank = 4096;
 constexpr int kSmallBlock = 1024;
 __global__ void __launch_bounds__(kSmallBlock) rank_small_kernel(uint64_t* __restrict__ keys, int n, int size) {
     extern __shared__ unsigned long long small_keys[];
@@ -248,31 +327,29 @@ extern "C" int spp_build_vip_cache(spp_ctx* ctx, const float* d_score, int64_t N
     int rc = SPP_OK;
     uint64_t* sorted = nullptr;
     DevBuf own;                        // keys of a ranking too large to stay with the context
-    const int scan_grid = N < ((int64_t)1 << 20) ? (int)((N + 1023) / 1024) : 1024;
     const int64_t max_cand = N - (hi - lo);
     int64_t nsel = 0, keep = 0;
 
     auto fail = [&](int code) { rc = code; };
     do {
         if (C == 0 || max_cand == 0) break;
-        // head of the workspace: histograms, threshold, partial sums of the scan; then two arrays of keys and the rows
-        const size_t head = ((size_t)kRankHistWords + 2 + 1024) * sizeof(uint32_t);
+        // head of the workspace: histograms, threshold, the workgroups' counts; then two arrays of keys and the rows
+        const size_t head = ((size_t)kRankHistWords + 2 + kRankGroups) * sizeof(uint32_t);
         rc = ctx->rankws.reserve(head);
         if (rc != SPP_OK) break;
         RankArgs ra;
         ra.score = d_score; ra.N = N; ra.lo = lo; ra.hi = hi; ra.C = (uint64_t)C;
         ra.hist = ctx->rankws.as<uint32_t>();
         uint32_t* from = ra.hist + kRankHistWords;
-        int* partial = reinterpret_cast<int*>(from + 2);
-        const int64_t hneed = (N + kBlock * 4 - 1) / (kBlock * 4);
-        const int hgrid = (int)(hneed < (int64_t)ctx->num_cu * 4 ? hneed : (int64_t)ctx->num_cu * 4);
+        uint32_t* count = from + 2;
+        const int64_t tiles = (N + kRankTile - 1) / kRankTile;
+        const int hgrid = (int)(tiles < (int64_t)ctx->num_cu ? tiles : (int64_t)ctx->num_cu);
+        const int rgrid = hgrid < kRankGroups ? hgrid : kRankGroups;
         fill_table_kernel<<<8, kBlock, 0, st>>>(reinterpret_cast<unsigned long long*>(ra.hist), kRankHistWords / 2, 0ull);
-        for (int pass = 0; pass < 3; ++pass) rank_hist_kernel<<<hgrid, kBlock, 0, st>>>(ra, pass);
-        rank_threshold_kernel<<<1, kBlock, 0, st>>>(ra, from);
+        for (int pass = 0; pass < 3; ++pass) rank_hist_kernel<<<hgrid, kRankBlock, 0, st>>>(ra, pass);
         // how many are kept decides the room for their keys
         int64_t* hp = ctx->h_pinned + 61;
-        scan_reduce_kernel<CandIn><<<scan_grid, kBlock, 0, st>>>(ScanLength(N), CandIn{ra, from}, partial);
-        scan_partials_kernel<CandFin><<<1, kBlock, 0, st>>>(partial, scan_grid, CandFin{hp});
+        rank_count_kernel<<<rgrid, kRankBlock, 0, st>>>(ra, from, count, hp);
         if (hipStreamSynchronize(st) != hipSuccess) { set_error("spp_build_vip_cache: candidate scan failed: %s", hipGetErrorString(hipGetLastError())); fail(SPP_E_HIP); break; }
         nsel = *hp;                    // ties at the threshold included
         if (nsel == 0) break;
@@ -290,7 +367,7 @@ extern "C" int spp_build_vip_cache(spp_ctx* ctx, const float* d_score, int64_t N
                 ctx->rankws = grown;
                 ra.hist = ctx->rankws.as<uint32_t>();
                 from = ra.hist + kRankHistWords;
-                partial = reinterpret_cast<int*>(from + 2);
+                count = from + 2;
             }
             base = ctx->rankws.as<char>();
         } else {
@@ -301,7 +378,7 @@ extern "C" int spp_build_vip_cache(spp_ctx* ctx, const float* d_score, int64_t N
         uint64_t* ka = reinterpret_cast<uint64_t*>(base + keys_at);
         uint64_t* kb = ka + nsel;
         int64_t* rowidx = reinterpret_cast<int64_t*>(kb + nsel);
-        scan_write_kernel<CandIn, CandOut><<<scan_grid, kBlock, 0, st>>>(ScanLength(N), CandIn{ra, from}, CandOut{ra, ka}, partial);
+        rank_place_kernel<<<rgrid, kRankBlock, 0, st>>>(ra, from, count, ka);
         if (nsel <= kSmallRank) {
             int size = 2;
             while (size < nsel) size <<= 1;

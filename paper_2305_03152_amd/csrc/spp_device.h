@@ -55,6 +55,23 @@ __device__ __forceinline__ unsigned wave_inclusive_max(unsigned v) {
     up(dpp_or_zero<0x143, 0xC>(v));
     return v;
 }
+// The wavefront's lanes whose value agrees with this lane's in the low BITS bits: four instructions a bit (the bit spread over a
+// word, its ballot, and one three-input operation for each half of the lanes).
+template <int BITS>
+__device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
+    const uint64_t all = __ballot(has);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int bit = 0; bit < BITS; ++bit) {
+        uint32_t m = (uint32_t)((int32_t)(value << (31 - bit)) >> 31);            // all ones where the bit is set
+        asm("" : "+v"(m));                       // else the ballot is of the shifted value, one instruction more
+        const uint64_t bm = __ballot(m != 0u);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bm, m, 0x90);              // lo & ~(bm ^ m)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bm >> 32), m, 0x90);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
 __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 
 // Exclusive scan over a 256-thread workgroup; returns the exclusive prefix of `v` and the

@@ -70,22 +70,6 @@ __device__ __forceinline__ void add_mix(unsigned long long mine, unsigned long l
     for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
     if (lane_id() == 0 && mine) atomicAdd(sum, mine);
 }
-// The wavefront's lanes whose value agrees with this lane's in the low BITS bits: four instructions a bit (the bit spread over a
-// word, its ballot, and one three-input operation for each half of the lanes).
-template <int BITS>
-__device__ __forceinline__ uint64_t lanes_alike(bool has, uint32_t value) {
-    const uint64_t all = __ballot(has);
-    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
-#pragma unroll
-    for (int bit = 0; bit < BITS; ++bit) {
-        uint32_t m = (uint32_t)((int32_t)(value << (31 - bit)) >> 31);            // all ones where the bit is set
-        asm("" : "+v"(m));                       // else the ballot is of the shifted value, one instruction more
-        const uint64_t bm = __ballot(m != 0u);
-        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bm, m, 0x90);              // lo & ~(bm ^ m)
-        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bm >> 32), m, 0x90);
-    }
-    return ((uint64_t)hi << 32) | lo;
-}
 
 // The passes that build the row blocks validate the CSR on the way: this one its offsets, the counting pass its ids, each
 // before it uses them; the passes after those two do nothing if either found something wrong.  (A pass of its own cost a
