@@ -139,6 +139,90 @@ __device__ __forceinline__ void vip_finish_vertices(const VipHop& a, int64_t u, 
         }
 }
 
+// The next hop's weights of U vertices whose sums are not zero (the others' are).  All threads call it with their vertices'
+// own ones; those without `has` come away with zeros.
+template <int U>
+__device__ __forceinline__ void vip_next_weights(const VipHop& a, const int64_t (&v)[U], const double (&S)[U], const bool (&has)[U],
+                                                 float (&ph32)[U], float (&yn)[U], unsigned long long& edges) {
+    double ph[U];
+    int64_t d[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) d[k] = a.rowptr[has[k] ? v[k] + 1 : 0] - a.rowptr[has[k] ? v[k] : 0];
+#pragma unroll
+    for (int k = 0; k < U; ++k) ph[k] = has[k] ? one_minus_exp(S[k]) : 0.0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const double dd = (double)d[k];
+        const double t = dd <= a.f_next ? 1.0 : small_quotient(a.f_next, dd);
+        ph32[k] = (float)ph[k];
+        yn[k] = d[k] > 0 ? (float)log1p_neg(t * ph[k]) : 0.0f;
+        edges += yn[k] != 0.0f ? (unsigned long long)d[k] : 0ull;
+    }
+}
+
+// The kWaveRows vertices from u0 on whose sums a wavefront holds in LDS, after a hop that is not the last: the arithmetic of those
+// with a sum alone, 64 lanes at a time (most vertices have none at the early hops: 5 and 25 % of 14M vertices have, spread
+// over nearly all wavefronts; the arithmetic of all of them took two thirds of the kernel).  queue: kTouchedQueue entries.
+constexpr int kWaveRows = 1024, kTouchedQueue = 512;
+__device__ __forceinline__ void vip_finish_touched(const VipHop& a, int64_t u0, int64_t N, double* acc, uint16_t* queue,
+                                                   unsigned long long& edges) {
+    constexpr int U = 4, kBatch = U * kWave;
+    const int lane = lane_id();
+    auto settled = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
+    int queued = 0;
+    auto finish = [&](int n) {                   // the last n of the queue, at most kBatch
+        settled();
+        int i[U];
+        int64_t v[U];
+        double S[U];
+        bool has[U];
+        float ph[U], yn[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            has[k] = k * kWave + lane < n;
+            i[k] = has[k] ? queue[queued - n + k * kWave + lane] : 0;
+            v[k] = u0 + i[k];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) S[k] = acc[i[k]];
+        vip_next_weights<U>(a, v, S, has, ph, yn, edges);
+        settled();
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (has[k]) acc[i[k]] = __hiloint2double(__float_as_int(ph[k]), __float_as_int(yn[k]));      // in place of its sum
+        queued -= n;
+        settled();
+    };
+    for (int b = 0; b < kWaveRows && u0 + b < N; b += kBatch) {
+        double S[U], T0[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) S[k] = acc[b + k * kWave + lane];
+        if (!a.first)
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int64_t u = u0 + b + k * kWave + lane;
+                T0[k] = a.tot[u < N ? u : N - 1];
+            }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int i = b + k * kWave + lane;
+            const bool inside = u0 + i < N, some = inside && S[k] != 0.0;
+            if (a.first ? inside : some) a.tot[u0 + i] = a.first ? S[k] : T0[k] + S[k];
+            const uint64_t m = __ballot(some);
+            if (some) queue[queued + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = (uint16_t)i;
+            queued += __popcll(m);
+        }
+        if (queued >= kBatch) finish(kBatch);
+    }
+    if (queued > 0) finish(queued);              // fewer than kBatch
+    settled();
+    for (int i = lane; i < kWaveRows && u0 + i < N; i += kWave) {
+        const double r = acc[i];                 // zeros where there was no sum
+        a.y_next[u0 + i] = __int_as_float(__double2loint(r));
+        if (a.p_hop) a.p_hop[u0 + i] = __int_as_float(__double2hiint(r));
+    }
+}
+
 // All vertices, grid-stride, four per thread and round: the four sums and running totals are in
 // flight together (one vertex per round leaves a pass over 10^8 vertices waiting on its own loads:
 // 0.87 ms where the bytes take 0.55).  sum_of(u) = S_h(u).
@@ -695,14 +779,21 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
 // = where the piece lies in the arrays.  With one share per block the workgroup finishes the
 // block's vertices itself (p^[h], running total, next hop's y); otherwise it leaves its sums in
 // part[j] for vip_finish_kernel.
-__global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __restrict__ vals,
-                                                             const uint16_t* __restrict__ x_row,
-                                                             const uint32_t* __restrict__ x_start,
-                                                             const uint32_t* __restrict__ x_prefix, int nch, int parts,
-                                                             int64_t N, double* __restrict__ part, int64_t part_stride,
-                                                             VipHop a, int alone, const uint32_t* __restrict__ how) {
-    extern __shared__ double acc[];
-    if (*how != kPulled) return;
+struct ReduceArgs {
+    const float* vals;
+    const uint16_t* x_row;
+    const uint32_t *x_start, *x_prefix;
+    int      nch, parts;
+    int64_t  N;
+    double*  part;
+    int64_t  part_stride;
+    int      alone;              // no vip_finish_kernel follows
+};
+__device__ __forceinline__ void reduce_block(const ReduceArgs& x, const VipHop& a, double* acc) {
+    const uint16_t* __restrict__ x_row = x.x_row;
+    const float* __restrict__ vals = x.vals;
+    const uint32_t *__restrict__ x_start = x.x_start, *__restrict__ x_prefix = x.x_prefix;
+    const int nch = x.nch, parts = x.parts;
     constexpr int R = 1 << kTileRowBits;
     uint32_t* prefix = reinterpret_cast<uint32_t*>(acc + R);     // [kXGroup + 1]
     uint32_t* start = prefix + kXGroup + 1;                      // [kXGroup]
@@ -782,13 +873,17 @@ __global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(const float* __rest
     __syncthreads();
     const int64_t u0 = rb << kTileRowBits;
     if (parts == 1) {
-        if (alone && blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, true);
+        if (x.alone && blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, true);
         unsigned long long edges = 0;            // not asked for: the hop after a pulled one is pulled
-        vip_finish_block<R>(a, u0, N, acc, edges);
+        vip_finish_block<R>(a, u0, x.N, acc, edges);
     } else {
-        double* __restrict__ out = part + (int64_t)j * part_stride + u0;
+        double* __restrict__ out = x.part + (int64_t)j * x.part_stride + u0;
         for (int i = threadIdx.x; i < R; i += kXBlock) out[i] = acc[i];
     }
+}
+__global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(ReduceArgs x, VipHop a, const uint32_t* __restrict__ how) {
+    extern __shared__ double acc[];
+    if (*how == kPulled) reduce_block(x, a, acc);
 }
 
 // y_1(v) for the training vertices (p^[0] = min(1, B/|T|), Sec. 3.1); optionally hop 0 into the
@@ -1344,14 +1439,17 @@ __global__ void __launch_bounds__(kBinBlock) vip_bin_fill_kernel(const int32_t* 
     });
 }
 
-// Sums a row block's entries in LDS and finishes its vertices.  Bound by the finishing arithmetic of 16
-// wavefronts per CU (the sums take the LDS): 14M vertices, 131 us with 13.4M entries, 84 with 0.8M, where the
-// bytes take 62 and 27.
+// Sums a row block's entries in LDS and finishes its vertices.  14M vertices, 115 us with 13.4M entries, 58 with 0.8M, where the
+// bytes take 62 and 27 (137 and 88 with the arithmetic of all vertices): four rounds of one workgroup per CU, whose
+// phases nothing overlaps.
+// The other form of the hop, the second pass of a pull, has the same workgroups: in one launch with it (one that finds nothing
+// to do costs 4.6 us).
 __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, const uint2* __restrict__ bins,
-                                                                    const uint32_t* __restrict__ base, int64_t N,
+                                                                    const uint32_t* __restrict__ base, int64_t N, ReduceArgs x,
                                                                     const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
-    if (*how != kPushed) return;
+    static_assert(kXBlock == kTileBlock, "either form's workgroups");
+    if (*how == kPulled) { reduce_block(x, a, acc); return; }
     constexpr int R = 1 << kTileRowBits;
     for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
     __syncthreads();
@@ -1359,8 +1457,16 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, false);
     unsigned long long edges = 0;
-    vip_finish_block<R>(a, (int64_t)blockIdx.x << kTileRowBits, N, acc, edges);
-    if (!a.last) plan_hop<kTileBlock>(a.next, edges);
+    const int64_t u0 = (int64_t)blockIdx.x << kTileRowBits;
+    if (a.last) {
+        vip_finish_block<R>(a, u0, N, acc, edges);
+        return;
+    }
+    static_assert(kTileWaves * kWaveRows == R, "a wavefront's vertices");
+    const int wave = threadIdx.x >> 6;
+    uint16_t* queue = reinterpret_cast<uint16_t*>(acc + R) + wave * kTouchedQueue;
+    vip_finish_touched(a, u0 + wave * kWaveRows, N, acc + wave * kWaveRows, queue, edges);
+    plan_hop<kTileBlock>(a.next, edges);
 }
 
 // The bins of a hop whose frontier holds most of the edges.  A tile of the CSR (kPartTile edges) puts its edges of a row block
@@ -1864,11 +1970,12 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
     const size_t bin_words = (size_t)kPushGroups * (size_t)g->nrb + 2 * (size_t)g->nrb + 1;
     const bool binned = g->has_x && parts == 1 && g->nrb <= kBinMaxBlocks &&
                         bin_entries * sizeof(uint2) + bin_words * sizeof(uint32_t) <= (size_t)g->x_entries * sizeof(float);
-    const size_t bin_lds = (size_t)g->nrb * sizeof(uint32_t), bin_sum_lds = sizeof(double) << kTileRowBits;
+    const size_t bin_lds = (size_t)g->nrb * sizeof(uint32_t), bin_sum_lds = (sizeof(double) << kTileRowBits) + kTileWaves * kTouchedQueue * sizeof(uint16_t);
     const size_t lds_bytes = (sizeof(double) << g->tile_rbits) + (size_t)(kTileWaves * kTileWin + g->nch + 1) * sizeof(uint32_t);
     const size_t x_lds_expand = (sizeof(float) << kXSrcBits) + sizeof(float);
     static_assert(kXPad == (1u << kXSrcBits), "a padding entry indexes the slot after the chunk's values");
     const size_t x_lds_reduce = (sizeof(double) << kTileRowBits) + (2 * kXGroup + 1) * sizeof(uint32_t);
+    const size_t bin_finish_lds = bin_sum_lds > x_lds_reduce ? bin_sum_lds : x_lds_reduce;
     const size_t hop_lds = g->has_x || lds_bytes < sizeof(PushLds) ? sizeof(PushLds) : lds_bytes;
     if (!binned && ctx->tile_lds_set < (int)hop_lds) {        // more than the 64 KB a launch may ask for by default
         SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_hop_kernel),
@@ -1887,7 +1994,7 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             for (const void* k : {reinterpret_cast<const void*>(&vip_bin_count_kernel), reinterpret_cast<const void*>(&vip_bin_fill_kernel)})
                 SPP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bin_lds));
             SPP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vip_bin_finish_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bin_sum_lds));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bin_finish_lds));
             ctx->push_lds_set = (int)bin_lds;
         }
         SPP_TRY(ctx->xvals.reserve((size_t)(g->x_entries > 0 ? g->x_entries : 4) * sizeof(float)));
@@ -1922,6 +2029,11 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
         ScopedTimer tt(ctx, SPP_T_VIP_TOTAL, st);
         double* acc = ctx->acc.as<double>();
         HopPlan plan{1, g->M, slots, how, fcursor, mirror, {flist, binned ? nullptr : seg_count, per_group(nT), tgrid}};
+        // the bins of a pushed hop (entries, counts, offsets), where a pulled one keeps its values
+        uint2* bins = binned ? ctx->xvals.as<uint2>() : nullptr;
+        uint32_t* off = binned ? reinterpret_cast<uint32_t*>(bins + bin_entries) : nullptr;
+        uint32_t* total = binned ? off + (size_t)kPushGroups * (size_t)g->nrb : nullptr;
+        uint32_t* bin_base = binned ? total + g->nrb : nullptr;
         vip_clear_kernel<<<vgrid, kBlock, 0, st>>>(ycur, include0 ? tot : nullptr, binned ? nullptr : acc, N);
         vip_init_kernel<<<tgrid, kBlock, 0, st>>>(d_T, nT, N, p0, (double)fanouts[0], g->rowptr, ycur, tot, include0, d_bad, plan);
         for (int h = 1; h <= L; ++h) {
@@ -1942,16 +2054,11 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
             a.bad_mirror = mirror + 2 * SPP_MAX_L;
             const uint32_t* how_h = how + h;
             if (binned) {
-                uint2* bins = ctx->xvals.as<uint2>();
-                uint32_t* off = reinterpret_cast<uint32_t*>(bins + bin_entries);
-                uint32_t* total = off + (size_t)kPushGroups * (size_t)g->nrb;
-                uint32_t* base = total + g->nrb;
                 launch_frontier_list(most, st, ycur, g->rowptr, N, flist, fcursor, how_h);
                 vip_bin_count_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcursor, ycur, g->rowptr, g->col, (int)g->nrb, off, how_h);
                 vip_bin_offsets_kernel<<<(unsigned)((g->nrb + kOffBins - 1) / kOffBins), 1024, 0, st>>>(off, (int)g->nrb, total, how_h);
                 vip_bin_fill_kernel<<<kPushGroups, kBinBlock, bin_lds, st>>>(flist, fcursor, ycur, g->rowptr, g->col, (int)g->nrb, off,
-                                                                            total, base, bins, how_h);
-                vip_bin_finish_kernel<<<(unsigned)g->nrb, kTileBlock, bin_sum_lds, st>>>(a, bins, base, N, how_h);
+                                                                            total, bin_base, bins, how_h);
             } else {
                 // as many workgroups as there are shares of row blocks, and one per CU at least for a push
                 const int64_t shares = g->has_x ? 0 : g->nrb * parts;
@@ -1965,8 +2072,9 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 const int egrid = eshare < ctx->num_cu ? (int)eshare : ctx->num_cu;
                 vip_expand_kernel<<<egrid, kXBlock, x_lds_expand, st>>>(g->x_src, g->x_chunk_first, g->x_nch, N, ycur,
                                                                         ctx->xvals.as<float>(), how_h);
-                vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(
-                    ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, a, binned, how_h);
+                const ReduceArgs x{ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, binned};
+                if (binned) vip_bin_finish_kernel<<<(unsigned)g->nrb, kTileBlock, bin_finish_lds, st>>>(a, bins, bin_base, N, x, how_h);
+                else vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(x, a, how_h);
                 fused = parts == 1;
             }
             if (!binned) vip_finish_kernel<<<vgrid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N);
