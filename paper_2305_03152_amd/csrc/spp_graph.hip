@@ -57,8 +57,8 @@ __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
 // (block, tile) counts, one pass that places a tile's edge words in LDS by block and writes them as
 // runs.  (A radix sort of 64-bit keys (block, source, row) took four passes over 16 bytes per edge, and
 // 16 bytes per edge of temporary memory whose allocation cost more than the sort.)  2.4M vertices, 121M
-// edges: the kernels of a build 9.2 -> 0.85 ms: 0.35 in the placing pass, most of it vector instructions,
-// 0.12 in the counting pass, 0.15 in the read-back and 0.20 in the sum over the CSR that it is compared with.
+// edges: the kernels of a build 9.2 -> 0.81 ms: 0.35 in the placing pass, most of it vector instructions,
+// 0.11 in the counting pass, 0.15 in the read-back and 0.175 in the sum over the CSR that it is compared with.
 constexpr int kPartBlock = 1024;
 constexpr int kPartWaves = kPartBlock / kWave;
 constexpr int kPartPer = kPartTile / kPartBlock;         // 64-edge batches per wavefront
@@ -98,12 +98,19 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64
     bool wrong = false;
     constexpr int kCopies = 8;                   // a lane adds to one of eight copies: most edges of a tile end in few blocks
     __shared__ uint32_t cnt[kPartMaxBlocks][kCopies];
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        for (int i = threadIdx.x; i < kPartMaxBlocks * kCopies; i += kPartBlock) (&cnt[0][0])[i] = 0u;
-        const int64_t e0 = tile * kPartTile + threadIdx.x;
-        uint32_t u[kPartPer];
+    uint32_t u[kPartPer], next[kPartPer];        // the next tile's ids are asked for before this one's are counted
+    auto load = [&](uint32_t (&v)[kPartPer], int64_t tile) {
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k) u[k] = e0 + k * kPartBlock < M ? (uint32_t)col[e0 + k * kPartBlock] : 0xFFFFFFFFu;
+        for (int k = 0; k < kPartPer; ++k) {
+            const int64_t e = tile * kPartTile + threadIdx.x + k * kPartBlock;
+            v[k] = (uint32_t)__builtin_nontemporal_load(col + (e < M ? e : M - 1));
+        }
+    };
+    load(u, blockIdx.x);
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        for (int i = threadIdx.x; i < nrb * kCopies; i += kPartBlock) (&cnt[0][0])[i] = 0u;
+        const int64_t e0 = tile * kPartTile + threadIdx.x;
+        load(next, tile + gridDim.x);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPartPer; ++k)
@@ -118,6 +125,8 @@ __global__ void __launch_bounds__(kPartBlock) part_count_kernel(int64_t N, int64
             for (int w = 0; w < kCopies; ++w) c += cnt[threadIdx.x][w];
             hist[(int64_t)threadIdx.x * ntiles + tile] = c;
         }
+#pragma unroll
+        for (int k = 0; k < kPartPer; ++k) u[k] = next[k];
         __syncthreads();
     }
     if (wrong) found->bad = 1;
@@ -371,8 +380,10 @@ __global__ void __launch_bounds__(kPartBlock) part_first_kernel(int64_t M, const
 // another way than the one that built it.  A wavefront takes 2^piece_bits edges at a time (a tile, or less where the
 // graph has fewer tiles than the chip wavefronts) and holds the ends of 64 rows in its lanes, among which an edge finds its
 // own; the first row is sought from the tile's entry in tile_row[] on and must hold the first edge (else the structure
-// is bad), later ones follow or, after a long run of empty rows, are found by bisection.  2.4M vertices, 121M edges: 194 us
-// (271 with a bisection over all rows for every 2048 edges' first one and one among the 64 rows for every edge).
+// is bad), later ones follow or, after a long run of empty rows, are found by bisection.  The next
+// edges and the next 64 rows' ends are asked for before those in hand are looked at.  2.4M vertices, 121M edges: 175 us (207 without;
+// 271 with a bisection over all rows for every 2048 edges' first one and one among the 64 rows for every edge).  Vector
+// instructions bound it, the two products above all: the bytes alone take 72.
 __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, const int64_t* __restrict__ rowptr,
                                                          const int32_t* __restrict__ col, const int32_t* __restrict__ tile_row,
                                                          int piece_bits, unsigned long long* __restrict__ mix, int* __restrict__ bad,
@@ -394,6 +405,16 @@ __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, c
         }
         if (rowptr[lo] > base || rowptr[lo + 1] <= base) { *bad = 1; continue; }
         uint32_t done = 0;
+        uint32_t ahead[U];                       // the ids of the edges that come next
+        auto load = [&](uint32_t p0) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t p = p0 + k * kWave + lane;
+                ahead[k] = (uint32_t)__builtin_nontemporal_load(col + base + (p < count ? p : count - 1));
+            }
+        };
+        auto row_end = [&](int64_t v) { return rowptr[v + 1 + lane < N ? v + 1 + lane : N]; };       // M at N
+        load(0);
         while (done < count) {
             if (done > 0) {
                 // the last row that starts at or before the edge (it holds it: rows after an empty one start where that does)
@@ -404,19 +425,20 @@ __global__ void __launch_bounds__(kBlock) csr_mix_kernel(int64_t N, int64_t M, c
                     if (rowptr[mid] <= base + done) lo = mid; else hi = mid - 1;
                 }
             }
-            // rows lo .. lo + 63, as long as they hold edges of the piece
+            // rows lo .. lo + 63, as long as they hold edges of the piece; the next 64 rows' ends are asked for before
+            int64_t ends = row_end(lo);
             for (bool more = true; more && done < count; lo += kWave) {
-                const int64_t end64 = (lo + 1 + lane <= N ? rowptr[lo + 1 + lane] : M) - base;
+                const int64_t end64 = ends - base;
+                ends = row_end(lo + kWave);
                 const uint32_t end = end64 < (int64_t)count ? (uint32_t)end64 : count;
-                const uint32_t stop = (uint32_t)__shfl((int)end, kWave - 1, kWave);
+                const uint32_t stop = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
                 more = stop > done;
                 for (uint32_t p0 = done; p0 < stop; p0 += U * kWave) {
                     uint32_t u[U];
 #pragma unroll
-                    for (int k = 0; k < U; ++k) {
-                        const uint32_t p = p0 + k * kWave + lane;
-                        u[k] = p < stop ? (uint32_t)col[base + p] : 0u;
-                    }
+                    for (int k = 0; k < U; ++k) u[k] = ahead[k];
+                    // the batches after these, or those of the next rows
+                    load(p0 + U * kWave < stop ? p0 + U * kWave : stop);
 #pragma unroll
                     for (int k = 0; k < U; ++k) {
                         const uint32_t p = p0 + k * kWave + lane;
