@@ -934,8 +934,8 @@ __device__ __forceinline__ float unit_or_flag(float x, int* bad) {
 // How a hop of the general propagation fills its bins: from a list of its frontier, or (kWhole) from the whole CSR, tile
 // by tile, where the frontier's rows hold at least half of the edges.  The kernel that writes a hop's
 // probabilities counts their vertices' out-edges and decides; on large graphs it counts a part of them (either form is correct
-// for any frontier).  2.4M vertices, 121M edges, list, fill and sum: by tiles 558 us
-// whatever the frontier; listed 1075 us with all edges, 345 with 23 % of them.
+// for any frontier).  2.4M vertices, 121M edges, a call of one hop: by tiles 605 us
+// whatever the frontier; listed 953 with all edges, 657 with 60 % of them, 585 with 51, 505 with 40, 343 with 23.
 constexpr uint32_t kListed = 1, kWhole = 2;
 struct FillRule {
     const int64_t* rowptr;               // null: always from the list (no tiles to walk)
@@ -1019,9 +1019,10 @@ __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __rest
 // 64 consecutive edges of that sequence whatever the row lengths, so its loads are contiguous).
 // It walks them in rounds of 8192 edges: an LDS atomic per edge counts the round's entries per bin and gives
 // the edge its place among them, one global atomic per bin reserves their range, and the entries, held in
-// registers meanwhile, are stored.  2.4M vertices, 121M edges: 859 us per dense hop (900 with 256 threads
-// that counted a portion in one walk over col[] and stored its entries in a second), 252 and 47 for
-// the sparser hops before it (299 and 92).  Nothing is busy for half of the time (vector units 35 %, LDS 44 %, a third of
+// registers meanwhile, are stored.  2.4M vertices, a hop of a quarter of 121M edges: 274 -> 230 us since all loads of a round
+// are under way together (a probability that was looked at where it was loaded, for the flag, had the next edge's wait for it).
+// Before that 859 us per dense hop (900 with 256 threads
+// that counted a portion in one walk over col[] and stored its entries in a second).  Nothing is busy for half of the time (vector units 35 %, LDS 44 %, a third of
 // that bank conflicts; 2.3 GB of traffic, which a copy moves in 360 us): wavefronts wait three quarters of their clocks, for
 // their loads, for the round's reservations (15k atomics on each bin's counter) and at the barriers around those, and the
 // two workgroups of a CU do not fill each other's waits.  (Rounds of 2048 edges:
@@ -1700,6 +1701,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
     const int64_t nf = (int64_t)*nf_ptr;
     const PortionMap<kFillBlock> pm(nf);
     const uint32_t rmask = (1u << rbits) - 1u;
+    bool wrong = false;
     for (int r = threadIdx.x; r < nrb; r += kFillBlock) count[r] = 0u;
     // Portions are handed out through a counter (the slot after the bins' cursors): their sizes
     // differ by the degrees of their vertices, and with fixed shares half of the wavefronts had
@@ -1715,19 +1717,28 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
         });
         for (uint32_t c0 = 0; c0 < total; c0 += kFillBlock * kFillPer) {
             uint32_t key[kFillPer], rank[kFillPer];
-            float x[kFillPer];
+            float x[kFillPer], p[kFillPer];
 #pragma unroll
-            for (int q = 0; q < kFillPer; ++q) key[q] = ~0u;
+            for (int q = 0; q < kFillPer; ++q) { key[q] = ~0u; x[q] = p[q] = 0.0f; }
             if (bin_edge<kFillPer>(c0, 0) < total) {
                 BinCursor<kFillBlock> cu;
                 cu.start(po, nv, bin_edge<kFillPer>(c0, 0));
 #pragma unroll
-                for (int q = 0; q < kFillPer; ++q)
-                    if (bin_edge<kFillPer>(c0, q) < total) {
-                        const int64_t k = cu.at(po, bin_edge<kFillPer>(c0, q));
-                        key[q] = (uint32_t)col[k];
-                        x[q] = unit_or_flag(t[k], bad) * cu.p;
-                    }
+                for (int q = 0; q < kFillPer; ++q) {             // beyond the last edge that one again: no load is conditional
+                    const uint32_t e = bin_edge<kFillPer>(c0, q);
+                    const int64_t k = cu.at(po, e < total ? e : total - 1);
+                    key[q] = (uint32_t)col[k];
+                    x[q] = t[k];
+                    p[q] = cu.p;
+                }
+            }
+            // only here: looked at where it is loaded, a probability was waited for before the next edge's was asked for
+#pragma unroll
+            for (int q = 0; q < kFillPer; ++q) {
+                if (bin_edge<kFillPer>(c0, q) >= total) key[q] = ~0u;
+                const float c = __builtin_amdgcn_fmed3f(x[q], 0.0f, 1.0f);
+                wrong |= !(c == x[q]);
+                x[q] = c == x[q] ? c * p[q] : 0.0f;
             }
 #pragma unroll
             for (int q = 0; q < kFillPer; ++q)
@@ -1750,6 +1761,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_bin_fill_kernel(const int3
         }
         __syncthreads();
     }
+    if (wrong) *bad = 1;
 }
 
 // Adds the entries of one share of one bin into the block's fp64 sums (LDS) and writes them to
