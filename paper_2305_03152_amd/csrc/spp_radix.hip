@@ -2,8 +2,8 @@
 // to build the chunked transposed edge structure and to rank cache candidates and local vertices
 // (Sec. 3.2).
 //
-// A tile is 4096 keys (1024 where the keys do not make four tiles of 4096 per CU: a pass over
-// 320k keys takes 23 us of kernels instead of 55) handled by one 256-thread workgroup; wavefront w owns the w-th quarter of
+// A tile is 4096 keys (1024 where the keys do not make four tiles of 4096 per CU, so that every CU has some;
+// up to 1M keys take the form with two launches per pass below) handled by one 256-thread workgroup; wavefront w owns the w-th quarter of
 // the tile and walks it in order, 64 keys at a time, so a key's stable rank among equal digits is
 // (count of that digit in earlier wavefronts' quarters) + (count earlier in its own quarter) +
 // (count in lower lanes of its own 64), the last from ballots.  Keys are then placed in digit
