@@ -23,6 +23,15 @@ __device__ __forceinline__ T here(T x) {
     return x;
 }
 
+// What the wavefront's lanes have written to LDS before is there for its other lanes' reads after, and what they have read before
+// is not overwritten by their writes after.  The hardware keeps a wavefront's LDS accesses in order; this keeps the compiler's,
+// which may otherwise take two lanes' accesses of different addresses past each other.  All lanes of the wavefront; no wait
+// and no instruction of its own.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Prefix sums are formed modulo 2^32 (counts up to 2^32 - 1 pass through int unchanged).
 __device__ __forceinline__ int uadd(int a, int b) { return (int)((unsigned)a + (unsigned)b); }
 

@@ -255,7 +255,9 @@ __global__ void __launch_bounds__(kPartBlock, 8) part_place_kernel(int64_t N, in
             const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
             uint16_t* c = cnt + (has ? blk * kPartWaves + wave : 0u);
             const uint32_t prior = *c;
+            wave_lds_order();                    // the lanes alike have read it
             if (has && below == 0) *c = (uint16_t)(prior + (uint32_t)__popcll(same));
+            wave_lds_order();                    // before the next 64 read it
             place[k] = (blk << 16) | (prior + below);
             u[k] = ((src & ((1u << kTileSrcLoBits) - 1u)) << kTileRowBits) | (u[k] & rmask);
         }

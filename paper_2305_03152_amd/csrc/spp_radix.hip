@@ -73,7 +73,9 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(const uint64_t* _
             const uint32_t below = (uint32_t)__popcll(m & lt_mask);
             uint32_t prior = 0;
             if (valid) prior = cnt[wave][d];
+            wave_lds_order();
             if (valid && below == 0) cnt[wave][d] = prior + (uint32_t)__popcll(m);
+            wave_lds_order();
             key[b] = k;
             rnk[b] = (uint16_t)(prior + below);
         }
@@ -171,6 +173,7 @@ __global__ void __launch_bounds__(kMidBlock) radix_mid_scatter_kernel(const uint
     }
 #pragma unroll
     for (int k = 0; k < 256 / kWave; ++k) cnt[wave][k * kWave + lane] = 0u;      // the wavefront's own
+    wave_lds_order();
     uint32_t rnk[kBatches];
 #pragma unroll
     for (int b = 0; b < kBatches; ++b) {
@@ -179,7 +182,9 @@ __global__ void __launch_bounds__(kMidBlock) radix_mid_scatter_kernel(const uint
         const uint64_t same = lanes_alike<8>(valid, d);
         const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
         const uint32_t prior = cnt[wave][d];
+        wave_lds_order();                        // the lanes alike have read it
         if (valid && below == 0) cnt[wave][d] = prior + (uint32_t)__popcll(same);
+        wave_lds_order();                        // before the next 64 read it
         rnk[b] = prior + below;
     }
     __syncthreads();

@@ -645,7 +645,9 @@ __global__ void __launch_bounds__(kBlock, 4) hop_sample_kernel(HopArgs a, BatchT
             }
             const uint32_t below = (uint32_t)__popcll(same & lt_mask);
             const uint32_t prior = cnt[wave][p];
+            wave_lds_order();
             if (has && below == 0) cnt[wave][p] = prior + (uint32_t)__popcll(same);
+            wave_lds_order();
             if (has) rank_lds[x] = (uint16_t)(prior + below);
         }
         __syncthreads();

@@ -168,10 +168,9 @@ __device__ __forceinline__ void vip_finish_touched(const VipHop& a, int64_t u0, 
                                                    unsigned long long& edges) {
     constexpr int U = 4, kBatch = U * kWave;
     const int lane = lane_id();
-    auto settled = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
     int queued = 0;
     auto finish = [&](int n) {                   // the last n of the queue, at most kBatch
-        settled();
+        wave_lds_order();
         int i[U];
         int64_t v[U];
         double S[U];
@@ -186,12 +185,12 @@ __device__ __forceinline__ void vip_finish_touched(const VipHop& a, int64_t u0, 
 #pragma unroll
         for (int k = 0; k < U; ++k) S[k] = acc[i[k]];
         vip_next_weights<U>(a, v, S, has, ph, yn, edges);
-        settled();
+        wave_lds_order();
 #pragma unroll
         for (int k = 0; k < U; ++k)
             if (has[k]) acc[i[k]] = __hiloint2double(__float_as_int(ph[k]), __float_as_int(yn[k]));      // in place of its sum
         queued -= n;
-        settled();
+        wave_lds_order();
     };
     for (int b = 0; b < kWaveRows && u0 + b < N; b += kBatch) {
         double S[U], T0[U];
@@ -215,7 +214,7 @@ __device__ __forceinline__ void vip_finish_touched(const VipHop& a, int64_t u0, 
         if (queued >= kBatch) finish(kBatch);
     }
     if (queued > 0) finish(queued);              // fewer than kBatch
-    settled();
+    wave_lds_order();
     for (int i = lane; i < kWaveRows && u0 + i < N; i += kWave) {
         const double r = acc[i];                 // zeros where there was no sum
         a.y_next[u0 + i] = __int_as_float(__double2loint(r));
@@ -595,7 +594,7 @@ __device__ __forceinline__ void pull_tiles(double* acc, const uint32_t* __restri
             if (how == kWindow) {
                 *reinterpret_cast<f32x4*>(win + 4 * lane) = y0;
                 if (lane < (kTileWin - 256) / 4) *reinterpret_cast<f32x4*>(win + 256 + 4 * lane) = y1;
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
             }
             int how_n = kEach;
             if (q0 + kStep < nvec) how_n = look(q0 + kStep, nxt, base_n, w0_n);
@@ -609,7 +608,7 @@ __device__ __forceinline__ void pull_tiles(double* acc, const uint32_t* __restri
                     v[u][2] = win[off + (cur.v[u].z >> kTileRowBits)];
                     v[u][3] = win[off + (cur.v[u].w >> kTileRowBits)];
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
             } else if (how == kGather) {
                 const float* __restrict__ yc = y + base;
 #pragma unroll
