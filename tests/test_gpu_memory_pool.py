@@ -75,6 +75,11 @@ def test_threads(spp):
     assert not errors, errors
 
 
+# What the device reports free is a multiple of 2 MiB: a difference of two readings is off by less than one such step either way,
+# and the runtime may hold part of a step from allocations before.  120000000 bytes (57.2 steps) have shown as 57 steps.
+STEP = 2 << 20
+
+
 def _free():
     """Bytes the device reports free, without what torch and handles that nothing refers to any more keep."""
     gc.collect()
@@ -92,7 +97,7 @@ def test_what_is_kept_serves_the_next_build(spp):
     before = _free()
     g = spp.Graph(ctx, rp, col, in_lists=True)
     built = _free()
-    assert before - built >= 4 * N * deg                                    # a word per edge, and what goes with it
+    assert before - built >= 4 * N * deg - 2 * STEP                         # a word per edge, and what goes with it
     for _ in range(2):
         g.close()
         assert _free() == built                                             # nothing went back ...
@@ -122,9 +127,10 @@ def test_what_is_kept_is_given_back_on_request(spp):
     N, deg = 1_000_000, 30
     rp = torch.arange(N + 1, dtype=torch.int64, device="cuda") * deg
     col = ((torch.arange(N, device="cuda").unsqueeze(1) + torch.arange(1, deg + 1, device="cuda")) % N).sort(1).values.to(torch.int32).reshape(-1)
+    spp.release_memory(0)                                               # else the build may find its memory there, and takes none
     before = _free()
     spp.Graph(ctx, rp, col, in_lists=True).close()
-    assert before - _free() > 4 * N * deg                               # the edges' words are kept
+    assert before - _free() > 4 * N * deg - 2 * STEP                    # the edges' words are kept
     spp.release_memory(0)
     assert before - _free() < 2 * N * deg
     ctx.close()
