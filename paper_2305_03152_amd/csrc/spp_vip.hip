@@ -772,33 +772,24 @@ __global__ void __launch_bounds__(kXBlock) vip_expand_kernel(const uint16_t* __r
     }
 }
 
-// Second pass.  The block's vectors form one sequence (vector q of the block: the pieces of chunks
-// 0, 1, ... end to end); the j-th of `parts` equal shares of it is walked by this workgroup, a
+// Second pass.  A row block's vectors form one sequence (vector q of the block: the pieces of chunks
+// 0, 1, ... end to end); the j-th of `parts` equal shares of it is added up by this workgroup, a
 // group of kXGroup pieces at a time: prefix[k] = first vector of piece k in that sequence, start[k]
-// = where the piece lies in the arrays.  With one share per block the workgroup finishes the
-// block's vertices itself (p^[h], running total, next hop's y); otherwise it leaves its sums in
-// part[j] for vip_finish_kernel.
+// = where the piece lies in the arrays.  Ends with a barrier.
 struct ReduceArgs {
     const float* vals;
     const uint16_t* x_row;
     const uint32_t *x_start, *x_prefix;
-    int      nch, parts;
-    int64_t  N;
-    double*  part;
-    int64_t  part_stride;
-    int      alone;              // no vip_finish_kernel follows
+    int      nch;
 };
-__device__ __forceinline__ void reduce_block(const ReduceArgs& x, const VipHop& a, double* acc) {
+__device__ __forceinline__ void reduce_share(const ReduceArgs& x, int64_t rb, int j, int parts, double* acc) {
     const uint16_t* __restrict__ x_row = x.x_row;
     const float* __restrict__ vals = x.vals;
     const uint32_t *__restrict__ x_start = x.x_start, *__restrict__ x_prefix = x.x_prefix;
-    const int nch = x.nch, parts = x.parts;
+    const int nch = x.nch;
     constexpr int R = 1 << kTileRowBits;
     uint32_t* prefix = reinterpret_cast<uint32_t*>(acc + R);     // [kXGroup + 1]
     uint32_t* start = prefix + kXGroup + 1;                      // [kXGroup]
-    const int64_t nrb = gridDim.x / parts;
-    const int64_t rb = blockIdx.x % nrb;
-    const int j = (int)(blockIdx.x / nrb);
     for (int i = threadIdx.x; i < R; i += kXBlock) acc[i] = 0.0;
     const uint32_t* __restrict__ pre_b = x_prefix + rb * (nch + 1);
     const uint32_t* __restrict__ sta_b = x_start + rb * nch;
@@ -870,19 +861,24 @@ __device__ __forceinline__ void reduce_block(const ReduceArgs& x, const VipHop& 
         }
     }
     __syncthreads();
-    const int64_t u0 = rb << kTileRowBits;
+}
+// With one share per block the workgroup finishes the block's vertices itself (p^[h], running total, next hop's y); otherwise
+// it leaves its sums in part[j].  vip_finish_kernel follows either way.
+__global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(ReduceArgs x, int parts, int64_t N, double* __restrict__ part,
+                                                             int64_t part_stride, VipHop a, const uint32_t* __restrict__ how) {
+    extern __shared__ double acc[];
+    if (*how != kPulled) return;
+    constexpr int R = 1 << kTileRowBits;
+    const int64_t nrb = gridDim.x / parts, rb = blockIdx.x % nrb, u0 = rb << kTileRowBits;
+    const int j = (int)(blockIdx.x / nrb);
+    reduce_share(x, rb, j, parts, acc);
     if (parts == 1) {
-        if (x.alone && blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, true);
         unsigned long long edges = 0;            // not asked for: the hop after a pulled one is pulled
-        vip_finish_block<R>(a, u0, x.N, acc, edges);
+        vip_finish_block<R>(a, u0, N, acc, edges);
     } else {
-        double* __restrict__ out = x.part + (int64_t)j * x.part_stride + u0;
+        double* __restrict__ out = part + (int64_t)j * part_stride + u0;
         for (int i = threadIdx.x; i < R; i += kXBlock) out[i] = acc[i];
     }
-}
-__global__ void __launch_bounds__(kXBlock) vip_reduce_kernel(ReduceArgs x, VipHop a, const uint32_t* __restrict__ how) {
-    extern __shared__ double acc[];
-    if (*how == kPulled) reduce_block(x, a, acc);
 }
 
 // y_1(v) for the training vertices (p^[0] = min(1, B/|T|), Sec. 3.1); optionally hop 0 into the
@@ -1449,16 +1445,20 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
                                                                     const uint32_t* __restrict__ how) {
     extern __shared__ double acc[];
     static_assert(kXBlock == kTileBlock, "either form's workgroups");
-    if (*how == kPulled) { reduce_block(x, a, acc); return; }
     constexpr int R = 1 << kTileRowBits;
-    for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
-    __syncthreads();
-    bin_add_entries(acc, bins, base[blockIdx.x], base[blockIdx.x + 1]);
-    __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, false);
+    const bool pulled = *how == kPulled;
+    if (pulled) {
+        reduce_share(x, blockIdx.x, 0, 1, acc);
+    } else {
+        for (int i = threadIdx.x; i < R; i += kTileBlock) acc[i] = 0.0;
+        __syncthreads();
+        bin_add_entries(acc, bins, base[blockIdx.x], base[blockIdx.x + 1]);
+        __syncthreads();
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) hop_done(a, pulled);
     unsigned long long edges = 0;
     const int64_t u0 = (int64_t)blockIdx.x << kTileRowBits;
-    if (a.last) {
+    if (a.last || pulled) {                      // the hop after a pulled one is pulled whatever its edges
         vip_finish_block<R>(a, u0, N, acc, edges);
         return;
     }
@@ -2083,9 +2083,9 @@ extern "C" int spp_vip_propagate(spp_ctx* ctx, const spp_graph* g, const int32_t
                 const int egrid = eshare < ctx->num_cu ? (int)eshare : ctx->num_cu;
                 vip_expand_kernel<<<egrid, kXBlock, x_lds_expand, st>>>(g->x_src, g->x_chunk_first, g->x_nch, N, ycur,
                                                                         ctx->xvals.as<float>(), how_h);
-                const ReduceArgs x{ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch, parts, N, acc, part_stride, binned};
+                const ReduceArgs x{ctx->xvals.as<float>(), g->x_row, g->x_start, g->x_prefix, g->x_nch};
                 if (binned) vip_bin_finish_kernel<<<(unsigned)g->nrb, kTileBlock, bin_finish_lds, st>>>(a, bins, bin_base, N, x, how_h);
-                else vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(x, a, how_h);
+                else vip_reduce_kernel<<<(unsigned)(g->nrb * parts), kXBlock, x_lds_reduce, st>>>(x, parts, N, acc, part_stride, a, how_h);
                 fused = parts == 1;
             }
             if (!binned) vip_finish_kernel<<<vgrid, kBlock, 0, st>>>(a, how_h, fused, acc, parts, part_stride, N);
