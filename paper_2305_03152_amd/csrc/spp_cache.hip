@@ -7,9 +7,9 @@
 // a workgroup's, one places them), packed as (~score bits) << 32 | id, and sorted: in one workgroup up to 4096 of them, else
 // stably by radix on the score bits only (the complement turns ascending into descending score, and
 // stability keeps ascending id among equal scores).  Before, all candidates were sorted, in buffers of
-// 16 bytes per candidate that each call allocated.  A call with 8-byte rows in device memory, 320k kept of 8M scores: 281 -> 167 us
-// with a workgroup per CU in the passes over the scores and two launches per pass of the sort; 60k of 1M 201 -> 114, 10k of 60k
-// 166 -> 112, 1.5M of 8M 477 -> 395.  Rows from the host add what the link takes: 8M scores, 320k rows of 256 bytes 1.70 ms, 1.53 of it.
+// 16 bytes per candidate that each call allocated.  A call with 8-byte rows in device memory, 320k kept of 8M scores: 280 -> 173 us
+// with a workgroup per CU in the passes over the scores and two launches per pass of the sort; 60k of 1M 196 -> 121, 10k of 60k
+// 162 -> 104, 1.5M of 8M 456 -> 378.  Rows from the host add what the link takes: 8M scores, 320k rows of 256 bytes 1.70 ms, 1.53 of it.
 #include "spp_common.h"
 #include "spp_device.h"
 #include "spp_rowcopy.h"
@@ -191,8 +191,8 @@ __global__ void __launch_bounds__(kRankBlock) rank_place_kernel(RankArgs a, cons
 }
 
 // Up to kSmallRank keys in one workgroup: a bitonic network in LDS over the whole keys (ids make them
-// distinct), padded with all ones.  A ranking of 4000 keys out of 20k 104 us, as by the eight launches of the radix sort; of 8000
-// out of 40k 141, and 111 by radix.
+// distinct), padded with all ones.  A ranking of 4000 keys out of 20k 105 us, as by the eight launches of the radix sort; of 8000
+// out of 40k 148, and 101 by radix.
 constexpr int kSmallRank = 4096;
 constexpr int kSmallBlock = 1024;
 __global__ void __launch_bounds__(kSmallBlock) rank_small_kernel(uint64_t* __restrict__ keys, int n, int size) {

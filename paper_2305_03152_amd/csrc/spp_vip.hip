@@ -929,8 +929,12 @@ __device__ __forceinline__ float unit_or_flag(float x, int* bad) {
 // How a hop of the general propagation fills its bins: from a list of its frontier, or (kWhole) from the whole CSR, tile
 // by tile, where the frontier's rows hold at least half of the edges.  The kernel that writes a hop's
 // probabilities counts their vertices' out-edges and decides; on large graphs it counts a part of them (either form is correct
-// for any frontier).  2.4M vertices, 121M edges, a call of one hop: by tiles 605 us
-// whatever the frontier; listed 953 with all edges, 657 with 60 % of them, 585 with 51, 505 with 40, 343 with 23.
+// for any frontier).  Where the two cross depends on the graph, and one half lies between; a call of one hop, us:
+//                                          by tiles   listed, with 40, 45, 50, 55, 60 and 100 % of the edges     equal at
+//   2.4M vertices, 121M edges, power law     601      497  520  561  600  644  956                                 55 %
+//   5M, 59M, power law                       417      381  406  432  458  484  684                                 47 %
+//   4.2M, 65M, RMAT                      395 to 436   372  406  441  446  477  699                                 43 %
+//   200k, 5.8M, power law                     65       88   91   93   95   99  120                           below 40 %
 constexpr uint32_t kListed = 1, kWhole = 2;
 struct FillRule {
     const int64_t* rowptr;               // null: always from the list (no tiles to walk)
@@ -1013,8 +1017,8 @@ __global__ void __launch_bounds__(kBlock) vipg_push_kernel(const int32_t* __rest
 // rows of its vertices end to end (prefix sums of their lengths in LDS; a wavefront takes runs of
 // 64 consecutive edges of that sequence whatever the row lengths, so its loads are contiguous).
 // It walks them in rounds of 8192 edges: an LDS atomic per edge counts the round's entries per bin and gives
-// the edge its place among them, one global atomic per bin reserves their range, and the entries, held in
-// registers meanwhile, are stored.  2.4M vertices, a hop of a quarter of 121M edges: 274 -> 230 us since all loads of a round
+// the edge its place among them, one global atomic per bin reserves their range, and the entries, held by their
+// threads meanwhile (in registers, of which eleven spill to memory: two workgroups per CU leave a lane 64), are stored.  2.4M vertices, a hop of a quarter of 121M edges: 274 -> 230 us since all loads of a round
 // are under way together (a probability that was looked at where it was loaded, for the flag, had the next edge's wait for it).
 // Before that 859 us per dense hop (900 with 256 threads
 // that counted a portion in one walk over col[] and stored its entries in a second).  Nothing is busy for half of the time (vector units 35 %, LDS 44 %, a third of
@@ -1184,7 +1188,8 @@ __device__ __forceinline__ void push_walk(BinPortion<kBinBlock>& po, int64_t nf,
 }
 
 // Adds entries [beg, end) into a row block's sums, by a workgroup of kTileBlock threads.  A thread asks for its next vectors
-// before it adds those it has: 121M entries 224 -> 209 us (one 8-byte load at a time: 325).
+// before it adds those it has: listed hops with all edges, 121M entries 196 us and 65M (RMAT) 159, where eight 8-byte loads
+// at a time with none ahead take 213 and 166 on the same box (one at a time, on another: 325).
 __device__ __forceinline__ void bin_add_entries(double* acc, const uint2* __restrict__ bins, int64_t beg, int64_t end) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int U = 4;                       // vectors of two entries per thread and round
@@ -1481,10 +1486,11 @@ __global__ void __launch_bounds__(kTileBlock) vip_bin_finish_kernel(VipHop a, co
 // the tile before, and nothing in the loop is loaded conditionally (after a conditional load the compiler waits for all).
 // The entries' weights and rows go to arrays of their own: 6 bytes per entry where a pair of words takes 8.  (Not so the listed
 // fill's, whose stores are scattered: it would store twice as often.)
-// 2.4M vertices, 121M edges: 381 us, 1.7 GB (pairs: 424, 2.0 GB), where the listed fill took 852; with seven barriers and waits
+// 2.4M vertices, 121M edges: 381 us, 1.7 GB (pairs: 424, 2.0 GB), where the listed fill takes 708 (852 before its loads
+// were under way together); with seven barriers and waits
 // for the stores 535 to 780.  What bounds it now: vector instructions half of the time (64 per 64 edges, the logarithm a third
 // of them), LDS a third, and what two workgroups per CU leave uncovered of the two barriers.  (That a tile's rows are waited for
-// together with most stores of the tile before costs nothing: 391 with a wait for the loads alone.)
+// together with most stores of the tile before costs nothing: 391 with a wait for the loads alone.)  Two registers of a lane's 64 spill to memory.
 constexpr int kMaxTileBlocks = 512;      // row blocks of a graph that has tiles
 struct PrepareLds {
     uint2    stage[kPartTile];           // the tile's entries by block: weight, destination
@@ -1561,7 +1567,7 @@ __global__ void __launch_bounds__(kFillBlock, 8) vipg_prepare_kernel(const uint3
         if (r.v1 - r.v0 >= (int32_t)tid) one();
         for (int64_t v = (int64_t)r.v0 + kFillBlock + tid; v <= r.v1; v += kFillBlock) { load_row((uint32_t)v); one(); }
     };
-    auto keep_offsets = [&]() {                  // for the wavefront that sets the cursors
+    auto keep_offsets = [&]() {                  // for the wavefronts that set the cursors
         if ((int)tid < nrb) { l.cnt[tid] = r.off_n - r.off; l.off[tid] = r.off; }
     };
     auto set_cursors = [&](uint32_t* shift) {    // 64 blocks to a wavefront, from the third on: the first ones have rows to mark
